@@ -456,7 +456,7 @@ void dcg_clear_cache(void);
  * scalar (inner) vectors 8 n^3 values, idx = 8 e + a.  All work is enqueued
  * on the legacy default stream and the calls return after it has finished.
  * The caller owns the vectors, the handle owns its operators (about
- * 33 KB per element) and workspaces.  Errors as above; dcg3d_last_error. */
+ * 5 KB per element) and workspaces.  Errors as above; dcg3d_last_error. */
 #define DCG3D_MAX_N 64
 #define DCG3D_DEFAULT_MAX_INNER 20000
 

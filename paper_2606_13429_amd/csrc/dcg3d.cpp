@@ -165,14 +165,76 @@ void invert8(const double A[kNb][kNb], double X[kNb][kNb]) {
     for (int j = 0; j < kNb; ++j) X[i][j] = M[i][kNb + j];
 }
 
-// Host assembly of every block the device path uses (layouts in dcg3d.hpp).
-void assemble3d(int n, double penalty, double dt, std::vector<double>& cd, std::vector<double>& ld,
+// Adds the face terms of an element of class c (per axis 0 at the low side,
+// 2 at the high side, 1 inside; n >= 2 cubes per side) to its volume block.
+template <typename Add>
+void add_faces(const CubeForms& F, const int c[3], Add add) {
+  for (int axis = 0; axis < 3; ++axis) {
+    if (c[axis] != 2) add(F.face[axis][0][0]);   // lower side of the +axis face
+    if (c[axis] != 0) add(F.face[axis][1][1]);   // upper side of the -axis face
+  }
+  if (c[0] == 2) add(F.out);
+}
+
+// The blocks of A_div and M_1 as MFMA operand tiles (layout in dcg3d.hpp).
+// The own block of a class sums the face terms in the order assemble3d does.
+std::vector<double> build_astar_tiles(int n, double penalty) {
+  auto forms = std::make_unique<CubeForms>();
+  CubeForms& F = *forms;
+  build_forms(n, penalty, F);
+  std::vector<double> out;
+  out.reserve((size_t)(dcg3::kFixedTiles + dcg3::kSelfClasses * dcg3::kSelfTiles) * 64);
+  auto tile = [&](const double (&B)[3][3][kNb][kNb], int r, int t, int h) {
+    for (int l = 0; l < 64; ++l) {
+      const int row = dcg3::row_of(r, l & 15), b = 2 * (l >> 4) + h;
+      out.push_back(row < 0 ? 0.0 : B[t][row >> 3][row & 7][b]);
+    }
+  };
+  for (int s = 1; s < kSlots; ++s) {
+    const int ax = (s - 1) / 2;
+    const auto& B = (s & 1) ? F.face[ax][1][0] : F.face[ax][0][1];
+    for (int i = 0; i < 3; ++i)
+      for (int j = 0; j < 3; ++j)
+        for (int a = 0; a < kNb; ++a)
+          for (int b = 0; b < kNb; ++b)
+            if (i != ax && j != ax && B[i][j][a][b] != 0.0)
+              throw Err3(DCG_EDEVICE, "face block couples components off its normal");
+    for (int t = 0; t < 3; ++t)
+      for (int h = 0; h < 2; ++h) {
+        if (t == ax || ax < 2) tile(B, 0, t, h);
+        if (t == ax || ax == 2) tile(B, 1, t, h);
+      }
+  }
+  double blk[3][3][kNb][kNb];
+  std::memset(blk, 0, sizeof(blk));
+  for (int i = 0; i < 3; ++i) std::memcpy(blk[i][i], F.mass, sizeof(F.mass));
+  for (int t = 0; t < 3; ++t)
+    for (int h = 0; h < 2; ++h) tile(blk, t < 2 ? 0 : 1, t, h);
+  for (int cls = 0; cls < dcg3::kSelfClasses; ++cls) {
+    const int c[3] = {cls % 3, (cls / 3) % 3, cls / 9};
+    std::memcpy(blk, F.vol, sizeof(blk));
+    add_faces(F, c, [&](const double (&B)[3][3][kNb][kNb]) {
+      for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j)
+          for (int a = 0; a < kNb; ++a)
+            for (int b = 0; b < kNb; ++b) blk[i][j][a][b] += B[i][j][a][b];
+    });
+    for (int t = 0; t < 3; ++t)
+      for (int h = 0; h < 2; ++h)
+        for (int r = 0; r < 2; ++r) tile(blk, r, t, h);
+  }
+  return out;
+}
+
+// Host assembly of the blocks per element (layouts of dcg3d_host_blocks and
+// dcg3d.hpp); cd may be NULL.
+void assemble3d(int n, double penalty, double dt, std::vector<double>* cd, std::vector<double>& ld,
                 std::vector<double>& dinv, std::vector<double>& me) {
   const int64_t ne = (int64_t)n * n * n;
   auto forms = std::make_unique<CubeForms>();   // 60 KB: keep it off the stack
   CubeForms& F = *forms;
   build_forms(n, penalty, F);
-  cd.assign((size_t)kSlots * ne * 576, 0.0);
+  if (cd) cd->assign((size_t)kSlots * ne * 576, 0.0);
   ld.assign((size_t)kSlots * ne * 64, 0.0);
   dinv.assign((size_t)ne * 64, 0.0);
   me.assign(64, 0.0);
@@ -192,28 +254,24 @@ void assemble3d(int n, double penalty, double dt, std::vector<double>& cd, std::
                 for (int b = 0; b < kNb; ++b) self[i][j][a][b] += B[i][j][a][b];
         };
         auto put = [&](int slot, const double (&B)[3][3][kNb][kNb]) {
-          double* blk = cd.data() + ((size_t)slot * ne + e) * 576;
+          double* blk = cd ? cd->data() + ((size_t)slot * ne + e) * 576 : nullptr;
           double* lb = ld.data() + ((size_t)slot * ne + e) * 64;
           for (int i = 0; i < 3; ++i)
             for (int j = 0; j < 3; ++j)
               for (int a = 0; a < kNb; ++a)
                 for (int b = 0; b < kNb; ++b) {
                   // row 8 j + a (test component j), column 8 i + b (trial i)
-                  blk[(8 * i + b) * 24 + 8 * j + a] = B[i][j][a][b];
+                  if (blk) blk[(8 * i + b) * 24 + 8 * j + a] = B[i][j][a][b];
                   if (i == j) lb[b * 8 + a] += B[i][j][a][b];
                 }
         };
+        int cls[3];
         for (int axis = 0; axis < 3; ++axis) {
-          if (c[axis] + 1 < n) {           // element is the lower side of the +axis face
-            add(F.face[axis][0][0]);
-            put(2 + 2 * axis, F.face[axis][0][1]);
-          }
-          if (c[axis] > 0) {               // upper side of the -axis face
-            add(F.face[axis][1][1]);
-            put(1 + 2 * axis, F.face[axis][1][0]);
-          }
+          cls[axis] = c[axis] == 0 ? 0 : (c[axis] + 1 == n ? 2 : 1);
+          if (cls[axis] != 2) put(2 + 2 * axis, F.face[axis][0][1]);
+          if (cls[axis] != 0) put(1 + 2 * axis, F.face[axis][1][0]);
         }
-        if (ex == n - 1) add(F.out);
+        add_faces(F, cls, add);
         put(0, self);
         // block-Jacobi: inverse of the diagonal block of (dt/3) L
         double dblk[kNb][kNb], inv[kNb][kNb];
@@ -255,10 +313,9 @@ struct dcg3d_ctx {
   int64_t ne = 0, nt = 0, ns = 0;     // elements, tensor length, scalar length
   double dt = 0, nu = 1, penalty = 0;
   dcg_options opt{};
-  double* Cd = nullptr;
+  double* At = nullptr;
   double* Ld = nullptr;
   double* Dinv = nullptr;
-  double* Me = nullptr;
   int inner_kind = DCG3D_INNER_FDM;
   double *fVx = nullptr, *fVxT = nullptr, *fVy = nullptr, *fVyT = nullptr, *flx = nullptr,
          *fly = nullptr;        // fast-diagonalisation factors (exact inner solve)
@@ -312,7 +369,7 @@ struct dcg3d_ctx {
   }
 
   ~dcg3d_ctx() {
-    for (double* b : {Cd, Ld, Dinv, Me, w, r, p, q, xh, pf, tz, s, yh, ir, iz, ip, iq, part, part2, dots,
+    for (double* b : {At, Ld, Dinv, w, r, p, q, xh, pf, tz, s, yh, ir, iz, ip, iq, part, part2, dots,
                       fVx, fVxT, fVy, fVyT, flx, fly})
       if (b) (void)hipFree(b);
     for (hipEvent_t e : evs) (void)hipEventDestroy(e);
@@ -334,16 +391,13 @@ struct dcg3d_ctx {
     ne = (int64_t)n * n * n;
     nt = ne * kDof;
     ns = ne * kNb;
-    std::vector<double> cd, ld, dinv, me;
-    assemble3d(n, penalty, dt, cd, ld, dinv, me);
-    Cd = dev_alloc<double>(cd.size());
+    std::vector<double> ld, dinv, me;
+    assemble3d(n, penalty, dt, nullptr, ld, dinv, me);
+    At = upload(build_astar_tiles(n, penalty));
     Ld = dev_alloc<double>(ld.size());
     Dinv = dev_alloc<double>(dinv.size());
-    Me = dev_alloc<double>(64);
-    H3(hipMemcpy(Cd, cd.data(), cd.size() * sizeof(double), hipMemcpyHostToDevice));
     H3(hipMemcpy(Ld, ld.data(), ld.size() * sizeof(double), hipMemcpyHostToDevice));
     H3(hipMemcpy(Dinv, dinv.data(), dinv.size() * sizeof(double), hipMemcpyHostToDevice));
-    H3(hipMemcpy(Me, me.data(), 64 * sizeof(double), hipMemcpyHostToDevice));
     if (inner_kind == DCG3D_INNER_FDM) {
       const int N = 2 * n;
       const dcg::FdmAxis fx = fdm3_axis(n, penalty, true), fy = fdm3_axis(n, penalty, false);
@@ -515,11 +569,12 @@ struct dcg3d_ctx {
   void copy(const double* x, double* y, int64_t len) {
     H3(hipMemcpyAsync(y, x, len * sizeof(double), hipMemcpyDeviceToDevice, nullptr));
   }
-  void astar(const double* x, double* y) {
+  // y = A* x and, with sv, sv = Z^T y
+  void astar(const double* x, double* y, double* sv = nullptr) {
     // the dominant kernel with the exact inner solve or none
     const bool timed = timing && (inner_kind == DCG3D_INNER_FDM || inner_kind == DCG3D_INNER_NONE);
     if (timed) time_mark();
-    H3(dcg3::launch_astar3(n, Cd, Me, 1.0 / nu, dt, x, y, nullptr));
+    H3(dcg3::launch_astar3(n, At, 1.0 / nu, dt, x, y, sv, nullptr));
     if (timed) time_mark();
   }
 
@@ -532,7 +587,7 @@ struct dcg3d_ctx {
       return 0;
     }
     if (inner_kind == DCG3D_INNER_FDM) {     // exact: E^{-1} = (3/dt) L^{-1}
-      H3(dcg3::launch_fdm_solve(n, fVx, fVxT, fVy, fVyT, flx, fly, 3.0 / dt, rhs, out, ir, iz, nullptr));
+      H3(dcg3::launch_fdm_solve(n, fVx, fVxT, fVy, fVyT, flx, fly, 3.0 / dt, rhs, out, ir, nullptr));
       inner_solves += 1;
       return 0;
     }
@@ -597,10 +652,9 @@ struct dcg3d_ctx {
     while (true) {   // one pass of Algorithm 2; further passes are warm restarts from x
     while (it < opt.max_outer && std::sqrt(rho) > tol * fnorm) {
       // q = M_D p = w - dt A_div Z E^{-1} Z^T w, w = A* p
-      astar(p, w);
-      H3(dcg3::launch_zt3(ne, w, s, nullptr));
+      astar(p, w, s);
       inner(s, yh, opt.c_A > 0.0 ? opt.c_A * tol * fnorm / std::sqrt(rho) : rel_in);
-      H3(dcg3::launch_adivz3(n, Cd, dt, w, yh, q, nullptr));
+      H3(dcg3::launch_adivz3(n, At, dt, w, yh, q, nullptr));
       const double pq = dot(p, q, nt);
       if (!(pq > 0.0) || !std::isfinite(pq)) {
         status = DCG_EBREAKDOWN;
@@ -616,8 +670,7 @@ struct dcg3d_ctx {
     }
     if (status == DCG_OK && std::sqrt(rho) > tol * fnorm) status = DCG_NOT_CONVERGED;
     // epilogue: x = (x_hat - pi(A* x_hat)) + pi(f)
-    astar(xh, w);
-    H3(dcg3::launch_zt3(ne, w, s, nullptr));
+    astar(xh, w, s);
     inner(s, yh, rel_in);
     copy(xh, x, nt);
     H3(dcg3::launch_zaxpy3(ne, -1.0, yh, x, nullptr));
@@ -635,10 +688,9 @@ struct dcg3d_ctx {
     astar(pf, w);
     copy(f, r, nt);
     H3(dcg3::launch_axpy(nt, -1.0, w, r, nullptr));
-    astar(xh, w);
-    H3(dcg3::launch_zt3(ne, w, s, nullptr));
+    astar(xh, w, s);
     inner(s, yh, rel_in);
-    H3(dcg3::launch_adivz3(n, Cd, dt, w, yh, q, nullptr));
+    H3(dcg3::launch_adivz3(n, At, dt, w, yh, q, nullptr));
     H3(dcg3::launch_axpy(nt, -1.0, q, r, nullptr));
     copy(r, p, nt);
     rho = dot(r, r, nt);
@@ -671,10 +723,9 @@ struct dcg3d_ctx {
         H3(dcg3::launch_zaxpy3(ne, 1.0, in, outv, nullptr));
         break;
       case DCG3D_OP_DEFLATED:
-        astar(in, w);
-        H3(dcg3::launch_zt3(ne, w, s, nullptr));
+        astar(in, w, s);
         inner(s, yh, tol);
-        H3(dcg3::launch_adivz3(n, Cd, dt, w, yh, outv, nullptr));
+        H3(dcg3::launch_adivz3(n, At, dt, w, yh, outv, nullptr));
         break;
       case DCG3D_OP_REDUCED:
         H3(dcg3::launch_lap3(n, Ld, dt / 3.0, in, outv, part, nullptr));
@@ -684,7 +735,7 @@ struct dcg3d_ctx {
         break;
       case DCG3D_OP_ADIVZ:
         H3(dcg3::launch_fill(nt, 0.0, tz, nullptr));
-        H3(dcg3::launch_adivz3(n, Cd, -1.0, tz, in, outv, nullptr));
+        H3(dcg3::launch_adivz3(n, At, -1.0, tz, in, outv, nullptr));
         break;
       default:
         throw Err3(DCG_EINVAL, "unknown operator");
@@ -875,7 +926,7 @@ dcg_status dcg3d_host_blocks(int32_t n, double penalty, double dt, int32_t which
       return DCG_OK;
     }
     std::vector<double> cd, ld, dinv, me;
-    assemble3d(n, penalty, dt, cd, ld, dinv, me);
+    assemble3d(n, penalty, dt, &cd, ld, dinv, me);
     const std::vector<double>* src[4] = {&cd, &ld, &dinv, &me};
     std::memcpy(out, src[which]->data(), src[which]->size() * sizeof(double));
     return DCG_OK;
@@ -893,8 +944,8 @@ dcg_status dcg3d_host_mg(int32_t n, double penalty, int32_t levels, int32_t leve
   if (which < 0 || which > 2 || (which == 1 && level < 2) || (which == 2 && level != 1))
     return fail3(nullptr, DCG_EINVAL, "which must be 0, 1 (level >= 2) or 2 (level 1)");
   return guarded3(nullptr, [&] {
-    std::vector<double> cd, ld, dinv, me;
-    assemble3d(n, penalty, 1.0, cd, ld, dinv, me);
+    std::vector<double> ld, dinv, me;
+    assemble3d(n, penalty, 1.0, nullptr, ld, dinv, me);
     const dcg3::Mg3Hierarchy H = dcg3::build_mg3(n, J, ld);
     const std::vector<double>& src =
         which == 0 ? H.lev[level - 1].op : (which == 1 ? H.lev[level - 1].ras : H.coarse_inv);

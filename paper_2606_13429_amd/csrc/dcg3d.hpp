@@ -9,17 +9,22 @@
 // Face slots of an element: 0 itself, 1 / 2 the -x / +x neighbour, 3 / 4 -y /
 // +y, 5 / 6 -z / +z.
 //
-//   Cd [7][ne][24][24]  the 3 x 3 block C_3 = [B_ij] of A_div (Section 3.1)
-//                       coupling element e (test) to its slot-s neighbour
-//                       (trial), column-major: entry (row r = 8 j + a,
-//                       column 8 i + b) at ((s ne + e) 24 + 8 i + b) 24 + r;
-//                       row block j = test component, column block i = trial
-//                       component within a row k of the tensor
+//   At [54 + 27 12][64] the 3 x 3 block C_3 = [B_ij] of A_div (Section 3.1),
+//                       row 8 j + a (test component j), column 8 i + b (trial
+//                       component i within a row of the tensor), and the mass
+//                       matrix of M_1, as A operands of the FP64 16 x 16 x 4
+//                       MFMA: tile (r, t, h), lane l = row row_of(r, l % 16)
+//                       (zero rows pad), column 8 t + 2 (l / 16) + h.  Tiles:
+//                       face slots s = 1..6 (normal axis a) for t, then h, row
+//                       tiles 0 and 1 where t = a, else only the one that
+//                       holds the rows j = a (the other blocks are zero);
+//                       then M_1 in block (t, t), the row tile that holds it;
+//                       then per class c = cx + 3 cy + 9 cz (0 low side, 2 high
+//                       side, 1 inside) the element's own block, t, h, r
 //   Ld [7][ne][8][8]    B_11 + B_22 + B_33 (the SIPG Laplacian of
 //                       Corollary 1), column-major per block
 //   Dinv[ne][8][8]      inverse of the diagonal block of (dt/3) Ld,
 //                       column-major (block-Jacobi preconditioner)
-//   Me [8][8]           element mass matrix of M_1 (uniform mesh)
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -31,6 +36,16 @@ constexpr int kNb = 8;        // Q1 basis functions per cube
 constexpr int kComp = 9;      // stress components
 constexpr int kDof = 72;      // values per element of a tensor vector
 constexpr int kSlots = 7;     // the element and its 6 face neighbours
+
+constexpr int kSlotTiles = 8;                       // table tiles of a face slot
+constexpr int kFixedTiles = 6 * kSlotTiles + 6;     // face slots and M_1
+constexpr int kSelfTiles = 12;                      // own block of one class
+constexpr int kSelfClasses = 27;
+// Row of C_3 at row m of row tile r (-1: padding): a lane's results of tile 0
+// are rows 4 q .. 4 q + 3, of tile 1 rows 16 + 2 q, 16 + 2 q + 1.
+constexpr int row_of(int r, int m) {
+  return r == 0 ? 4 * (m & 3) + (m >> 2) : ((m >> 2) < 2 ? 16 + 2 * (m & 3) + (m >> 2) : -1);
+}
 
 // Scalars of the inner PCG iteration, kept on the device between launches.
 struct PcgScalars {
@@ -46,11 +61,12 @@ struct PcgScalars {
 // Workgroup count of the partial-sum kernels for vectors of length len.
 int partial_blocks(int64_t len);
 
-// y = A* x = inv_nu (C_9 (x) M_1) x + dt A_div x, tensor vectors.
-hipError_t launch_astar3(int n, const double* Cd, const double* Me, double inv_nu, double dt,
-                         const double* x, double* y, hipStream_t st);
+// y = A* x = inv_nu (C_9 (x) M_1) x + dt A_div x, tensor vectors; with s != NULL
+// also s = Z^T y.
+hipError_t launch_astar3(int n, const double* At, double inv_nu, double dt, const double* x, double* y,
+                         double* s, hipStream_t st);
 // q = w - dt A_div Z yh (Z = V of eq. (Vmatrix), d = 3); yh a scalar vector.
-hipError_t launch_adivz3(int n, const double* Cd, double dt, const double* w, const double* yh,
+hipError_t launch_adivz3(int n, const double* At, double dt, const double* w, const double* yh,
                          double* q, hipStream_t st);
 // s = Z^T w.
 hipError_t launch_zt3(int64_t ne, const double* w, double* s, hipStream_t st);
@@ -71,12 +87,12 @@ hipError_t launch_pcg_step(int64_t ne, const double* Dinv, double* x, double* r,
                            PcgScalars* sc, hipStream_t st);
 // Exact inner solve out = scale V diag(1 / (lx_i + ly_j + ly_k)) V^T in by fast
 // diagonalisation (V = Vy (x) Vy (x) Vx on the tensor index (Iz, Iy, Ix);
-// the y and z axes share one factor), in six axis passes through the
-// scalar buffers t1, t2; Vd row-major [j][i] = (V_d)_{j i}, VdT its
-// transpose.  Needs 2 n <= 256.
+// the y and z axes share one factor), in three launches through the scalar
+// buffer t; Vd row-major [j][i] = (V_d)_{j i}, VdT its transpose.  Needs
+// 2 n <= 128.
 hipError_t launch_fdm_solve(int n, const double* Vx, const double* VxT, const double* Vy,
                             const double* VyT, const double* lx, const double* ly, double scale,
-                            const double* in, double* out, double* t1, double* t2, hipStream_t st);
+                            const double* in, double* out, double* t, hipStream_t st);
 // out[0] = sum_i x_i y_i (fixed summation order).
 hipError_t launch_dot(int64_t len, const double* x, const double* y, double* part, double* out,
                       hipStream_t st);

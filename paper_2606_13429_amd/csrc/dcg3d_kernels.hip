@@ -1,11 +1,10 @@
 // Kernels of the three-dimensional deflated CG (the d = 3 block structure of
 // Section 3.1; deflation as in Algorithm 2 with V of eq. (Vmatrix)).
 //
-// The A* product and the deflation correction are HBM-bound FP64 streams of
-// the 24 x 24 blocks C_3 (32 KB per element): one thread per (element, row of
-// C_3) computes that row for the three tensor rows k, so every block entry is
-// read once and used three times; the neighbour values of 8 elements are
-// staged in LDS.  The inner Laplace system (dt/3) L (Corollary 1, d = 3) is
+// The A* product and the deflation correction run as FP64 MFMA products of the
+// 24 x 24 blocks C_3, which are a table of the uniform grid, with the vectors
+// of 16 elements a wavefront, and so does the exact inner solve by fast
+// diagonalisation.  The iterative inner Laplace system (dt/3) L (Corollary 1, d = 3) is
 // solved by block-Jacobi preconditioned CG whose scalars stay on the device;
 // every reduction is a fixed-order two-stage sum, so results are
 // reproducible bit for bit.
@@ -17,8 +16,7 @@ namespace dcg3 {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kEpw = 8;                    // elements per workgroup (A* and A_div Z)
-constexpr int kAThreads = kEpw * 24;       // one thread per row of C_3
+typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kMaxPartials = 1024;
 
 __device__ __forceinline__ int nbr3(int n, int e, int s) {
@@ -54,98 +52,213 @@ __device__ double final_sum(const double* __restrict__ part, int cnt, double* ld
   return block_sum(v, lds);
 }
 
-__global__ __launch_bounds__(kAThreads) void k_astar3(int n, const double* __restrict__ Cd,
-                                                      const double* __restrict__ Me, double inv_nu,
-                                                      double dt, const double* __restrict__ x,
-                                                      double* __restrict__ y) {
+// ---- A* and A_div Z as FP64 MFMA products.  On the uniform grid the block of
+// a face neighbour does not depend on the element and the element's own block
+// only on its class (which sides of the domain it touches, 27 classes), so
+// C_3 is a table (build_astar_tiles) and not a stream: one wavefront takes 16
+// consecutive elements as the columns and the tensor row k its B operand
+// comes from, the 24 rows of C_3 are two 16-row tiles (a0: rows 0..15, a1:
+// rows 16..23 and padding), and the blocks of a face normal to axis a that the
+// form leaves zero (i != a and j != a, Section 3.3.2) are not multiplied.
+// Column 8 t + 2 q + h of a 24-column block is step (t, h), lane group q, so
+// that a lane's operands of one t are one 16-byte load; rows are permuted so
+// that a lane's results are consecutive in memory.  Lanes outside the domain
+// enter zeros; a wavefront whose elements are of several classes runs the 6
+// steps of the own block once per class.
+//
+// With every block read from memory (1.07 GB a launch at n = 32, the HBM
+// rate) the two products took 205 and 200 us; with the table 41 and 17 us,
+// bound by the latency of the vector and table reads (12 us of matrix work).
+__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ int axis_class(int x, int n) { return x == 0 ? 0 : (x == n - 1 ? 2 : 1); }
+
+// Class of element e; -1 outside the mesh.
+__device__ __forceinline__ int elem_class(int n, int ne, int e) {
+  if (e >= ne) return -1;
+  return axis_class(e % n, n) + 3 * axis_class((e / n) % n, n) + 9 * axis_class(e / (n * n), n);
+}
+
+// Workgroup index with the 8 XCDs (dispatched round robin) on contiguous
+// ranges of elements, so that the planes z +- 1 of a range stay in one L2.
+__device__ __forceinline__ int band_index(int b, int G) {
+  return (G & 7) ? b : (b & 7) * (G >> 3) + (b >> 3);
+}
+
+// G groups of 16 elements per workgroup, a wavefront per group and tensor row.
+template <int G>
+__global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restrict__ At, double inv_nu,
+                                                    double dt, const double* __restrict__ x,
+                                                    double* __restrict__ y, double inv_sqrt3,
+                                                    double* __restrict__ s) {
+  __shared__ double tab[kFixedTiles * 64];
+  __shared__ double zl[G * 16][3][kNb];
   const int ne = n * n * n;
-  __shared__ double xs[kEpw][kSlots][kDof];
-  __shared__ double me[kNb * kNb];
-  const int tid = threadIdx.x;
-  const int e0 = blockIdx.x * kEpw;
-  if (tid < kNb * kNb) me[tid] = Me[tid];
-  for (int idx = tid; idx < kEpw * kSlots * kDof; idx += kAThreads) {
-    const int el = idx / (kSlots * kDof), rem = idx % (kSlots * kDof);
-    const int s = rem / kDof, v = rem % kDof;
-    const int e = e0 + el;
-    const int nb = e < ne ? nbr3(n, e, s) : -1;
-    xs[el][s][v] = nb >= 0 ? x[(int64_t)nb * kDof + v] : 0.0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int k = __builtin_amdgcn_readfirstlane(w % 3), grp = w / 3;
+  const int col = lane & 15, q = lane >> 4;
+  const int e = (band_index(blockIdx.x, gridDim.x) * G + grp) * 16 + col;
+  const bool live = e < ne;
+  double2 v[kSlots][3];
+#pragma unroll
+  for (int sl = 0; sl < kSlots; ++sl) {
+    const int nb = live ? nbr3(n, e, sl) : -1;
+    const double2* p = reinterpret_cast<const double2*>(x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) v[sl][t] = nb >= 0 ? p[4 * t] : make_double2(0.0, 0.0);
   }
+  // sigma_{k1 k1} + sigma_{k2 k2} of the other two rows, for the mass term
+  const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
+  double2 o1 = make_double2(0.0, 0.0), o2 = o1;
+  if (live) {
+    o1 = *reinterpret_cast<const double2*>(x + (int64_t)e * kDof + 32 * k1 + 2 * q);
+    o2 = *reinterpret_cast<const double2*>(x + (int64_t)e * kDof + 32 * k2 + 2 * q);
+  }
+  for (int i = threadIdx.x; i < kFixedTiles * 64; i += G * 192) tab[i] = At[i];
   __syncthreads();
-  const int el = tid / 24, r = tid % 24;
-  const int e = e0 + el;
-  if (e >= ne) return;
-  double acc[3] = {0.0, 0.0, 0.0};
-  for (int s = 0; s < kSlots; ++s) {
-    if (nbr3(n, e, s) < 0) continue;
-    const double* c = Cd + ((int64_t)s * ne + e) * 576 + r;
-    const double* xv = xs[el][s];
-#pragma unroll 8
-    for (int col = 0; col < 24; ++col) {
-      const double cv = __builtin_nontemporal_load(c + col * 24);   // streamed once per launch
-      acc[0] += cv * xv[col];
-      acc[1] += cv * xv[24 + col];
-      acc[2] += cv * xv[48 + col];
-    }
+  v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0, m0 = a0, m1 = a0;
+  int tile = 0;
+#pragma unroll
+  for (int sl = 1; sl < kSlots; ++sl) {
+    const int ax = (sl - 1) >> 1;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double b = h ? v[sl][t].y : v[sl][t].x;
+        if (t == ax || ax < 2) a0 = mfma64(tab[(tile++) * 64 + lane], b, a0);
+        if (t == ax || ax == 2) a1 = mfma64(tab[(tile++) * 64 + lane], b, a1);
+      }
   }
   // (C_9 (x) M_1) x on the element: off-diagonal components carry weight 1,
   // the diagonal ones 2/3 on themselves and -1/3 on the other two.
-  const int j = r >> 3, a = r & 7;
-  const double* xe = xs[el][0];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    double m = 0.0;
-    if (k != j) {
-      const double* xc = xe + 8 * (3 * k + j);
+  for (int t = 0; t < 3; ++t)
 #pragma unroll
-      for (int b = 0; b < kNb; ++b) m += me[a * kNb + b] * xc[b];
-    } else {
-      const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
-#pragma unroll
-      for (int b = 0; b < kNb; ++b) {
-        const double dv = (2.0 / 3.0) * xe[32 * k + b] - (1.0 / 3.0) * (xe[32 * k1 + b] + xe[32 * k2 + b]);
-        m += me[a * kNb + b] * dv;
-      }
+    for (int h = 0; h < 2; ++h) {
+      double b = h ? v[0][t].y : v[0][t].x;
+      if (t == k) b = (2.0 / 3.0) * b - (1.0 / 3.0) * (h ? o1.y + o2.y : o1.x + o2.x);
+      const double m = tab[(tile++) * 64 + lane];
+      if (t < 2) m0 = mfma64(m, b, m0);
+      else m1 = mfma64(m, b, m1);
     }
-    y[(int64_t)e * kDof + 8 * (3 * k + j) + a] = inv_nu * m + dt * acc[k];
+  // the element's own block, once per class in the wavefront
+  const int cls = elem_class(n, ne, e);
+  uint64_t pending = __ballot(live);
+  while (pending) {
+    const int c = __builtin_amdgcn_readfirstlane(__shfl(cls, __builtin_ctzll(pending), 64));
+    const bool mine = cls == c;
+    const double* S = At + ((int64_t)kFixedTiles + c * kSelfTiles) * 64 + lane;
+    double a[kSelfTiles];
+#pragma unroll
+    for (int i = 0; i < kSelfTiles; ++i) a[i] = S[64 * i];
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const double b = mine ? (h ? v[0][t].y : v[0][t].x) : 0.0;
+        a0 = mfma64(a[4 * t + 2 * h], b, a0);
+        a1 = mfma64(a[4 * t + 2 * h + 1], b, a1);
+      }
+    pending &= ~__ballot(mine);
+  }
+  double r0[4], r1[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r0[i] = inv_nu * m0[i] + dt * a0[i];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) r1[i] = inv_nu * m1[i] + dt * a1[i];
+  if (live) {   // rows 4 q .. 4 q + 3 and 16 + 2 q, 16 + 2 q + 1
+    double2* yp = reinterpret_cast<double2*>(y + (int64_t)e * kDof + 24 * k);
+    yp[2 * q] = make_double2(r0[0], r0[1]);
+    yp[2 * q + 1] = make_double2(r0[2], r0[3]);
+    yp[8 + q] = make_double2(r1[0], r1[1]);
+  }
+  if (!s) return;
+  // s = Z^T y: rows 8 k .. 8 k + 7 of the three tensor rows
+  if (k < 2) {
+    if ((q >> 1) == k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) zl[16 * grp + col][k][4 * (q & 1) + i] = r0[i];
+  } else {
+    zl[16 * grp + col][2][2 * q] = r1[0];
+    zl[16 * grp + col][2][2 * q + 1] = r1[1];
+  }
+  __syncthreads();
+  if (k == 0 && live) {
+    const double(*z)[kNb] = zl[16 * grp + col];
+    double2 sv;
+    sv.x = ((z[0][2 * q] + z[1][2 * q]) + z[2][2 * q]) * inv_sqrt3;
+    sv.y = ((z[0][2 * q + 1] + z[1][2 * q + 1]) + z[2][2 * q + 1]) * inv_sqrt3;
+    *reinterpret_cast<double2*>(s + (int64_t)e * kNb + 2 * q) = sv;
   }
 }
 
-__global__ __launch_bounds__(kAThreads) void k_adivz3(int n, const double* __restrict__ Cd, double dt,
-                                                      double inv_sqrt3, const double* __restrict__ w,
-                                                      const double* __restrict__ yh,
-                                                      double* __restrict__ q) {
+// q = w - dt A_div Z yh: the products of k_astar3 with the one column block
+// t = k of C_3 that a multiple of the identity meets.
+__global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict__ At, double dt,
+                                                double inv_sqrt3, const double* __restrict__ w,
+                                                const double* __restrict__ yh, double* __restrict__ qv) {
   const int ne = n * n * n;
-  __shared__ double ys[kEpw][kSlots][kNb];
-  const int tid = threadIdx.x;
-  const int e0 = blockIdx.x * kEpw;
-  for (int idx = tid; idx < kEpw * kSlots * kNb; idx += kAThreads) {
-    const int el = idx / (kSlots * kNb), rem = idx % (kSlots * kNb);
-    const int s = rem / kNb, b = rem % kNb;
-    const int e = e0 + el;
-    const int nb = e < ne ? nbr3(n, e, s) : -1;
-    ys[el][s][b] = nb >= 0 ? yh[(int64_t)nb * kNb + b] * inv_sqrt3 : 0.0;
-  }
-  __syncthreads();
-  const int el = tid / 24, r = tid % 24;
-  const int e = e0 + el;
-  if (e >= ne) return;
-  // (A_div Z yh) at tensor row k, test component j: column block i = k of C_3
-  double acc[3] = {0.0, 0.0, 0.0};
-  for (int s = 0; s < kSlots; ++s) {
-    if (nbr3(n, e, s) < 0) continue;
-    const double* c = Cd + ((int64_t)s * ne + e) * 576 + r;
+  const int lane = threadIdx.x & 63;
+  const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane & 15, q = lane >> 4;
+  const int e = band_index(blockIdx.x, gridDim.x) * 16 + col;
+  const bool live = e < ne;
+  double2 v[kSlots];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int b = 0; b < kNb; ++b) acc[k] += __builtin_nontemporal_load(c + (8 * k + b) * 24) * ys[el][s][b];
+  for (int sl = 0; sl < kSlots; ++sl) {
+    const int nb = live ? nbr3(n, e, sl) : -1;
+    v[sl] = make_double2(0.0, 0.0);
+    if (nb >= 0) {
+      v[sl] = *reinterpret_cast<const double2*>(yh + (int64_t)nb * kNb + 2 * q);
+      v[sl].x *= inv_sqrt3;
+      v[sl].y *= inv_sqrt3;
+    }
   }
-  const int j = r >> 3, a = r & 7;
+  double2 wv[3];
+  const double2* wp = reinterpret_cast<const double2*>(w + (int64_t)(live ? e : 0) * kDof + 24 * k);
+  wv[0] = wp[2 * q];
+  wv[1] = wp[2 * q + 1];
+  wv[2] = wp[8 + q];
+  v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int64_t i = (int64_t)e * kDof + 8 * (3 * k + j) + a;
-    q[i] = w[i] - dt * acc[k];
+  for (int sl = 1; sl < kSlots; ++sl) {
+    const int ax = (sl - 1) >> 1;
+    // first tile of (slot, t = k): two per step where t = axis, else one
+    const double* T = At + ((sl - 1) * kSlotTiles + 2 * k + (k > ax ? 2 : 0)) * 64 + lane;
+    if (k == ax) {
+      a0 = mfma64(T[0], v[sl].x, a0);
+      a1 = mfma64(T[64], v[sl].x, a1);
+      a0 = mfma64(T[128], v[sl].y, a0);
+      a1 = mfma64(T[192], v[sl].y, a1);
+    } else if (ax < 2) {
+      a0 = mfma64(T[0], v[sl].x, a0);
+      a0 = mfma64(T[64], v[sl].y, a0);
+    } else {
+      a1 = mfma64(T[0], v[sl].x, a1);
+      a1 = mfma64(T[64], v[sl].y, a1);
+    }
   }
+  const int cls = elem_class(n, ne, e);
+  uint64_t pending = __ballot(live);
+  while (pending) {
+    const int c = __builtin_amdgcn_readfirstlane(__shfl(cls, __builtin_ctzll(pending), 64));
+    const bool mine = cls == c;
+    const double* S = At + ((int64_t)kFixedTiles + c * kSelfTiles + 4 * k) * 64 + lane;
+    const double bx = mine ? v[0].x : 0.0, by = mine ? v[0].y : 0.0;
+    a0 = mfma64(S[0], bx, a0);
+    a1 = mfma64(S[64], bx, a1);
+    a0 = mfma64(S[128], by, a0);
+    a1 = mfma64(S[192], by, a1);
+    pending &= ~__ballot(mine);
+  }
+  if (!live) return;
+  double2* op = reinterpret_cast<double2*>(qv + (int64_t)e * kDof + 24 * k);
+  op[2 * q] = make_double2(wv[0].x - dt * a0[0], wv[0].y - dt * a0[1]);
+  op[2 * q + 1] = make_double2(wv[1].x - dt * a0[2], wv[1].y - dt * a0[3]);
+  op[8 + q] = make_double2(wv[2].x - dt * a1[0], wv[2].y - dt * a1[1]);
 }
 
 __global__ __launch_bounds__(kThreads) void k_zt3(int64_t ne, double inv_sqrt3,
@@ -361,50 +474,126 @@ __global__ __launch_bounds__(kThreads) void k_fill(int64_t len, double v, double
   if (i < len) x[i] = v;
 }
 
-// Position of tensor index (Ix, Iy, Iz), I = 2 e_axis + i_axis, in the
-// element-major scalar layout 8 e + a or in the tensor layout (Iz N + Iy) N + Ix.
-template <bool ELEM>
-__device__ __forceinline__ int64_t fdm_pos(int n, int Ix, int Iy, int Iz) {
-  const int N = 2 * n;
-  if (ELEM) {
-    const int64_t e = ((int64_t)(Iz >> 1) * n + (Iy >> 1)) * n + (Ix >> 1);
-    return 8 * e + (Ix & 1) + 2 * (Iy & 1) + 4 * (Iz & 1);
+// ---- exact inner solve by fast diagonalisation: three launches of FP64 MFMA
+// products on the N^3 tensor (N = 2 n), layout (Iz N + Iy) N + Ix, element-
+// major 8 e + a at the ends:
+//   k_fdm_plane  per plane Iz and chunk of 16 columns: U = S Bx, then Ay U
+//   k_fdm_z      per 16 lines along z: U = Vz^T S scaled, then Vz U
+// so each launch holds its intermediate in LDS and a workgroup's two products
+// share one 16-column chunk.  A workgroup of 4 wavefronts gives each the row
+// tiles w, w + 4, ..; column 8 t + 2 q + h of a contraction is step (t, h),
+// lane group q.  (Six passes of one thread per output took 10-13 us each at
+// n = 32, bound by their 64-step chain of table loads; the three launches
+// take 8.0-8.7 us each.)
+constexpr int kFdmThreads = 256;
+constexpr int kFdmMaxN = 128;
+constexpr int kFdmPad = 17;                // LDS row of 16 columns
+
+// out[m][c] = sum_k A(m, k) U[k][c] for the wavefront's row tiles; A is N x N
+// row-major, U in LDS (rows up to the next multiple of 8 are zero-filled).
+template <typename Store>
+__device__ __forceinline__ void fdm_rows(int N, const double* __restrict__ A, const double* U, Store store) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = lane & 15, q = lane >> 4;
+  for (int m0 = 16 * w; m0 < N; m0 += 64) {
+    const int row = m0 + col;
+    const double* Ar = A + (int64_t)(row < N ? row : 0) * N + 2 * q;
+    v4d acc = {0.0, 0.0, 0.0, 0.0}, acc1 = acc;
+#pragma unroll 4
+    for (int k0 = 0; k0 < N; k0 += 8) {
+      double2 a = make_double2(0.0, 0.0);
+      if (row < N && k0 + 2 * q < N) a = *reinterpret_cast<const double2*>(Ar + k0);
+      acc = mfma64(a.x, U[(k0 + 2 * q) * kFdmPad + col], acc);
+      acc1 = mfma64(a.y, U[(k0 + 2 * q + 1) * kFdmPad + col], acc1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) store(m0 + 4 * v + q, acc[v] + acc1[v]);
   }
-  return ((int64_t)Iz * N + Iy) * N + Ix;
 }
 
-// One pass of the fast diagonalisation: out_i = sum_j A[j N + i] in_j along
-// one axis of the (2n)^3 tensor, optionally scaled by
-// scale / (lx[Ix] + ly[Iy] + ly[Iz]).  One workgroup takes 256 / N lines of N
-// values, staged in LDS; thread (line, i) forms output i of its line.
+// Rows [N, next multiple of 8) of U: the padding of a contraction over N rows.
+__device__ __forceinline__ void fdm_pad_rows(int N, double* U) {
+  for (int i = threadIdx.x; i < ((N + 7) & ~7) * 16 - N * 16; i += kFdmThreads)
+    U[(N + i / 16) * kFdmPad + i % 16] = 0.0;
+}
+
 template <bool IN_ELEM, bool OUT_ELEM>
-__global__ __launch_bounds__(kThreads) void k_fdm_axis(int n, int axis, const double* __restrict__ A,
-                                                       const double* __restrict__ in,
-                                                       double* __restrict__ out,
-                                                       const double* __restrict__ lx,
-                                                       const double* __restrict__ ly, double scale) {
-  __shared__ double line[kThreads];
+__global__ __launch_bounds__(kFdmThreads) void k_fdm_plane(int n, const double* __restrict__ Bx,
+                                                           const double* __restrict__ Ay,
+                                                           const double* __restrict__ in,
+                                                           double* __restrict__ out) {
+  __shared__ double U[kFdmMaxN * kFdmPad];
   const int N = 2 * n;
-  const int lpw = kThreads / N;
-  const int ll = threadIdx.x / N, i = threadIdx.x % N;
-  const int64_t g = (int64_t)blockIdx.x * lpw + ll;
-  const bool live = ll < lpw && g < (int64_t)N * N;
-  int I[3] = {0, 0, 0};
-  if (live) {
-    const int o1 = int(g % N), o2 = int(g / N);
-    const int a1 = axis == 0 ? 1 : 0, a2 = axis == 2 ? 1 : 2;
-    I[a1] = o1;
-    I[a2] = o2;
-    I[axis] = i;
-    line[threadIdx.x] = in[fdm_pos<IN_ELEM>(n, I[0], I[1], I[2])];
+  const int Iz = blockIdx.y, c0 = 16 * blockIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = lane & 15, q = lane >> 4;
+  const int c = c0 + col;
+  // element-major position of (Ix, Iy) in this plane
+  const int64_t ez = (int64_t)(Iz >> 1) * n * n;
+  auto elem = [&](int Ix, int Iy) {
+    return 8 * (ez + (int64_t)(Iy >> 1) * n + (Ix >> 1)) + (Ix & 1) + 2 * (Iy & 1) + 4 * (Iz & 1);
+  };
+  for (int m0 = 16 * w; m0 < N; m0 += 64) {
+    const int row = m0 + col;              // Iy of the A operand
+    v4d acc = {0.0, 0.0, 0.0, 0.0}, acc1 = acc;
+#pragma unroll 4
+    for (int k0 = 0; k0 < N; k0 += 8) {
+      const int kk = k0 + 2 * q;
+      double2 a = make_double2(0.0, 0.0);
+      double b0 = 0.0, b1 = 0.0;
+      if (kk < N) {
+        if (row < N)
+          a = *reinterpret_cast<const double2*>(
+              in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
+        if (c < N) {
+          b0 = Bx[(int64_t)kk * N + c];
+          b1 = Bx[(int64_t)(kk + 1) * N + c];
+        }
+      }
+      acc = mfma64(a.x, b0, acc);
+      acc1 = mfma64(a.y, b1, acc1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int Iy = m0 + 4 * v + q;
+      if (Iy < N) U[Iy * kFdmPad + col] = acc[v] + acc1[v];
+    }
   }
+  fdm_pad_rows(N, U);
   __syncthreads();
-  if (!live) return;
-  const double* lv = line + ll * N;
-  double acc = 0.0;
-  for (int j = 0; j < N; ++j) acc += A[j * N + i] * lv[j];
-  if (lx) acc *= scale / (lx[I[0]] + ly[I[1]] + ly[I[2]]);
-  out[fdm_pos<OUT_ELEM>(n, I[0], I[1], I[2])] = acc;
+  fdm_rows(N, Ay, U, [&](int Iy, double v) {
+    if (Iy < N && c < N) out[OUT_ELEM ? elem(c, Iy) : ((int64_t)Iz * N + Iy) * N + c] = v;
+  });
+}
+
+// t[.][j] <- Vz (scale / (lx + ly + lz)) Vz^T t[.][j] for the 16 lines j = Iy N + Ix
+// of the workgroup (in place: a workgroup reads and writes its own lines only).
+__global__ __launch_bounds__(kFdmThreads) void k_fdm_z(int n, const double* __restrict__ V,
+                                                       const double* __restrict__ VT,
+                                                       const double* __restrict__ lx,
+                                                       const double* __restrict__ ly, double scale,
+                                                       double* __restrict__ t) {
+  __shared__ double S[kFdmMaxN * kFdmPad];
+  __shared__ double U[kFdmMaxN * kFdmPad];
+  const int N = 2 * n;
+  const int64_t NN = (int64_t)N * N;
+  const int64_t j0 = 16 * (int64_t)blockIdx.x;
+  const int col = threadIdx.x & 15;
+  const int64_t j = j0 + col;
+  const bool live = j < NN;
+  for (int k = threadIdx.x >> 4; k < N; k += kFdmThreads / 16)
+    S[k * kFdmPad + col] = live ? t[k * NN + j] : 0.0;
+  fdm_pad_rows(N, S);
+  const double lxy = live ? lx[j % N] + ly[j / N] : 0.0;
+  __syncthreads();
+  fdm_rows(N, VT, S, [&](int Iz, double v) {
+    if (Iz < N) U[Iz * kFdmPad + col] = live ? v * (scale / (lxy + ly[Iz])) : 0.0;
+  });
+  fdm_pad_rows(N, U);
+  __syncthreads();
+  fdm_rows(N, V, U, [&](int Iz, double v) {
+    if (Iz < N && live) t[Iz * NN + j] = v;
+  });
 }
 
 int blocks_for(int64_t len) { return int((len + kThreads - 1) / kThreads); }
@@ -418,17 +607,24 @@ int partial_blocks(int64_t len) {
   return int(b < kMaxPartials ? (b > 0 ? b : 1) : kMaxPartials);
 }
 
-hipError_t launch_astar3(int n, const double* Cd, const double* Me, double inv_nu, double dt,
-                         const double* x, double* y, hipStream_t st) {
-  const int ne = n * n * n;
-  k_astar3<<<(ne + kEpw - 1) / kEpw, kAThreads, 0, st>>>(n, Cd, Me, inv_nu, dt, x, y);
+hipError_t launch_astar3(int n, const double* At, double inv_nu, double dt, const double* x, double* y,
+                         double* s, hipStream_t st) {
+  const int64_t groups = ((int64_t)n * n * n + 15) / 16;
+  // two groups per workgroup share the 27 KB table; on small meshes one, to
+  // put a workgroup on more compute units
+  if (groups >= 512) {
+    const unsigned grid = unsigned(((groups + 1) / 2 + 7) & ~int64_t(7));
+    k_astar3<2><<<grid, 384, 0, st>>>(n, At, inv_nu, dt, x, y, kInvSqrt3, s);
+  } else {
+    k_astar3<1><<<unsigned(groups), 192, 0, st>>>(n, At, inv_nu, dt, x, y, kInvSqrt3, s);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_adivz3(int n, const double* Cd, double dt, const double* w, const double* yh,
+hipError_t launch_adivz3(int n, const double* At, double dt, const double* w, const double* yh,
                          double* q, hipStream_t st) {
-  const int ne = n * n * n;
-  k_adivz3<<<(ne + kEpw - 1) / kEpw, kAThreads, 0, st>>>(n, Cd, dt, kInvSqrt3, w, yh, q);
+  const int64_t groups = ((int64_t)n * n * n + 15) / 16;
+  k_adivz3<<<unsigned((groups + 7) & ~int64_t(7)), 192, 0, st>>>(n, At, dt, kInvSqrt3, w, yh, q);
   return hipGetLastError();
 }
 
@@ -471,17 +667,13 @@ hipError_t launch_pcg_step(int64_t ne, const double* Dinv, double* x, double* r,
 
 hipError_t launch_fdm_solve(int n, const double* Vx, const double* VxT, const double* Vy,
                             const double* VyT, const double* lx, const double* ly, double scale,
-                            const double* in, double* out, double* t1, double* t2, hipStream_t st) {
+                            const double* in, double* out, double* t, hipStream_t st) {
   const int N = 2 * n;
-  if (N > kThreads) return hipErrorInvalidValue;
-  const int lpw = kThreads / N;
-  const int grid = int(((int64_t)N * N + lpw - 1) / lpw);
-  k_fdm_axis<true, false><<<grid, kThreads, 0, st>>>(n, 0, Vx, in, t1, nullptr, nullptr, 0.0);
-  k_fdm_axis<false, false><<<grid, kThreads, 0, st>>>(n, 1, Vy, t1, t2, nullptr, nullptr, 0.0);
-  k_fdm_axis<false, false><<<grid, kThreads, 0, st>>>(n, 2, Vy, t2, t1, lx, ly, scale);
-  k_fdm_axis<false, false><<<grid, kThreads, 0, st>>>(n, 2, VyT, t1, t2, nullptr, nullptr, 0.0);
-  k_fdm_axis<false, false><<<grid, kThreads, 0, st>>>(n, 1, VyT, t2, t1, nullptr, nullptr, 0.0);
-  k_fdm_axis<false, true><<<grid, kThreads, 0, st>>>(n, 0, VxT, t1, out, nullptr, nullptr, 0.0);
+  if (N > kFdmMaxN) return hipErrorInvalidValue;
+  const dim3 planes((N + 15) / 16, N);
+  k_fdm_plane<true, false><<<planes, kFdmThreads, 0, st>>>(n, Vx, VyT, in, t);
+  k_fdm_z<<<unsigned(((int64_t)N * N + 15) / 16), kFdmThreads, 0, st>>>(n, Vy, VyT, lx, ly, scale, t);
+  k_fdm_plane<false, true><<<planes, kFdmThreads, 0, st>>>(n, VxT, Vy, t, out);
   return hipGetLastError();
 }
 
