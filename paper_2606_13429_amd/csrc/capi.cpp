@@ -297,7 +297,7 @@ dcg_status dcg_bdf2_rhs(dcg_handle h, const double* s1, const double* s2, const 
   if (!std::isfinite(c)) return fail(h, DCG_EINVAL, "c must be finite");
   return guarded(h, [&]() {
     const hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    DCG_HIP(dcg::launch_bdf2_rhs(h->mesh->ne, h->mesh->M1, 1.0 / h->nu, s1, s2, F, c, f, x0, st));
+    DCG_HIP(dcg::launch_bdf2_rhs(h->mesh->ne, h->mesh->Ct, 1.0 / h->nu, s1, s2, F, c, f, x0, st));
     DCG_HIP(hipStreamSynchronize(st));
     return DCG_OK;
   });

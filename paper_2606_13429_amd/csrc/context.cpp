@@ -47,36 +47,10 @@ void threaded(int64_t count, Fn fn) {
   for (auto& x : th) x.join();
 }
 
-// Uploads a [ne][slot][rows][cols] block array into the device layout
-// double2 [slot][cols/2][ne][rows] in chunks of squares.
-void upload_blocks_pairs(const std::vector<double>& host, int64_t ne, int rows, int ncol,
-                         double2* dev) {
-  const int kcs = ncol / 2;
-  const int64_t chunk = 1 << 15;
-  std::vector<double2> stage(size_t(chunk) * kSlots * kcs * rows);
-  for (int64_t e0 = 0; e0 < ne; e0 += chunk) {
-    const int64_t cnt = std::min(chunk, ne - e0);
-    threaded(cnt, [&](int64_t de) {
-      const int64_t e = e0 + de;
-      for (int s = 0; s < kSlots; ++s)
-        for (int kc = 0; kc < kcs; ++kc)
-          for (int r = 0; r < rows; ++r) {
-            const double* src = &host[((e * kSlots + s) * rows + r) * ncol + 2 * kc];
-            stage[((size_t(s) * kcs + kc) * cnt + de) * rows + r] = make_double2(src[0], src[1]);
-          }
-    });
-    for (int s = 0; s < kSlots; ++s)
-      for (int kc = 0; kc < kcs; ++kc)
-        DCG_HIP(hipMemcpy(dev + ((int64_t(s) * kcs + kc) * ne + e0) * rows,
-                          &stage[(size_t(s) * kcs + kc) * cnt * rows], sizeof(double2) * cnt * rows,
-                          hipMemcpyHostToDevice));
-  }
-}
-
 // The div-div form acts on each row sigma_k = (sigma_k1, sigma_k2) of the
 // stress separately and identically (Section 3.3.2), so every 16 x 16 block of
 // A_div is diag(C, C) in the ordering (sigma_11, sigma_12 | sigma_21, sigma_22)
-// x 4 corners, C 8 x 8.  Returns the C blocks [ne][slot][8][8] after checking
+// x 4 corners, C 8 x 8.  Returns the C blocks [ne][slot][8][8], column-major, after checking
 // that structure exactly.
 std::vector<double> row_blocks(const std::vector<double>& A, int64_t ne) {
   std::vector<double> C(size_t(ne) * kSlots * 64);
@@ -90,7 +64,7 @@ std::vector<double> row_blocks(const std::vector<double>& A, int64_t ne) {
           throw Error(DCG_EDEVICE, "A_div block is not diag(C, C)");
       }
     for (int r = 0; r < 8; ++r)
-      for (int c = 0; c < 8; ++c) C[size_t(b) * 64 + r * 8 + c] = a[r * 16 + c];
+      for (int c = 0; c < 8; ++c) C[size_t(b) * 64 + c * 8 + r] = a[r * 16 + c];
   }
   return C;
 }
@@ -249,6 +223,27 @@ void upload_weights(const HostLevel& hl, T* dev) {
   DCG_HIP(hipMemcpy(dev, t.data(), t.size() * sizeof(T), hipMemcpyHostToDevice));
 }
 
+// The blocks [ne][5][rows * cols] of an operator as its table: the four
+// neighbour blocks, then the own block of every square class.  Every square
+// must carry the blocks of the table bit for bit (and none where a neighbour
+// is missing), which the uniform grid guarantees and this checks.
+void append_block_table(const std::vector<double>& blocks, int n, int len, std::vector<double>& out) {
+  std::vector<const double*> src(4 + 9, nullptr);
+  for (int64_t e = 0; e < int64_t(n) * n; ++e) {
+    const int ex = int(e % n), ey = int(e / n);
+    const bool has[4] = {ex > 0, ex < n - 1, ey > 0, ey < n - 1};
+    for (int s = 0; s < kSlots; ++s) {
+      if (s > 0 && !has[s - 1]) continue;
+      const double* b = &blocks[(e * kSlots + s) * len];
+      const double*& first = src[s > 0 ? s - 1 : 4 + square_class(ex, ey, n)];
+      if (!first) first = b;
+      else if (std::memcmp(first, b, sizeof(double) * len) != 0)
+        throw Error(DCG_EINVAL, "operator blocks differ within a square class");
+    }
+  }
+  for (const double* b : src) out.insert(out.end(), b, b + len);
+}
+
 struct Key {
   int device, n;
   double penalty;
@@ -275,14 +270,21 @@ std::shared_ptr<MeshContext> build_context(int device, int n, double penalty) {
   ctx->ne = n * n;
   ctx->penalty = penalty;
   const int64_t ne = ctx->ne;
-  ctx->Cdiv = static_cast<double2*>(ctx->alloc(sizeof(double) * ne * kSlots * 64));
-  ctx->AdivZ = static_cast<double2*>(ctx->alloc(sizeof(double) * ne * kSlots * 64));
-  ctx->M1 = static_cast<double*>(ctx->alloc(sizeof(double) * ne * 16));
-  ctx->cols = static_cast<int32_t*>(ctx->alloc(sizeof(int32_t) * ne * kSlots));
-  upload_blocks_pairs(row_blocks(hc.Adiv, ne), ne, 8, 8, ctx->Cdiv);
-  upload_blocks_pairs(hc.AdivZ, ne, 16, 4, ctx->AdivZ);
-  DCG_HIP(hipMemcpy(ctx->M1, hc.M1.data(), sizeof(double) * ne * 16, hipMemcpyHostToDevice));
-  upload_cols(hc.cols, ne, ctx->cols);
+  for (int64_t e = 1; e < ne; ++e)
+    if (std::memcmp(&hc.M1[0], &hc.M1[e * 16], sizeof(double) * 16) != 0)
+      throw Error(DCG_EINVAL, "element mass matrices differ");
+  std::vector<double> ct(hc.M1.begin(), hc.M1.begin() + 16), azt;
+  append_block_table(row_blocks(hc.Adiv, ne), n, 64, ct);
+  append_block_table(hc.AdivZ, n, 64, azt);
+  for (size_t o = 0; o < azt.size(); o += 64) {   // [16][4] -> [2][16][2]
+    double t[64];
+    for (int r = 0; r < 16; ++r)
+      for (int c = 0; c < 4; ++c) t[(c >> 1) * 32 + r * 2 + (c & 1)] = azt[o + r * 4 + c];
+    std::memcpy(&azt[o], t, sizeof(t));
+  }
+  if (ct.size() != kCtLen || azt.size() != kAzLen) throw Error(DCG_EDEVICE, "operator table length");
+  ctx->Ct = upload_class_table<double>(ctx.get(), ct);
+  ctx->AZt = upload_class_table<double>(ctx.get(), azt);
   // the tensor blocks are not needed on the host any more
   std::vector<double>().swap(hc.Adiv);
   std::vector<double>().swap(hc.AdivZ);

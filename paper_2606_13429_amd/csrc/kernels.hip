@@ -1,11 +1,7 @@
 // gfx950 kernels of the deflated-CG hot path (paper Section 4, Algorithms 2-4).
 //
-// Everything here is bandwidth bound (well under 1 flop per byte), so the
-// kernels are organised around coalesced 16-byte loads of the stored
-// operators: a wavefront of 64 lanes reads 1 KiB per load instruction, the
-// operator layouts (kernels.hpp) put consecutive lanes on consecutive
-// 16-byte words, and vector operands come from L2 / LDS.  Dot products are
-// two-stage and deterministic: a fixed-order wave64 shuffle tree and an LDS
+// The operators of the uniform grid are tables (kernels.hpp), so the kernels
+// stream vectors only and are bound by those.  Dot products are two-stage and deterministic: a fixed-order wave64 shuffle tree and an LDS
 // tree per workgroup, per-workgroup partials, and one fixed-order final
 // pass (no floating-point atomics anywhere).
 #include <hip/hip_ext.h>
@@ -39,14 +35,8 @@ __device__ inline double block_sum(double v, double* lds) {
   return s;
 }
 
-using mg::ld4;   // 4-vector loads shared with the multigrid kernels
-
-// A 16-byte load with the non-temporal hint, for operator blocks that a
-// launch streams once.
-typedef double stream2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ stream2 load_stream(const double2* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const stream2*>(p));
-}
+using mg::ld4;   // 4-vector loads and stores shared with the multigrid kernels
+using mg::st4;
 
 inline int grid_for(int64_t items, int per_block, int cap) {
   int64_t g = (items + per_block - 1) / per_block;
@@ -55,17 +45,48 @@ inline int grid_for(int64_t items, int per_block, int cap) {
 }
 
 // ============================================================ outer kernels
-// w = (1/nu) M u + dt A_div u, s = Z^T w.  Thread (square e, row r); one
-// workgroup = 16 squares.  M = C (x) M_1 with C the dev-dev coefficient
-// matrix (Section 3.1): rows 11/22 see (u11 - u22)/2, rows 12/21 see u.
 __device__ inline int slot_id(const Slots& sl) { return sl.list ? sl.list[blockIdx.y] : 0; }
 
+// The value of the other lane of a pair (lanes 2 i, 2 i + 1).
+__device__ __forceinline__ double pair_swap(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, int(uint32_t(b)), 0xB1, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), 0xB1, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, uint64_t(uint32_t(lo)) | (uint64_t(uint32_t(hi)) << 32));
+}
+
+// acc += B u for a table block B (8 x 8, column-major, wave-uniform address):
+// two columns of coefficients (32 scalar registers) at a time.
+__device__ __forceinline__ void block_product(const double* __restrict__ B, const double (&u)[8],
+                                              double (&acc)[8]) {
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) acc[r] += B[8 * m + r] * u[m];
+    // keeps the next columns' scalar loads from being hoisted past the
+    // scalar register file; vector memory may pass
+    if (m & 1) __builtin_amdgcn_sched_barrier(0x30);
+  }
+}
+
+// w = (1/nu) M u + dt A_div u, s = Z^T w.  Thread (square e, stress row k),
+// lane pairs sharing a square: the 8 values of stress row k of a square are
+// 64 contiguous bytes and meet the same 8 x 8 block C for both k (A_div =
+// diag(C, C)).  On the uniform grid the block of a neighbour does not depend
+// on the square and the own block only on its class, so the coefficients are
+// the same for all lanes and come through the scalar cache, one of them feeding
+// 64 products; a wavefront with squares of several classes runs the own block
+// once per class.  M = C_dev (x) M_1 with C_dev the dev-dev coefficient matrix
+// (Section 3.1): rows 11/22 see (u11 - u22)/2, rows 12/21 see u.
+// Bound by the vectors (268 MB at n = 1024 in 76 us).  With the blocks of every
+// square read from memory the plain product took 159 us at n = 512 and 650 us
+// at n = 1024 (HBM bound, 0.85 and 3.4 GB); now 29 and 76 us.
 template <int MODE>
 __global__ __launch_bounds__(kThreads) void k_astar(
-    const double2* __restrict__ C, const int32_t* __restrict__ cols, const double* __restrict__ M1,
-    int ne, const double* __restrict__ x, const double* __restrict__ p_old,
-    const double* __restrict__ b, const Scalars* __restrict__ sc, double* __restrict__ p_new,
-    double* __restrict__ w, double* __restrict__ s, double* __restrict__ part, Slots sl) {
+    const double* __restrict__ Ct, int n, const double* __restrict__ x,
+    const double* __restrict__ p_old, const double* __restrict__ b, const Scalars* __restrict__ sc,
+    double* __restrict__ p_new, double* __restrict__ w, double* __restrict__ s,
+    double* __restrict__ part, Slots sl) {
   __shared__ double lds[4];
   const int slot = slot_id(sl);
   x += slot * sl.tstride;
@@ -77,81 +98,105 @@ __global__ __launch_bounds__(kThreads) void k_astar(
   sc += slot;
   if (part) part += slot * kSlotPart;
   const double dt = sc->dt, inv_nu = sc->inv_nu;
-  const int r = threadIdx.x & 15;
   const double beta = MODE == kAstarDir ? sc->beta : 0.0;
-  const int groups = (ne + 15) >> 4;
-  double dot = 0.0;
-  for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-    const int e = (g << 4) + (threadIdx.x >> 4);
-    const bool valid = e < ne;
-    double acc = 0.0, wv = 0.0;
-    // Lane r of a square loads value r of each vector it needs; the 16 lanes of
-    // the square exchange values by shuffles (the neighbour of a slot is the
-    // same for all 16, so the branches and shuffles are uniform within the
-    // group).  u0 = the direction at the own square.
-    double u0 = 0.0;
-    if (valid) {
-      u0 = x[16 * (int64_t)e + r];
-      if (MODE == kAstarDir) u0 += beta * p_old[16 * (int64_t)e + r];
-    }
-    // A_div part, row r of diag(C, C): row r % 8 of C applied to the 8 values
-    // of stress row r / 8 of each neighbour
-    const int o = (r >> 3) * 8;
+  const int ne = n * n;
+  const int id = mg::xcd_band(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
+  const int e = id >> 1, k = id & 1;
+  const bool valid = e < ne;
+  const int ex = e & (n - 1), ey = e / n;
+  auto load = [&](int64_t i, bool ok, double (&u)[8]) {   // u of stress row i = 2 e + k
+    if (ok) {
+      ld4(x + 8 * i, u);
+      ld4(x + 8 * i + 4, u + 4);
+      if (MODE == kAstarDir) {
+        double p[8];
+        ld4(p_old + 8 * i, p);
+        ld4(p_old + 8 * i + 4, p + 4);
 #pragma unroll
-    for (int slot = 0; slot < 5; ++slot) {
-      const int c = valid ? cols[slot * ne + e] : -1;
-      double ur = u0;
-      if (slot != 0 && c >= 0) {
-        ur = x[16 * (int64_t)c + r];
-        if (MODE == kAstarDir) ur += beta * p_old[16 * (int64_t)c + r];
+        for (int m = 0; m < 8; ++m) u[m] += beta * p[m];
       }
-      double u[8];
+    } else {
 #pragma unroll
-      for (int m = 0; m < 8; ++m) u[m] = __shfl(ur, o + m, 16);
-      if (c >= 0) {
-        // the blocks are streamed once per launch: non-temporal loads keep
-        // them from displacing the vectors in the caches (181 -> 168 us at
-        // n = 512)
-        const double2* Cb = C + ((int64_t)slot * 4 * ne + e) * 8 + (r & 7);
-#pragma unroll
-        for (int kc = 0; kc < 4; ++kc) {
-          const stream2 a = load_stream(Cb + (int64_t)kc * ne * 8);
-          acc += a.x * u[2 * kc] + a.y * u[2 * kc + 1];
-        }
-      }
+      for (int m = 0; m < 8; ++m) u[m] = 0.0;
     }
-    // mass part (1/nu)(C_dev (x) M_1) u of the own square: row (cc, j) needs
-    // the corners of sigma_11 and sigma_22 (cc = 0, 3) or of sigma_cc (cc = 1, 2)
-    const int cc = r >> 2, j = r & 3;
-    double s11[4], s22[4], sc4[4];
+  };
+  double u0[8], acc[8];
+  load(id, valid, u0);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) acc[r] = 0.0;
+  {
+    const int cls = square_class(ex, ey, n);
+    uint64_t pending = __ballot(valid);
+    while (pending) {
+      const int c = __builtin_amdgcn_readlane(cls, __builtin_ctzll(pending));
+      const bool mine = valid && cls == c;
+      const double* S = Ct + kCtSelf + 64 * c;
+      double v[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) v[m] = mine ? u0[m] : 0.0;
+      block_product(S, v, acc);
+      pending &= ~__ballot(mine);
+    }
+  }
+  // the neighbours x-1, x+1, y-1, y+1, one ahead of its products
+  auto neighbour = [&](int sn, double (&u)[8]) {
+    const int off = sn == 0 ? -1 : (sn == 1 ? 1 : (sn == 2 ? -n : n));
+    const bool in = valid && (sn == 0 ? ex > 0 : (sn == 1 ? ex < n - 1 : (sn == 2 ? ey > 0 : ey < n - 1)));
+    load(id + 2 * (int64_t)off, in, u);
+  };
+  double un[4][8];
+#pragma unroll
+  for (int sn = 0; sn < 4; ++sn) neighbour(sn, un[sn]);
+#pragma unroll
+  for (int sn = 0; sn < 4; ++sn) block_product(Ct + kCtNbr + 64 * sn, un[sn], acc);
+  // mass part: the diagonal component of this row (row k, component k) and the
+  // other one; wv[r]: component r / 4, corner r % 4
+  double wv[8];
+  {
+    double ud[4], uo[4], d[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      s11[m] = __shfl(u0, m, 16);
-      s22[m] = __shfl(u0, 12 + m, 16);
-      sc4[m] = __shfl(u0, 4 * cc + m, 16);
+      ud[m] = k ? u0[4 + m] : u0[m];
+      uo[m] = k ? u0[m] : u0[4 + m];
+      const double other = pair_swap(ud[m]);
+      d[m] = k ? other - ud[m] : ud[m] - other;   // u11 - u22
     }
-    if (valid) {
-      double m1[4];
-      ld4(M1 + 16 * (int64_t)e + 4 * j, m1);
-      double mu;
-      if (cc == 0 || cc == 3) {
-        mu = 0.5 * (m1[0] * (s11[0] - s22[0]) + m1[1] * (s11[1] - s22[1]) +
-                    m1[2] * (s11[2] - s22[2]) + m1[3] * (s11[3] - s22[3]));
-        if (cc == 3) mu = -mu;
-      } else {
-        mu = m1[0] * sc4[0] + m1[1] * sc4[1] + m1[2] * sc4[2] + m1[3] * sc4[3];
-      }
-      wv = inv_nu * mu + dt * acc;
-      if (MODE == kAstarResidual) {
-        wv = b[16 * (int64_t)e + r] - wv;
-        dot += wv * wv;
-      }
-      if (w) w[16 * (int64_t)e + r] = wv;
-      if (MODE == kAstarDir || MODE == kAstarFirst) p_new[16 * (int64_t)e + r] = u0;
+    const double* M = Ct + kCtMass;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      double md = 0.5 * (M[4 * j] * d[0] + M[4 * j + 1] * d[1] + M[4 * j + 2] * d[2] + M[4 * j + 3] * d[3]);
+      if (k) md = -md;
+      const double mo = M[4 * j] * uo[0] + M[4 * j + 1] * uo[1] + M[4 * j + 2] * uo[2] + M[4 * j + 3] * uo[3];
+      wv[j] = inv_nu * (k ? mo : md) + dt * acc[j];
+      wv[4 + j] = inv_nu * (k ? md : mo) + dt * acc[4 + j];
     }
-    // s = Z^T w: lanes r = j and r = 12 + j of the same square
-    const double w22 = __shfl_down(wv, 12, 16);
-    if (s && valid && r < 4) s[4 * (int64_t)e + r] = (wv + w22) * kInvSqrt2;
+  }
+  double dot = 0.0;
+  if (MODE == kAstarResidual && valid) {
+    double bv[8];
+    ld4(b + 8 * (int64_t)id, bv);
+    ld4(b + 8 * (int64_t)id + 4, bv + 4);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      wv[r] = bv[r] - wv[r];
+      dot += wv[r] * wv[r];
+    }
+  }
+  if (valid) {
+    if (w) {
+      st4(w + 8 * (int64_t)id, wv);
+      st4(w + 8 * (int64_t)id + 4, wv + 4);
+    }
+    if (MODE == kAstarDir || MODE == kAstarFirst) {
+      st4(p_new + 8 * (int64_t)id, u0);
+      st4(p_new + 8 * (int64_t)id + 4, u0 + 4);
+    }
+  }
+  if (s) {   // s = Z^T w: w11 of the even lane, w22 of the odd one
+    double sv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sv[j] = (wv[j] + pair_swap(wv[4 + j])) * kInvSqrt2;
+    if (valid && !k) st4(s + 4 * (int64_t)e, sv);
   }
   if (MODE == kAstarResidual) {
     const double t = block_sum(dot, lds);
@@ -159,13 +204,49 @@ __global__ __launch_bounds__(kThreads) void k_astar(
   }
 }
 
+// Row r of A_div Z at square e: the table's neighbour blocks and the own one of
+// the square's class times z of the square and its neighbours; az in LDS.
+__device__ __forceinline__ double az_row(const double* az, int r, int e, int n,
+                                         const double* __restrict__ z) {
+  const int ex = e & (n - 1), ey = e / n;
+  double zc[5][4];
+#pragma unroll
+  for (int sn = 0; sn < 5; ++sn) {
+    const int off = sn == 1 ? -1 : (sn == 2 ? 1 : (sn == 3 ? -n : (sn == 4 ? n : 0)));
+    const bool in = sn == 0 || (sn == 1 ? ex > 0 : (sn == 2 ? ex < n - 1 : (sn == 3 ? ey > 0 : ey < n - 1)));
+#pragma unroll
+    for (int m = 0; m < 4; ++m) zc[sn][m] = 0.0;
+    if (in) ld4(z + 4 * ((int64_t)e + off), zc[sn]);
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int sn = 0; sn < 5; ++sn) {
+    const double2* c = reinterpret_cast<const double2*>(
+        az + (sn == 0 ? kAzSelf + 64 * square_class(ex, ey, n) : kAzNbr + 64 * (sn - 1))) + r;
+    const double2 c0 = c[0], c1 = c[16];
+    acc += c0.x * zc[sn][0] + c0.y * zc[sn][1] + c1.x * zc[sn][2] + c1.y * zc[sn][3];
+  }
+  return acc;
+}
+
+__device__ __forceinline__ void az_stage(const double* __restrict__ AZ, double* az) {
+  for (int i = threadIdx.x; i < kAzLen / 2; i += kThreads)
+    reinterpret_cast<double2*>(az)[i] = reinterpret_cast<const double2*>(AZ)[i];
+  __syncthreads();
+}
+
 // q = w - c (A_div Z) z, partial (p, q); prologue: r = w - c AZ z -> q, p_out,
-// partials (w, w), (r, r).
+// partials (w, w), (r, r).  Thread (square, row), 16 squares per workgroup and
+// trip; a workgroup takes a contiguous range of squares and keeps the table
+// (6.5 KB) in LDS: in registers it left 16 wavefronts a compute unit, too few
+// to hide the trips' loads (35 us at n = 512, 32 us so).  Bound by w, p and q:
+// 108 MB at n = 512 (128 us with the blocks of every square read from memory).
 template <bool PROLOGUE>
 __global__ __launch_bounds__(kThreads) void k_deflate(
-    const double2* __restrict__ AZ, const int32_t* __restrict__ cols, int ne, double c,
-    const double* __restrict__ z, const double* __restrict__ w, const double* __restrict__ p,
-    double* __restrict__ q, double* __restrict__ p_out, double* __restrict__ part, Slots sl) {
+    const double* __restrict__ AZ, int n, double c, const double* __restrict__ z,
+    const double* __restrict__ w, const double* __restrict__ p, double* __restrict__ q,
+    double* __restrict__ p_out, double* __restrict__ part, Slots sl) {
+  __shared__ __align__(16) double az[kAzLen];
   __shared__ double lds[4];
   const int slot = slot_id(sl);
   z += slot * sl.sstride;
@@ -174,33 +255,26 @@ __global__ __launch_bounds__(kThreads) void k_deflate(
   q += slot * sl.tstride;
   if (p_out) p_out += slot * sl.tstride;
   part += slot * kSlotPart;
-  const int r = threadIdx.x & 15;
-  const int groups = (ne + 15) >> 4;
+  const int ne = n * n, r = threadIdx.x & 15;
+  const int groups = (ne + 15) >> 4, per = (groups + gridDim.x - 1) / gridDim.x;
+  const int g0 = mg::xcd_band(blockIdx.x, gridDim.x) * per;
+  const int g1 = g0 + per < groups ? g0 + per : groups;
+  az_stage(AZ, az);
   double d0 = 0.0, d1 = 0.0;
-  for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-    const int e = (g << 4) + (threadIdx.x >> 4);
-    if (e >= ne) continue;
-    double acc = 0.0;
-#pragma unroll
-    for (int slot = 0; slot < 5; ++slot) {
-      const int col = cols[slot * ne + e];
-      if (col < 0) continue;
-      const double2* zc = reinterpret_cast<const double2*>(z + 4 * (int64_t)col);
-      const double2* Ab = AZ + ((int64_t)slot * 2 * ne + e) * 16 + r;
-      const stream2 a0 = load_stream(Ab), a1 = load_stream(Ab + (int64_t)ne * 16);
-      const double2 z0 = zc[0], z1 = zc[1];
-      acc += a0.x * z0.x + a0.y * z0.y + a1.x * z1.x + a1.y * z1.y;
-    }
+#pragma unroll 2
+  for (int g = g0; g < g1; ++g) {
+    const int e = (g << 4) + (threadIdx.x >> 4);   // ne is a multiple of 16
     const int64_t i = 16 * (int64_t)e + r;
     const double wv = w[i];
-    const double qv = wv - c * acc;
+    const double pv = PROLOGUE ? 0.0 : p[i];
+    const double qv = wv - c * az_row(az, r, e, n, z);
     q[i] = qv;
     if (PROLOGUE) {
       p_out[i] = qv;
       d0 += wv * wv;
       d1 += qv * qv;
     } else {
-      d0 += p[i] * qv;
+      d0 += pv * qv;
     }
   }
   const double t0 = block_sum(d0, lds);
@@ -211,23 +285,15 @@ __global__ __launch_bounds__(kThreads) void k_deflate(
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_adivz(const double2* __restrict__ AZ,
-                                                    const int32_t* __restrict__ cols, int ne,
+__global__ __launch_bounds__(kThreads) void k_adivz(const double* __restrict__ AZ, int n,
                                                     const double* __restrict__ y,
                                                     double* __restrict__ out) {
+  __shared__ __align__(16) double az[kAzLen];
   const int e = blockIdx.x * 16 + (threadIdx.x >> 4);
   const int r = threadIdx.x & 15;
-  if (e >= ne) return;
-  double acc = 0.0;
-  for (int slot = 0; slot < 5; ++slot) {
-    const int col = cols[slot * ne + e];
-    if (col < 0) continue;
-    const double2* zc = reinterpret_cast<const double2*>(y + 4 * (int64_t)col);
-    const double2* Ab = AZ + ((int64_t)slot * 2 * ne + e) * 16 + r;
-    const double2 a0 = Ab[0], a1 = Ab[(int64_t)ne * 16];
-    acc += a0.x * zc[0].x + a0.y * zc[0].y + a1.x * zc[1].x + a1.y * zc[1].y;
-  }
-  out[16 * (int64_t)e + r] = acc;
+  az_stage(AZ, az);
+  if (e >= n * n) return;
+  out[16 * (int64_t)e + r] = az_row(az, r, e, n, y);
 }
 
 // x += alpha p; r -= alpha q; partial (r, r) [flexible: (r,q), (p,r)]
@@ -286,10 +352,13 @@ __global__ __launch_bounds__(kThreads) void k_axpy_dot(int64_t n, double a,
   if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(kThreads) void k_reduce(const double* __restrict__ part, int nb,
+// One workgroup of 16 wavefronts: the partials of a launch are a few loads per
+// thread, then a shuffle tree and one pass over the wavefront sums (fixed order).
+constexpr int kReduceThreads = 1024;
+__global__ __launch_bounds__(kReduceThreads) void k_reduce(const double* __restrict__ part, int nb,
                                                      int op, Scalars* __restrict__ sc, Slots sl,
                                                      double aux, int iaux) {
-  __shared__ double sm[kThreads];
+  __shared__ double sm[kReduceThreads / 64];
   const int slot = slot_id(sl);
   part += slot * kSlotPart;
   sc += slot;
@@ -298,14 +367,16 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const double* __restrict__ 
   double sums[3] = {0.0, 0.0, 0.0};
   for (int slot = 0; slot < nslot; ++slot) {
     double v = 0.0;
-    for (int i = threadIdx.x; i < nb; i += kThreads) v += part[slot * kPartStride + i];
-    sm[threadIdx.x] = v;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nb; i += kReduceThreads) v += part[slot * kPartStride + i];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int h = kThreads / 2; h > 0; h >>= 1) {
-      if (threadIdx.x < h) sm[threadIdx.x] += sm[threadIdx.x + h];
-      __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int i = 0; i < kReduceThreads / 64; ++i) t += sm[i];
+      sums[slot] = t;
     }
-    sums[slot] = sm[0];
     __syncthreads();
   }
   if (threadIdx.x != 0) return;
@@ -461,7 +532,7 @@ __global__ __launch_bounds__(kThreads) void k_reconstruct(int ne, const double* 
 
 // BDF2 right-hand side and warm start: f = (1/nu) (C (x) M_1)(4/3 s1 - 1/3 s2)
 // + c F, x0 = 2 s1 - s2; thread (square, row).
-__global__ __launch_bounds__(kThreads) void k_bdf2_rhs(int ne, const double* __restrict__ M1,
+__global__ __launch_bounds__(kThreads) void k_bdf2_rhs(int ne, const double* __restrict__ Ct,
                                                        double inv_nu, const double* __restrict__ s1,
                                                        const double* __restrict__ s2,
                                                        const double* __restrict__ F, double c,
@@ -476,7 +547,7 @@ __global__ __launch_bounds__(kThreads) void k_bdf2_rhs(int ne, const double* __r
   for (int k = 0; k < 16; ++k)
     u[k] = 4.0 / 3.0 * s1[16 * e + k] - 1.0 / 3.0 * s2[16 * e + k];
   double m[4];
-  ld4(M1 + 16 * e + 4 * j, m);
+  ld4(Ct + kCtMass + 4 * j, m);
   double mu;
   if (cc == 0 || cc == 3) {
     mu = 0.5 * (m[0] * (u[0] - u[12]) + m[1] * (u[1] - u[13]) + m[2] * (u[2] - u[14]) +
@@ -653,51 +724,46 @@ __global__ __launch_bounds__(kThreads) void k_copy(int64_t n, const T* __restric
 }  // namespace
 
 // ============================================================ launchers
-hipError_t launch_astar(int mode, const double2* C, const int32_t* cols, const double* M1, int ne,
-                        const double* x, const double* p_old, const double* b, const Scalars* sc,
-                        double* p_new, double* w, double* s, double* part, hipStream_t st,
-                        const Slots& sl, int count, hipEvent_t ev0, hipEvent_t ev1) {
-  const dim3 grid(grid_for(ne, 16, kPartStride), count);
+hipError_t launch_astar(int mode, const double* Ct, int n, const double* x, const double* p_old,
+                        const double* b, const Scalars* sc, double* p_new, double* w, double* s,
+                        double* part, hipStream_t st, const Slots& sl, int count, hipEvent_t ev0,
+                        hipEvent_t ev1) {
+  if (n < 16 || (n & (n - 1))) return hipErrorInvalidValue;   // squares of a row by masking
+  const dim3 grid(astar_blocks(n * n), count);
   // timed launches record their events in the dispatch packet itself
+#define DCG_ASTAR(M)                                                                            \
+  hipExtLaunchKernelGGL(k_astar<M>, grid, dim3(kThreads), 0, st, ev0, ev1, 0, Ct, n, x, p_old, b, \
+                        sc, p_new, w, s, part, sl)
   switch (mode) {
-    case kAstarPlain:
-      hipExtLaunchKernelGGL(k_astar<kAstarPlain>, grid, dim3(kThreads), 0, st, ev0, ev1, 0, C, cols,
-                            M1, ne, x, p_old, b, sc, p_new, w, s, part, sl);
-      break;
-    case kAstarDir:
-      hipExtLaunchKernelGGL(k_astar<kAstarDir>, grid, dim3(kThreads), 0, st, ev0, ev1, 0, C, cols,
-                            M1, ne, x, p_old, b, sc, p_new, w, s, part, sl);
-      break;
-    case kAstarFirst:
-      hipExtLaunchKernelGGL(k_astar<kAstarFirst>, grid, dim3(kThreads), 0, st, ev0, ev1, 0, C, cols,
-                            M1, ne, x, p_old, b, sc, p_new, w, s, part, sl);
-      break;
-    case kAstarResidual:
-      hipExtLaunchKernelGGL(k_astar<kAstarResidual>, grid, dim3(kThreads), 0, st, ev0, ev1, 0, C,
-                            cols, M1, ne, x, p_old, b, sc, p_new, w, s, part, sl);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case kAstarPlain: DCG_ASTAR(kAstarPlain); break;
+    case kAstarDir: DCG_ASTAR(kAstarDir); break;
+    case kAstarFirst: DCG_ASTAR(kAstarFirst); break;
+    case kAstarResidual: DCG_ASTAR(kAstarResidual); break;
+    default: return hipErrorInvalidValue;
   }
+#undef DCG_ASTAR
   return hipGetLastError();
 }
 
-int astar_blocks(int ne) { return grid_for(ne, 16, kPartStride); }
+// one thread per square and stress row; n <= 2048 keeps it under kPartStride
+int astar_blocks(int ne) { return (2 * ne + kThreads - 1) / kThreads; }
+int deflate_blocks(int ne) { return grid_for(ne, 16, 2048); }
 
-hipError_t launch_deflate(bool prologue, const double2* AZ, const int32_t* cols, int ne, double c,
-                          const double* z, const double* w, const double* p, double* q,
-                          double* p_out, double* part, hipStream_t st, const Slots& sl, int count) {
-  const dim3 grid(grid_for(ne, 16, kPartStride), count);
+hipError_t launch_deflate(bool prologue, const double* AZ, int n, double c, const double* z,
+                          const double* w, const double* p, double* q, double* p_out, double* part,
+                          hipStream_t st, const Slots& sl, int count) {
+  if (n < 16 || (n & (n - 1))) return hipErrorInvalidValue;
+  const dim3 grid(deflate_blocks(n * n), count);
   if (prologue)
-    k_deflate<true><<<grid, kThreads, 0, st>>>(AZ, cols, ne, c, z, w, p, q, p_out, part, sl);
+    k_deflate<true><<<grid, kThreads, 0, st>>>(AZ, n, c, z, w, p, q, p_out, part, sl);
   else
-    k_deflate<false><<<grid, kThreads, 0, st>>>(AZ, cols, ne, c, z, w, p, q, p_out, part, sl);
+    k_deflate<false><<<grid, kThreads, 0, st>>>(AZ, n, c, z, w, p, q, p_out, part, sl);
   return hipGetLastError();
 }
 
-hipError_t launch_adivz(const double2* AZ, const int32_t* cols, int ne, const double* y, double* out,
-                        hipStream_t st) {
-  k_adivz<<<grid_for(ne, 16, 1 << 30), kThreads, 0, st>>>(AZ, cols, ne, y, out);
+hipError_t launch_adivz(const double* AZ, int n, const double* y, double* out, hipStream_t st) {
+  if (n < 16 || (n & (n - 1))) return hipErrorInvalidValue;
+  k_adivz<<<grid_for(n * n, 16, 1 << 30), kThreads, 0, st>>>(AZ, n, y, out);
   return hipGetLastError();
 }
 
@@ -744,7 +810,7 @@ hipError_t launch_axpy_dot(int64_t nvec, double a, const double* q, double* r, d
 
 hipError_t launch_reduce(const double* part, int nblocks, int op, Scalars* sc, hipStream_t st,
                          const Slots& sl, int count, double aux, int iaux) {
-  k_reduce<<<dim3(1, count), kThreads, 0, st>>>(part, nblocks, op, sc, sl, aux, iaux);
+  k_reduce<<<dim3(1, count), kReduceThreads, 0, st>>>(part, nblocks, op, sc, sl, aux, iaux);
   return hipGetLastError();
 }
 
@@ -766,10 +832,10 @@ hipError_t launch_reconstruct(int ne, const double* xh, const double* zt, const 
   return hipGetLastError();
 }
 
-hipError_t launch_bdf2_rhs(int ne, const double* M1, double inv_nu, const double* s1,
+hipError_t launch_bdf2_rhs(int ne, const double* Ct, double inv_nu, const double* s1,
                            const double* s2, const double* F, double c, double* f, double* x0,
                            hipStream_t st) {
-  k_bdf2_rhs<<<grid_for(16 * (int64_t)ne, kThreads, 1 << 30), kThreads, 0, st>>>(ne, M1, inv_nu, s1, s2,
+  k_bdf2_rhs<<<grid_for(16 * (int64_t)ne, kThreads, 1 << 30), kThreads, 0, st>>>(ne, Ct, inv_nu, s1, s2,
                                                                                 F, c, f, x0);
   return hipGetLastError();
 }

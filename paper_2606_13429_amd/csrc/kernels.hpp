@@ -5,10 +5,9 @@
 // a product can exceed 2^31):
 //   tensor vectors   [16 e + 4 c + j]                 (FP64)
 //   scalar vectors   [4 e + j]                        (FP64 or level real T)
-//   A_div = diag(C, C) per block (one C for each stress row), stored as
-//   C                double2 [slot][kc=4][Ne][row=8]   row r, columns 2kc, 2kc+1
-//   A_div Z          double2 [slot][kc=2][Ne][row=16]
-//   M_1              double  [Ne][16]
+//   A_div, M_1       double  table Ct (below): A_div = diag(C, C) per block (one
+//                    8 x 8 block C for each stress row)
+//   A_div Z          double  table AZt (below), blocks 16 x 4
 //   L_k              T       [slot][Ne][row=4][4]
 //   cols             int32   [slot][Ne]               -1 = none
 //   RAS factors      T       [class][36 blocks P <= Q][16][16]  packed upper blocks of the
@@ -102,25 +101,33 @@ __host__ __device__ inline int square_class(int ex, int ey, int n) {
   return 3 * cy + cx;
 }
 
+// Operator tables of the tensor products.  On the uniform grid the block that
+// couples a square to its neighbour in a direction is the same for every
+// square that has one, and the own block depends on the square's class only
+// (the host checks both bit for bit), so the operators are two tables of a
+// few KB:
+//   Ct   [M_1 4 x 4][C of x-1, x+1, y-1, y+1][own C per class], C 8 x 8 column-major
+//   AZt  [A_div Z of x-1, x+1, y-1, y+1][own per class], blocks 16 x 4 as [columns 0, 1 | 2, 3][row][2]
+constexpr int kCtMass = 0, kCtNbr = 16, kCtSelf = kCtNbr + 4 * 64, kCtLen = kCtSelf + 9 * 64;
+constexpr int kAzNbr = 0, kAzSelf = 4 * 64, kAzLen = kAzSelf + 9 * 64;
+
 // workgroups (= partial sums) of the reducing launches for ``ne`` squares
-int astar_blocks(int ne);     // launch_astar and launch_deflate
+int astar_blocks(int ne);     // launch_astar
+int deflate_blocks(int ne);   // launch_deflate
 int refine_blocks(int ne);    // launch_refine_residual
 
 // (ev0, ev1: when non-null, recorded at the start and end of the dispatch)
-hipError_t launch_astar(int mode, const double2* C, const int32_t* cols, const double* M1, int ne,
-                        const double* x, const double* p_old, const double* b, const Scalars* sc,
-                        double* p_new, double* w, double* s, double* part, hipStream_t st,
-                        const Slots& sl = Slots(), int count = 1, hipEvent_t ev0 = nullptr,
-                        hipEvent_t ev1 = nullptr);
+hipError_t launch_astar(int mode, const double* Ct, int n, const double* x, const double* p_old,
+                        const double* b, const Scalars* sc, double* p_new, double* w, double* s,
+                        double* part, hipStream_t st, const Slots& sl = Slots(), int count = 1,
+                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // q = w - c * (A_div Z) z ; partial (p, q).  With ``prologue``: r = w - c AZ z
 // written to q and to p_out, partials (w, w) and (q, q).
-hipError_t launch_deflate(bool prologue, const double2* AZ, const int32_t* cols, int ne, double c,
-                          const double* z, const double* w, const double* p, double* q,
-                          double* p_out, double* part, hipStream_t st, const Slots& sl = Slots(),
-                          int count = 1);
+hipError_t launch_deflate(bool prologue, const double* AZ, int n, double c, const double* z,
+                          const double* w, const double* p, double* q, double* p_out, double* part,
+                          hipStream_t st, const Slots& sl = Slots(), int count = 1);
 // q = AZ y (plain product, no partials)
-hipError_t launch_adivz(const double2* AZ, const int32_t* cols, int ne, const double* y, double* out,
-                        hipStream_t st);
+hipError_t launch_adivz(const double* AZ, int n, const double* y, double* out, hipStream_t st);
 // x += alpha p ; r -= alpha q ; partial (r, r)  [flexible: + (r,q), (p,r)]
 hipError_t launch_cg_update(bool flexible, int64_t nvec, const Scalars* sc, const double* p,
                             const double* q, double* x, double* r, double* part, int* nblocks,
@@ -140,7 +147,7 @@ hipError_t launch_reconstruct(int ne, const double* xh, const double* zt, const 
                               const Slots& sl = Slots(), int count = 1);
 hipError_t launch_scale(int64_t n, double c, const double* in, double* out, hipStream_t st);
 // f = (1/nu) M (4/3 s1 - 1/3 s2) + c F ; x0 = 2 s1 - s2
-hipError_t launch_bdf2_rhs(int ne, const double* M1, double inv_nu, const double* s1,
+hipError_t launch_bdf2_rhs(int ne, const double* Ct, double inv_nu, const double* s1,
                            const double* s2, const double* F, double c, double* f, double* x0,
                            hipStream_t st);
 

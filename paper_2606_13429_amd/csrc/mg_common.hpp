@@ -139,6 +139,12 @@ __device__ __forceinline__ int xcd_band_index(int b, int G) {
   return ((G & 7) || G > kXcdBandMaxGrid) ? b : (b & 7) * (G >> 3) + (b >> 3);
 }
 
+// The same order without the size limit, for launches that stream vectors only
+// (each XCD then reads contiguous rows of squares).
+__device__ __forceinline__ int xcd_band(int b, int G) {
+  return (G & 7) ? b : (b & 7) * (G >> 3) + (b >> 3);
+}
+
 // Index of block (P, Q), P <= Q, in the packed upper-triangular order
 // (row by row) of the symmetric tile inverses.
 __host__ __device__ constexpr int blk_index(int P, int Q) { return P * (15 - P) / 2 + Q; }

@@ -60,10 +60,8 @@ struct MeshContext {
   int device = 0;
   int n = 0, J = 0, ne = 0;
   double penalty = 10.0;
-  double2* Cdiv = nullptr;        // [5][4][ne][8]: A_div = diag(C, C) per block
-  double2* AdivZ = nullptr;       // [5][2][ne][16]
-  double* M1 = nullptr;           // [ne][16]
-  int32_t* cols = nullptr;        // [5][ne]
+  double* Ct = nullptr;           // tables of A_div and M_1, and of A_div Z (kernels.hpp)
+  double* AZt = nullptr;
   std::vector<DeviceLevel> lv;    // lv[k - 1]
   double* coarse_inv = nullptr;   // [1024][1024]
   size_t bytes = 0;

@@ -149,9 +149,7 @@ size_t workspace_bytes(int n, bool fp32) {
 
 // Bytes of a mesh context (the allocations of the context upload).
 size_t context_bytes(int n, bool fp32) {
-  const size_t ne = size_t(n) * n;
-  size_t b = ne * kSlots * (64 + 64) * sizeof(double) + ne * 16 * sizeof(double) +
-             ne * kSlots * sizeof(int32_t);
+  size_t b = (kCtLen + kAzLen) * sizeof(double);
   for (int nk = n; nk >= kCoarsestN; nk /= 2) {
     const size_t nek = size_t(nk) * nk;
     b += nek * kSlots * (sizeof(int32_t) + 16 * sizeof(double) + (fp32 ? 16 * sizeof(float) : 0));
@@ -423,20 +421,20 @@ void Server::Impl::enqueue_step(Group& g) {
                          hipMemcpyHostToDevice, st));
   auto cnt = [&](int list) { return g.counts[list]; };
   auto sl = [&](int list) { return slot_addr(g, list); };
-  const int nbA = astar_blocks(ne);
+  const int nbD = deflate_blocks(ne);
 
   // outer-iteration work
   if (cnt(kLDeflPro)) {
-    DCG_HIP(launch_deflate(true, m.AdivZ, m.cols, ne, kTwo, g.zb, g.b, nullptr, g.r, g.p[0],
+    DCG_HIP(launch_deflate(true, m.AZt, m.n, kTwo, g.zb, g.b, nullptr, g.r, g.p[0],
                            g.ws.part, st, sl(kLDeflPro), cnt(kLDeflPro)));
-    DCG_HIP(launch_reduce(g.ws.part, nbA, kRedB2Rho, g.ws.sc, st, sl(kLDeflPro), cnt(kLDeflPro)));
+    DCG_HIP(launch_reduce(g.ws.part, nbD, kRedB2Rho, g.ws.sc, st, sl(kLDeflPro), cnt(kLDeflPro)));
   }
   for (int pi = 0; pi < 2; ++pi) {
     const int list = pi ? kLDeflIter1 : kLDeflIter0;
     if (!cnt(list)) continue;
-    DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, g.zref, g.w, g.p[pi], g.q, nullptr,
+    DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, g.zref, g.w, g.p[pi], g.q, nullptr,
                            g.ws.part, st, sl(list), cnt(list)));
-    DCG_HIP(launch_reduce(g.ws.part, nbA, flex ? kRedFcgAlpha : kRedAlpha, g.ws.sc, st, sl(list),
+    DCG_HIP(launch_reduce(g.ws.part, nbD, flex ? kRedFcgAlpha : kRedAlpha, g.ws.sc, st, sl(list),
                           cnt(list)));
     int nbu = 0;
     DCG_HIP(launch_cg_update(flex, g.N, g.ws.sc, g.p[pi], g.q, g.xh, g.r, g.ws.part, &nbu, st,
@@ -447,9 +445,9 @@ void Server::Impl::enqueue_step(Group& g) {
   if (cnt(kLPostEpi)) {
     const int c = cnt(kLPostEpi);
     DCG_HIP(launch_reconstruct(ne, g.xh, g.zref, g.zb, g.ws.sc, g.q, st, sl(kLPostEpi), c));
-    DCG_HIP(launch_astar(kAstarResidual, m.Cdiv, m.cols, m.M1, ne, g.q, nullptr, g.b, g.ws.sc,
+    DCG_HIP(launch_astar(kAstarResidual, m.Ct, m.n, g.q, nullptr, g.b, g.ws.sc,
                          nullptr, g.w, nullptr, g.ws.part, st, sl(kLPostEpi), c));
-    DCG_HIP(launch_reduce(g.ws.part, nbA, kRedRes, g.ws.sc, st, sl(kLPostEpi), c));
+    DCG_HIP(launch_reduce(g.ws.part, astar_blocks(ne), kRedRes, g.ws.sc, st, sl(kLPostEpi), c));
     for (int k = 0; k < c; ++k) {
       const int i = L[kLPostEpi * kBatch + k];
       DCG_HIP(hipMemcpyAsync(g.slots[i].req->x, g.q + i * g.N, sizeof(double) * g.N,
@@ -459,16 +457,16 @@ void Server::Impl::enqueue_step(Group& g) {
   // the next inner right-hand side s = Z^T (...)
   if (cnt(kLZt)) DCG_HIP(launch_zt(ne, g.b, g.s, st, sl(kLZt), cnt(kLZt)));
   if (cnt(kLAstarFirst))
-    DCG_HIP(launch_astar(kAstarFirst, m.Cdiv, m.cols, m.M1, ne, g.r, g.p[0], nullptr, g.ws.sc,
+    DCG_HIP(launch_astar(kAstarFirst, m.Ct, m.n, g.r, g.p[0], nullptr, g.ws.sc,
                          g.p[1], g.w, g.s, nullptr, st, sl(kLAstarFirst), cnt(kLAstarFirst)));
   for (int pi = 0; pi < 2; ++pi) {
     const int list = pi ? kLAstarDir1 : kLAstarDir0;
     if (!cnt(list)) continue;
-    DCG_HIP(launch_astar(kAstarDir, m.Cdiv, m.cols, m.M1, ne, g.r, g.p[pi], nullptr, g.ws.sc,
+    DCG_HIP(launch_astar(kAstarDir, m.Ct, m.n, g.r, g.p[pi], nullptr, g.ws.sc,
                          g.p[1 - pi], g.w, g.s, nullptr, st, sl(list), cnt(list)));
   }
   if (cnt(kLAstarPlain))
-    DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, g.xh, nullptr, nullptr, g.ws.sc,
+    DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, g.xh, nullptr, nullptr, g.ws.sc,
                          nullptr, g.w, g.s, nullptr, st, sl(kLAstarPlain), cnt(kLAstarPlain)));
 
   // inner Multigrid iteration: starts, one batched W-cycle, refinement

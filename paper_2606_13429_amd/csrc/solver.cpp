@@ -193,14 +193,15 @@ LvState run_wcycle_finest(dcg_ctx* h, const InnerWs& w, hipStream_t st) {
 }
 
 // Resets the device scalar block and stores the operator parameters dt, 1/nu
-// the kernels read from it.
+// the kernels read from it (at setup, so that dcg_apply finds them there, and
+// at the start of a solve).  No wait: the pinned block is next written by the
+// copy back that the stream runs after this one.
 void set_params(dcg_ctx* h, hipStream_t st) {
   Scalars init{};
   init.dt = h->dt;
   init.inv_nu = 1.0 / h->nu;
   *h->ws.sc_host = init;
   DCG_HIP(hipMemcpyAsync(h->ws.sc, h->ws.sc_host, sizeof(Scalars), hipMemcpyHostToDevice, st));
-  DCG_HIP(hipStreamSynchronize(st));
 }
 
 void read_scalars(dcg_ctx* h, const Scalars* sc, hipStream_t st) {
@@ -300,8 +301,8 @@ void handle_init(dcg_ctx* h) {
   ws.part = static_cast<double*>(ws.alloc(sizeof(double) * 3 * kPartStride));
   ws.sc = static_cast<Scalars*>(ws.alloc(sizeof(Scalars)));
   DCG_HIP(hipHostMalloc(reinterpret_cast<void**>(&ws.sc_host), sizeof(Scalars), hipHostMallocDefault));
-  std::memset(ws.sc_host, 0, sizeof(Scalars));
-  DCG_HIP(hipMemcpy(ws.sc, ws.sc_host, sizeof(Scalars), hipMemcpyHostToDevice));
+  set_params(h, nullptr);
+  DCG_HIP(hipStreamSynchronize(nullptr));
   ws.lvb.allocate(m, h->fp32, false, ws);
   LevelBuffers& nl = h->noalloc_lvb;
   nl.f.assign(m.J, nullptr);
@@ -396,7 +397,7 @@ dcg_status outer_fcg(dcg_ctx* h, double lim, double& rho, int& it, int& cycles_t
   const bool inf = h->opt.m_max == 0;
   const int R = inf ? h->opt.max_outer + 1 : h->opt.m_max + 1;
   store_reserve(fs, R, N);
-  const int nbA = astar_blocks(ne);
+  const int nbD = deflate_blocks(ne);
   dcg_status status = DCG_OK;
   for (int i = 0;; ++i) {   // i: iteration of this pass (the window restarts with a pass)
     if (rho <= lim) break;
@@ -419,15 +420,15 @@ dcg_status outer_fcg(dcg_ctx* h, double lim, double& rho, int& it, int& cycles_t
     DCG_HIP(launch_fcg_direction(N, base, ws.r, fs.dptr, first, mi, R, fs.coef, fs.d[slot], ws.part,
                                  &nbd, st));
     DCG_HIP(launch_reduce(ws.part, nbd, kRedDr, ws.sc, st));
-    DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, fs.d[slot], nullptr, nullptr,
+    DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, fs.d[slot], nullptr, nullptr,
                          ws.sc, nullptr, ws.w, ws.s, nullptr, st));
     const int c = inner(h, ws.s, ws.zref, tol_outer(rho), st);
     cycles_total += c;
     cycles_outer += c;
     ++inner_solves;
-    DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, ws.zref, ws.w, fs.d[slot], fs.q[slot],
+    DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, ws.zref, ws.w, fs.d[slot], fs.q[slot],
                            nullptr, ws.part, st));
-    DCG_HIP(launch_reduce(ws.part, nbA, kRedFcgAlpha, ws.sc, st));   // alpha = (d, r) / (d, q)
+    DCG_HIP(launch_reduce(ws.part, nbD, kRedFcgAlpha, ws.sc, st));   // alpha = (d, r) / (d, q)
     DCG_HIP(launch_copy<double>(1, &ws.sc->pq, fs.dq + slot, st));
     int nbu = 0;
     DCG_HIP(launch_cg_update(false, N, ws.sc, fs.d[slot], fs.q[slot], ws.xh, ws.r, ws.part, &nbu, st));
@@ -479,13 +480,13 @@ dcg_status outer_gmres(dcg_ctx* h, double lim, double& rho, int& it, int& cycles
     }
     const int j = it - it0;
     // q = M_D v_j
-    DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, fs.d[j], nullptr, nullptr, ws.sc,
+    DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, fs.d[j], nullptr, nullptr, ws.sc,
                          nullptr, ws.w, ws.s, nullptr, st));
     const int c = inner(h, ws.s, ws.zref, tol_outer(rnorm * rnorm), st);
     cycles_total += c;
     cycles_outer += c;
     ++inner_solves;
-    DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, ws.zref, ws.w, fs.d[j], ws.q, nullptr,
+    DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, ws.zref, ws.w, fs.d[j], ws.q, nullptr,
                            ws.part, st));
     // two Gram-Schmidt passes in place on q, then ||q||^2
     int nbd = 0;
@@ -559,7 +560,7 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
   // inside the outer loop with c_A tol for the prologue, start and epilogue solves
   const bool adaptive = h->opt.c_A > 0.0;
   const double tol_c = adaptive ? h->opt.c_A * tol : h->opt.c_F * tol;
-  const int nbA = astar_blocks(ne);
+  const int nbD = deflate_blocks(ne);
   dcg_stats stats{};
   int cycles_total = 0, inner_solves = 0, cycles_outer = 0;
   set_params(h, stream);
@@ -568,9 +569,9 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
   DCG_HIP(launch_zt(ne, b, ws.s, stream));
   cycles_total += inner(h, ws.s, ws.zb, tol_c, stream);
   ++inner_solves;
-  DCG_HIP(launch_deflate(true, m.AdivZ, m.cols, ne, kTwo, ws.zb, b, nullptr, ws.r, ws.p[0], ws.part,
+  DCG_HIP(launch_deflate(true, m.AZt, m.n, kTwo, ws.zb, b, nullptr, ws.r, ws.p[0], ws.part,
                          stream));
-  DCG_HIP(launch_reduce(ws.part, nbA, kRedB2Rho, ws.sc, stream));
+  DCG_HIP(launch_reduce(ws.part, nbD, kRedB2Rho, ws.sc, stream));
   read_scalars(h, stream);
   const double b2 = ws.sc_host->b2;
   if (!std::isfinite(b2) || !std::isfinite(ws.sc_host->rho))
@@ -600,11 +601,11 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
       // y_0 = E^{-1} Z^T A* x (Algorithm 1 applied to the deflated system);
       // ws.r holds f_D
       DCG_HIP(launch_copy<double>(N, x, ws.xh, stream));
-      DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, ws.xh, nullptr, nullptr,
+      DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, ws.xh, nullptr, nullptr,
                            ws.sc, nullptr, ws.w, ws.s, nullptr, stream));
       cycles_total += inner(h, ws.s, ws.zt, tol_c, stream);
       ++inner_solves;
-      DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, ws.zt, ws.w, ws.w, ws.q, nullptr,
+      DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, ws.zt, ws.w, ws.w, ws.q, nullptr,
                              ws.part, stream));
       int nbu = 0;
       DCG_HIP(launch_axpy_dot(N, -1.0, ws.q, ws.r, ws.part, &nbu, stream));
@@ -630,7 +631,7 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
         }
         // p_i = r_i + beta p_{i-1} fused into w = A* p_i, s = Z^T w
         const bool atimed = h->ktime;   // events recorded in the dispatch packet
-        DCG_HIP(launch_astar(i == 0 ? kAstarFirst : kAstarDir, m.Cdiv, m.cols, m.M1, ne,
+        DCG_HIP(launch_astar(i == 0 ? kAstarFirst : kAstarDir, m.Ct, m.n,
                              ws.r, ws.p[pidx], nullptr, ws.sc, ws.p[1 - pidx], ws.w, ws.s, nullptr,
                              stream, Slots(), 1, atimed ? h->aev[0] : nullptr,
                              atimed ? h->aev[1] : nullptr));
@@ -640,9 +641,9 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
         cycles_outer += c;
         ++inner_solves;
         // q = w - A* Z y = M_D p  (y = (2/dt) z)
-        DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, ws.zref, ws.w, ws.p[pidx], ws.q,
+        DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, ws.zref, ws.w, ws.p[pidx], ws.q,
                                nullptr, ws.part, stream));
-        DCG_HIP(launch_reduce(ws.part, nbA, flex ? kRedFcgAlpha : kRedAlpha, ws.sc, stream));
+        DCG_HIP(launch_reduce(ws.part, nbD, flex ? kRedFcgAlpha : kRedAlpha, ws.sc, stream));
         int nbu = 0;
         DCG_HIP(launch_cg_update(flex, N, ws.sc, ws.p[pidx], ws.q, ws.xh, ws.r, ws.part, &nbu,
                                  stream));
@@ -669,23 +670,23 @@ dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* 
     stats.rel_res_recurrence = std::sqrt(std::max(rho, 0.0) / b2);
 
     // epilogue: x = (x_hat - pi(A* x_hat)) + pi(b)  (eq. (x_defl))
-    DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, ws.xh, nullptr, nullptr,
+    DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, ws.xh, nullptr, nullptr,
                          ws.sc, nullptr, ws.w, ws.s, nullptr, stream));
     cycles_total += inner(h, ws.s, ws.zt, tol_c, stream);
     ++inner_solves;
     DCG_HIP(launch_reconstruct(ne, ws.xh, ws.zt, ws.zb, ws.sc, x, stream));
-    DCG_HIP(launch_astar(kAstarResidual, m.Cdiv, m.cols, m.M1, ne, x, nullptr, b, ws.sc,
+    DCG_HIP(launch_astar(kAstarResidual, m.Ct, m.n, x, nullptr, b, ws.sc,
                          nullptr, ws.w, nullptr, ws.part, stream));
-    DCG_HIP(launch_reduce(ws.part, nbA, kRedRes, ws.sc, stream));
+    DCG_HIP(launch_reduce(ws.part, astar_blocks(ne), kRedRes, ws.sc, stream));
     read_scalars(h, stream);
     rel_true = std::sqrt(ws.sc_host->res2 / b2);
     if (status != DCG_OK || rel_true <= tol || pass >= h->opt.restarts) break;
     // Algorithm 2 again from x_0 = x: restore r = f_D from the stored pi(b)
     ++pass;
     warm = true;
-    DCG_HIP(launch_deflate(true, m.AdivZ, m.cols, ne, kTwo, ws.zb, b, nullptr, ws.r, ws.p[0],
+    DCG_HIP(launch_deflate(true, m.AZt, m.n, kTwo, ws.zb, b, nullptr, ws.r, ws.p[0],
                            ws.part, stream));
-    DCG_HIP(launch_reduce(ws.part, nbA, kRedB2Rho, ws.sc, stream));
+    DCG_HIP(launch_reduce(ws.part, nbD, kRedB2Rho, ws.sc, stream));
   }
   if (h->opt.restarts > 0 && status == DCG_OK && rel_true > tol) status = DCG_NOT_CONVERGED;
   stats.restarts = pass;
@@ -827,10 +828,9 @@ dcg_status apply(dcg_ctx* h, dcg_op op, int level, const void* in, const void* i
   const int ne = m.ne;
   const double* x = static_cast<const double*>(in);
   double* y = static_cast<double*>(out);
-  if (op == DCG_OP_ASTAR || op == DCG_OP_DEFLATED) set_params(h, st);
   switch (op) {
     case DCG_OP_ASTAR:
-      DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, x, nullptr,
+      DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, x, nullptr,
                            nullptr, h->ws.sc, nullptr, y, nullptr, nullptr, st));
       break;
     case DCG_OP_ZT:
@@ -840,7 +840,7 @@ dcg_status apply(dcg_ctx* h, dcg_op op, int level, const void* in, const void* i
       DCG_HIP(launch_z(ne, x, 1.0, y, st));
       break;
     case DCG_OP_ADIVZ:
-      DCG_HIP(launch_adivz(m.AdivZ, m.cols, ne, x, y, st));
+      DCG_HIP(launch_adivz(m.AZt, m.n, x, y, st));
       break;
     case DCG_OP_INNER: {
       inner(h, x, h->ws.zref, h->opt.c_F * kApplyTol, st);
@@ -848,10 +848,10 @@ dcg_status apply(dcg_ctx* h, dcg_op op, int level, const void* in, const void* i
       break;
     }
     case DCG_OP_DEFLATED: {
-      DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, x, nullptr,
+      DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, x, nullptr,
                            nullptr, h->ws.sc, nullptr, h->ws.w, h->ws.s, nullptr, st));
       inner(h, h->ws.s, h->ws.zref, h->opt.c_F * kApplyTol, st);
-      DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, h->ws.zref, h->ws.w, x, y, nullptr,
+      DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, h->ws.zref, h->ws.w, x, y, nullptr,
                              h->ws.part, st));
       break;
     }
@@ -995,10 +995,10 @@ dcg_status apply_noalloc(dcg_ctx* h, dcg_op op, const double* in, double* out, h
     init.inv_nu = 1.0 / h->nu;
     *h->ws.sc_host = init;
     DCG_HIP(hipMemcpyAsync(w.sc, h->ws.sc_host, sizeof(Scalars), hipMemcpyHostToDevice, st));
-    DCG_HIP(launch_astar(kAstarPlain, m.Cdiv, m.cols, m.M1, ne, in, nullptr, nullptr, w.sc, nullptr,
+    DCG_HIP(launch_astar(kAstarPlain, m.Ct, m.n, in, nullptr, nullptr, w.sc, nullptr,
                          wv, sv, nullptr, st));
     inner(h, w, sv, zref, h->opt.c_F * kApplyTol, st);
-    DCG_HIP(launch_deflate(false, m.AdivZ, m.cols, ne, kTwo, zref, wv, in, out, nullptr, w.part, st));
+    DCG_HIP(launch_deflate(false, m.AZt, m.n, kTwo, zref, wv, in, out, nullptr, w.part, st));
   } else {
     inner(h, w, in, zref, h->opt.c_F * kApplyTol, st);
     DCG_HIP(launch_scale(4 * int64_t(ne), 2.0 / h->dt, zref, out, st));
