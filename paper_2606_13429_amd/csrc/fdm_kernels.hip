@@ -4,107 +4,142 @@
 //   T1 = S V,  T2 = (V^T T1) ./ (lam_i + lam_k),  T3 = V T2,  Z = T3 V^T,
 // with S, Z the scalar vectors rearranged from the element-major layout
 // 4 e + j (e = ey n + ex, j = ix + 2 iy) to the row-major tensor (Iy, Ix),
-// Ix = 2 ex + ix.  The products are FP64 register-blocked GEMMs staged
-// through LDS (each thread forms a 2 x 2 or 4 x 4 block of C).  The
+// Ix = 2 ex + ix.  The products are FP64 MFMA GEMMs staged through LDS.  The
 // same solve serves as the exact coarsest-level solve of a shortened
 // multigrid hierarchy, whose level vectors may be FP32.
 #include <cstdint>
 
 #include "kernels.hpp"
+#include "mg_common.hpp"
 
 namespace dcg {
 namespace {
 
-template <int TILE, int KK>
-struct GemmCfg {
-  static constexpr int kT = TILE;                   // C tile per workgroup
-  static constexpr int kK = KK;                     // k step
-  static constexpr int kR = TILE / 16;              // outputs per thread along each axis
-};
-constexpr int kGThreads = 256;
+constexpr int kGThreads = 512;
 
-// C = A B (N x N row-major); with la: C[i][k] *= 1 / (la[i] + lb[k]).  A
-// 16 x 16 grid of threads, each forming a kR x kR block of the TILE x TILE tile.
-template <int TILE, int KK>
-__global__ __launch_bounds__(kGThreads) void k_gemm(int N, const double* __restrict__ A,
-                                                    const double* __restrict__ B, double* __restrict__ C,
+// Position of tensor entry (Iy, Ix) in the element-major layout.
+__device__ __forceinline__ int64_t tensor_to_elem(int n, int a, int c) {
+  return 4 * ((int64_t)(a >> 1) * n + (c >> 1)) + (c & 1) + 2 * (a & 1);
+}
+
+// C = A B, N x N row-major FP64; with la: C[i][k] *= 1 / (la[i] + lb[k]).
+// AELEM: A is an element-major vector (of type TIN);
+// CELEM: C is written element-major (as TOUT), so the layout changes need no
+// launches of their own.  One TILE x TILE block of C per workgroup; two groups
+// of 4 wavefronts take half of every K-slab each, a wavefront (TILE / 2)^2 outputs
+// in 16 x 16 x 4 MFMA tiles, so that a SIMD has a second wavefront to issue from
+// while one reads its operands.  K-slabs of KK are double-buffered in LDS with
+// the next slab's loads in flight (registers) during the products.
+// The LDS strides spread an operand's 64 values evenly over the banks.  N is a
+// multiple of TILE and KK.
+// Bound by the FP64 matrix rate: at N = 1024 a product takes 50 us, 43 TFLOP/s
+// (126 us with vector FMAs, 2 x 2 outputs a thread).
+template <int TILE, int KK, bool AELEM, bool CELEM, typename TIN, typename TOUT>
+__global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm(int N, const TIN* __restrict__ A,
+                                                    const double* __restrict__ B, TOUT* __restrict__ C,
                                                     const double* __restrict__ la,
                                                     const double* __restrict__ lb) {
-  using G = GemmCfg<TILE, KK>;
-  __shared__ double As[G::kK][G::kT + 2];   // A tile transposed: As[k][row]
-  __shared__ double Bs[G::kK][G::kT + 2];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int row0 = blockIdx.y * G::kT, col0 = blockIdx.x * G::kT;
-  double acc[G::kR][G::kR] = {};
-  for (int k0 = 0; k0 < N; k0 += G::kK) {
-    for (int t = tid; t < G::kT * G::kK; t += kGThreads) {
-      const int r = t / G::kK, kk = t % G::kK;      // A: row r, column k0 + kk
-      const int gr = row0 + r, gk = k0 + kk;
-      As[kk][r] = (gr < N && gk < N) ? A[(int64_t)gr * N + gk] : 0.0;
-      const int kb = t / G::kT, c = t % G::kT;      // B: row k0 + kb, column c
-      const int gkb = k0 + kb, gc = col0 + c;
-      Bs[kb][c] = (gkb < N && gc < N) ? B[(int64_t)gkb * N + gc] : 0.0;
+  using V = mg::Mfma<double>::v4;
+  constexpr int SA = KK + 2, SB = TILE + 16, R = TILE / 32, NL = TILE * KK / (2 * kGThreads);
+  __shared__ __align__(16) double As[2][TILE * SA];   // As[row][k]
+  __shared__ __align__(16) double Bs[2][KK * SB];     // Bs[k][col]
+  const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) & 3, half = tid >> 8;
+  const int row0 = blockIdx.y * TILE, col0 = blockIdx.x * TILE;
+  const int wr = (w >> 1) * 16 * R, wc = (w & 1) * 16 * R;
+  const int n = N >> 1;
+  // the slab in flight (vectors, which stay in registers where arrays written
+  // under a condition went through LDS)
+  typedef double slab_t __attribute__((ext_vector_type(4)));
+  static_assert(NL == 2, "two 16-byte loads of A and of B per thread and slab");
+  slab_t ra, rb;
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int t = tid + u * kGThreads;
+      const int r = t / (KK / 2), kk = 2 * (t % (KK / 2));        // A: row r, columns kk, kk + 1
+      const TIN* a = A + (AELEM ? tensor_to_elem(n, row0 + r, k0 + kk) : (int64_t)(row0 + r) * N + k0 + kk);
+      ra[2 * u] = double(a[0]);
+      ra[2 * u + 1] = double(a[1]);
+      const int kb = t / (TILE / 2), c = 2 * (t % (TILE / 2));    // B: row kb, columns c, c + 1
+      const double2 bv = *reinterpret_cast<const double2*>(B + (int64_t)(k0 + kb) * N + col0 + c);
+      rb[2 * u] = bv.x;
+      rb[2 * u + 1] = bv.y;
     }
-    __syncthreads();
+  };
+  auto stage = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < G::kK; ++kk) {
-      double a[G::kR], b[G::kR];
+    for (int u = 0; u < NL; ++u) {
+      const int t = tid + u * kGThreads;
+      const int r = t / (KK / 2), kk = 2 * (t % (KK / 2));
+      *reinterpret_cast<double2*>(&As[buf][r * SA + kk]) = make_double2(ra[2 * u], ra[2 * u + 1]);
+      const int kb = t / (TILE / 2), c = 2 * (t % (TILE / 2));
+      *reinterpret_cast<double2*>(&Bs[buf][kb * SB + c]) = make_double2(rb[2 * u], rb[2 * u + 1]);
+    }
+  };
+  V acc[R][R];
 #pragma unroll
-      for (int q = 0; q < G::kR; ++q) {
-        a[q] = As[kk][ty * G::kR + q];
-        b[q] = Bs[kk][tx * G::kR + q];
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j) acc[i][j] = V{0.0, 0.0, 0.0, 0.0};
+  fetch(0);
+  stage(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < N; k0 += KK, buf ^= 1) {
+    const bool more = k0 + KK < N;
+    if (more) fetch(k0 + KK);
+    const double* ap = &As[buf][(wr + (lane & 15)) * SA + (lane >> 4) + half * (KK / 2)];
+    const double* bp = &Bs[buf][((lane >> 4) + half * (KK / 2)) * SB + wc + (lane & 15)];
+#pragma unroll
+    for (int k = 0; k < KK / 2; k += 4) {
+      double a[R], b[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        a[i] = ap[16 * i * SA + k];
+        b[i] = bp[k * SB + 16 * i];
       }
 #pragma unroll
-      for (int i = 0; i < G::kR; ++i)
+      for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < G::kR; ++j) acc[i][j] += a[i] * b[j];
+        for (int j = 0; j < R; ++j) acc[i][j] = mg::Mfma<double>::mac(a[i], b[j], acc[i][j]);
     }
+    if (more) stage(buf ^ 1);   // last read before the previous barrier
     __syncthreads();
   }
+  // the other half of the contraction, through LDS
+  double* red = &Bs[0][0];
+  static_assert(2 * KK * SB >= TILE * TILE, "the partial tile fits the B slabs");
+  if (half) {
 #pragma unroll
-  for (int i = 0; i < G::kR; ++i) {
-    const int gr = row0 + ty * G::kR + i;
-    if (gr >= N) continue;
+    for (int i = 0; i < R * R; ++i)
 #pragma unroll
-    for (int j = 0; j < G::kR; ++j) {
-      const int gc = col0 + tx * G::kR + j;
-      if (gc >= N) continue;
-      double v = acc[i][j];
-      if (la) v *= 1.0 / (la[gr] + lb[gc]);
-      C[(int64_t)gr * N + gc] = v;
-    }
+      for (int v = 0; v < 4; ++v) red[((i * 4 + v) * 4 + w) * 64 + lane] = acc[i / R][i % R][v];
   }
+  __syncthreads();
+  if (half) return;
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int gr = row0 + wr + 16 * i + 4 * v + (lane >> 4), gc = col0 + wc + 16 * j + (lane & 15);
+        double x = acc[i][j][v] + red[(((i * R + j) * 4 + v) * 4 + w) * 64 + lane];
+        if (la) x *= 1.0 / (la[gr] + lb[gc]);
+        C[CELEM ? tensor_to_elem(n, gr, gc) : (int64_t)gr * N + gc] = TOUT(x);
+      }
 }
 
-// to_tensor: T[(2 ey + iy) N + 2 ex + ix] = s[4 e + j]; otherwise the inverse.
-template <typename Tin, typename Tout>
-__global__ __launch_bounds__(kGThreads) void k_fdm_permute(int n, int to_tensor,
-                                                           const Tin* __restrict__ in,
-                                                           Tout* __restrict__ out) {
-  const int64_t i = blockIdx.x * (int64_t)kGThreads + threadIdx.x;
-  const int64_t total = 4 * (int64_t)n * n;
-  if (i >= total) return;
-  const int N = 2 * n;
-  const int64_t e = i >> 2;
-  const int j = int(i & 3);
-  const int ex = int(e % n), ey = int(e / n);
-  const int64_t t = (int64_t)(2 * ey + (j >> 1)) * N + 2 * ex + (j & 1);
-  if (to_tensor) out[t] = Tout(in[i]);
-  else out[i] = Tout(in[t]);
-}
-
-hipError_t gemm(int N, const double* A, const double* B, double* C, const double* la,
-                const double* lb, hipStream_t st) {
-  // 32 x 32 tiles (2 x 2 per thread) keep at least about 4 workgroups per CU up
-  // to N = 1024; 64 x 64 (4 x 4 per thread) above
-  if (N <= 1024) {
-    const dim3 grid((N + 31) / 32, (N + 31) / 32);
-    k_gemm<32, 16><<<grid, kGThreads, 0, st>>>(N, A, B, C, la, lb);
-  } else {
-    const dim3 grid((N + 63) / 64, (N + 63) / 64);
-    k_gemm<64, 16><<<grid, kGThreads, 0, st>>>(N, A, B, C, la, lb);
-  }
+template <bool AELEM, bool CELEM, typename TIN, typename TOUT>
+hipError_t gemm(int N, const TIN* A, const double* B, TOUT* C, const double* la, const double* lb,
+                hipStream_t st) {
+  // 64 x 64 tiles fill the compute units from N = 1024 on (256 workgroups);
+  // below, 32 x 32 tiles do
+  if (N % 64) return hipErrorInvalidValue;
+  if (N >= 1024)
+    k_gemm<64, 32, AELEM, CELEM><<<dim3(N / 64, N / 64), kGThreads, 0, st>>>(N, A, B, C, la, lb);
+  else
+    k_gemm<32, 64, AELEM, CELEM><<<dim3(N / 32, N / 32), kGThreads, 0, st>>>(N, A, B, C, la, lb);
   return hipGetLastError();
 }
 
@@ -119,10 +154,6 @@ hipError_t gemm(int N, const double* A, const double* B, double* C, const double
 // [p N / P, (p + 1) N / P), p = t / N, P = 256 / N; the P partials of a
 // column are added in LDS in ascending p (fixed order).
 constexpr int kFThreads = 256;
-
-__device__ __forceinline__ int64_t tensor_to_elem(int n, int a, int c) {
-  return 4 * ((int64_t)(a >> 1) * n + (c >> 1)) + (c & 1) + 2 * (a & 1);
-}
 
 // sum over p of part[p N + c] for the threads t < N (column c = t)
 __device__ __forceinline__ double column_total(const double* part, int N, int P, int c) {
@@ -200,17 +231,11 @@ hipError_t fdm_solve(int n, const double* V, const double* VT, const double* lam
     k_fdm_pass2<T><<<N, kFThreads, 0, st>>>(n, V, VT, t0, z);
     return hipGetLastError();
   }
-  const int64_t total = 4 * (int64_t)n * n;
-  const int pb = int((total + kGThreads - 1) / kGThreads);
-  k_fdm_permute<T, double><<<pb, kGThreads, 0, st>>>(n, 1, s, t0);
-  hipError_t e = hipGetLastError();
+  hipError_t e = gemm<true, false>(N, s, V, t1, nullptr, nullptr, st);                      // x: S V
   if (e != hipSuccess) return e;
-  if ((e = gemm(N, t0, V, t1, nullptr, nullptr, st)) != hipSuccess) return e;   // x: S V
-  if ((e = gemm(N, VT, t1, t2, lam, lam, st)) != hipSuccess) return e;          // y: V^T T1, scaled
-  if ((e = gemm(N, V, t2, t0, nullptr, nullptr, st)) != hipSuccess) return e;   // y: V T2
-  if ((e = gemm(N, t0, VT, t1, nullptr, nullptr, st)) != hipSuccess) return e;  // x: T3 V^T
-  k_fdm_permute<double, T><<<pb, kGThreads, 0, st>>>(n, 0, t1, z);
-  return hipGetLastError();
+  if ((e = gemm<false, false>(N, VT, t1, t2, lam, lam, st)) != hipSuccess) return e;        // y: V^T T1, scaled
+  if ((e = gemm<false, false>(N, V, t2, t0, nullptr, nullptr, st)) != hipSuccess) return e;  // y: V T2
+  return gemm<false, true>(N, t0, VT, z, nullptr, nullptr, st);                             // x: T3 V^T
 }
 
 }  // namespace
