@@ -489,8 +489,10 @@ constexpr int kFdmThreads = 256;
 constexpr int kFdmMaxN = 128;
 constexpr int kFdmPad = 17;                // LDS row of 16 columns
 
+constexpr int kFdmTrip = 4;                // steps of 8 whose loads are issued together
+
 // out[m][c] = sum_k A(m, k) U[k][c] for the wavefront's row tiles; A is N x N
-// row-major, U in LDS (rows up to the next multiple of 8 are zero-filled).
+// row-major, U in LDS (rows up to the next multiple of 32 are zero-filled).
 template <typename Store>
 __device__ __forceinline__ void fdm_rows(int N, const double* __restrict__ A, const double* U, Store store) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -499,21 +501,27 @@ __device__ __forceinline__ void fdm_rows(int N, const double* __restrict__ A, co
     const int row = m0 + col;
     const double* Ar = A + (int64_t)(row < N ? row : 0) * N + 2 * q;
     v4d acc = {0.0, 0.0, 0.0, 0.0}, acc1 = acc;
-#pragma unroll 4
-    for (int k0 = 0; k0 < N; k0 += 8) {
-      double2 a = make_double2(0.0, 0.0);
-      if (row < N && k0 + 2 * q < N) a = *reinterpret_cast<const double2*>(Ar + k0);
-      acc = mfma64(a.x, U[(k0 + 2 * q) * kFdmPad + col], acc);
-      acc1 = mfma64(a.y, U[(k0 + 2 * q + 1) * kFdmPad + col], acc1);
+    for (int k0 = 0; k0 < N; k0 += 8 * kFdmTrip) {
+      double2 a[kFdmTrip];
+#pragma unroll
+      for (int u = 0; u < kFdmTrip; ++u) {
+        a[u] = make_double2(0.0, 0.0);
+        if (row < N && k0 + 8 * u + 2 * q < N) a[u] = *reinterpret_cast<const double2*>(Ar + k0 + 8 * u);
+      }
+#pragma unroll
+      for (int u = 0; u < kFdmTrip; ++u) {
+        acc = mfma64(a[u].x, U[(k0 + 8 * u + 2 * q) * kFdmPad + col], acc);
+        acc1 = mfma64(a[u].y, U[(k0 + 8 * u + 2 * q + 1) * kFdmPad + col], acc1);
+      }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) store(m0 + 4 * v + q, acc[v] + acc1[v]);
   }
 }
 
-// Rows [N, next multiple of 8) of U: the padding of a contraction over N rows.
+// Rows [N, next multiple of 32) of U: the padding of a contraction over N rows.
 __device__ __forceinline__ void fdm_pad_rows(int N, double* U) {
-  for (int i = threadIdx.x; i < ((N + 7) & ~7) * 16 - N * 16; i += kFdmThreads)
+  for (int i = threadIdx.x; i < (((N + 31) & ~31) - N) * 16; i += kFdmThreads)
     U[(N + i / 16) * kFdmPad + i % 16] = 0.0;
 }
 
@@ -536,22 +544,29 @@ __global__ __launch_bounds__(kFdmThreads) void k_fdm_plane(int n, const double* 
   for (int m0 = 16 * w; m0 < N; m0 += 64) {
     const int row = m0 + col;              // Iy of the A operand
     v4d acc = {0.0, 0.0, 0.0, 0.0}, acc1 = acc;
-#pragma unroll 4
-    for (int k0 = 0; k0 < N; k0 += 8) {
-      const int kk = k0 + 2 * q;
-      double2 a = make_double2(0.0, 0.0);
-      double b0 = 0.0, b1 = 0.0;
-      if (kk < N) {
-        if (row < N)
-          a = *reinterpret_cast<const double2*>(
-              in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
-        if (c < N) {
-          b0 = Bx[(int64_t)kk * N + c];
-          b1 = Bx[(int64_t)(kk + 1) * N + c];
+    for (int k0 = 0; k0 < N; k0 += 8 * kFdmTrip) {
+      double2 a[kFdmTrip];
+      double b0[kFdmTrip], b1[kFdmTrip];
+#pragma unroll
+      for (int u = 0; u < kFdmTrip; ++u) {
+        const int kk = k0 + 8 * u + 2 * q;
+        a[u] = make_double2(0.0, 0.0);
+        b0[u] = b1[u] = 0.0;
+        if (kk < N) {
+          if (row < N)
+            a[u] = *reinterpret_cast<const double2*>(
+                in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
+          if (c < N) {
+            b0[u] = Bx[(int64_t)kk * N + c];
+            b1[u] = Bx[(int64_t)(kk + 1) * N + c];
+          }
         }
       }
-      acc = mfma64(a.x, b0, acc);
-      acc1 = mfma64(a.y, b1, acc1);
+#pragma unroll
+      for (int u = 0; u < kFdmTrip; ++u) {
+        acc = mfma64(a[u].x, b0[u], acc);
+        acc1 = mfma64(a[u].y, b1[u], acc1);
+      }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
