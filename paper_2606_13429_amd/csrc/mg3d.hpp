@@ -29,11 +29,14 @@
 //                        6 - (n_k - 1 - x) (n_k - 1 - x < 3), else 3;
 //                        levels with n_k < 6 take one class per cube,
 //                        cls = e (at most 125)
-// The coarsest level keeps the dense inverse of its operator, row-major.
+// The coarsest level keeps the dense inverse of its operator, row-major, and a
+// level 2 <= k < J of at most kFoldMaxDofs unknowns the dense matrix of its two
+// coarse cycles (Algorithm 4, gamma = 2, from zero; both are fixed linear maps of
+// f_k).
 // On the device, levels with more than kSplitMaxN cubes per side store both
 // tables with the row index fastest (op [27][7 slots][8 columns][8 rows],
 // ras [343][200 columns][8 rows], from op_rows_fastest / rows_fastest), so
-// that the eight threads of a cube read one contiguous segment per column;
+// that a column is one contiguous segment, and a task list (mg3_tasks);
 // smaller levels keep the row-major tables (one lane per row segment).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -49,7 +52,8 @@ constexpr int kRasClassMinN = 6;   // smaller levels: one class per cube
 constexpr int kDiamond = 25;
 constexpr int kRasCols = 8 * kDiamond;
 constexpr int kMaxCoarsest = 4;
-constexpr int kSplitMaxN = 16;     // levels up to this size: one lane per term group
+constexpr int kSplitMaxN = 8;      // levels up to this size: one lane per term group
+constexpr int kFoldMaxDofs = 4096; // largest level (8 x 8 x 8 cubes) kept as a dense matrix
 
 // Offsets (dx, dy, dz) of the diamond, |dx| + |dy| + |dz| <= 2, in the order
 // z, then y, then x ascending.
@@ -83,17 +87,32 @@ int mg3_num_levels(int n, int levels);
 // coarsest inverse.  Throws std::runtime_error on failure.
 Mg3Hierarchy build_mg3(int n, int J, const std::vector<double>& ld);
 
+// Tasks of the MFMA kernels of a level: groups of 16 cubes of one RAS class (and
+// so of one operator class), entry 16 t + i the i-th cube of task t -- or, past
+// the last one, the complement ~e of the task's first cube e, whose values a lane
+// may read -- and the RAS class of every task.  Cubes of a class ascending.
+void mg3_tasks(int nk, std::vector<int32_t>& cubes, std::vector<int32_t>& cls);
+
 // ---- launchers (guard: the kernels do nothing while *guard == 0; NULL = run)
+// The tables and task list of one level on the device.
+struct Mg3LevelDev {
+  int n = 0;
+  const double* op = nullptr;
+  const double* ras = nullptr;        // levels >= 2
+  const int32_t* cubes = nullptr;     // task list (levels above kSplitMaxN)
+  const int32_t* cls = nullptr;
+  int tasks = 0;
+};
 // r = f - L_k z (f = NULL: 0, z = NULL: 0), and with part != NULL the
 // per-workgroup partial sums of r^2.
-hipError_t launch_mg3_res(int nk, const double* op, const double* f, const double* z, double* r,
+hipError_t launch_mg3_res(const Mg3LevelDev& L, const double* f, const double* z, double* r,
                           double* part, const int32_t* guard, hipStream_t st);
-int mg3_res_blocks(int nk);
-// True when level nk runs the small-level kernels (one lane per term group
-// without LDS staging, row-major tables) rather than the brick kernels.
+int mg3_res_blocks(const Mg3LevelDev& L);
+// True when level nk runs the small-level kernels (one lane per term group,
+// row-major tables) rather than the MFMA kernels.
 bool mg3_split(int nk);
-// z = (zero ? 0 : z) + S_k r, ras the level's class table.
-hipError_t launch_mg3_ras(int nk, const double* ras, const double* r, double* z, bool zero,
+// z = (zero ? 0 : z) + S_k r.
+hipError_t launch_mg3_ras(const Mg3LevelDev& L, const double* r, double* z, bool zero,
                           const int32_t* guard, hipStream_t st, hipEvent_t ev0 = nullptr,
                           hipEvent_t ev1 = nullptr);
 // fc = P_k^T r (nf = fine cubes per side).
@@ -105,6 +124,16 @@ hipError_t launch_mg3_prolong(int nf, const double* zc, double* z, bool assign,
 // z = inv f (dense, m x m, row-major).
 hipError_t launch_mg3_dense(int m, const double* inv, const double* f, double* z,
                             const int32_t* guard, hipStream_t st);
+
+// ---- dense forms of a small level (set-up)
+// L = the level operator, S = the RAS update, dense m x m row-major, m = 8 nk^3
+// (nk <= kSplitMaxN: row-major tables).
+hipError_t launch_mg3_dense_tables(int nk, const double* op, const double* ras, double* L, double* S,
+                                   hipStream_t st);
+// K = P C P^T of the level nk, C dense on the next coarser one.
+hipError_t launch_mg3_dense_coarse(int nk, const double* C, double* K, hipStream_t st);
+// A += c B (len elements; B = NULL: c times the identity, len = m^2).
+hipError_t launch_mg3_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st);
 
 // Device state of one Multigrid iteration (Algorithm 3).
 struct Mg3Scalars {

@@ -290,6 +290,26 @@ void diamond_offsets(int off[kDiamond][3]) {
         }
 }
 
+void mg3_tasks(int nk, std::vector<int32_t>& cubes, std::vector<int32_t>& cls) {
+  std::vector<std::vector<int32_t>> of(kRasClasses);
+  for (int z = 0; z < nk; ++z)
+    for (int y = 0; y < nk; ++y)
+      for (int x = 0; x < nk; ++x)
+        of[ras_axis(x, nk) + 7 * ras_axis(y, nk) + 49 * ras_axis(z, nk)].push_back(
+            int32_t(index({x, y, z}, nk)));
+  cubes.clear();
+  cls.clear();
+  // the interior class first: its tasks are most of the level and run in mesh order
+  constexpr int inner = 3 + 7 * 3 + 49 * 3;
+  for (int i = 0; i < kRasClasses; ++i) {
+    const int c = i == 0 ? inner : (i <= inner ? i - 1 : i);
+    for (size_t j = 0; j < of[c].size(); j += 16) {
+      cls.push_back(c);
+      for (size_t t = j; t < j + 16; ++t) cubes.push_back(t < of[c].size() ? of[c][t] : ~of[c][j]);
+    }
+  }
+}
+
 std::vector<double> rows_fastest(const std::vector<double>& t, int cols) {
   const size_t per = (size_t)8 * cols, nc = t.size() / per;
   std::vector<double> out(t.size());

@@ -1,8 +1,8 @@
 // Kernels of the three-dimensional multigrid inner solve (Section 4.2, the 3D
 // case; layouts in mg3d.hpp).  Level vectors hold 8 FP64 values per cube.
-// The residual and the RAS step run on bricks staged in LDS on large levels
-// and split every output over a few lanes on small ones; the transfers run
-// one thread per (cube, row).  The class tables (operator
+// The residual and the RAS step run as MFMA products over tasks of 16 cubes of
+// a class on large levels and split every output over a few lanes on small
+// ones; the transfers run one thread per (cube, row).  The class tables (operator
 // 27 x 7 blocks, RAS updates 343 x 8 x 200) are shared by every cube of a
 // class and stay in the caches.
 #include <hip/hip_ext.h>
@@ -36,111 +36,6 @@ __device__ double block_sum(double v, double* sh) {
   return sh[0];
 }
 
-// ---- residual and RAS step on large levels (n_k > kSplitMaxN): bricks of
-// 4 x 4 x 4 cubes per 512-thread workgroup.  The workgroup stages the input
-// vector on the brick and a halo (zeros outside the domain) in LDS,
-// component-major with a padded stride; thread t computes row t & 7 of cube
-// t >> 3 of the brick.  These levels store the class tables with the row
-// index fastest (mg3d.hpp), so the eight threads of a cube read one
-// contiguous 64-byte segment per column and the cubes of one class in a
-// wavefront share it.
-constexpr int kBrick = 4;
-constexpr int kBrickThreads = 512;
-
-template <int H>
-struct Box {
-  static constexpr int X = kBrick + 2 * H;
-  static constexpr int N = X * X * X;
-  static constexpr int S = N + 1;   // component stride (padding spreads the banks)
-};
-
-__host__ __device__ constexpr int bricks_along(int n) { return (n + kBrick - 1) / kBrick; }
-
-// lds[b S + c] = v on box cube c, component b (0 outside the domain or v = NULL).
-template <int H>
-__device__ __forceinline__ void stage_box(int n, int x0, int y0, int z0, const double* __restrict__ v,
-                                          double* lds) {
-  using B = Box<H>;
-  for (int i = threadIdx.x; i < B::N * 8; i += kBrickThreads) {
-    const int c = i >> 3, b = i & 7;
-    const int x = x0 - H + c % B::X, y = y0 - H + (c / B::X) % B::X, z = z0 - H + c / (B::X * B::X);
-    double val = 0.0;
-    if (v && x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n)
-      val = v[8 * (((int64_t)z * n + y) * n + x) + b];
-    lds[b * B::S + c] = val;
-  }
-}
-
-struct Lane {
-  int row;        // the thread's row of its cube
-  int x, y, z;    // the cube
-  int lx, ly, lz; // its place in the brick
-  int x0, y0, z0; // the brick's origin
-  bool valid;     // inside the domain
-  int64_t e;
-};
-
-__device__ __forceinline__ Lane lane_cube(int n) {
-  const int nb = bricks_along(n);
-  const int b = blockIdx.x;
-  Lane L;
-  L.row = threadIdx.x & 7;
-  const int c = threadIdx.x >> 3;
-  L.lx = c & 3;
-  L.ly = (c >> 2) & 3;
-  L.lz = c >> 4;
-  L.x0 = (b % nb) * kBrick;
-  L.y0 = ((b / nb) % nb) * kBrick;
-  L.z0 = (b / (nb * nb)) * kBrick;
-  L.x = L.x0 + L.lx;
-  L.y = L.y0 + L.ly;
-  L.z = L.z0 + L.lz;
-  L.valid = L.x < n && L.y < n && L.z < n;
-  L.e = ((int64_t)L.z * n + L.y) * n + L.x;
-  return L;
-}
-
-__global__ __launch_bounds__(kBrickThreads) void k_mg3_res(int n, const double* __restrict__ opT,
-                                                           const double* __restrict__ f,
-                                                           const double* __restrict__ z,
-                                                           double* __restrict__ r,
-                                                           double* __restrict__ part,
-                                                           const int32_t* __restrict__ guard) {
-  if (stopped(guard)) return;
-  using B = Box<1>;
-  __shared__ double zs[8 * B::S];
-  __shared__ double sh[kBrickThreads / 64];
-  const Lane L = lane_cube(n);
-  stage_box<1>(n, L.x0, L.y0, L.z0, z, zs);
-  __syncthreads();
-  constexpr int off[kSlots] = {0, -1, 1, -B::X, B::X, -B::X * B::X, B::X * B::X};
-  const int cls = op_axis(L.x, n) + 3 * op_axis(L.y, n) + 9 * op_axis(L.z, n);
-  // opT[cls][slot][b][row]
-  const double* col = opT + (int64_t)cls * kSlots * 64 + L.row;
-  const int o = ((L.lz + 1) * B::X + L.ly + 1) * B::X + L.lx + 1;
-  double acc = (L.valid && f) ? f[8 * L.e + L.row] : 0.0;
-#pragma unroll
-  for (int s = 0; s < kSlots; ++s) {
-    const double* cs = col + 64 * s;
-    const double* zn = zs + o + off[s];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc -= cs[8 * b] * zn[b * B::S];
-  }
-  if (L.valid) r[8 * L.e + L.row] = acc;
-  if (part) {   // the workgroup's sum of r^2, fixed order: lanes, then wavefronts
-    double v = L.valid ? acc * acc : 0.0;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double sum = 0.0;
-      for (int w = 0; w < kBrickThreads / 64; ++w) sum += sh[w];
-      part[blockIdx.x] = sum;
-    }
-  }
-}
-
 // The diamond (|dx| + |dy| + |dz| <= 2) as cube offsets, in the order of
 // diamond_offsets().
 struct DiamondOff {
@@ -161,41 +56,160 @@ struct DiamondOff {
   }
 };
 
-// The diamond as offsets in the halo-2 box, in the same order.
-struct DiamondBox {
-  int o[kDiamond];
-  constexpr DiamondBox() : o() {
-    const DiamondOff D;
-    for (int d = 0; d < kDiamond; ++d) o[d] = (D.d[d][2] * Box<2>::X + D.d[d][1]) * Box<2>::X + D.d[d][0];
-  }
+// ---- residual and RAS step on large levels (n_k > kSplitMaxN): one wavefront
+// per task of 16 cubes of one class, the class's rows times the cubes' gathered
+// inputs as FP64 MFMA products.  Lane l supplies input values 2 q, 2 q + 1 (q =
+// l / 16) of the neighbour cubes of cube l % 16 -- one 16-byte load and two
+// 16 x 16 x 4 steps per neighbour -- and the table entry of row 2 (m & 3) +
+// (m >> 2 & 1), m = l % 16, at the same column (rows 8..15 of the product repeat
+// rows 0..7), and receives rows 2 q, 2 q + 1 of its cube.  Every operand comes
+// from L1 / L2 with no LDS and no barrier; the class tables (12.8 KB) stay in L1
+// for the tasks of the interior.  Bound by the load latency and the matrix rate (50
+// steps of a RAS task are 1.3 us).  A task holds one class, so the 1/2 to 1/4 of
+// a level that lies near the boundary costs what the interior does; bricks of
+// 4 x 4 x 4 cubes in LDS, a table entry loaded per lane, took 28.8 us a RAS step
+// and 13.0 us a residual at n = 32, the split kernels below 12.5 and 5.1 us at
+// n = 16; tasks take 12.9 and 5.4 us, 5.2 and 3.8 us.
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+constexpr int kInterior = 3 + 7 * 3 + 49 * 3;   // class at least 3 cubes from every side
+
+struct Task {
+  int q, row;        // lane group; table row of the lane
+  int cls;           // RAS class
+  int x, y, z, e;    // the lane's cube
+  bool valid;
 };
 
-__global__ __launch_bounds__(kBrickThreads) void k_mg3_ras(int n, const double* __restrict__ rasT,
-                                                           const double* __restrict__ r,
-                                                           double* __restrict__ z, int zero,
-                                                           const int32_t* __restrict__ guard) {
-  if (stopped(guard)) return;
-  using B = Box<2>;
-  __shared__ double rs[8 * B::S];
-  const Lane L = lane_cube(n);
-  stage_box<2>(n, L.x0, L.y0, L.z0, r, rs);
-  __syncthreads();
-  constexpr DiamondBox D;
-  const int cls = ras_axis(L.x, n) + 7 * ras_axis(L.y, n) + 49 * ras_axis(L.z, n);
-  // rasT[cls][column 200][row]
-  const double* col = rasT + (int64_t)cls * 8 * kRasCols + L.row;
-  const int o = ((L.lz + 2) * B::X + L.ly + 2) * B::X + L.lx + 2;
-  double acc = (L.valid && !zero) ? z[8 * L.e + L.row] : 0.0;
-  // five diamond cubes per loop trip keep the code small with their table
-  // loads in flight together
-#pragma unroll 5
-  for (int d = 0; d < kDiamond; ++d) {
-    const double* cd = col + 64 * d;
-    const double* rd = rs + o + D.o[d];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc += cd[8 * b] * rd[b * B::S];
+// Workgroups go round robin to the 8 XCDs: each takes a contiguous run of tasks,
+// so that the cubes it reads share its L2 (remainder tasks keep their index).
+__device__ __forceinline__ int xcd_index(int b, int G) {
+  const int per = G >> 3;
+  return b < 8 * per ? (b & 7) * per + (b >> 3) : b;
+}
+
+__device__ __forceinline__ Task load_task(int n, const int32_t* __restrict__ cubes,
+                                          const int32_t* __restrict__ cls, int tasks) {
+  Task t;
+  const int lane = threadIdx.x, id = xcd_index(blockIdx.x, tasks);
+  t.q = lane >> 4;
+  t.row = 2 * (lane & 3) + ((lane >> 2) & 1);
+  t.cls = cls[id];
+  const int e = cubes[16 * id + (lane & 15)];
+  t.valid = e >= 0;
+  t.e = e >= 0 ? e : ~e;   // padding repeats a cube of the task
+  t.x = t.e % n;
+  t.y = (t.e / n) % n;
+  t.z = t.e / (n * n);
+  return t;
+}
+
+// Values 2 q, 2 q + 1 of the cube at offset (dx, dy, dz), zero outside the
+// domain; IN: the task's class has every such cube inside (no tests, one
+// base address).
+template <bool IN>
+__device__ __forceinline__ double2 task_input(const Task& t, int n, int dx, int dy, int dz,
+                                              const double* __restrict__ v) {
+  if (!IN) {
+    const int x = t.x + dx, y = t.y + dy, z = t.z + dz;
+    if (x < 0 || y < 0 || z < 0 || x >= n || y >= n || z >= n) return make_double2(0.0, 0.0);
   }
-  if (L.valid) z[8 * L.e + L.row] = acc;
+  return *reinterpret_cast<const double2*>(v + 8 * ((dz * n + dy) * n + dx) + 8 * (int64_t)t.e + 2 * t.q);
+}
+
+// The products of one task: residual terms L z (7 face slots) or the RAS update
+// (25 diamond cubes); A points at the lane's table entries.
+template <bool IN>
+__device__ __forceinline__ void res_products(const Task& t, int n, const double* __restrict__ A,
+                                             const double* __restrict__ z, v4d& a0, v4d& a1) {
+  double2 v[kSlots];
+#pragma unroll
+  for (int s = 0; s < kSlots; ++s) {
+    const int dx = s == 1 ? -1 : (s == 2 ? 1 : 0), dy = s == 3 ? -1 : (s == 4 ? 1 : 0),
+              dz = s == 5 ? -1 : (s == 6 ? 1 : 0);
+    v[s] = task_input<IN>(t, n, dx, dy, dz, z);
+  }
+#pragma unroll
+  for (int s = 0; s < kSlots; ++s) {
+    a0 = mfma64(A[64 * s], v[s].x, a0);
+    a1 = mfma64(A[64 * s + 8], v[s].y, a1);
+  }
+}
+
+template <bool IN>
+__device__ __forceinline__ void ras_products(const Task& t, int n, const double* __restrict__ A,
+                                             const double* __restrict__ r, v4d& a0, v4d& a1) {
+  constexpr DiamondOff D;
+  double2 v[kDiamond];
+#pragma unroll
+  for (int d = 0; d < kDiamond; ++d) v[d] = task_input<IN>(t, n, D.d[d][0], D.d[d][1], D.d[d][2], r);
+#pragma unroll
+  for (int d = 0; d < kDiamond; ++d) {
+    a0 = mfma64(A[64 * d], v[d].x, a0);
+    a1 = mfma64(A[64 * d + 8], v[d].y, a1);
+  }
+}
+
+__global__ __launch_bounds__(64) void k_mg3_res(int n, int tasks, const int32_t* __restrict__ cubes,
+                                                      const int32_t* __restrict__ tcls,
+                                                      const double* __restrict__ opT,
+                                                      const double* __restrict__ f,
+                                                      const double* __restrict__ z,
+                                                      double* __restrict__ r,
+                                                      double* __restrict__ part,
+                                                      const int32_t* __restrict__ guard) {
+  if (stopped(guard)) return;
+  const Task t = load_task(n, cubes, tcls, tasks);
+  // operator class: 0 low side, 2 high side, 1 inside of the distance class
+  const int p[3] = {t.cls % 7, (t.cls / 7) % 7, t.cls / 49};
+  int oc = 0;
+#pragma unroll
+  for (int a = 2; a >= 0; --a) oc = 3 * oc + (p[a] == 0 ? 0 : (p[a] == 6 ? 2 : 1));
+  // opT[cls][slot][b][row]
+  const double* A = opT + (int64_t)oc * kSlots * 64 + 16 * t.q + t.row;
+  v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
+  if (z) {
+    if (t.cls == kInterior) res_products<true>(t, n, A, z, a0, a1);
+    else res_products<false>(t, n, A, z, a0, a1);
+  }
+  double2 rv = make_double2(0.0, 0.0);
+  if (t.valid) {
+    if (f) rv = *reinterpret_cast<const double2*>(f + 8 * (int64_t)t.e + 2 * t.q);
+    rv.x -= a0[0] + a1[0];
+    rv.y -= a0[1] + a1[1];
+    *reinterpret_cast<double2*>(r + 8 * (int64_t)t.e + 2 * t.q) = rv;
+  }
+  if (part) {   // the task's sum of r^2, fixed order
+    double v = rv.x * rv.x + rv.y * rv.y;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if (threadIdx.x == 0) part[blockIdx.x] = v;
+  }
+}
+
+__global__ __launch_bounds__(64) void k_mg3_ras(int n, int tasks, const int32_t* __restrict__ cubes,
+                                                      const int32_t* __restrict__ tcls,
+                                                      const double* __restrict__ rasT,
+                                                      const double* __restrict__ r,
+                                                      double* __restrict__ z, int zero,
+                                                      const int32_t* __restrict__ guard) {
+  if (stopped(guard)) return;
+  const Task t = load_task(n, cubes, tcls, tasks);
+  // rasT[cls][column 200][row]
+  const double* A = rasT + (int64_t)t.cls * 8 * kRasCols + 16 * t.q + t.row;
+  double2 zv = make_double2(0.0, 0.0);
+  if (t.valid && !zero) zv = *reinterpret_cast<const double2*>(z + 8 * (int64_t)t.e + 2 * t.q);
+  v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
+  if (t.cls == kInterior) ras_products<true>(t, n, A, r, a0, a1);
+  else ras_products<false>(t, n, A, r, a0, a1);
+  if (t.valid) {
+    zv.x += a0[0] + a1[0];
+    zv.y += a0[1] + a1[1];
+    *reinterpret_cast<double2*>(z + 8 * (int64_t)t.e + 2 * t.q) = zv;
+  }
 }
 
 // ---- residual and RAS step on small levels (n_k <= kSplitMaxN): one lane
@@ -333,17 +347,101 @@ __global__ __launch_bounds__(kThreads) void k_mg3_prolong(int nf, const double* 
   z[8 * e + i] = assign ? acc : z[8 * e + i] + acc;
 }
 
-__global__ __launch_bounds__(kThreads) void k_mg3_dense(int m, const double* __restrict__ inv,
+// z = A f, A dense m x m (m even): one wavefront per row, lanes over pairs of
+// columns, a fixed shuffle sum.  Bound by the matrix (134 MB at m = 4096).
+__global__ __launch_bounds__(kThreads) void k_mg3_dense(int m, const double* __restrict__ A,
                                                         const double* __restrict__ f,
                                                         double* __restrict__ z,
                                                         const int32_t* __restrict__ guard) {
   if (stopped(guard)) return;
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  if (i >= m) return;
-  const double* row = inv + (int64_t)i * m;
+  const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (i >= m) return;   // whole wavefronts
+  const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
+  const double2* f2 = reinterpret_cast<const double2*>(f);
   double acc = 0.0;
-  for (int j = 0; j < m; ++j) acc += row[j] * f[j];
-  z[i] = acc;
+#pragma unroll 8
+  for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
+    const double2 a = row[j], b = f2[j];
+    acc += a.x * b.x + a.y * b.y;
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);
+  if ((threadIdx.x & 63) == 0) z[i] = acc;
+}
+
+// Dense L and S of a small level from its row-major tables (both cleared
+// before): thread (cube, row, diamond cube).
+__global__ __launch_bounds__(kThreads) void k_mg3_dense_tables(int n, const double* __restrict__ op,
+                                                               const double* __restrict__ ras,
+                                                               double* __restrict__ L,
+                                                               double* __restrict__ S) {
+  constexpr DiamondOff D;
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t ne = (int64_t)n * n * n, m = 8 * ne;
+  if (i >= m * 32) return;
+  const int d = int(i & 31), row = int((i >> 5) & 7);
+  const int64_t e = i >> 8;
+  if (d >= kDiamond) return;
+  const int x = int(e % n), y = int((e / n) % n), zz = int(e / ((int64_t)n * n));
+  int off[3] = {0, 0, 0};
+  for (int k = 0; k < kDiamond; ++k)
+    if (k == d) {
+      off[0] = D.d[k][0];
+      off[1] = D.d[k][1];
+      off[2] = D.d[k][2];
+    }
+  const int qx = x + off[0], qy = y + off[1], qz = zz + off[2];
+  if (qx < 0 || qy < 0 || qz < 0 || qx >= n || qy >= n || qz >= n) return;
+  const int64_t at = (8 * e + row) * m + 8 * (((int64_t)qz * n + qy) * n + qx);
+  const int rc = n < kRasClassMinN ? int(e) : ras_axis(x, n) + 7 * ras_axis(y, n) + 49 * ras_axis(zz, n);
+  const double* K = ras + ((int64_t)rc * 8 + row) * kRasCols + 8 * d;
+  for (int b = 0; b < 8; ++b) S[at + b] = K[b];
+  int slot = -1;
+  if (!off[0] && !off[1] && !off[2]) slot = 0;
+  for (int a = 0; a < 3; ++a)
+    if (!off[(a + 1) % 3] && !off[(a + 2) % 3] && (off[a] == 1 || off[a] == -1))
+      slot = 1 + 2 * a + (off[a] > 0);
+  if (slot < 0) return;
+  const int oc = op_axis(x, n) + 3 * op_axis(y, n) + 9 * op_axis(zz, n);
+  const double* B = op + ((oc * kSlots + slot) * 8 + row) * 8;
+  for (int b = 0; b < 8; ++b) L[at + b] = B[b];
+}
+
+// K = P C P^T: entry (8 c + i, 8 c' + i') sums the injection coefficients of the
+// two fine corners with the coarse block of their parents.
+__global__ __launch_bounds__(kThreads) void k_mg3_dense_coarse(int n, const double* __restrict__ C,
+                                                               double* __restrict__ K) {
+  const int64_t m = 8 * (int64_t)n * n * n, mc = m / 8;
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (t >= m * m) return;
+  const int64_t R = t / m, Cc = t % m;
+  const int nc = n / 2;
+  auto parent = [&](int64_t v, int& q, int& i) {
+    const int64_t e = v >> 3;
+    const int x = int(e % n), y = int((e / n) % n), z = int(e / ((int64_t)n * n));
+    q = (x & 1) | ((y & 1) << 1) | ((z & 1) << 2);
+    i = int(v & 7);
+    return ((int64_t)(z >> 1) * nc + (y >> 1)) * nc + (x >> 1);
+  };
+  int q, i, q2, i2;
+  const int64_t E = parent(R, q, i), F = parent(Cc, q2, i2);
+  double acc = 0.0;
+  for (int I = 0; I < 8; ++I) {
+    const double pi = inject(q, i, I);
+    if (pi == 0.0) continue;
+    double a = 0.0;
+    for (int J = 0; J < 8; ++J) a += C[(8 * E + I) * mc + 8 * F + J] * inject(q2, i2, J);
+    acc += pi * a;
+  }
+  K[t] = acc;
+}
+
+__global__ __launch_bounds__(kThreads) void k_mg3_dense_add(int64_t m, double c, const double* B,
+                                                            double* A) {
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (t >= m * m) return;
+  if (B) A[t] += c * B[t];
+  else if (t / m == t % m) A[t] += c;
 }
 
 __global__ __launch_bounds__(kThreads) void k_mg3_start(int64_t len, double* __restrict__ z,
@@ -391,37 +489,42 @@ __global__ __launch_bounds__(kThreads) void k_mg3_scale(int64_t len, double a,
 
 unsigned cube_blocks(int64_t cubes) { return unsigned((cubes + kCubesPerBlock - 1) / kCubesPerBlock); }
 
-unsigned brick_blocks(int n) { return unsigned(bricks_along(n) * bricks_along(n) * bricks_along(n)); }
+// One wavefront per workgroup: the level of 16 cubes per side has 516 tasks, two
+// per compute unit, where workgroups of four left half of the units idle.
+unsigned task_blocks(const Mg3LevelDev& L) { return unsigned(L.tasks); }
 
 }  // namespace
 
 bool mg3_split(int nk) { return nk <= kSplitMaxN; }
 
-int mg3_res_blocks(int nk) {
-  return mg3_split(nk) ? int((8 * (int64_t)nk * nk * nk + kThreads / 8 - 1) / (kThreads / 8))
-                       : int(brick_blocks(nk));
+int mg3_res_blocks(const Mg3LevelDev& L) {
+  return mg3_split(L.n) ? int((8 * (int64_t)L.n * L.n * L.n + kThreads / 8 - 1) / (kThreads / 8))
+                        : int(task_blocks(L));
 }
 
-hipError_t launch_mg3_res(int nk, const double* op, const double* f, const double* z, double* r,
+hipError_t launch_mg3_res(const Mg3LevelDev& L, const double* f, const double* z, double* r,
                           double* part, const int32_t* guard, hipStream_t st) {
-  if (mg3_split(nk))
-    hipLaunchKernelGGL(k_mg3_res_split, dim3(mg3_res_blocks(nk)), dim3(kThreads), 0, st, nk, op, f, z,
+  if (mg3_split(L.n)) {
+    hipLaunchKernelGGL(k_mg3_res_split, dim3(mg3_res_blocks(L)), dim3(kThreads), 0, st, L.n, L.op, f, z,
                        r, part, guard);
-  else
-    hipLaunchKernelGGL(k_mg3_res, dim3(mg3_res_blocks(nk)), dim3(kBrickThreads), 0, st, nk, op, f, z, r,
-                       part, guard);
+  } else {
+    if (!L.cubes || L.tasks <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mg3_res, dim3(task_blocks(L)), dim3(64), 0, st, L.n, L.tasks, L.cubes,
+                       L.cls, L.op, f, z, r, part, guard);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_mg3_ras(int nk, const double* ras, const double* r, double* z, bool zero,
+hipError_t launch_mg3_ras(const Mg3LevelDev& L, const double* r, double* z, bool zero,
                           const int32_t* guard, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  if (mg3_split(nk)) {
-    const int64_t outs = 8 * (int64_t)nk * nk * nk;
+  if (mg3_split(L.n)) {
+    const int64_t outs = 8 * (int64_t)L.n * L.n * L.n;
     hipExtLaunchKernelGGL(k_mg3_ras_split, dim3(unsigned((outs + kThreads / 32 - 1) / (kThreads / 32))),
-                          dim3(kThreads), 0, st, ev0, ev1, 0, nk, ras, r, z, int(zero), guard);
+                          dim3(kThreads), 0, st, ev0, ev1, 0, L.n, L.ras, r, z, int(zero), guard);
   } else {
-    hipExtLaunchKernelGGL(k_mg3_ras, dim3(brick_blocks(nk)), dim3(kBrickThreads), 0, st, ev0, ev1, 0, nk,
-                          ras, r, z, int(zero), guard);
+    if (!L.cubes || L.tasks <= 0) return hipErrorInvalidValue;
+    hipExtLaunchKernelGGL(k_mg3_ras, dim3(task_blocks(L)), dim3(64), 0, st, ev0, ev1, 0, L.n,
+                          L.tasks, L.cubes, L.cls, L.ras, r, z, int(zero), guard);
   }
   return hipGetLastError();
 }
@@ -443,8 +546,34 @@ hipError_t launch_mg3_prolong(int nf, const double* zc, double* z, bool assign,
 
 hipError_t launch_mg3_dense(int m, const double* inv, const double* f, double* z,
                             const int32_t* guard, hipStream_t st) {
-  hipLaunchKernelGGL(k_mg3_dense, dim3((m + kThreads - 1) / kThreads), dim3(kThreads), 0, st, m, inv,
-                     f, z, guard);
+  hipLaunchKernelGGL(k_mg3_dense, dim3((m + kThreads / 64 - 1) / (kThreads / 64)), dim3(kThreads), 0, st,
+                     m, inv, f, z, guard);
+  return hipGetLastError();
+}
+
+hipError_t launch_mg3_dense_tables(int nk, const double* op, const double* ras, double* L, double* S,
+                                   hipStream_t st) {
+  if (!mg3_split(nk)) return hipErrorInvalidValue;
+  const int64_t m = 8 * (int64_t)nk * nk * nk;
+  for (double* A : {L, S}) {
+    const hipError_t e = hipMemsetAsync(A, 0, m * m * sizeof(double), st);   // set-up, never captured
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_mg3_dense_tables, dim3(unsigned((m * 32 + kThreads - 1) / kThreads)),
+                     dim3(kThreads), 0, st, nk, op, ras, L, S);
+  return hipGetLastError();
+}
+
+hipError_t launch_mg3_dense_coarse(int nk, const double* C, double* K, hipStream_t st) {
+  const int64_t m = 8 * (int64_t)nk * nk * nk;
+  hipLaunchKernelGGL(k_mg3_dense_coarse, dim3(unsigned((m * m + kThreads - 1) / kThreads)), dim3(kThreads),
+                     0, st, nk, C, K);
+  return hipGetLastError();
+}
+
+hipError_t launch_mg3_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st) {
+  hipLaunchKernelGGL(k_mg3_dense_add, dim3(unsigned((m * m + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                     st, m, c, B, A);
   return hipGetLastError();
 }
 
