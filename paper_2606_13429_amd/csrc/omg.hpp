@@ -26,8 +26,9 @@
 //                        domain); cls = px + 7 py with p = x (x < 3),
 //                        6 - (n_k - 1 - x) (n_k - 1 - x < 3), else 3; levels
 //                        below 6 squares per side take cls = e
-// and the coarsest level the dense inverse of its operator, row-major.  The
-// MFMA kernels read both tables in the operand order of v_mfma_f64_16x16x4f64
+// and the coarsest level the dense inverse of its operator, row-major, the level
+// of 16 x 16 squares (when it is not the finest) the dense matrix of its two
+// coarse cycles (both are fixed linear maps of f_k).  The MFMA kernels read both tables in the operand order of v_mfma_f64_16x16x4f64
 // (a 16-row table times 16 squares' gathered inputs, four columns a step):
 //   opm  [9][20][64], rasm [49][52][64]: entry (cls, s, l) = row l % 16,
 //                        column 4 s + l / 16 of the row-major table above
@@ -51,6 +52,9 @@ constexpr int kOmgCoarsest = 8;
 constexpr int kOmgOpCols = 5 * kOmgDofs;   // self and the four edge neighbours
 constexpr int kOmgRasSteps = kOmgRasCols / 4;
 constexpr int kOmgOpSteps = kOmgOpCols / 4;
+constexpr int kOmgSplitMaxN = 16;      // levels up to this size: one lane per term group
+constexpr int kOmgTaskMaxN = 128;      // levels up to this size: tasks of 16 squares of a class
+constexpr int kOmgFoldMaxDofs = 4096;  // largest level (16 x 16 squares) kept as a dense matrix
 
 struct OmgLevel {
   int n = 0;
@@ -81,19 +85,43 @@ int omg_num_levels(int n);
 // inverses by Cholesky) and the coarsest inverse.  Throws on failure.
 OmgHierarchy build_omg(int n, double penalty, double dt, double nu);
 
+// Tasks of the kernels of a middle level: groups of 16 squares of one RAS class
+// (and so of one operator class), entry 16 t + i the i-th square of task t -- or,
+// past the last one, the complement ~e of the task's first square e, whose values
+// a lane may read -- and the RAS class of every task.  Squares of a class ascending.
+void omg_tasks(int nk, std::vector<int32_t>& squares, std::vector<int32_t>& cls);
+constexpr int kOmgRasInterior = 3 + 7 * 3;   // class at least 3 squares from every side
+constexpr int kOmgOpInterior = 1 + 3 * 1;
+
+// The tables (row-major and in the operand order) and the task list (levels
+// above kOmgSplitMaxN up to kOmgTaskMaxN) of one level on the device.
+struct OmgLevelDev {
+  int n = 0;
+  const double *op = nullptr, *ras = nullptr, *opm = nullptr, *rasm = nullptr;
+  const int32_t *squares = nullptr, *cls = nullptr;
+  int tasks = 0;
+};
+
 // ---- launchers (FP64; level vectors as above)
-// r = f - A*_k z (f may be NULL: r = -A*_k z); op and opm the level's
-// operator table in both orders.
-hipError_t launch_omg_res(int nk, const double* op, const double* opm, const double* f, const double* z,
-                          double* r, hipStream_t st);
-// z = (zero ? 0 : z) + S_k r; ras and rasm the level's RAS table in both orders.
-hipError_t launch_omg_ras(int nk, const double* ras, const double* rasm, const double* r, double* z,
-                          bool zero, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// r = f - A*_k z (f may be NULL: r = -A*_k z).
+hipError_t launch_omg_res(const OmgLevelDev& L, const double* f, const double* z, double* r,
+                          hipStream_t st);
+// z = (zero ? 0 : z) + S_k r.
+hipError_t launch_omg_ras(const OmgLevelDev& L, const double* r, double* z, bool zero, hipStream_t st,
+                          hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // fc = P_k^T r (nf fine squares per side).
 hipError_t launch_omg_restrict(int nf, const double* r, double* fc, hipStream_t st);
 // z += P_k zc, or z = P_k zc with assign.
 hipError_t launch_omg_prolong(int nf, const double* zc, double* z, bool assign, hipStream_t st);
-// z = inv f (dense m x m, row-major).
-hipError_t launch_omg_dense(int m, const double* inv, const double* f, double* z, hipStream_t st);
+// z = A f (dense m x m, row-major, m even).
+hipError_t launch_omg_dense(int m, const double* A, const double* f, double* z, hipStream_t st);
+
+// ---- dense forms of a small level (set-up; nk <= kOmgSplitMaxN)
+// L = the level operator, S = the RAS update, m x m row-major, m = 16 nk^2.
+hipError_t launch_omg_dense_tables(const OmgLevelDev& L, double* A, double* S, hipStream_t st);
+// K = P C P^T of level nk, C dense on the next coarser one.
+hipError_t launch_omg_dense_coarse(int nk, const double* C, double* K, hipStream_t st);
+// A += c B (m x m; B = NULL: c times the identity).
+hipError_t launch_omg_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st);
 
 }  // namespace dcg

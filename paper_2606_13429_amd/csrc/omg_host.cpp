@@ -2,9 +2,11 @@
 // preconditioner (layouts in omg.hpp): class tables of the level operators,
 // the Galerkin products P^T A* P (Algorithm 2's rule), the RAS update tables
 // of Section 4.2 and the coarsest inverse.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <stdexcept>
+#include <thread>
 #include <vector>
 
 #include "host_setup.hpp"
@@ -210,13 +212,21 @@ std::vector<double> coarsest_inverse(const std::vector<double>& op, int n) {
       }
     }
   cholesky(A, m);
-  std::vector<double> inv((size_t)m * m), col(m);
-  for (int j = 0; j < m; ++j) {
-    std::fill(col.begin(), col.end(), 0.0);
-    col[j] = 1.0;
-    cho_solve(A, m, col.data());
-    for (int i = 0; i < m; ++i) inv[(size_t)i * m + j] = col[i];
-  }
+  // the columns are independent: one strided share per thread
+  std::vector<double> inv((size_t)m * m);
+  const int nt = int(std::max(1u, std::min(8u, std::thread::hardware_concurrency())));
+  std::vector<std::thread> th;
+  for (int t = 0; t < nt; ++t)
+    th.emplace_back([&, t] {
+      std::vector<double> col(m);
+      for (int j = t; j < m; j += nt) {
+        std::fill(col.begin(), col.end(), 0.0);
+        col[j] = 1.0;
+        cho_solve(A, m, col.data());
+        for (int i = 0; i < m; ++i) inv[(size_t)i * m + j] = col[i];
+      }
+    });
+  for (auto& x : th) x.join();
   return inv;
 }
 
@@ -255,6 +265,22 @@ std::vector<double> omg_op_rows(const std::vector<double>& op) {
         for (int b = 0; b < D; ++b)
           out[((size_t)c * D + a) * kOmgOpCols + D * s + b] = op[(((size_t)c * kSlots + s) * D + a) * D + b];
   return out;
+}
+
+void omg_tasks(int nk, std::vector<int32_t>& squares, std::vector<int32_t>& cls) {
+  std::vector<std::vector<int32_t>> of(kOmgRasClasses);
+  for (int y = 0; y < nk; ++y)
+    for (int x = 0; x < nk; ++x) of[ras_axis(x, nk) + 7 * ras_axis(y, nk)].push_back(y * nk + x);
+  squares.clear();
+  cls.clear();
+  // the interior class first: its tasks are most of the level and run in mesh order
+  for (int i = 0; i < kOmgRasClasses; ++i) {
+    const int c = i == 0 ? kOmgRasInterior : (i <= kOmgRasInterior ? i - 1 : i);
+    for (size_t j = 0; j < of[c].size(); j += 16) {
+      cls.push_back(c);
+      for (size_t t = j; t < j + 16; ++t) squares.push_back(t < of[c].size() ? of[c][t] : ~of[c][j]);
+    }
+  }
 }
 
 int omg_num_levels(int n) {

@@ -4,13 +4,9 @@
 // The RAS step and the residual split every output (square, row) over a few
 // lanes on levels of at most kOmgSplitMaxN squares per side (one lane per
 // diamond square resp. face slot, one round of 128-byte loads each, a fixed
-// shuffle sum), where a launch has few workgroups and its time is one
-// thread's chain of loads.  Larger levels stage the input of an 8 x 8 brick
-// in LDS and run the step as FP64 MFMA products of the class tables with the
-// brick's gathered inputs (measured against vector-FMA bricks with the table
-// rows read per lane or through scalar loads: 2-5x faster from 128 squares
-// per side up, 1.3x at 64; slower than the split kernels below 64, where
-// every brick is a boundary brick whose several classes cost one trip each).
+// shuffle sum).  Larger levels run them as FP64 MFMA products of a class table
+// with the inputs of 16 squares: gathered by each wavefront for the squares of one
+// class up to kOmgTaskMaxN, staged in LDS by 8 x 8 bricks above.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -23,7 +19,6 @@ namespace {
 
 constexpr int D = kOmgDofs;
 constexpr int kThreads = 256;
-constexpr int kOmgSplitMaxN = 32;
 
 __device__ __forceinline__ int op_axis(int x, int n) { return x == 0 ? 0 : (x == n - 1 ? 2 : 1); }
 __device__ __forceinline__ int ras_axis(int x, int n) {
@@ -106,6 +101,110 @@ __global__ __launch_bounds__(kThreads) void k_omg_res_split(int n, const double*
   if (s == 0 && e < ne) r[D * e + row] = (f ? f[D * e + row] : 0.0) + acc;
 }
 
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// ---- middle levels (kOmgSplitMaxN < n_k <= kOmgTaskMaxN): one wavefront per task
+// of 16 squares of one class, the class's 16 rows times the squares' gathered
+// inputs with v_mfma_f64_16x16x4f64, four table columns a step.  Lane l supplies
+// row l % 16, column 4 s + l / 16 of the table (the operand-order tables make a
+// step's operand one contiguous 512-byte run) and input value 4 s + l / 16 of
+// square l % 16's window, and receives rows 4 v + l / 16 (v = 0..3) of that square.
+// All operands come from L1 / L2: no LDS, no barrier, and boundary tasks cost what
+// interior ones do.  A RAS step takes 5.5 / 6.5 / 12.3 us and a residual 3.5 / 4.1 /
+// 6.6 us at n = 32 / 64 / 128, where the split kernels (32) took 8.7 and 4.8 us and
+// the bricks below 19.7 / 20.7 and 8.8 / 8.7 us; at 256 the gathers, 16 lanes in 16
+// cache lines, make it 37 us against the bricks' 27.5 us.
+struct Task {
+  int q, cls, x, y, e;   // lane group, RAS class, the lane's square
+  bool valid;
+};
+
+// Workgroups go round robin to the 8 XCDs: each takes a contiguous run of tasks.
+__device__ __forceinline__ Task load_task(int n, const int32_t* __restrict__ squares,
+                                          const int32_t* __restrict__ cls, int tasks) {
+  const int b = blockIdx.x, per = tasks >> 3;
+  const int id = b < 8 * per ? (b & 7) * per + (b >> 3) : b;
+  Task t;
+  t.q = threadIdx.x >> 4;
+  t.cls = cls[id];
+  const int e = squares[16 * id + (threadIdx.x & 15)];
+  t.valid = e >= 0;
+  t.e = e >= 0 ? e : ~e;   // padding repeats a square of the task
+  t.x = t.e % n;
+  t.y = t.e / n;
+  return t;
+}
+
+// The four table steps of each of the NB neighbours at OFF; loads are
+// unconditional (from the square itself outside the domain).
+template <int NB, typename OFF>
+__device__ __forceinline__ v4d task_products(const Task& t, int n, OFF off, const double* __restrict__ A,
+                                             const double* __restrict__ v) {
+  double u[NB][4];
+#pragma unroll
+  for (int d = 0; d < NB; ++d) {
+    const int dx = off(d, 0), dy = off(d, 1);
+    const bool in = t.x + dx >= 0 && t.y + dy >= 0 && t.x + dx < n && t.y + dy < n;
+    const double* p = v + D * (int64_t)(t.e + (in ? dy * n + dx : 0)) + t.q;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double x = p[4 * s];
+      u[d][s] = in ? x : 0.0;
+    }
+  }
+  v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
+#pragma unroll
+  for (int d = 0; d < NB; ++d) {
+    a0 = mfma64(A[64 * (4 * d)], u[d][0], a0);
+    a1 = mfma64(A[64 * (4 * d + 1)], u[d][1], a1);
+    a0 = mfma64(A[64 * (4 * d + 2)], u[d][2], a0);
+    a1 = mfma64(A[64 * (4 * d + 3)], u[d][3], a1);
+  }
+  return a0 + a1;
+}
+
+__global__ __launch_bounds__(64) void k_omg_ras(int n, int tasks, const int32_t* __restrict__ squares,
+                                                const int32_t* __restrict__ cls,
+                                                const double* __restrict__ rasm,
+                                                const double* __restrict__ r, double* __restrict__ z,
+                                                int zero) {
+  const Task t = load_task(n, squares, cls, tasks);
+  constexpr Diamond2 DM;
+  auto off = [&](int d, int a) { return DM.d[d][a]; };
+  double zv[4];
+  double* zp = z + D * (int64_t)t.e + t.q;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) zv[v] = zero ? 0.0 : zp[4 * v];
+  const double* A = rasm + (int64_t)t.cls * kOmgRasSteps * 64 + threadIdx.x;
+  const v4d a = task_products<kOmgDiamond>(t, n, off, A, r);
+  if (t.valid)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) zp[4 * v] = zv[v] + a[v];
+}
+
+__global__ __launch_bounds__(64) void k_omg_res(int n, int tasks, const int32_t* __restrict__ squares,
+                                                const int32_t* __restrict__ cls,
+                                                const double* __restrict__ opm,
+                                                const double* __restrict__ f,
+                                                const double* __restrict__ z, double* __restrict__ r) {
+  const Task t = load_task(n, squares, cls, tasks);
+  auto off = [&](int s, int a) { return kSlotOff[s][a]; };
+  // operator class: 0 low side, 2 high side, 1 inside of the distance class
+  const int px = t.cls % 7, py = t.cls / 7;
+  const int oc = (px == 0 ? 0 : (px == 6 ? 2 : 1)) + 3 * (py == 0 ? 0 : (py == 6 ? 2 : 1));
+  double fv[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) fv[v] = f ? f[D * (int64_t)t.e + 4 * v + t.q] : 0.0;
+  const double* A = opm + (int64_t)oc * kOmgOpSteps * 64 + threadIdx.x;
+  const v4d a = task_products<kSlots>(t, n, off, A, z);
+  if (t.valid)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) r[D * (int64_t)t.e + 4 * v + t.q] = fv[v] - a[v];
+}
+
 // ---- large levels: 8 x 8 bricks with their input staged in LDS
 constexpr int kBrick = 8;
 
@@ -141,10 +240,7 @@ __device__ __forceinline__ void stage_box(int n, int x0, int y0, const double* _
 // accumulators; boundary bricks, dispatched first, take the distinct classes
 // of each wavefront one after the other with the table read from global
 // memory, keeping for each square the product with its own class.
-typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kMfmaThreads = 256;   // 4 wavefronts x 16 squares = one brick
-constexpr int kRasInterior = 3 + 7 * 3;
-constexpr int kOpInterior = 1 + 3 * 1;
 
 struct MfmaLane {
   int x0, y0, x, y, q, o1, o2;   // brick, square, output row group, LDS offsets (halo 1 / 2)
@@ -187,10 +283,6 @@ __device__ __forceinline__ MfmaLane mfma_lane(int n) {
   L.o2 = (ly + 2) * Box2<2>::X + lx + 2;
   L.e = (int64_t)L.y * n + L.x;
   return L;
-}
-
-__device__ __forceinline__ v4d mfma64(double a, double b, v4d c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // Copies one class table (steps x 64 doubles, operand order) into LDS.
@@ -271,7 +363,7 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(3)
   __shared__ int scls[kBrick * kBrick], sperm[kBrick * kBrick];
   MfmaLane L = mfma_lane(n);
   const int lane = threadIdx.x & 63;
-  if (L.interior) stage_table<kOmgRasSteps>(rasm + (int64_t)kRasInterior * kOmgRasSteps * 64, kt);
+  if (L.interior) stage_table<kOmgRasSteps>(rasm + (int64_t)kOmgRasInterior * kOmgRasSteps * 64, kt);
   stage_box<2>(n, L.x0, L.y0, r, rs);
   if (!L.interior) sort_squares(L, n, [n](int x, int y) { return ras_class(x, y, n); }, scls, sperm);
   v4d acc;
@@ -309,7 +401,7 @@ __global__ __launch_bounds__(kMfmaThreads) void k_omg_res_m(int n, const double*
   __shared__ int scls[kBrick * kBrick], sperm[kBrick * kBrick];
   MfmaLane L = mfma_lane(n);
   const int lane = threadIdx.x & 63;
-  if (L.interior) stage_table<kOmgOpSteps>(opm + (int64_t)kOpInterior * kOmgOpSteps * 64, kt);
+  if (L.interior) stage_table<kOmgOpSteps>(opm + (int64_t)kOmgOpInterior * kOmgOpSteps * 64, kt);
   stage_box<1>(n, L.x0, L.y0, z, zs);
   if (!L.interior)
     sort_squares(L, n, [n](int x, int y) { return op_axis(x, n) + 3 * op_axis(y, n); }, scls, sperm);
@@ -385,49 +477,149 @@ __global__ __launch_bounds__(kThreads) void k_omg_prolong(int nf, const double* 
   z[t] = assign ? acc : z[t] + acc;
 }
 
-// z = inv f: one wavefront per row, lanes over the columns, a fixed shuffle sum.
-__global__ __launch_bounds__(kThreads) void k_omg_dense(int m, const double* __restrict__ inv,
+// z = A f, A dense m x m (m even): one wavefront per row, lanes over pairs of
+// columns, a fixed shuffle sum.  Bound by the matrix (134 MB at m = 4096).
+__global__ __launch_bounds__(kThreads) void k_omg_dense(int m, const double* __restrict__ A,
                                                         const double* __restrict__ f,
                                                         double* __restrict__ z) {
-  const int row = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (i >= m) return;   // whole wavefronts
+  const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
+  const double2* f2 = reinterpret_cast<const double2*>(f);
   double acc = 0.0;
-  if (row < m) {
-    const double* a = inv + (int64_t)row * m;
-    for (int j = lane; j < m; j += 64) acc += a[j] * f[j];
+#pragma unroll 8
+  for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
+    const double2 a = row[j], b = f2[j];
+    acc += a.x * b.x + a.y * b.y;
   }
 #pragma unroll
-  for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s, 64);
-  if (row < m && lane == 0) z[row] = acc;
+  for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);
+  if ((threadIdx.x & 63) == 0) z[i] = acc;
 }
 
-unsigned blocks_for(int64_t threads) { return unsigned((threads + kThreads - 1) / kThreads); }
+// Dense operator and RAS update of a small level from its row-major tables (both
+// cleared before): thread (square, row, diamond square).
+__global__ __launch_bounds__(kThreads) void k_omg_dense_tables(int n, const double* __restrict__ op,
+                                                               const double* __restrict__ ras,
+                                                               double* __restrict__ A,
+                                                               double* __restrict__ S) {
+  constexpr Diamond2 DM;
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t m = D * (int64_t)n * n;
+  if (i >= m * 16) return;
+  const int d = int(i & 15), row = int((i >> 4) % D);
+  const int64_t e = i / (16 * D);
+  if (d >= kOmgDiamond) return;
+  int dx = 0, dy = 0;
+  for (int k = 0; k < kOmgDiamond; ++k)
+    if (k == d) {
+      dx = DM.d[k][0];
+      dy = DM.d[k][1];
+    }
+  const int x = int(e % n), y = int(e / n), qx = x + dx, qy = y + dy;
+  if (qx < 0 || qy < 0 || qx >= n || qy >= n) return;
+  const int64_t at = (D * e + row) * m + D * ((int64_t)qy * n + qx);
+  const double* K = ras + ((int64_t)ras_class(x, y, n) * D + row) * kOmgRasCols + D * d;
+  for (int b = 0; b < D; ++b) S[at + b] = K[b];
+  for (int s = 0; s < kSlots; ++s)
+    if (kSlotOff[s][0] == dx && kSlotOff[s][1] == dy) {
+      const double* B = op + (((op_axis(x, n) + 3 * op_axis(y, n)) * kSlots + s) * D + row) * D;
+      for (int b = 0; b < D; ++b) A[at + b] = B[b];
+    }
+}
+
+// K = P C P^T: entry (16 e + 4 c + i, 16 e' + 4 c' + i') sums the injection
+// coefficients of the two fine corners with the coarse block of their parents.
+__global__ __launch_bounds__(kThreads) void k_omg_dense_coarse(int n, const double* __restrict__ C,
+                                                               double* __restrict__ K) {
+  const int64_t m = D * (int64_t)n * n, mc = m / 4;
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (t >= m * m) return;
+  const int nc = n / 2;
+  auto parent = [&](int64_t v, int& q, int& i) {   // first coarse dof of the component
+    const int64_t e = v / D;
+    const int x = int(e % n), y = int(e / n), dof = int(v % D);
+    q = (x & 1) | ((y & 1) << 1);
+    i = dof & 3;
+    return D * ((int64_t)(y >> 1) * nc + (x >> 1)) + 4 * (dof >> 2);
+  };
+  int q, i, q2, i2;
+  const int64_t E = parent(t / m, q, i), F = parent(t % m, q2, i2);
+  double acc = 0.0;
+  for (int I = 0; I < 4; ++I) {
+    double a = 0.0;
+    for (int J = 0; J < 4; ++J) a += C[(E + I) * mc + F + J] * inject(q2, i2, J);
+    acc += inject(q, i, I) * a;
+  }
+  K[t] = acc;
+}
+
+__global__ __launch_bounds__(kThreads) void k_omg_dense_add(int64_t m, double c, const double* B,
+                                                            double* A) {
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (t >= m * m) return;
+  if (B) A[t] += c * B[t];
+  else if (t / m == t % m) A[t] += c;
+}
+
 unsigned bricks(int nk) { return unsigned((nk / kBrick) * (nk / kBrick)); }
+unsigned blocks_for(int64_t threads) { return unsigned((threads + kThreads - 1) / kThreads); }
 
 }  // namespace
 
-hipError_t launch_omg_res(int nk, const double* op, const double* opm, const double* f, const double* z,
-                          double* r, hipStream_t st) {
-  if (nk <= kOmgSplitMaxN) {
-    hipLaunchKernelGGL(k_omg_res_split, dim3(blocks_for(8 * (int64_t)D * nk * nk)), dim3(kThreads), 0, st,
-                       nk, op, f, z, r);
+hipError_t launch_omg_res(const OmgLevelDev& L, const double* f, const double* z, double* r,
+                          hipStream_t st) {
+  if (L.n <= kOmgSplitMaxN) {
+    hipLaunchKernelGGL(k_omg_res_split, dim3(blocks_for(8 * (int64_t)D * L.n * L.n)), dim3(kThreads), 0, st,
+                       L.n, L.op, f, z, r);
+  } else if (L.n <= kOmgTaskMaxN) {
+    if (!L.squares || L.tasks <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_omg_res, dim3(L.tasks), dim3(64), 0, st, L.n, L.tasks, L.squares, L.cls, L.opm, f,
+                       z, r);
   } else {
-    if (nk % kBrick) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_omg_res_m, dim3(bricks(nk)), dim3(kMfmaThreads), 0, st, nk, opm, f, z, r);
+    if (L.n % kBrick) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_omg_res_m, dim3(bricks(L.n)), dim3(kMfmaThreads), 0, st, L.n, L.opm, f, z, r);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_omg_ras(int nk, const double* ras, const double* rasm, const double* r, double* z,
-                          bool zero, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  if (nk <= kOmgSplitMaxN) {
-    hipExtLaunchKernelGGL(k_omg_ras_split, dim3(blocks_for(16 * (int64_t)D * nk * nk)), dim3(kThreads), 0,
-                          st, ev0, ev1, 0, nk, ras, r, z, int(zero));
+hipError_t launch_omg_ras(const OmgLevelDev& L, const double* r, double* z, bool zero, hipStream_t st,
+                          hipEvent_t ev0, hipEvent_t ev1) {
+  if (L.n <= kOmgSplitMaxN) {
+    hipExtLaunchKernelGGL(k_omg_ras_split, dim3(blocks_for(16 * (int64_t)D * L.n * L.n)), dim3(kThreads), 0,
+                          st, ev0, ev1, 0, L.n, L.ras, r, z, int(zero));
+  } else if (L.n <= kOmgTaskMaxN) {
+    if (!L.squares || L.tasks <= 0) return hipErrorInvalidValue;
+    hipExtLaunchKernelGGL(k_omg_ras, dim3(L.tasks), dim3(64), 0, st, ev0, ev1, 0, L.n, L.tasks, L.squares,
+                          L.cls, L.rasm, r, z, int(zero));
   } else {
-    if (nk % kBrick) return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(k_omg_ras_m, dim3(bricks(nk)), dim3(kMfmaThreads), 0, st, ev0, ev1, 0, nk, rasm,
-                          r, z, int(zero));
+    if (L.n % kBrick) return hipErrorInvalidValue;
+    hipExtLaunchKernelGGL(k_omg_ras_m, dim3(bricks(L.n)), dim3(kMfmaThreads), 0, st, ev0, ev1, 0, L.n,
+                          L.rasm, r, z, int(zero));
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_omg_dense_tables(const OmgLevelDev& L, double* A, double* S, hipStream_t st) {
+  if (L.n > kOmgSplitMaxN) return hipErrorInvalidValue;
+  const int64_t m = D * (int64_t)L.n * L.n;
+  for (double* M : {A, S}) {
+    const hipError_t e = hipMemsetAsync(M, 0, m * m * sizeof(double), st);   // set-up, never captured
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_omg_dense_tables, dim3(blocks_for(m * 16)), dim3(kThreads), 0, st, L.n, L.op, L.ras,
+                     A, S);
+  return hipGetLastError();
+}
+
+hipError_t launch_omg_dense_coarse(int nk, const double* C, double* K, hipStream_t st) {
+  const int64_t m = D * (int64_t)nk * nk;
+  hipLaunchKernelGGL(k_omg_dense_coarse, dim3(blocks_for(m * m)), dim3(kThreads), 0, st, nk, C, K);
+  return hipGetLastError();
+}
+
+hipError_t launch_omg_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st) {
+  hipLaunchKernelGGL(k_omg_dense_add, dim3(blocks_for(m * m)), dim3(kThreads), 0, st, m, c, B, A);
   return hipGetLastError();
 }
 

@@ -11,6 +11,7 @@
 #include "../../include/dcg.h"
 #include "host_setup.hpp"
 #include "kernels.hpp"
+#include "omg.hpp"
 
 namespace dcg {
 
@@ -157,6 +158,8 @@ struct OuterMg {
   std::vector<int> n;
   std::vector<double*> op, ras, f, z, r;
   std::vector<double*> opm, rasm;   // the tables in MFMA operand order
+  std::vector<OmgLevelDev> lev;     // what the level kernels take
+  std::vector<double*> fold;        // the two coarse cycles of a small level as a matrix
   double* cinv = nullptr;
   double* zp = nullptr;            // B r of the current outer iteration (16 n^2)
   hipGraphExec_t graph = nullptr;
