@@ -495,21 +495,11 @@ struct dcg3d_ctx {
     const int64_t m = 8 * (int64_t)nk * nk * nk;
     if (m > dcg3::kFoldMaxDofs || (k > 2 && !mg_fold[i - 1])) return;
     struct Temp {
-      std::vector<double*> v;
-      ~Temp() {
-        for (double* b : v) (void)hipFree(b);
-      }
-      double* add(int64_t len) {
-        v.push_back(dev_alloc<double>(len));
-        return v.back();
-      }
+      double* p = nullptr;
+      ~Temp() { (void)hipFree(p); }
     } tmp;
-    double* L = tmp.add(m * m);
-    double* S = tmp.add(m * m);
-    double* E = tmp.add(m * m);
-    double* Ei = tmp.add(m * m);
-    double* P = tmp.add(m * m);
-    double* T = tmp.add(m * m);
+    tmp.p = dev_alloc<double>(6 * m * m);
+    double *L = tmp.p, *S = L + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
     double* C = dev_alloc<double>(m * m);
     mg_fold[i] = C;
     const size_t bytes = size_t(m * m) * sizeof(double);

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
                                                     double dt, const double* __restrict__ x,
                                                     double* __restrict__ y, double inv_sqrt3,
                                                     double* __restrict__ s) {
-  __shared__ double tab[kFixedTiles * 64];
+  __shared__ __align__(16) double tab[kFixedTiles * 64];
   __shared__ double zl[G * 16][3][kNb];
   const int ne = n * n * n;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -107,16 +107,30 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
     const int nb = live ? nbr3(n, e, sl) : -1;
     const double2* p = reinterpret_cast<const double2*>(x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q);
 #pragma unroll
-    for (int t = 0; t < 3; ++t) v[sl][t] = nb >= 0 ? p[4 * t] : make_double2(0.0, 0.0);
+    for (int t = 0; t < 3; ++t) {   // unconditional loads (of element 0 outside the domain)
+      v[sl][t] = p[4 * t];
+      v[sl][t].x = nb >= 0 ? v[sl][t].x : 0.0;
+      v[sl][t].y = nb >= 0 ? v[sl][t].y : 0.0;
+    }
   }
   // sigma_{k1 k1} + sigma_{k2 k2} of the other two rows, for the mass term
   const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
-  double2 o1 = make_double2(0.0, 0.0), o2 = o1;
-  if (live) {
-    o1 = *reinterpret_cast<const double2*>(x + (int64_t)e * kDof + 32 * k1 + 2 * q);
-    o2 = *reinterpret_cast<const double2*>(x + (int64_t)e * kDof + 32 * k2 + 2 * q);
+  const double* xe = x + (int64_t)(live ? e : 0) * kDof + 2 * q;
+  const double2 o1 = *reinterpret_cast<const double2*>(xe + 32 * k1);
+  const double2 o2 = *reinterpret_cast<const double2*>(xe + 32 * k2);
+  constexpr int TT = G * 192, NS = (kFixedTiles * 32 + TT - 1) / TT;
+  double2 tv[NS];
+#pragma unroll
+  for (int u = 0; u < NS; ++u) {
+    const int i = threadIdx.x + u * TT;
+    tv[u] = reinterpret_cast<const double2*>(At)[i < kFixedTiles * 32 ? i : 0];
   }
-  for (int i = threadIdx.x; i < kFixedTiles * 64; i += G * 192) tab[i] = At[i];
+  __builtin_amdgcn_sched_barrier(0);   // every load of the element is in flight
+#pragma unroll
+  for (int u = 0; u < NS; ++u) {
+    const int i = threadIdx.x + u * TT;
+    if (i < kFixedTiles * 32) reinterpret_cast<double2*>(tab)[i] = tv[u];
+  }
   __syncthreads();
   v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0, m0 = a0, m1 = a0;
   int tile = 0;
@@ -210,12 +224,9 @@ __global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict_
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
     const int nb = live ? nbr3(n, e, sl) : -1;
-    v[sl] = make_double2(0.0, 0.0);
-    if (nb >= 0) {
-      v[sl] = *reinterpret_cast<const double2*>(yh + (int64_t)nb * kNb + 2 * q);
-      v[sl].x *= inv_sqrt3;
-      v[sl].y *= inv_sqrt3;
-    }
+    const double2 yv = *reinterpret_cast<const double2*>(yh + (int64_t)(nb >= 0 ? nb : 0) * kNb + 2 * q);
+    v[sl].x = nb >= 0 ? yv.x * inv_sqrt3 : 0.0;
+    v[sl].y = nb >= 0 ? yv.y * inv_sqrt3 : 0.0;
   }
   double2 wv[3];
   const double2* wp = reinterpret_cast<const double2*>(w + (int64_t)(live ? e : 0) * kDof + 24 * k);

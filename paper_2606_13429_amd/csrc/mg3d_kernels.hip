@@ -113,11 +113,16 @@ __device__ __forceinline__ Task load_task(int n, const int32_t* __restrict__ cub
 template <bool IN>
 __device__ __forceinline__ double2 task_input(const Task& t, int n, int dx, int dy, int dz,
                                               const double* __restrict__ v) {
-  if (!IN) {
-    const int x = t.x + dx, y = t.y + dy, z = t.z + dz;
-    if (x < 0 || y < 0 || z < 0 || x >= n || y >= n || z >= n) return make_double2(0.0, 0.0);
-  }
-  return *reinterpret_cast<const double2*>(v + 8 * ((dz * n + dy) * n + dx) + 8 * (int64_t)t.e + 2 * t.q);
+  const double* own = v + 8 * (int64_t)t.e + 2 * t.q;
+  const int64_t o = 8 * ((dz * n + dy) * n + dx);
+  if (IN) return *reinterpret_cast<const double2*>(own + o);
+  // the load is unconditional (from the cube itself outside the domain)
+  const int x = t.x + dx, y = t.y + dy, z = t.z + dz;
+  const bool in = x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
+  double2 r = *reinterpret_cast<const double2*>(own + (in ? o : 0));
+  r.x = in ? r.x : 0.0;
+  r.y = in ? r.y : 0.0;
+  return r;
 }
 
 // The products of one task: residual terms L z (7 face slots) or the RAS update
