@@ -708,6 +708,24 @@ __global__ __launch_bounds__(kThreads) void k_coarse(const double* __restrict__ 
   if (lane == 0) z[row] = static_cast<T>(acc);
 }
 
+// z = A f, A dense FP64: one wavefront per row, lanes over pairs of columns, a
+// fixed shuffle sum.  Bound by the matrix (134 MB at m = 4096).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_fold(int m, const double* __restrict__ A,
+                                                   const T* __restrict__ f, T* __restrict__ z) {
+  const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (i >= m) return;   // whole wavefronts
+  const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
+  double acc = 0.0;
+#pragma unroll 8
+  for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
+    const double2 a = row[j];
+    acc += a.x * static_cast<double>(f[2 * j]) + a.y * static_cast<double>(f[2 * j + 1]);
+  }
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) z[i] = static_cast<T>(acc);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_fill(int64_t n, T v, T* __restrict__ x) {
   const int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
@@ -893,6 +911,13 @@ hipError_t launch_coarse(const double* inv, const T* f, T* z, hipStream_t st) {
 }
 
 template <typename T>
+hipError_t launch_fold(int m, const double* A, const T* f, T* z, hipStream_t st) {
+  if (m <= 0 || m % 16) return hipErrorInvalidValue;
+  k_fold<T><<<m / (kThreads / 64), kThreads, 0, st>>>(m, A, f, z);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_fill(int64_t n, T v, T* x, hipStream_t st) {
   k_fill<T><<<grid_for(n, kThreads, 1 << 30), kThreads, 0, st>>>(n, v, x);
   return hipGetLastError();
@@ -913,6 +938,7 @@ hipError_t launch_copy(int64_t n, const T* x, T* y, hipStream_t st) {
   template hipError_t launch_restrict<T>(int, const T*, T*, hipStream_t);                      \
   template hipError_t launch_prolong<T>(int, const T*, T*, hipStream_t);                       \
   template hipError_t launch_coarse<T>(const double*, const T*, T*, hipStream_t);              \
+  template hipError_t launch_fold<T>(int, const double*, const T*, T*, hipStream_t);           \
   template hipError_t launch_fill<T>(int64_t, T, T*, hipStream_t);                             \
   template hipError_t launch_copy<T>(int64_t, const T*, T*, hipStream_t);
 

@@ -188,6 +188,9 @@ template <typename T>
 hipError_t launch_prolong(int nc, const T* ec, T* z, hipStream_t st);
 template <typename T>
 hipError_t launch_coarse(const double* inv, const T* f, T* z, hipStream_t st);
+// z = A f, A dense FP64 m x m (m a multiple of 16) and level vectors of type T
+template <typename T>
+hipError_t launch_fold(int m, const double* A, const T* f, T* z, hipStream_t st);
 template <typename T>
 hipError_t launch_fill(int64_t n, T v, T* x, hipStream_t st);
 template <typename T>
@@ -269,6 +272,14 @@ template <typename T>
 hipError_t launch_restrict_res_b(const RestrictArgs<T>& a, hipStream_t st);
 template <typename T>
 hipError_t launch_coarse_b(const double* inv, const T* f, T* z, hipStream_t st);
+// z = A f for kBatch columns, A dense FP64 m x m (m a multiple of 512)
+template <typename T>
+hipError_t launch_fold_b(int m, const double* A, const T* f, T* z, hipStream_t st);
+// f = the unit vectors j0 .. j0 + kBatch - 1 of a level of ne squares, and
+// A[row][j0 + c] = column c of (has_z ? z : 0) + pending Ye (Ye may be NULL)
+hipError_t launch_unit_columns(int ne, int j0, double* f, hipStream_t st);
+hipError_t launch_store_columns(int ne, int j0, bool has_z, const double* z, const double* Ye, double* A,
+                                hipStream_t st);
 template <typename T>
 hipError_t launch_resolve_b(int ne, bool has_z, const T* z, const T* Ye, T* out, hipStream_t st);
 

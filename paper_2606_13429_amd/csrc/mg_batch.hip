@@ -277,6 +277,70 @@ __global__ __launch_bounds__(kThreads) void k_coarse_b(const double* __restrict_
   }
 }
 
+// z = A f for kBatch columns, A dense FP64 m x m: workgroup R owns rows 16 R ..
+// 16 R + 15, wavefront w of 8 an eighth of the contraction in FP64 MFMA steps,
+// summed in LDS in wavefront order.  Bound by the matrix (134 MB at m = 4096) and
+// the loads' latency, hence four groups of 16 columns' loads in flight.
+constexpr int kFoldWaves = 8;
+template <typename T>
+__global__ __launch_bounds__(64 * kFoldWaves) void k_fold_b(int m, const double* __restrict__ A,
+                                                            const T* __restrict__ f, T* __restrict__ z) {
+  using V = Mfma<double>::v4;
+  __shared__ double red[kFoldWaves][4][64];
+  const int R = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, k = lane >> 4;
+  const double* ir = A + (int64_t)(16 * R + r) * m + 4 * k;
+  V acc = {0.0, 0.0, 0.0, 0.0}, acc1 = acc;
+  const int per = m / 16 / kFoldWaves, g0 = per * wave;
+  for (int g = g0; g < g0 + per; g += 4) {   // contraction dofs 16 g .. 16 g + 63
+    double av[4][4];
+    T bv[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      ld4(ir + 16 * (g + u), av[u]);
+      ld4(f + at(4 * (g + u) + k, r), bv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      acc = Mfma<double>::mac(av[u][0], static_cast<double>(bv[u][0]), acc);
+      acc1 = Mfma<double>::mac(av[u][1], static_cast<double>(bv[u][1]), acc1);
+      acc = Mfma<double>::mac(av[u][2], static_cast<double>(bv[u][2]), acc);
+      acc1 = Mfma<double>::mac(av[u][3], static_cast<double>(bv[u][3]), acc1);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][v][lane] = acc[v] + acc1[v];
+  __syncthreads();
+  if (wave < 4) {   // wavefront v: rows 4 v + k of the block: square 4 R + v, corner k
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFoldWaves; ++w) s += red[w][wave][lane];
+    z[at(4 * R + wave, r) + k] = static_cast<T>(s);
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_unit_columns(int ne, int j0, double* __restrict__ f) {
+  const int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+  if (i >= 4 * (int64_t)B * ne) return;
+  const int64_t e = i / (4 * B);
+  const int c = int((i >> 2) % B), j = int(i & 3);
+  f[i] = 4 * e + j == j0 + c ? 1.0 : 0.0;
+}
+
+__global__ __launch_bounds__(kThreads) void k_store_columns(int ne, int j0, int has_z,
+                                                            const double* __restrict__ z,
+                                                            const double* __restrict__ Ye,
+                                                            double* __restrict__ A) {
+  const int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x;
+  if (i >= 4 * (int64_t)B * ne) return;
+  const int64_t row = i / B, e = row >> 2;
+  const int c = int(i % B), j = int(row & 3);
+  double v = has_z ? z[at(e, c) + j] : 0.0;
+  if (Ye) v = ((v + Ye[at(3 * e, c) + j]) + Ye[at(3 * e + 1, c) + j]) + Ye[at(3 * e + 2, c) + j];
+  A[row * 4 * ne + j0 + c] = v;
+}
+
 // out = (has_z ? z : 0) + pending Ye for kBatch requests.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_resolve_b(int ne, int has_z, const T* __restrict__ z,
@@ -296,6 +360,26 @@ template <typename T>
 hipError_t launch_resolve_b(int ne, bool has_z, const T* z, const T* Ye, T* out, hipStream_t st) {
   const int64_t n = 4 * (int64_t)B * ne;
   k_resolve_b<T><<<int((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(ne, has_z, z, Ye, out);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_fold_b(int m, const double* A, const T* f, T* z, hipStream_t st) {
+  if (m <= 0 || m % (64 * kFoldWaves)) return hipErrorInvalidValue;
+  k_fold_b<T><<<m / 16, 64 * kFoldWaves, 0, st>>>(m, A, f, z);
+  return hipGetLastError();
+}
+
+hipError_t launch_unit_columns(int ne, int j0, double* f, hipStream_t st) {
+  const int64_t n = 4 * (int64_t)B * ne;
+  k_unit_columns<<<int((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(ne, j0, f);
+  return hipGetLastError();
+}
+
+hipError_t launch_store_columns(int ne, int j0, bool has_z, const double* z, const double* Ye, double* A,
+                                hipStream_t st) {
+  const int64_t n = 4 * (int64_t)B * ne;
+  k_store_columns<<<int((n + kThreads - 1) / kThreads), kThreads, 0, st>>>(ne, j0, has_z, z, Ye, A);
   return hipGetLastError();
 }
 
@@ -323,6 +407,7 @@ hipError_t launch_coarse_b(const double* inv, const T* f, T* z, hipStream_t st) 
   template hipError_t launch_sweep_b<T>(const SweepArgs<T>&, hipStream_t);                  \
   template hipError_t launch_restrict_res_b<T>(const RestrictArgs<T>&, hipStream_t);        \
   template hipError_t launch_coarse_b<T>(const double*, const T*, T*, hipStream_t);       \
+  template hipError_t launch_fold_b<T>(int, const double*, const T*, T*, hipStream_t);     \
   template hipError_t launch_resolve_b<T>(int, bool, const T*, const T*, T*, hipStream_t);
 
 DCG_MGB_INSTANTIATE(float)

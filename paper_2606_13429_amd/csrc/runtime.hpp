@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <map>
 #include <memory>
 #include <mutex>
 #include <stdexcept>
@@ -55,6 +56,18 @@ struct DeviceLevel {
   int gx_extra_n[3] = {0, 0, 0};
 };
 
+// The two coarse cycles that level 2 (32 x 32 squares) gives level 3 (Algorithm 4:
+// from zero, then from the first's result) as one dense FP64 matrix: both are
+// fixed linear maps of the level's right-hand side for given m1, m2.
+constexpr int kFoldN = 2 * kCoarsestN;                     // squares per side of level 2
+constexpr int64_t kFoldDofs = 4 * int64_t(kFoldN) * kFoldN;
+constexpr size_t kFoldBytes = size_t(kFoldDofs) * kFoldDofs * sizeof(double);
+struct FoldMatrix {
+  int device = 0;
+  double* C = nullptr;            // [kFoldDofs][kFoldDofs] row-major
+  ~FoldMatrix();
+};
+
 // Dt-independent operators of one mesh on one device; shared by handles and
 // by the serving engine (reference counted through shared_ptr).
 struct MeshContext {
@@ -70,12 +83,23 @@ struct MeshContext {
   std::mutex mu;                  // guards lazy factor uploads
   std::unique_ptr<HostContext> host;   // kept until both factor precisions exist
   bool have_f32 = false, have_f64 = false;
+  // the fold matrices in use by (m1, m2), and the last one made, which stays
+  // with the context (one per mesh, given back with it)
+  std::mutex fold_mu;
+  std::map<std::pair<int, int>, std::weak_ptr<FoldMatrix>> folds;
+  std::shared_ptr<FoldMatrix> last_fold;
 
   ~MeshContext();
   void ensure_factors(bool fp32);   // uploads L_k and tile inverses of that precision
   void* alloc(size_t bytes);
   std::vector<void*> allocations;
 };
+
+// True when cycles with post-smoothing m2 on the full hierarchy of J levels use
+// the fold matrix; get_fold returns it (made on first use), or NULL where its
+// memory cannot be had.  The calling thread's device is the mesh's.
+inline bool fold_applies(int J, int post) { return J >= 3 && post >= 1; }
+std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post);
 
 // Exact coarsest-level solve of a shortened hierarchy (coarsest level larger
 // than the stored 16 x 16 one) by fast diagonalisation: the axis factors of
@@ -105,9 +129,10 @@ struct Workspace;
 struct LevelBuffers {
   bool batched = false;
   std::vector<void*> f, rr, z[2], Y[2];
-  // Allocates every level of ``m`` through ws.alloc; the pending-output
-  // buffers are zeroed once (cover slots no block uses are never written).
-  void allocate(const MeshContext& m, bool fp32, bool batch, Workspace& ws);
+  // Allocates every level of ``m`` (with levels > 0 the coarsest ``levels``) through
+  // ws.alloc; the pending-output buffers are zeroed once (cover slots no block
+  // uses are never written).
+  void allocate(const MeshContext& m, bool fp32, bool batch, Workspace& ws, int levels = 0);
 };
 
 // Stored directions of the flexible outer iteration (R slots of (d, q) with
@@ -209,6 +234,7 @@ struct dcg_ctx {
   // solved by fast diagonalisation (cfdm, factors in the workspace)
   int lbase = 0;
   dcg::CoarseFdm cfdm;
+  std::shared_ptr<dcg::FoldMatrix> fold;   // full hierarchy only
   // level-buffer view of dcg_apply_noalloc (pointers into the static scratch
   // array; the tables are sized at setup so that the call allocates nothing)
   dcg::LevelBuffers noalloc_lvb;

@@ -105,6 +105,7 @@ struct Group {
   GroupKey key{};
   std::shared_ptr<MeshContext> mesh;
   Workspace ws;
+  std::shared_ptr<FoldMatrix> fold;
   int64_t N = 0, M = 0;   // tensor and scalar vector lengths
   double *b = nullptr, *xh = nullptr, *r = nullptr, *p[2] = {nullptr, nullptr};
   double *w = nullptr, *q = nullptr, *s = nullptr, *zref = nullptr, *zb = nullptr;
@@ -164,6 +165,12 @@ size_t context_bytes(int n, bool fp32) {
   return b + size_t(kCoarseDofs) * kCoarseDofs * sizeof(double);
 }
 
+// A group takes the fold matrix when the budget holds 16 of them: a smaller
+// budget keeps the memory (and so the admissions) of the stepwise cycle.
+size_t group_fold_bytes(int n, int post, size_t budget) {
+  return fold_applies(num_levels(n), post) && kFoldBytes <= budget / 16 ? kFoldBytes : 0;
+}
+
 }  // namespace
 
 struct Server::Impl {
@@ -217,7 +224,7 @@ size_t Server::Impl::used_bytes() const {
   size_t b = 0;
   std::map<int, size_t> ctx;
   for (const auto& kv : groups) {
-    b += kv.second->ws.bytes;
+    b += kv.second->ws.bytes + (kv.second->fold ? kFoldBytes : 0);
     ctx[kv.first.n] = kv.second->mesh->bytes;
   }
   for (const auto& kv : ctx) b += kv.second;
@@ -272,6 +279,7 @@ Group* Server::Impl::create_group(const GroupKey& key) {
   DCG_HIP(hipHostMalloc(reinterpret_cast<void**>(&g->lists_host),
                         sizeof(int32_t) * kNumLists * kBatch, hipHostMallocDefault));
   ws.lvb.allocate(m, fp32, true, ws);
+  if (group_fold_bytes(key.n, key.post, budget)) g->fold = get_fold(*g->mesh, key.pre, key.post);
   DCG_HIP(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking));
   DCG_HIP(hipStreamCreateWithFlags(&g->capture, hipStreamNonBlocking));
   DCG_HIP(hipEventCreateWithFlags(&g->done, hipEventDisableTiming));
@@ -324,7 +332,8 @@ void Server::Impl::admit() {
       bool have_ctx = false;
       for (const auto& kv : groups)
         if (kv.first.n == key.n && kv.first.penalty == key.penalty) have_ctx = true;
-      const size_t need = workspace_bytes(key.n, fp32) + (have_ctx ? 0 : context_bytes(key.n, fp32));
+      const size_t need = workspace_bytes(key.n, fp32) + (have_ctx ? 0 : context_bytes(key.n, fp32)) +
+                          group_fold_bytes(key.n, key.post, budget);
       if (need > budget) {
         failed.emplace_back(r, Error(DCG_ENOMEM, "request needs " + std::to_string(need) +
                                                      " bytes of HBM, the budget is " +
@@ -483,7 +492,8 @@ void Server::Impl::enqueue_step(Group& g) {
     }
     g.any_cycle = cnt(kLInnerAll) > 0;
     if (!g.any_cycle) return;
-    const Cycle<T> cyc(m, g.ws.lvb, g.key.pre, g.key.post);
+    Cycle<T> cyc(m, g.ws.lvb, g.key.pre, g.key.post);
+    cyc.fold = g.fold ? g.fold->C : nullptr;
     LvState fs;
     if (opt.use_graph) {
       if (!g.graph) {
@@ -777,7 +787,8 @@ void Server::prepare(const dcg_mesh& mesh) {
   DCG_HIP(hipGetDevice(&cur));
   DCG_HIP(hipSetDevice(impl->device));
   try {
-    (void)get_context(mesh.n, mesh.penalty, impl->fp32);
+    const auto m = get_context(mesh.n, mesh.penalty, impl->fp32);
+    if (group_fold_bytes(mesh.n, mesh.post, impl->budget)) (void)get_fold(*m, mesh.pre, mesh.post);
   } catch (...) {
     (void)hipSetDevice(cur);
     throw;

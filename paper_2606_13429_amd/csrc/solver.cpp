@@ -52,7 +52,7 @@ void FcgStore::release() {
   R = 0;
 }
 
-void LevelBuffers::allocate(const MeshContext& m, bool fp32, bool batch, Workspace& ws) {
+void LevelBuffers::allocate(const MeshContext& m, bool fp32, bool batch, Workspace& ws, int levels) {
   batched = batch;
   const size_t rs = fp32 ? sizeof(float) : sizeof(double);
   const size_t cols = batch ? kBatch : 1;
@@ -62,7 +62,7 @@ void LevelBuffers::allocate(const MeshContext& m, bool fp32, bool batch, Workspa
     z[b].assign(m.J, nullptr);
     Y[b].assign(m.J, nullptr);
   }
-  for (int k = 1; k <= m.J; ++k) {
+  for (int k = 1; k <= (levels > 0 ? levels : m.J); ++k) {
     const size_t ne = size_t(m.lv[k - 1].ne);
     f[k - 1] = ws.alloc(rs * 4 * ne * cols);
     if (!batch) rr[k - 1] = ws.alloc(rs * 4 * ne);
@@ -74,6 +74,62 @@ void LevelBuffers::allocate(const MeshContext& m, bool fp32, bool batch, Workspa
       }
     }
   }
+}
+
+FoldMatrix::~FoldMatrix() {
+  int cur = 0;
+  (void)hipGetDevice(&cur);
+  (void)hipSetDevice(device);
+  if (C) (void)hipFree(C);
+  (void)hipSetDevice(cur);
+}
+
+// The matrix is what the two cycles make of the unit vectors: 256 batches of 16
+// columns through the FP64 batched cycle, on four streams (a batch fills a
+// quarter of the compute units and is bound by its launches).
+std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
+  if (!fold_applies(m.J, post)) return nullptr;
+  m.ensure_factors(false);
+  std::lock_guard<std::mutex> lk(m.fold_mu);
+  std::weak_ptr<FoldMatrix>& slot = m.folds[{pre, post}];
+  if (auto have = slot.lock()) {
+    m.last_fold = have;
+    return have;
+  }
+  auto F = std::make_shared<FoldMatrix>();
+  F->device = m.device;
+  if (hipMalloc(reinterpret_cast<void**>(&F->C), kFoldBytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;   // the cycles run their steps
+  }
+  constexpr int kStreams = 4;
+  struct Lane {
+    Workspace ws;
+    LevelBuffers lb;
+    hipStream_t st = nullptr;
+    ~Lane() {
+      if (st) (void)hipStreamDestroy(st);
+    }
+  } lane[kStreams];
+  for (Lane& l : lane) {
+    DCG_HIP(hipStreamCreateWithFlags(&l.st, hipStreamNonBlocking));
+    l.lb.allocate(m, false, true, l.ws, 2);
+  }
+  DCG_HIP(hipStreamSynchronize(nullptr));   // the cleared buffers
+  const int ne = kFoldN * kFoldN;
+  for (int j0 = 0, i = 0; j0 < int(kFoldDofs); j0 += kBatch, ++i) {
+    Lane& l = lane[i % kStreams];
+    const Cycle<double> c(m, l.lb, pre, post);
+    DCG_HIP(launch_unit_columns(ne, j0, c.f(2), l.st));
+    LvState s;
+    c.wcycle(2, s, l.st);
+    c.wcycle(2, s, l.st);
+    DCG_HIP(launch_store_columns(ne, j0, s.has_z, c.z(2, s.zb), s.has_y ? c.Y(2, s.yb) : nullptr, F->C, l.st));
+  }
+  for (Lane& l : lane) DCG_HIP(hipStreamSynchronize(l.st));
+  slot = F;
+  m.last_fold = F;
+  return F;
 }
 
 }  // namespace dcg
@@ -124,6 +180,7 @@ Cycle<T> make_cycle(dcg_ctx* h, const InnerWs& w) {
   c.base = h->lbase;
   c.group = h->opt.ras_group;
   c.cfdm = w.cfdm;
+  c.fold = h->fold ? h->fold->C : nullptr;
   if (h->ktime && h->kcycle++ % h->kstride == 0) {   // a sampled W-cycle
     c.timer.ev = h->kev;
     c.timer.max = dcg_ctx::kMaxTimed;
@@ -347,6 +404,7 @@ void handle_init(dcg_ctx* h) {
     h->cfdm.VT = VT;
     h->cfdm.lam = lam;
   }
+  if (h->opt.inner == DCG_INNER_MG && h->lbase == 0) h->fold = get_fold(m, h->mp.pre, h->mp.post);
 }
 
 // ------------------------------------------------------------ stored directions
@@ -740,6 +798,7 @@ void apply_level(dcg_ctx* h, dcg_op op, int k, const void* in, const void* in2, 
   cyc.base = h->lbase;
   cyc.group = h->opt.ras_group;
   if (h->lbase > 0) cyc.cfdm = &h->cfdm;
+  cyc.fold = h->fold ? h->fold->C : nullptr;
   switch (op) {
     case DCG_OP_LAPLACE:
       DCG_HIP(launch_lap<T>(false, level_L<T>(d), d.cols, d.ne, nullptr, x, y, st));
@@ -791,7 +850,8 @@ void apply_level(dcg_ctx* h, dcg_op op, int k, const void* in, const void* in2, 
       if (h->lbase > 0) throw Error(DCG_EINVAL, "the batched operators run the full hierarchy (levels = 0)");
       LevelBuffers& lb = h->ws.lvb_batch;
       if (lb.f.empty()) lb.allocate(m, h->fp32, true, h->ws);
-      const Cycle<T> bc(m, lb, h->mp.pre, h->mp.post);
+      Cycle<T> bc(m, lb, h->mp.pre, h->mp.post);
+      bc.fold = h->fold ? h->fold->C : nullptr;
       const int64_t mb = mk * kBatch;
       const bool ras = op == DCG_OP_RAS_BATCH;
       if (ras && k < 2) throw Error(DCG_EINVAL, "RAS smoother exists on levels >= 2");
