@@ -7,6 +7,7 @@
 #include <thread>
 #include <tuple>
 
+#include "mg_common.hpp"
 #include "runtime.hpp"
 
 namespace dcg {
@@ -158,6 +159,26 @@ void check_tile_geometry(const HostLevel& hl) {
       if (hl.tile_dst[int64_t(t) * kTileSlots + p] != 3 * e + rank || hl.dw[e] != 1.0 / count)
         throw Error(DCG_EINVAL, "RAS tile geometry differs from the cover lists");
     }
+}
+
+// The classes of the nine tile positions; every tile must be of its position's
+// class, which the uniform grid guarantees and this checks.
+uint64_t tile_classes(const HostLevel& hl) {
+  const int tpr = hl.n / kTileCore;
+  uint64_t c9 = 0, seen = 0;
+  for (int t = 0; t < hl.tiles; ++t) {
+    const int TX = t % tpr, TY = t / tpr;
+    const int p = 3 * (TY == 0 ? 0 : (TY == tpr - 1 ? 2 : 1)) + (TX == 0 ? 0 : (TX == tpr - 1 ? 2 : 1));
+    const uint64_t c = uint64_t(hl.tile_class[t]);
+    if (c > 15) throw Error(DCG_EINVAL, "more than 16 distinct RAS tiles");
+    if (!(seen >> p & 1)) {
+      seen |= uint64_t(1) << p;
+      c9 |= c << (4 * p);
+    }
+    if (mg::tile_class_of(c9, TX, TY, tpr) != int(c))
+      throw Error(DCG_EINVAL, "RAS tiles differ within a position class");
+  }
+  return c9;
 }
 
 // Extra workgroups of the grouped RAS step with g x g tiles per group: for
@@ -322,9 +343,7 @@ std::shared_ptr<MeshContext> build_context(int device, int n, double penalty) {
         DCG_HIP(hipMemcpy(dl.gx_extra[gi], ex.data(), sizeof(int32_t) * ex.size(),
                           hipMemcpyHostToDevice));
       }
-      dl.fcls = static_cast<int32_t*>(ctx->alloc(sizeof(int32_t) * hl.tile_class.size()));
-      DCG_HIP(hipMemcpy(dl.fcls, hl.tile_class.data(), sizeof(int32_t) * hl.tile_class.size(),
-                        hipMemcpyHostToDevice));
+      dl.cls9 = tile_classes(hl);
     }
   }
   ctx->coarse_inv = static_cast<double*>(ctx->alloc(sizeof(double) * kCoarseDofs * kCoarseDofs));

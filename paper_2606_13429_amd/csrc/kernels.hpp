@@ -14,7 +14,7 @@
 //                                                     symmetric (L_k)_t^{-1}, row-major, one per
 //                                                     distinct local problem (interior tiles of
 //                                                     the uniform grid share one)
-//   factor classes   int32   [tile]                   class of the tile's inverse
+//   factor classes   9 x 4 bits                       class of the tile's inverse by position
 //   RAS weights      T       [Ne]                     1 / #blocks containing the square
 //   pending slots    int32   [tile][32]               3 e + k for block square e
 //   coarsest inverse double  [1024][1024]
@@ -207,13 +207,11 @@ struct SweepArgs {
   const T* Fm = nullptr;            // the same, full, in MFMA operand order [classes][8][8][64][4]
   const int32_t* gextra = nullptr;  // grouped step: (group, class) of the extra workgroups
   int nextra = 0;
-  const int32_t* fcls = nullptr;    // [tiles] class of the tile's inverse in F
+  uint64_t cls9 = 0;                // class of a tile's inverse by its position (mg::tile_class_of)
   const T* dw = nullptr;            // [ne] partition-of-unity weight 1 / #blocks
   const int32_t* ext = nullptr;     // [tiles][52] block squares + outside neighbours
   int tiles = 0, n = 0, ne = 0;
-  const T* L = nullptr;             // level operator [5][ne][4][4] (batched kernels)
-  const T* Lc = nullptr;            // its class table [9][5][4][4]
-  const int32_t* cols = nullptr;    // [5][ne]
+  const T* Lc = nullptr;            // class table [9][5][4][4] of the level operator
   const int32_t* dst = nullptr;     // [tiles][32] pending slot 3 e + k of each block square
   const T* f = nullptr;
   const T* z_old = nullptr;
@@ -229,9 +227,7 @@ struct SweepArgs {
 template <typename T>
 struct RestrictArgs {
   int n = 0, ne = 0;                // fine level
-  const T* L = nullptr;
-  const T* Lc = nullptr;            // class table of L
-  const int32_t* cols = nullptr;
+  const T* Lc = nullptr;            // class table of the level operator
   const T* f = nullptr;
   const T* z_old = nullptr;
   const T* Y_old = nullptr;         // pending tile outputs [ne][3][4]

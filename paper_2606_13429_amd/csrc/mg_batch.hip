@@ -69,9 +69,7 @@ __device__ __forceinline__ void current_z_b(const SweepArgs<T>& a, int e, int c,
 //   3. U = f - L_k z on the 32 block squares (128 x kBatch), in LDS, each
 //      operator row loaded once for four requests;
 //   4. wavefront w computes the row blocks P = w and P = 7 - w of
-//      (L_k)_t^{-1} U: 8 column blocks Q x 4 MFMA k-steps each.  Blocks
-//      with P <= Q are read as stored (row r, columns 4k..4k+3 as one
-//      vector load), the others as the transpose of the stored (Q, P);
+//      (L_k)_t^{-1} U: 8 column blocks Q x 4 MFMA k-steps each;
 //   5. Y_t = D_t U written to the pending slot of each block square.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_sweep_b(SweepArgs<T> a) {
@@ -85,21 +83,14 @@ __global__ __launch_bounds__(kThreads) void k_sweep_b(SweepArgs<T> a) {
   const bool need_z = a.has_z || a.has_y || a.prol;
 
   // MFMA A operands: lane (r, k) of k-step kk holds row 16 P + r, column
-  // 16 Q + 4 k + kk of the tile inverse; column blocks are loaded two ahead
-  // of their use (the first two before the gather and residual phases)
-  const T* Ft = a.F + (int64_t)a.fcls[t] * (36 * 256);   // grid = tiles
+  // 16 Q + 4 k + kk of the tile inverse, one vector of the operand-order copy;
+  // column blocks are loaded two ahead of their use (the first two before the
+  // gather and residual phases)
+  const int tpr = a.n >> 2;
+  const T* Ft = a.Fm + (int64_t)tile_class_of(a.cls9, t % tpr, t / tpr, tpr) * (64 * 256);   // grid = tiles
   auto load_q = [&](int Q, T (&dst)[2][4]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int P = Pw[h];
-      if (P <= Q) {
-        ld4(Ft + blk_index(P, Q) * 256 + r * 16 + 4 * k, dst[h]);
-      } else {
-        const T* bt = Ft + blk_index(Q, P) * 256 + 64 * k + r;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) dst[h][kk] = bt[16 * kk];
-      }
-    }
+    for (int h = 0; h < 2; ++h) ld4(Ft + ((Pw[h] * 8 + Q) * 64 + lane) * 4, dst[h]);
   };
   T av[3][2][4];
   load_q(0, av[0]);
@@ -134,13 +125,14 @@ __global__ __launch_bounds__(kThreads) void k_sweep_b(SweepArgs<T> a) {
       for (int cc = 0; cc < 4; ++cc) u[cc] = a.f[at(e, 4 * g + cc) + j];
       if (need_z) {
         const int ex = e % a.n, ey = e / a.n;
+        const T* Lrow = a.Lc + square_class(ex, ey, a.n) * 80;
         T acc[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
         for (int s = 0; s < 5; ++s) {
           const int dx = s == 1 ? -1 : (s == 2 ? 1 : 0), dy = s == 3 ? -1 : (s == 4 ? 1 : 0);
           if (ex + dx < 0 || ex + dx >= a.n || ey + dy < 0 || ey + dy >= a.n) continue;
           T l[4];
-          ld4(a.L + (((int64_t)s * a.ne + e) * 4 + j) * 4, l);
+          ld4(Lrow + 16 * s + 4 * j, l);
           const int q = nbr_slot(p, s);
 #pragma unroll
           for (int cc = 0; cc < 4; ++cc) {
@@ -223,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void k_restrict_res_b(RestrictArgs<T> a) 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       T l[4];
-      ld4(a.L + (((int64_t)s * a.ne + e) * 4 + j) * 4, l);
+      ld4(a.Lc + (square_class(ex, ey, a.n) * 5 + s) * 16 + 4 * j, l);
       acc[j] += l[0] * z[0] + l[1] * z[1] + l[2] * z[2] + l[3] * z[3];
     }
   }

@@ -145,6 +145,14 @@ __device__ __forceinline__ int xcd_band(int b, int G) {
   return (G & 7) ? b : (b & 7) * (G >> 3) + (b >> 3);
 }
 
+// Class of the tile (TX, TY), tpr tiles per side, from the packed classes of the
+// nine tile positions (first / inner / last along each axis, 4 bits each at
+// 3 cy + cx).
+__host__ __device__ __forceinline__ int tile_class_of(uint64_t cls9, int TX, int TY, int tpr) {
+  const int cx = TX == 0 ? 0 : (TX == tpr - 1 ? 2 : 1), cy = TY == 0 ? 0 : (TY == tpr - 1 ? 2 : 1);
+  return int(cls9 >> (4 * (3 * cy + cx))) & 15;
+}
+
 // Index of block (P, Q), P <= Q, in the packed upper-triangular order
 // (row by row) of the symmetric tile inverses.
 __host__ __device__ constexpr int blk_index(int P, int Q) { return P * (15 - P) / 2 + Q; }

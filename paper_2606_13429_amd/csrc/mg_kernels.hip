@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kThreads) void k_sweep(SweepArgs<T> a) {
   // Every global load of the step is issued up front (one memory round
   // trip): the first factor blocks, the operator rows of this thread's
   // residual rows, and the iterate of the squares this thread resolves.
-  const T* Ft = a.F + (int64_t)(live ? a.fcls[t] : 0) * (36 * 256);
+  const int tpr = a.n >> 2;
+  const T* Ft = a.F + (int64_t)(live ? tile_class_of(a.cls9, t % tpr, t / tpr, tpr) : 0) * (36 * 256);
   T pf[NP][4];
   if (live) {
 #pragma unroll
@@ -301,9 +302,9 @@ __global__ __launch_bounds__(kThreads) void k_sweep(SweepArgs<T> a) {
 // The step is bound by memory latency, so every load that does not depend
 // on another is issued first (the iterate, pending outputs and, in the
 // first post-smoothing step (PROL), the coarse correction of the frame; f;
-// the operator's class table; the tile classes), and the class inverse,
-// which needs the first tile's class, as soon as the frame registers are
-// free.  The pending slot and weight of an output follow from the tile
+// the operator's class table), and the class inverse as soon as the frame
+// registers are free.  The class follows from the tile's position, the pending slot
+// and weight of an output from the tile
 // geometry (checked against the host's cover lists when the context is
 // built), so the outputs need no table.
 //   1. z_new on the frame of squares within distance 2 of the group core
@@ -384,7 +385,6 @@ void k_sweep_g(SweepArgs<T> a) {
   __shared__ __align__(16) T zf[FS * FS][4];
   __shared__ __align__(16) T rf[RS * RS][4];
   __shared__ __align__(16) T lc[NLC];
-  __shared__ int tcls[NT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tpr = a.n >> 2, gpr = tpr / GX, G0 = gpr * gpr;
   // workgroups 0 .. G0 - 1 run the class of each group's first tile, the
@@ -397,10 +397,10 @@ void k_sweep_g(SweepArgs<T> a) {
   const int r = lane & 15, k = lane >> 4;
   const int Pw[2] = {wave, 7 - wave};
 
-  // ---- every load that needs no other one, in one batch: the tile
-  // classes, the operator's class table, f, and the frame values
-  const int c0 = extra ? a.gextra[2 * (blockIdx.x - G0) + 1] : a.fcls[t00];
-  const int tc = tid < NT ? a.fcls[t00 + (tid / GX) * tpr + tid % GX] : 0;
+  // ---- every load that needs no other one, in one batch: the operator's
+  // class table, f, and the frame values
+  const int TX0 = GX * (g % gpr), TY0 = GX * (g / gpr);
+  const int c0 = extra ? a.gextra[2 * (blockIdx.x - G0) + 1] : tile_class_of(a.cls9, TX0, TY0, tpr);
   T lcv[NLU][4];
 #pragma unroll
   for (int u = 0; u < NLU; ++u)
@@ -432,8 +432,7 @@ void k_sweep_g(SweepArgs<T> a) {
     }
   }
 
-  // ---- LDS: tile classes, class table, z_new on the frame
-  if (tid < NT) tcls[tid] = tc;
+  // ---- LDS: class table, z_new on the frame
 #pragma unroll
   for (int u = 0; u < NLU; ++u)
     if (tid + u * kThreads < NLC / 4) st4(&lc[4 * (tid + u * kThreads)], lcv[u]);
@@ -501,7 +500,7 @@ void k_sweep_g(SweepArgs<T> a) {
   // tiles of this class (other columns enter as zeros); the B operand of
   // lane (r, k) is tile r's residual at block slot 4 Q + k
   const int rtx = 4 * (r % GX) + 1, rty = 4 * (r / GX) + 1;   // tile r in the residual frame
-  const bool col = r < NT && tcls[r < NT ? r : 0] == c0;
+  const bool col = r < NT && tile_class_of(a.cls9, TX0 + r % GX, TY0 + r / GX, tpr) == c0;
   const T* Fc = a.Fm + (int64_t)c0 * (64 * 256);
   V acc0 = {T(0), T(0), T(0), T(0)}, acc1 = {T(0), T(0), T(0), T(0)};
 #pragma unroll

@@ -38,14 +38,13 @@ struct DeviceLevel {
   int32_t* tile_ext = nullptr;    // [tiles][52]
   int32_t* tile_dst = nullptr;    // [tiles][32]
   // packed symmetric inverses of the distinct local problems (bit-identical
-  // local matrices and weights share one), [classes][36][16][16], and the
-  // class of every tile
+  // local matrices and weights share one), [classes][36][16][16]
   float* F32 = nullptr;
   double* F64 = nullptr;
   // the same inverses in MFMA operand order, [classes][8][8][64][4]
   float* Fm32 = nullptr;
   double* Fm64 = nullptr;
-  int32_t* fcls = nullptr;        // [tiles]
+  uint64_t cls9 = 0;              // class of a tile by its position (mg::tile_class_of)
   int classes = 0;
   float* dw32 = nullptr;          // [ne] 1 / #blocks containing the square
   double* dw64 = nullptr;

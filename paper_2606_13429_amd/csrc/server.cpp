@@ -158,7 +158,7 @@ size_t context_bytes(int n, bool fp32) {
       const size_t tiles = nek / 16;
       // distinct local problems: 9 on the uniform grid (3 x 3 tile positions)
       const size_t classes = std::min<size_t>(tiles, 16);
-      b += tiles * (52 + 32 + 1) * sizeof(int32_t);
+      b += tiles * (52 + 32) * sizeof(int32_t);
       b += (classes * 36 * 256 + nek) * (fp32 ? sizeof(float) : sizeof(double));
     }
   }

@@ -102,15 +102,13 @@ struct Cycle {
     SweepArgs<T> a;
     a.F = level_F<T>(d);
     a.Fm = level_Fm<T>(d);
-    a.fcls = d.fcls;
+    a.cls9 = d.cls9;
     a.dw = level_dw<T>(d);
     a.ext = d.tile_ext;
     a.tiles = d.tiles;
     a.n = d.n;
     a.ne = d.ne;
-    a.L = level_L<T>(d);
     a.Lc = level_Lc<T>(d);
-    a.cols = d.cols;
     a.dst = d.tile_dst;
     a.f = f(k);
     a.has_z = s.has_z;
@@ -161,9 +159,7 @@ struct Cycle {
     RestrictArgs<T> a;
     a.n = d.n;
     a.ne = d.ne;
-    a.L = level_L<T>(d);
     a.Lc = level_Lc<T>(d);
-    a.cols = d.cols;
     a.f = f(k);
     a.has_z = s.has_z;
     a.has_y = s.has_y;
