@@ -312,10 +312,20 @@ __global__ __launch_bounds__(kThreads) void k_sweep(SweepArgs<T> a) {
 //      core squares are written to z_new;
 //   2. r = f - L_k z_new on the block squares (core + 1), in LDS, one
 //      thread per square, the operator rows from the class table in LDS;
-//   3. per class: wavefront w computes row blocks w and 7 - w of
-//      (L_k)_c^{-1} U_c, 8 column blocks x 4 k-steps, the operand fragments
-//      read in MFMA order (one 16 / 32 byte vector per lane and fragment);
+//   3. per class: (L_k)_c^{-1} U_c in 16 x 16 row and column blocks x 4 k-steps,
+//      the operand fragments read in MFMA order (one 16 / 32 byte vector per lane
+//      and fragment);
 //   4. Y_t = D_t u_t written to the pending slot of each block square.
+//
+// NW wavefronts per workgroup, NS workgroups per group of tiles.  A level of few
+// groups leaves compute units idle while the others work through 256 MFMAs of one
+// group (0.9 us in FP32, 1.7 us in FP64) after 64 / 128 KB of class inverse, so its
+// groups are split: each workgroup forms the whole residual and NS-th of the rows,
+// KS wavefronts share the contraction of a row block, and the frame takes one pass
+// of 512 threads.  With 16 tiles per group, a step in FP32 (FP64), 4 wavefronts
+// against this: n = 64 6.4 -> 5.0 (9.2 -> 6.9) us with NS = 4 (per-tile kernel 6.8
+// (8.1)), n = 128 7.0 -> 5.8 (10.2 -> 8.1) with NS = 2, n = 256 8.9 -> 8.4 with 8
+// wavefronts; n = 512 16.3 -> 16.9, kept at 4 wavefronts.
 template <typename T, bool PROL>
 __device__ __forceinline__ void load_frame(const SweepArgs<T>& a, int e, bool ok, T (&v)[PROL ? 8 : 4][4]) {
   // v[0] z_old, v[1..3] pending Y, v[4] coarse z, v[5..7] coarse pending Y
@@ -366,49 +376,59 @@ __device__ __forceinline__ void combine_frame(const SweepArgs<T>& a, int e,
   }
 }
 
-template <typename T, int GX, bool PROL>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 2)))
+template <typename T, int GX, bool PROL, int NW, int NS>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 && sizeof(T) == 4 ? 5 : 2)))
 void k_sweep_g(SweepArgs<T> a) {
   using V = typename Mfma<T>::v4;
+  constexpr int NTH = 64 * NW;
   constexpr int C = 4 * GX;        // core squares per side
   constexpr int FS = C + 4;        // z frame: core +- 2
   constexpr int RS = C + 2;        // residual frame: core +- 1
   constexpr int NT = GX * GX;      // tiles = MFMA columns in use
-  constexpr int NZ = (FS * FS + kThreads - 1) / kThreads;   // frame squares per thread
-  constexpr int NR = (RS * RS + kThreads - 1) / kThreads;   // residual squares per thread
+  constexpr int NZ = (FS * FS + NTH - 1) / NTH;   // frame squares per thread
+  constexpr int NR = (RS * RS + NTH - 1) / NTH;   // residual squares per thread
   constexpr int NV = PROL ? 8 : 4; // loaded 4-vectors per frame square
   constexpr int NLC = 9 * 5 * 16;  // class table of the level operator
-  constexpr int NLU = (NLC / 4 + kThreads - 1) / kThreads;
-  // class-inverse fragments requested ahead of the MFMA loop
-  constexpr int PD = 4;
+  constexpr int NLU = (NLC / 4 + NTH - 1) / NTH;
+  constexpr int RB = 8 / NS;       // row blocks of the workgroup
+  constexpr int HP = RB > NW ? RB / NW : 1;   // row blocks per wavefront
+  constexpr int KS = NW > RB ? NW / RB : 1;   // wavefronts sharing a row block's contraction
+  constexpr int NQ = 8 / KS;       // column blocks per wavefront
+  constexpr int PD = NW == 8 ? NQ : 4;        // class-inverse fragments requested ahead
   static_assert(NT <= 16, "at most 16 tiles per group");
   __shared__ __align__(16) T zf[FS * FS][4];
   __shared__ __align__(16) T rf[RS * RS][4];
   __shared__ __align__(16) T lc[NLC];
+  __shared__ __align__(16) T red[KS > 1 ? NW * 64 : 1][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tpr = a.n >> 2, gpr = tpr / GX, G0 = gpr * gpr;
   // workgroups 0 .. G0 - 1 run the class of each group's first tile, the
-  // extra ones a further class of the group in the extra list
-  const bool extra = (int)blockIdx.x >= G0;
-  const int g = extra ? a.gextra[2 * (blockIdx.x - G0)] : xcd_band_index(blockIdx.x, G0);
+  // extra ones a further class of the group in the extra list; with NS > 1 each
+  // of them is NS workgroups that form the residual and one part of the rows each
+  const int base = G0 + a.nextra, part = NS > 1 ? blockIdx.x / base : 0, bid = blockIdx.x - part * base;
+  const bool extra = bid >= G0;
+  const int g = extra ? a.gextra[2 * (bid - G0)] : xcd_band_index(bid, G0);
   const int X0 = C * (g % gpr), Y0 = C * (g / gpr);
   const int t00 = GX * (g / gpr) * tpr + GX * (g % gpr);
   const bool need_z = a.has_z || a.has_y || PROL;
   const int r = lane & 15, k = lane >> 4;
-  const int Pw[2] = {wave, 7 - wave};
+  int Pw[HP];
+  Pw[0] = part * RB + wave % RB;
+  if constexpr (HP == 2) Pw[1] = 7 - wave;
+  const int Q0 = wave / RB * NQ;
 
   // ---- every load that needs no other one, in one batch: the operator's
   // class table, f, and the frame values
   const int TX0 = GX * (g % gpr), TY0 = GX * (g / gpr);
-  const int c0 = extra ? a.gextra[2 * (blockIdx.x - G0) + 1] : tile_class_of(a.cls9, TX0, TY0, tpr);
+  const int c0 = extra ? a.gextra[2 * (bid - G0) + 1] : tile_class_of(a.cls9, TX0, TY0, tpr);
   T lcv[NLU][4];
 #pragma unroll
   for (int u = 0; u < NLU; ++u)
-    if (tid + u * kThreads < NLC / 4) ld4(a.Lc + 4 * (tid + u * kThreads), lcv[u]);
+    if (tid + u * NTH < NLC / 4) ld4(a.Lc + 4 * (tid + u * NTH), lcv[u]);
   T fr[NR][4];
 #pragma unroll
   for (int u = 0; u < NR; ++u) {
-    const int q = tid + u * kThreads;
+    const int q = tid + u * NTH;
     const int rx = q % RS, ry = q / RS;
     const int X = X0 + rx - 1, Y = Y0 + ry - 1;
     fr[u][0] = fr[u][1] = fr[u][2] = fr[u][3] = T(0);
@@ -420,7 +440,7 @@ void k_sweep_g(SweepArgs<T> a) {
   if (need_z) {
 #pragma unroll
     for (int u = 0; u < NZ; ++u) {
-      const int q = tid + u * kThreads;
+      const int q = tid + u * NTH;
       const int fx = q % FS, fy = q / FS;
       const int X = X0 + fx - 2, Y = Y0 + fy - 2;
       const bool ox = fx < 2 || fx >= FS - 2, oy = fy < 2 || fy >= FS - 2;
@@ -435,11 +455,11 @@ void k_sweep_g(SweepArgs<T> a) {
   // ---- LDS: class table, z_new on the frame
 #pragma unroll
   for (int u = 0; u < NLU; ++u)
-    if (tid + u * kThreads < NLC / 4) st4(&lc[4 * (tid + u * kThreads)], lcv[u]);
+    if (tid + u * NTH < NLC / 4) st4(&lc[4 * (tid + u * NTH)], lcv[u]);
   if (need_z) {
 #pragma unroll
     for (int u = 0; u < NZ; ++u) {
-      const int q = tid + u * kThreads;
+      const int q = tid + u * NTH;
       if (q >= FS * FS) continue;
       const int fx = q % FS, fy = q / FS;
       const int X = X0 + fx - 2, Y = Y0 + fy - 2;
@@ -447,17 +467,17 @@ void k_sweep_g(SweepArgs<T> a) {
       combine_frame<T, PROL>(a, Y * a.n + X, fv[u], z);
       st4(&zf[q][0], z);
       const bool core = fx >= 2 && fx < FS - 2 && fy >= 2 && fy < FS - 2;
-      if (a.write_z && !extra && core) st4(a.z_new + 4 * ((int64_t)Y * a.n + X), z);
+      if (a.write_z && !extra && part == 0 && core) st4(a.z_new + 4 * ((int64_t)Y * a.n + X), z);
     }
   }
 
   // ---- the class inverse of this workgroup's class, requested now that the frame
   // registers are free; it arrives while the residual is formed
-  auto load_q = [&](const T* F, int Q, T (&dst)[2][4]) {
+  auto load_q = [&](const T* F, int Q, T (&dst)[HP][4]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) ld4(F + ((Pw[h] * 8 + Q) * 64 + lane) * 4, dst[h]);
+    for (int h = 0; h < HP; ++h) ld4(F + ((Pw[h] * 8 + Q0 + Q) * 64 + lane) * 4, dst[h]);
   };
-  T av[PD][2][4];
+  T av[PD][HP][4];
   {
     const T* F0 = a.Fm + (int64_t)c0 * (64 * 256);
 #pragma unroll
@@ -468,7 +488,7 @@ void k_sweep_g(SweepArgs<T> a) {
   // ---- residual on the block squares
 #pragma unroll
   for (int u = 0; u < NR; ++u) {
-    const int q = tid + u * kThreads;
+    const int q = tid + u * NTH;
     if (q >= RS * RS) continue;
     const int rx = q % RS, ry = q / RS;
     const int X = X0 + rx - 1, Y = Y0 + ry - 1;
@@ -502,25 +522,40 @@ void k_sweep_g(SweepArgs<T> a) {
   const int rtx = 4 * (r % GX) + 1, rty = 4 * (r / GX) + 1;   // tile r in the residual frame
   const bool col = r < NT && tile_class_of(a.cls9, TX0 + r % GX, TY0 + r / GX, tpr) == c0;
   const T* Fc = a.Fm + (int64_t)c0 * (64 * 256);
-  V acc0 = {T(0), T(0), T(0), T(0)}, acc1 = {T(0), T(0), T(0), T(0)};
+  V accs[HP];
 #pragma unroll
-  for (int Q = 0; Q < 8; ++Q) {
+  for (int h = 0; h < HP; ++h) accs[h] = V{T(0), T(0), T(0), T(0)};
+#pragma unroll
+  for (int Q = 0; Q < NQ; ++Q) {
     T bq[4] = {T(0), T(0), T(0), T(0)};
     if (col) {
       int px, py;
-      slot_pos(4 * Q + k, px, py);
+      slot_pos(4 * (Q0 + Q) + k, px, py);
       ld4(&rf[(rty + py) * RS + rtx + px][0], bq);
     }
-    T aq[2][4];
+    T aq[HP][4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < HP; ++h)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) aq[h][kk] = av[Q % PD][h][kk];
-    if (Q + PD < 8) load_q(Fc, Q + PD, av[Q % PD]);
+    if (Q + PD < NQ) load_q(Fc, Q + PD, av[Q % PD]);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      acc0 = Mfma<T>::mac(aq[0][kk], bq[kk], acc0);
-      acc1 = Mfma<T>::mac(aq[1][kk], bq[kk], acc1);
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int h = 0; h < HP; ++h) accs[h] = Mfma<T>::mac(aq[h][kk], bq[kk], accs[h]);
+  }
+
+  if constexpr (KS > 1) {          // the parts of a row block's contraction, through LDS
+    T out[4] = {accs[0][0], accs[0][1], accs[0][2], accs[0][3]};
+    st4(red[tid], out);
+    __syncthreads();
+    if (wave >= RB) return;
+#pragma unroll
+    for (int p = 1; p < KS; ++p) {
+      T o[4];
+      ld4(red[tid + 64 * RB * p], o);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) accs[0][v] += o[v];
     }
   }
 
@@ -530,8 +565,8 @@ void k_sweep_g(SweepArgs<T> a) {
   const int t = t00 + (r / GX) * tpr + r % GX;
   constexpr int NO = sizeof(T) == 4 ? 1 : 4;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const V& acc = h == 0 ? acc0 : acc1;
+  for (int h = 0; h < HP; ++h) {
+    const V& acc = accs[h];
 #pragma unroll
     for (int v = 0; v < NO; ++v) {
       const int p = NO == 1 ? 4 * Pw[h] + k : 4 * Pw[h] + v;
@@ -665,8 +700,20 @@ hipError_t launch_sweep_g(const SweepArgs<T>& a, int gx, hipStream_t st, hipEven
   if (!a.Fm || (a.nextra > 0 && !a.gextra)) return hipErrorInvalidValue;
   grid += a.nextra;
   // timed launches record their events in the dispatch packet itself
-#define DCG_SWEEP_G(G, P)                                                                        \
-  hipExtLaunchKernelGGL(k_sweep_g<T, G, P>, dim3(grid), dim3(kThreads), 0, st, ev0, ev1, 0, a)
+  // NS: as many workgroups per group as the compute units take at once (a second
+  // round costs more than it saves: NS = 4 at 100 groups 6.2 against 5.8 us in FP32,
+  // 9.0 against 8.1 in FP64, NS = 2 at 324 groups 9.8 against 8.6).  8 wavefronts up
+  // to two workgroups per compute unit; larger grids run 4, which leaves room for
+  // more workgroups (n = 512, 1156 of them: 16.3 against 16.9 us)
+  const int ns = 4 * grid <= 256 ? 4 : (2 * grid <= 256 ? 2 : 1);
+#define DCG_SWEEP_L(G, P, NW, NS)                                                                    \
+  hipExtLaunchKernelGGL((k_sweep_g<T, G, P, NW, NS>), dim3(NS * grid), dim3(64 * NW), 0, st, ev0,    \
+                        ev1, 0, a)
+#define DCG_SWEEP_G(G, P)                                                                            \
+  if (ns == 4) DCG_SWEEP_L(G, P, 8, 4);                                                              \
+  else if (ns == 2) DCG_SWEEP_L(G, P, 8, 2);                                                         \
+  else if (grid <= 512) DCG_SWEEP_L(G, P, 8, 1);                                                     \
+  else DCG_SWEEP_L(G, P, 4, 1)
   switch (gx * 2 + (a.prol ? 1 : 0)) {
     case 2: DCG_SWEEP_G(1, false); break;
     case 3: DCG_SWEEP_G(1, true); break;
@@ -677,6 +724,7 @@ hipError_t launch_sweep_g(const SweepArgs<T>& a, int gx, hipStream_t st, hipEven
     default: return hipErrorInvalidValue;
   }
 #undef DCG_SWEEP_G
+#undef DCG_SWEEP_L
   return hipGetLastError();
 }
 

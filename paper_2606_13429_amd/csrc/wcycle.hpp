@@ -28,11 +28,12 @@ inline int waves_per_tile(int tiles) { return tiles >= 4096 ? 1 : (tiles >= 1024
 // Tiles per side of a workgroup of the grouped (MFMA) RAS step, 0 for the
 // per-tile kernel.  ``choice`` is dcg_options.ras_group: 0 picks by level
 // size, -1 forces the per-tile kernel, 1 / 2 / 4 that group side.  Measured
-// on MI355X (FP32, per step): 4 x 4 groups take 17.7 / 10.0 / 7.5 us at
-// n = 512 / 256 / 128, 2 x 2 groups 36 / 14 / 8.3 us, single tiles
-// 106 / 32 / 11 us, the per-tile kernel 60 / 18 / 9.2 us.
+// on MI355X (per step): 4 x 4 groups take 16.3 / 8.6 / 5.8 / 5.0 us at
+// n = 512 / 256 / 128 / 64 in FP32, 2 x 2 groups 34 / 14.5 / 7.6 / 5.7 us, single
+// tiles 102 / 31 / 11.5 / 5.5 us, the per-tile kernel 60 / 18 / 9.2 / 6.8 us; in
+// FP64 at n = 128 / 64 8.1 / 6.9, 13.7 / 7.6, 22 / 9.2 and (n = 64) 8.1 us.
 #ifndef DCG_GROUP_MIN_TILES
-#define DCG_GROUP_MIN_TILES 1024
+#define DCG_GROUP_MIN_TILES 256
 #endif
 inline int ras_group_side(int tiles, int choice) {
   if (choice < 0) return 0;
