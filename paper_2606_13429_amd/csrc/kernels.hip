@@ -570,48 +570,49 @@ __global__ __launch_bounds__(kThreads) void k_scale(int64_t n, double c,
 
 // ============================================================ inner refinement
 // r = s - L64 z (first: r = s) in FP64, fJ = (T) r, partial ||r||^2.
-// Thread (square e, row a): one workgroup = 64 squares.
+// Thread per square, one wavefront per workgroup, the operator rows from the class
+// table in scalar registers: bound by bytes (20 MB at n = 512, FP32 levels: 4 us) and
+// the latency of one round of loads, 13.7 -> 10.2 us with a thread per row reading
+// the table and the stencil per row.
 template <typename T, bool FIRST>
-__global__ __launch_bounds__(kThreads) void k_refine_residual(
+__global__ __launch_bounds__(64) void k_refine_residual(
     const double* __restrict__ Lc, int n, int ne, const double* __restrict__ s,
     const double* __restrict__ z, T* __restrict__ fJ, double* __restrict__ part, Slots sl,
     const Scalars* __restrict__ guard) {
-  __shared__ double lds[4];
   if (guard && guard->inner_done) return;
   const int slot = slot_id(sl);
   s += slot * sl.sstride;
   if (z) z += slot * sl.sstride;
   fJ += slot * sl.lstride;
   part += slot * kSlotPart;
-  const int a = threadIdx.x & 3;
   const int groups = (ne + 63) >> 6;
   double nrm = 0.0;
   for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-    const int e = (g << 6) + (threadIdx.x >> 2);
+    const int e = (g << 6) + threadIdx.x;
     if (e >= ne) continue;
-    double acc = 0.0;
+    double r[4];
+    ld4(s + 4 * (int64_t)e, r);
     if (!FIRST) {                // blocks of the square's class, neighbours from (ex, ey)
       const int ex = e % n, ey = e / n;
-      const double* Le = Lc + square_class(ex, ey, n) * 80 + 4 * a;
+      double zq[5][4], acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int sn = 0; sn < 5; ++sn) {
         const int dx = sn == 1 ? -1 : (sn == 2 ? 1 : 0), dy = sn == 3 ? -1 : (sn == 4 ? 1 : 0);
-        if (ex + dx < 0 || ex + dx >= n || ey + dy < 0 || ey + dy >= n) continue;
-        double l[4], zc[4];
-        ld4(Le + 16 * sn, l);
-        ld4(z + 4 * ((int64_t)e + dx + (int64_t)dy * n), zc);
-        acc += l[0] * zc[0] + l[1] * zc[1] + l[2] * zc[2] + l[3] * zc[3];
+        zq[sn][0] = zq[sn][1] = zq[sn][2] = zq[sn][3] = 0.0;
+        if (ex + dx >= 0 && ex + dx < n && ey + dy >= 0 && ey + dy < n)
+          ld4(z + 4 * ((int64_t)e + dx + (int64_t)dy * n), zq[sn]);
       }
+      mg::class_rows(Lc, square_class(ex, ey, n), zq, acc);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) r[a] -= acc[a];
     }
-    const int64_t i = 4 * (int64_t)e + a;
-    const double rv = s[i] - acc;
-    fJ[e * sl.lsq + a] = static_cast<T>(rv);
-    nrm += rv * rv;
+    const T o[4] = {static_cast<T>(r[0]), static_cast<T>(r[1]), static_cast<T>(r[2]), static_cast<T>(r[3])};
+    st4(fJ + e * sl.lsq, o);
+    nrm += (r[0] * r[0] + r[1] * r[1]) + (r[2] * r[2] + r[3] * r[3]);
   }
-  const double t = block_sum(nrm, lds);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
+  for (int o = 32; o > 0; o >>= 1) nrm += __shfl_xor(nrm, o);
+  if (threadIdx.x == 0) part[blockIdx.x] = nrm;
 }
-
 
 // ============================================================ multigrid levels
 // out = L z (RES = false) or out = f - L z (RES = true); thread (square, row).
@@ -872,9 +873,9 @@ hipError_t launch_refine_residual(bool first, const double* Lc64, int n, int ne,
   if (!Lc64 || n < 3 || int64_t(n) * n != ne) return hipErrorInvalidValue;
   const dim3 grid(refine_blocks(ne), count);
   if (first)
-    k_refine_residual<T, true><<<grid, kThreads, 0, st>>>(Lc64, n, ne, s, z, fJ, part, sl, guard);
+    k_refine_residual<T, true><<<grid, 64, 0, st>>>(Lc64, n, ne, s, z, fJ, part, sl, guard);
   else
-    k_refine_residual<T, false><<<grid, kThreads, 0, st>>>(Lc64, n, ne, s, z, fJ, part, sl, guard);
+    k_refine_residual<T, false><<<grid, 64, 0, st>>>(Lc64, n, ne, s, z, fJ, part, sl, guard);
   return hipGetLastError();
 }
 

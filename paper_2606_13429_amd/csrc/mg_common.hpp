@@ -61,6 +61,26 @@ __device__ __forceinline__ T pcoef(int ch, int a, int A) {
   return T(wx * wy) * T(0.25);
 }
 
+// acc += the four rows of a square's operator blocks times the five squares of its
+// stencil, the blocks of class ``cls`` of a table [9][5][4][4] through scalar loads:
+// one pass per class present in the wavefront, interior wavefronts hold one.
+template <typename T>
+__device__ __forceinline__ void class_rows(const T* __restrict__ Lc, int cls, const T (&zq)[5][4],
+                                           T (&acc)[4]) {
+  for (;;) {
+    const int c = __builtin_amdgcn_readfirstlane(cls);
+    if (cls != c) continue;
+    const T* l = Lc + 80 * c;
+#pragma unroll
+    for (int s = 0; s < 5; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] += l[16 * s + 4 * j] * zq[s][0] + l[16 * s + 4 * j + 1] * zq[s][1] +
+                  l[16 * s + 4 * j + 2] * zq[s][2] + l[16 * s + 4 * j + 3] * zq[s][3];
+    break;
+  }
+}
+
 // Position (relative to the tile origin) of block slot p < 32.
 __device__ __forceinline__ void slot_pos(int p, int& px, int& py) {
   if (p < 16) { px = p & 3; py = p >> 2; }

@@ -640,6 +640,80 @@ __global__ __launch_bounds__(kThreads) void k_restrict_res(RestrictArgs<T> a) {
   }
 }
 
+// The same step per 16 x 16 fine squares, for levels of enough of them: z_new of
+// the tile and a ring of one square goes through LDS, so that z and the pending
+// outputs are read once per square instead of once per neighbour and row, and a
+// thread forms the four rows of its square from the class table in scalar
+// registers (one pass per class present in the wavefront).  Bound by the loads'
+// latency at n <= 256 and by bytes (z, Y, f in, z out: 24 MB at n = 512 in FP32)
+// above: FP32 n = 512 17.1 -> 7.9, n = 256 6.4 -> 4.5, n = 128 4.5 -> 3.9 us, FP64
+// n = 128 5.5 -> 5.0 us.
+constexpr int kRTile = 16;
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_restrict_tile(RestrictArgs<T> a) {
+  constexpr int C = kRTile, FS = C + 2, NZ = (FS * FS + kThreads - 1) / kThreads;
+  static_assert(C * C == kThreads, "a thread per square of the tile");
+  __shared__ __align__(16) T zf[FS * FS][4];
+  __shared__ __align__(16) T rf[C * C][4];
+  const int tid = threadIdx.x, tx = tid % C, ty = tid / C;
+  const int tr = a.n / C, g = xcd_band_index(blockIdx.x, gridDim.x);
+  const int X0 = C * (g % tr), Y0 = C * (g / tr);
+  const int64_t e = (int64_t)(Y0 + ty) * a.n + X0 + tx;
+  T res[4], zv[NZ][4], yv[NZ][3][4];
+  ld4(a.f + 4 * e, res);
+#pragma unroll
+  for (int u = 0; u < NZ; ++u) {
+    const int q = tid + u * kThreads, fx = q % FS, fy = q / FS, X = X0 + fx - 1, Y = Y0 + fy - 1;
+    const bool corner = (fx == 0 || fx == FS - 1) && (fy == 0 || fy == FS - 1);
+    const bool ok = q < FS * FS && !corner && X >= 0 && Y >= 0 && X < a.n && Y < a.n;
+    const int64_t c = (int64_t)Y * a.n + X;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) zv[u][j] = yv[u][0][j] = yv[u][1][j] = yv[u][2][j] = T(0);
+    if (!ok) continue;
+    if (a.has_z) ld4(a.z_old + 4 * c, zv[u]);
+    if (a.has_y)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) ld4(a.Y_old + 12 * c + 4 * k, yv[u][k]);
+  }
+#pragma unroll
+  for (int u = 0; u < NZ; ++u) {
+    const int q = tid + u * kThreads;
+    if (q >= FS * FS) continue;
+    if (a.has_y)
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zv[u][j] += yv[u][k][j];
+    st4(&zf[q][0], zv[u]);
+    const int fx = q % FS, fy = q / FS;
+    if (a.write_z && fx >= 1 && fx <= C && fy >= 1 && fy <= C)
+      st4(a.z_new + 4 * ((int64_t)(Y0 + fy - 1) * a.n + X0 + fx - 1), zv[u]);
+  }
+  __syncthreads();
+  T zq[5][4], acc[4] = {T(0), T(0), T(0), T(0)};   // squares outside the mesh hold zeros
+#pragma unroll
+  for (int s = 0; s < 5; ++s) {
+    const int dx = s == 1 ? -1 : (s == 2 ? 1 : 0), dy = s == 3 ? -1 : (s == 4 ? 1 : 0);
+    ld4(zf[(ty + 1 + dy) * FS + tx + 1 + dx], zq[s]);
+  }
+  class_rows(a.Lc, square_class(X0 + tx, Y0 + ty, a.n), zq, acc);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) res[j] -= acc[j];
+  st4(&rf[tid][0], res);
+  __syncthreads();
+  const int ex = (tid >> 2) % (C / 2), ey = (tid >> 2) / (C / 2), k = tid & 3;
+  T rc = T(0);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    T r[4];
+    ld4(rf[(2 * ey + (c >> 1)) * C + 2 * ex + (c & 1)], r);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) rc += pcoef<T>(c, j, k) * r[j];
+  }
+  a.rc[4 * ((int64_t)(Y0 / 2 + ey) * (a.n >> 1) + X0 / 2 + ex) + k] = rc;
+}
+
 // out = z (or 0) + pending Y: resolves a level's pending update.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_resolve(int ne, int has_z, const T* __restrict__ z,
@@ -731,6 +805,12 @@ hipError_t launch_sweep_g(const SweepArgs<T>& a, int gx, hipStream_t st, hipEven
 template <typename T>
 hipError_t launch_restrict_res(const RestrictArgs<T>& a, hipStream_t st) {
   const int nc = a.n / 2;
+  // n = 64 (16 workgroups): 4.1 us in FP32 and 4.8 in FP64, against 4.6 and 5.2 with
+  // a thread per row; below, fewer workgroups than the 64 of that kernel at n = 64
+  if (a.n % kRTile == 0 && a.n >= 64) {
+    k_restrict_tile<T><<<(a.n / kRTile) * (a.n / kRTile), kThreads, 0, st>>>(a);
+    return hipGetLastError();
+  }
   const int grid = (nc * nc + 15) / 16;
   k_restrict_res<T><<<grid, kThreads, 0, st>>>(a);
   return hipGetLastError();
