@@ -39,21 +39,43 @@ __device__ __forceinline__ void add_pending_b(const T* Ye, int64_t e, int c, T z
   for (int j = 0; j < 4; ++j) z[j] = ((z[j] + y0[j]) + y1[j]) + y2[j];
 }
 
-template <typename T>
-__device__ __forceinline__ void current_z_b(const SweepArgs<T>& a, int e, int c, T z[4]) {
-  if (a.has_z) {
-    ld4(a.z_old + at(e, c), z);
-  } else {
-    z[0] = z[1] = z[2] = z[3] = T(0);
+// Loads of square e, request c: z_old, pending Y, and with PROL the coarse z and its
+// pending Y; z_new from them.
+template <typename T, bool PROL>
+__device__ __forceinline__ void load_z_b(const SweepArgs<T>& a, int e, int c, T (&v)[PROL ? 8 : 4][4]) {
+#pragma unroll
+  for (int i = 0; i < (PROL ? 8 : 4); ++i) v[i][0] = v[i][1] = v[i][2] = v[i][3] = T(0);
+  if (e < 0) return;
+  if (a.has_z) ld4(a.z_old + at(e, c), v[0]);
+  if (a.has_y)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) ld4(a.Y_old + at(3 * (int64_t)e + i, c), v[1 + i]);
+  if constexpr (PROL) {
+    const int E = ((e / a.n) >> 1) * a.nc + ((e % a.n) >> 1);
+    ld4(a.zc + at(E, c), v[4]);
+    if (a.c_has_y)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) ld4(a.Yc + at(3 * (int64_t)E + i, c), v[5 + i]);
   }
-  if (a.has_y) add_pending_b(a.Y_old, e, c, z);
-  if (a.prol) {
-    const int ex = e % a.n, ey = e / a.n;
-    const int E = (ey >> 1) * a.nc + (ex >> 1);
-    const int ch = (ex & 1) + 2 * (ey & 1);
+}
+
+template <typename T, bool PROL>
+__device__ __forceinline__ void combine_z_b(const SweepArgs<T>& a, int e, const T (&v)[PROL ? 8 : 4][4],
+                                            T (&z)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    z[j] = v[0][j];
+    if (a.has_y) z[j] = ((z[j] + v[1][j]) + v[2][j]) + v[3][j];
+  }
+  if constexpr (PROL) {
+    if (e < 0) return;
+    const int ch = ((e % a.n) & 1) + 2 * ((e / a.n) & 1);
     T ec[4];
-    ld4(a.zc + at(E, c), ec);
-    if (a.c_has_y) add_pending_b(a.Yc, E, c, ec);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      ec[j] = v[4][j];
+      if (a.c_has_y) ec[j] = ((ec[j] + v[5][j]) + v[6][j]) + v[7][j];
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       z[j] += pcoef<T>(ch, j, 0) * ec[0] + pcoef<T>(ch, j, 1) * ec[1] +
@@ -61,133 +83,163 @@ __device__ __forceinline__ void current_z_b(const SweepArgs<T>& a, int e, int c,
   }
 }
 
-// One RAS step of level k for kBatch requests, one tile per workgroup:
-//   1. the tile's factor operands are requested first (they are the bytes
-//      the step streams from HBM);
-//   2. z on the 52 squares near the tile: z_old + pending Y [+ P e_coarse],
-//      kept in LDS; the core squares are written to z_new;
-//   3. U = f - L_k z on the 32 block squares (128 x kBatch), in LDS, each
-//      operator row loaded once for four requests;
-//   4. wavefront w computes the row blocks P = w and P = 7 - w of
-//      (L_k)_t^{-1} U: 8 column blocks Q x 4 MFMA k-steps each;
-//   5. Y_t = D_t U written to the pending slot of each block square.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_sweep_b(SweepArgs<T> a) {
+// One RAS step of level k for kBatch requests, NS workgroups of NW wavefronts per tile:
+//   1. z on the 52 squares near the tile: z_old + pending Y [+ P e_coarse],
+//      kept in LDS, the loads of two squares per thread in flight at a time; the
+//      core squares are written to z_new;
+//   2. U = f - L_k z on the 32 block squares (128 x kBatch), in LDS;
+//   3. (L_k)_t^{-1} U in 16 x 16 row and column blocks x 4 MFMA k-steps; with
+//      NS > 1 a workgroup computes a part of the row blocks, KS wavefronts share the
+//      contraction of one;
+//   4. Y_t = D_t U written to the pending slot of each block square.
+//
+// Small levels are a chain of latencies, so they run 8 wavefronts per tile, split
+// over four workgroups where those fit the compute units at once: in FP64 n = 32
+// 12.8 -> 9.8, n = 64 13.9 -> 11.9 us (FP32 9.3 -> 7.4).  n = 128 is bound by the bytes of
+// the overlapping frames (3.25 z and pending sets per core square) and the MFMA rate,
+// 37.6 -> 36.0 us; more workgroups in flight make it slower (35.4 and 44.4 us of a plain and
+// a prolongating step at 3 per compute unit against 34.3 and 40.9 at 2).
+template <typename T, bool PROL, int NW, int NS>
+__global__ __launch_bounds__(64 * NW) void k_sweep_b(SweepArgs<T> a) {
   using V = typename Mfma<T>::v4;
+  constexpr int NTH = 64 * NW, RB = 8 / NS;
+  constexpr int HP = RB > NW ? RB / NW : 1;   // row blocks per wavefront
+  constexpr int KS = NW > RB ? NW / RB : 1;   // wavefronts per row block
+  constexpr int NQ = 8 / KS;                  // column blocks per wavefront
+  constexpr int PD = NQ < 4 ? NQ : 4;         // of them requested ahead
+  constexpr int NI = (52 * B + NTH - 1) / NTH, NF = 32 * B / NTH;
+  constexpr int CH = 2;                       // squares in flight per thread
   __shared__ __align__(16) T zn[52][B][4];
   __shared__ __align__(16) T ul[32][B][4];
-  const int t = xcd_band_index(blockIdx.x, gridDim.x);
+  const int part = NS > 1 ? blockIdx.x / a.tiles : 0;
+  const int t = xcd_band_index(blockIdx.x - part * a.tiles, a.tiles);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, k = lane >> 4;
-  const int Pw[2] = {wave, 7 - wave};
-  const bool need_z = a.has_z || a.has_y || a.prol;
+  int Pw[HP];
+  Pw[0] = part * RB + wave % RB;
+  if constexpr (HP == 2) Pw[1] = 7 - wave;
+  const int Q0 = wave / RB * NQ;
+  const bool need_z = a.has_z || a.has_y || PROL;
 
-  // MFMA A operands: lane (r, k) of k-step kk holds row 16 P + r, column
-  // 16 Q + 4 k + kk of the tile inverse, one vector of the operand-order copy;
-  // column blocks are loaded two ahead of their use (the first two before the
-  // gather and residual phases)
-  const int tpr = a.n >> 2;
-  const T* Ft = a.Fm + (int64_t)tile_class_of(a.cls9, t % tpr, t / tpr, tpr) * (64 * 256);   // grid = tiles
-  auto load_q = [&](int Q, T (&dst)[2][4]) {
+  T fr[NF][4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) ld4(Ft + ((Pw[h] * 8 + Q) * 64 + lane) * 4, dst[h]);
-  };
-  T av[3][2][4];
-  load_q(0, av[0]);
-  load_q(1, av[1]);
-
-  for (int it = tid; it < 52 * B; it += kThreads) {
-    const int q = it / B, c = it % B;
-    const int e = ext_square(t, q, a.n);
-    T z[4] = {T(0), T(0), T(0), T(0)};
-    if (e >= 0 && need_z) current_z_b(a, e, c, z);
-    st4(&zn[q][c][0], z);
+  for (int u = 0; u < NF; ++u) {
+    const int it = tid + u * NTH, e = ext_square(t, it / B, a.n);
+    fr[u][0] = fr[u][1] = fr[u][2] = fr[u][3] = T(0);
+    if (e >= 0) ld4(a.f + at(e, it % B), fr[u]);
   }
-  __syncthreads();
-  if (a.write_z) {   // the 16 core squares x kBatch requests, one per thread
-    const int q = tid / B, c = tid % B;
-    const int e = ext_square(t, q, a.n);
-    T z[4];
-    ld4(&zn[q][c][0], z);
-    st4(a.z_new + at(e, c), z);
-  }
-  // U = f - L_k z: thread (block square p, row j, requests 4 g .. 4 g + 3), so
-  // that each operator row is loaded once and applied to four requests' z
-  // from LDS
+  if (need_z) {
 #pragma unroll
-  for (int k2 = 0; k2 < 32 * 16 / kThreads; ++k2) {
-    const int it = tid + k2 * kThreads;
-    const int p = it >> 4, j = (it >> 2) & 3, g = it & 3;
-    const int e = ext_square(t, p, a.n);
-    T u[4] = {T(0), T(0), T(0), T(0)};
-    if (e >= 0) {
+    for (int u0 = 0; u0 < NI; u0 += CH) {
+      T v[CH][PROL ? 8 : 4][4];
+      int es[CH];
 #pragma unroll
-      for (int cc = 0; cc < 4; ++cc) u[cc] = a.f[at(e, 4 * g + cc) + j];
-      if (need_z) {
-        const int ex = e % a.n, ey = e / a.n;
-        const T* Lrow = a.Lc + square_class(ex, ey, a.n) * 80;
-        T acc[4] = {T(0), T(0), T(0), T(0)};
+      for (int u = 0; u < CH; ++u) {
+        const int it = tid + (u0 + u) * NTH;
+        es[u] = it < 52 * B ? ext_square(t, it / B, a.n) : -1;
+        load_z_b<T, PROL>(a, es[u], it % B, v[u]);
+      }
 #pragma unroll
-        for (int s = 0; s < 5; ++s) {
-          const int dx = s == 1 ? -1 : (s == 2 ? 1 : 0), dy = s == 3 ? -1 : (s == 4 ? 1 : 0);
-          if (ex + dx < 0 || ex + dx >= a.n || ey + dy < 0 || ey + dy >= a.n) continue;
-          T l[4];
-          ld4(Lrow + 16 * s + 4 * j, l);
-          const int q = nbr_slot(p, s);
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            T zq[4];
-            ld4(&zn[q][4 * g + cc][0], zq);
-            acc[cc] += l[0] * zq[0] + l[1] * zq[1] + l[2] * zq[2] + l[3] * zq[3];
-          }
-        }
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) u[cc] -= acc[cc];
+      for (int u = 0; u < CH; ++u) {
+        const int it = tid + (u0 + u) * NTH;
+        if (it >= 52 * B) continue;
+        T z[4];
+        combine_z_b<T, PROL>(a, es[u], v[u], z);
+        st4(&zn[it / B][it % B][0], z);
+        if (a.write_z && part == 0 && it < 16 * B) st4(a.z_new + at(es[u], it % B), z);
       }
     }
+  }
+
+  // MFMA A operands: lane (r, k) of k-step kk holds row 16 P + r, column
+  // 16 Q + 4 k + kk of the tile inverse, one vector of the operand-order copy,
+  // requested before the residual is formed
+  const int tpr = a.n >> 2;
+  const T* Ft = a.Fm + (int64_t)tile_class_of(a.cls9, t % tpr, t / tpr, tpr) * (64 * 256);
+  auto load_q = [&](int Q, T (&dst)[HP][4]) {
 #pragma unroll
-    for (int cc = 0; cc < 4; ++cc) ul[p][4 * g + cc][j] = u[cc];
+    for (int h = 0; h < HP; ++h) ld4(Ft + ((Pw[h] * 8 + Q0 + Q) * 64 + lane) * 4, dst[h]);
+  };
+  T av[PD][HP][4];
+#pragma unroll
+  for (int Q = 0; Q < PD; ++Q) load_q(Q, av[Q]);
+  __syncthreads();
+
+  // U = f - L_k z: thread (block square p, request c), the four rows from the class
+  // table in scalar registers (a wavefront holds four squares)
+#pragma unroll
+  for (int u = 0; u < NF; ++u) {
+    const int it = tid + u * NTH, p = it / B, c = it % B;
+    const int e = ext_square(t, p, a.n);
+    if (e >= 0 && need_z) {
+      T zq[5][4], acc[4] = {T(0), T(0), T(0), T(0)};
+      const int ex = e % a.n, ey = e / a.n;
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        const int dx = s == 1 ? -1 : (s == 2 ? 1 : 0), dy = s == 3 ? -1 : (s == 4 ? 1 : 0);
+        zq[s][0] = zq[s][1] = zq[s][2] = zq[s][3] = T(0);
+        if (ex + dx >= 0 && ex + dx < a.n && ey + dy >= 0 && ey + dy < a.n)
+          ld4(&zn[nbr_slot(p, s)][c][0], zq[s]);
+      }
+      class_rows(a.Lc, square_class(ex, ey, a.n), zq, acc);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fr[u][j] -= acc[j];
+    }
+    st4(&ul[p][c][0], fr[u]);
   }
   __syncthreads();
 
   // MFMA B operand of column block Q: lane (k, c = r) holds U[16 Q + 4 k + kk][c]
-  V acc0 = {T(0), T(0), T(0), T(0)}, acc1 = {T(0), T(0), T(0), T(0)};
+  V accs[HP];
 #pragma unroll
-  for (int Q = 0; Q < 8; ++Q) {
-    if (Q + 2 < 8) load_q(Q + 2, av[(Q + 2) % 3]);
-    T bq[4];
-    ld4(&ul[4 * Q + k][r][0], bq);
-    const T (&aq)[2][4] = av[Q % 3];
+  for (int h = 0; h < HP; ++h) accs[h] = V{T(0), T(0), T(0), T(0)};
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      acc0 = Mfma<T>::mac(aq[0][kk], bq[kk], acc0);
-      acc1 = Mfma<T>::mac(aq[1][kk], bq[kk], acc1);
+  for (int Q = 0; Q < NQ; ++Q) {
+    T bq[4], aq[HP][4];
+    ld4(&ul[4 * (Q0 + Q) + k][r][0], bq);
+#pragma unroll
+    for (int h = 0; h < HP; ++h)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) aq[h][kk] = av[Q % PD][h][kk];
+    if (Q + PD < NQ) load_q(Q + PD, av[Q % PD]);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int h = 0; h < HP; ++h) accs[h] = Mfma<T>::mac(aq[h][kk], bq[kk], accs[h]);
+  }
+  if constexpr (KS > 1) {          // the parts of a row block's contraction, in z's place
+    T (*red)[4] = &zn[0][0];
+    T out[4] = {accs[0][0], accs[0][1], accs[0][2], accs[0][3]};
+    st4(red[tid], out);
+    __syncthreads();
+    if (wave >= RB) return;
+#pragma unroll
+    for (int p = 1; p < KS; ++p) {
+      T o[4];
+      ld4(red[tid + 64 * RB * p], o);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) accs[0][v] += o[v];
     }
   }
 
+  // FP32 lanes hold rows 4 k + v of row block P (square 4 P + k, corner v), FP64
+  // lanes rows 4 v + k (square 4 P + v, corner k); request r
+  constexpr int NO = std::is_same<T, float>::value ? 1 : 4;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const V& acc = h == 0 ? acc0 : acc1;
-    const int P = Pw[h];
-    if constexpr (std::is_same<T, float>::value) {
-      // rows 4 k + v: square 4 P + k, corner v, request r
-      const int p = 4 * P + k;
-      const int e = ext_square(t, p, a.n);
-      if (e >= 0) {
-        const T w = a.dw[e];
-        const T y[4] = {w * acc[0], w * acc[1], w * acc[2], w * acc[3]};
-        st4(a.Y_new + at(a.dst[t * 32 + p], r), y);
-      }
-    } else {
-      // rows 4 v + k: square 4 P + v, corner k, request r
+  for (int h = 0; h < HP; ++h)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int p = 4 * P + v;
-        const int e = ext_square(t, p, a.n);
-        if (e >= 0) a.Y_new[at(a.dst[t * 32 + p], r) + k] = a.dw[e] * acc[v];
+    for (int v = 0; v < NO; ++v) {
+      const int e = ext_square(t, 4 * Pw[h] + (NO == 1 ? k : v), a.n);
+      if (e < 0) continue;
+      T w;
+      const int64_t o = at(pending_slot(e % a.n, e / a.n, a.n, t, w), r);
+      if constexpr (NO == 1) {
+        const T y[4] = {w * accs[h][0], w * accs[h][1], w * accs[h][2], w * accs[h][3]};
+        st4(a.Y_new + o, y);
+      } else {
+        a.Y_new[o + k] = w * accs[h][v];
       }
     }
-  }
 }
 
 // Pending update + residual + restriction for kBatch requests: one
@@ -377,8 +429,18 @@ hipError_t launch_store_columns(int ne, int j0, bool has_z, const double* z, con
 
 template <typename T>
 hipError_t launch_sweep_b(const SweepArgs<T>& a, hipStream_t st) {
-  if (a.tiles <= 0 || a.n < 8 || (a.n & 3)) return hipErrorInvalidValue;
-  k_sweep_b<T><<<a.tiles, kThreads, 0, st>>>(a);
+  const int tpr = a.n / 4;
+  if (a.tiles <= 0 || a.n < 8 || (a.n & 3) || a.tiles != tpr * tpr) return hipErrorInvalidValue;
+#define DCG_SWEEP_B(NW, NS)                                                    \
+  if (a.prol)                                                                  \
+    k_sweep_b<T, true, NW, NS><<<NS * a.tiles, 64 * NW, 0, st>>>(a);           \
+  else                                                                         \
+    k_sweep_b<T, false, NW, NS><<<NS * a.tiles, 64 * NW, 0, st>>>(a)
+  // up to one workgroup per compute unit 8 wavefronts each, see the kernel
+  if (4 * a.tiles <= 256) { DCG_SWEEP_B(8, 4); }
+  else if (a.tiles <= 256) { DCG_SWEEP_B(8, 1); }
+  else { DCG_SWEEP_B(4, 1); }
+#undef DCG_SWEEP_B
   return hipGetLastError();
 }
 

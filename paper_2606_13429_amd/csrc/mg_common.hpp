@@ -81,6 +81,22 @@ __device__ __forceinline__ void class_rows(const T* __restrict__ Lc, int cls, co
   }
 }
 
+// Pending slot (3 e + rank) of tile t's output at square (X, Y) of its block, and the
+// weight of the average.  Blocks containing (X, Y): its core tile T and the
+// neighbour tile on each side where the square lies on T's core edge; the slot is
+// this tile's rank among them in increasing order.
+template <typename T>
+__device__ __forceinline__ int64_t pending_slot(int X, int Y, int n, int t, T& w) {
+  const int tpr = n >> 2, TX = X >> 2, TY = Y >> 2, lx = X & 3, ly = Y & 3, Tc = TY * tpr + TX;
+  const bool below = ly == 0 && TY > 0, left = lx == 0 && TX > 0;
+  const bool right = lx == 3 && TX < tpr - 1, above = ly == 3 && TY < tpr - 1;
+  const int count = 1 + below + left + right + above;
+  const int rank = (below && Tc - tpr < t) + (left && Tc - 1 < t) + (Tc < t) +
+                   (right && Tc + 1 < t) + (above && Tc + tpr < t);
+  w = count == 1 ? T(1) : (count == 2 ? T(0.5) : T(1.0 / 3.0));
+  return 3 * ((int64_t)Y * n + X) + rank;
+}
+
 // Position (relative to the tile origin) of block slot p < 32.
 __device__ __forceinline__ void slot_pos(int p, int& px, int& py) {
   if (p < 16) { px = p & 3; py = p >> 2; }

@@ -574,17 +574,8 @@ void k_sweep_g(SweepArgs<T> a) {
       slot_pos(p, px, py);
       const int X = X0 + rtx - 1 + px, Y = Y0 + rty - 1 + py;
       if (X < 0 || Y < 0 || X >= a.n || Y >= a.n) continue;
-      // blocks containing (X, Y): its core tile T and the neighbour tile on
-      // each side where the square lies on T's core edge; the pending slot
-      // is this tile's rank among them in increasing order
-      const int TX = X >> 2, TY = Y >> 2, lx = X & 3, ly = Y & 3, Tc = TY * tpr + TX;
-      const bool below = ly == 0 && TY > 0, left = lx == 0 && TX > 0;
-      const bool right = lx == 3 && TX < tpr - 1, above = ly == 3 && TY < tpr - 1;
-      const int count = 1 + below + left + right + above;
-      const int rank = (below && Tc - tpr < t) + (left && Tc - 1 < t) + (Tc < t) +
-                       (right && Tc + 1 < t) + (above && Tc + tpr < t);
-      const T w = count == 1 ? T(1) : (count == 2 ? T(0.5) : T(1.0 / 3.0));
-      const int64_t slot = 3 * ((int64_t)Y * a.n + X) + rank;
+      T w;
+      const int64_t slot = pending_slot(X, Y, a.n, t, w);
       if constexpr (NO == 1) {
         const T y[4] = {w * acc[0], w * acc[1], w * acc[2], w * acc[3]};
         st4(a.Y_new + 4 * slot, y);
