@@ -147,93 +147,89 @@ hipError_t gemm(int N, const TIN* A, const double* B, TOUT* C, const double* la,
   return hipGetLastError();
 }
 
-// Small grids (N = 2 n in {32, 64, 128, 256}: coarse levels) in two passes
+// Small grids (N = 2 n in {32, 64, 128}: coarse levels) in two passes
 // with the layout change folded into the loads and stores, one workgroup per
 // row:
-//   pass 1: T2[i][k] = (sum_a sum_c V[a][i] S[a][c] V[c][k]) / (lam_i + lam_k),
-//           row i of U = V^T S, then of U V;
-//   pass 2: Z[a][c] = sum_i sum_k V[a][i] T2[i][k] V[c][k],
-//           row a of W = V T2, then of W V^T.
+//   forward:  T2[i][k] = (sum_a sum_c V[a][i] S[a][c] V[c][k]) / (lam_i + lam_k),
+//             row i of U = V^T S, then of U V;
+//   backward: Z[a][c] = sum_i sum_k V[a][i] T2[i][k] V[c][k],
+//             row a of W = V T2, then of W V^T.
 // Thread t forms a partial sum for column t % N over the contraction range
-// [p N / P, (p + 1) N / P), p = t / N, P = 256 / N; the P partials of a
-// column are added in LDS in ascending p (fixed order).
-constexpr int kFThreads = 256;
+// [p LEN, (p + 1) LEN), p = t / N; the P partials of a column are added in
+// LDS in ascending p (fixed order).  A workgroup reads two N x N matrices for 4 N^2
+// flop, so the passes are bound by one round of loads: both products' operands are
+// requested at the start, N / 8 per thread and product.  At N = 128 / 64 / 32 a pass
+// takes 6.7 / 3.5 / 2.7 us (7.7 / 4.2 / 4.3 with 256 threads that loaded one product's
+// operands after the other).  At N = 256 the two matrices are 1 MB through one
+// compute unit's cache: 19 us a pass, 38 for the solve, against 24 as four products below.
+template <int N>
+struct FdmRows {
+  static constexpr int P = 8, LEN = N / P, threads = N * P;
+};
 
 // sum over p of part[p N + c] for the threads t < N (column c = t)
-__device__ __forceinline__ double column_total(const double* part, int N, int P, int c) {
+template <int N>
+__device__ __forceinline__ double column_total(const double* part, int c) {
   double t = 0.0;
-  for (int p = 0; p < P; ++p) t += part[p * N + c];
+#pragma unroll
+  for (int p = 0; p < FdmRows<N>::P; ++p) t += part[p * N + c];
   return t;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kFThreads) void k_fdm_pass1(int n, const double* __restrict__ V,
-                                                         const double* __restrict__ VT,
-                                                         const double* __restrict__ lam,
-                                                         const T* __restrict__ s, double* __restrict__ T2) {
-  __shared__ double lhs[kFThreads];
-  __shared__ double mid[kFThreads];
-  __shared__ double part[kFThreads];
-  const int N = 2 * n, P = kFThreads / N, len = N / P;
-  const int tid = threadIdx.x, c = tid % N, q0 = (tid / N) * len;
-  const int i = blockIdx.x;
-  if (tid < N) lhs[tid] = VT[(int64_t)i * N + tid];     // row i of V^T
+template <int N, bool FWD, typename TIN, typename TOUT>
+__global__ __launch_bounds__(FdmRows<N>::threads) void k_fdm_row(const double* __restrict__ V,
+                                                                 const double* __restrict__ VT,
+                                                                 const double* __restrict__ lam,
+                                                                 const TIN* __restrict__ in,
+                                                                 TOUT* __restrict__ out) {
+  using F = FdmRows<N>;
+  constexpr int n = N / 2;
+  __shared__ double lhs[N], mid[N], part[F::threads];
+  const int tid = threadIdx.x, c = tid % N, q0 = (tid / N) * F::LEN, row = blockIdx.x;
+  const double* M = (FWD ? V : VT) + (int64_t)q0 * N + c;   // the second product's matrix
+  double b1[F::LEN], b2[F::LEN];
+#pragma unroll
+  for (int j = 0; j < F::LEN; ++j)
+    b1[j] = FWD ? double(in[tensor_to_elem(n, q0 + j, c)]) : double(in[(int64_t)(q0 + j) * N + c]);
+#pragma unroll
+  for (int j = 0; j < F::LEN; ++j) b2[j] = M[(int64_t)j * N];
+  if (tid < N) lhs[tid] = (FWD ? VT : V)[(int64_t)row * N + tid];
   __syncthreads();
-  // rows a, a + 1 (a even) of column c sit at sc[0] and sc[2] of the square
-  // row a / 2; consecutive square rows are 4 n apart
-  const T* sc = s + tensor_to_elem(n, q0, c);
-  const int64_t step = 4 * (int64_t)n;
   double u = 0.0;
-#pragma unroll 8
-  for (int a = q0; a < q0 + len; a += 2, sc += step)
-    u += lhs[a] * double(sc[0]) + lhs[a + 1] * double(sc[2]);
+#pragma unroll
+  for (int j = 0; j < F::LEN; ++j) u += lhs[q0 + j] * b1[j];
   part[tid] = u;
   __syncthreads();
-  if (tid < N) mid[tid] = column_total(part, N, P, tid);   // U[i][c]
+  if (tid < N) mid[tid] = column_total<N>(part, tid);
   __syncthreads();
   double t = 0.0;
-#pragma unroll 16
-  for (int q = q0; q < q0 + len; ++q) t += mid[q] * V[(int64_t)q * N + c];
+#pragma unroll
+  for (int j = 0; j < F::LEN; ++j) t += mid[q0 + j] * b2[j];
   part[tid] = t;
   __syncthreads();
-  if (tid < N) T2[(int64_t)i * N + tid] = column_total(part, N, P, tid) * (1.0 / (lam[i] + lam[tid]));
+  if (tid >= N) return;
+  const double x = column_total<N>(part, tid);
+  if (FWD) out[(int64_t)row * N + tid] = TOUT(x * (1.0 / (lam[row] + lam[tid])));
+  else out[tensor_to_elem(n, row, tid)] = TOUT(x);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kFThreads) void k_fdm_pass2(int n, const double* __restrict__ V,
-                                                         const double* __restrict__ VT,
-                                                         const double* __restrict__ T2, T* __restrict__ z) {
-  __shared__ double lhs[kFThreads];
-  __shared__ double mid[kFThreads];
-  __shared__ double part[kFThreads];
-  const int N = 2 * n, P = kFThreads / N, len = N / P;
-  const int tid = threadIdx.x, c = tid % N, q0 = (tid / N) * len;
-  const int a = blockIdx.x;
-  if (tid < N) lhs[tid] = V[(int64_t)a * N + tid];      // row a of V
-  __syncthreads();
-  double w = 0.0;
-#pragma unroll 16
-  for (int i = q0; i < q0 + len; ++i) w += lhs[i] * T2[(int64_t)i * N + c];
-  part[tid] = w;
-  __syncthreads();
-  if (tid < N) mid[tid] = column_total(part, N, P, tid);   // W[a][c]
-  __syncthreads();
-  double v = 0.0;
-#pragma unroll 16
-  for (int k = q0; k < q0 + len; ++k) v += mid[k] * VT[(int64_t)k * N + c];
-  part[tid] = v;
-  __syncthreads();
-  if (tid < N) z[tensor_to_elem(n, a, tid)] = T(column_total(part, N, P, tid));
+template <int N, typename T>
+hipError_t fdm_rows(const double* V, const double* VT, const double* lam, const T* s, T* z, double* t,
+                    hipStream_t st) {
+  k_fdm_row<N, true, T, double><<<N, FdmRows<N>::threads, 0, st>>>(V, VT, lam, s, t);
+  k_fdm_row<N, false, double, T><<<N, FdmRows<N>::threads, 0, st>>>(V, VT, lam, t, z);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t fdm_solve(int n, const double* V, const double* VT, const double* lam, const T* s, T* z,
                      double* t0, double* t1, double* t2, hipStream_t st) {
   const int N = 2 * n;
-  if (N >= 32 && N <= kFThreads && kFThreads % N == 0) {
-    k_fdm_pass1<T><<<N, kFThreads, 0, st>>>(n, V, VT, lam, s, t0);
-    k_fdm_pass2<T><<<N, kFThreads, 0, st>>>(n, V, VT, t0, z);
-    return hipGetLastError();
+  switch (N) {
+    case 32: return fdm_rows<32, T>(V, VT, lam, s, z, t0, st);
+    case 64: return fdm_rows<64, T>(V, VT, lam, s, z, t0, st);
+    case 128: return fdm_rows<128, T>(V, VT, lam, s, z, t0, st);
+    default: break;
   }
   hipError_t e = gemm<true, false>(N, s, V, t1, nullptr, nullptr, st);                      // x: S V
   if (e != hipSuccess) return e;
