@@ -30,21 +30,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# Algorithmic bytes of one finest-level RAS step (k_sweep), per finest square,
-# s = bytes per real: packed symmetric tile inverse 36 * 256 / 16 = 576 s,
-# operator L_J 5 x 4 x 4 = 80 s, f 4 s, pending-output writes 8 s, weight s;
-# plus, by step type: z_old 4 s, pending reads 12 s, z_new 4 s, coarse
-# iterate + pending (4 + 12) s / 4.  The four finest steps of a W-cycle are
-# one zero-start step (no L, no z), two steps with a pending update and one
-# with the prolongation; the model averages them.
 def astar_bytes(n):
     """Algorithmic HBM bytes of one k_astar launch with the fused direction
-    update (2D): the 8 x 8 FP64 row blocks C of A_div that exist (the square and
-    its edge neighbours, 512 B each), the element mass M_1 (128 B per square),
-    r and p read, p and w written (4 x 128 B) and s = Z^T w (32 B) per square."""
-    ne = n * n
-    nblocks = ne + 4 * n * (n - 1)
-    return 512 * nblocks + (128 + 4 * 128 + 32) * ne
+    update (2D): r and p read, p and w written (4 x 128 B) and s = Z^T w (32 B)
+    per square; the operator is a table of its class blocks, read from cache."""
+    return (4 * 128 + 32) * n * n
 
 
 def copy_gbs(nbytes=1 << 30, reps=10):
@@ -174,33 +164,6 @@ def err_vs_oracle(dcg):
 # sources must match, else the bench reports traffic as null.
 TRAFFIC = {"source_digest": "3b55b51a6e6af9d0", "n": 512,
            "fetch_kib": 9428.6, "fetch_scale": 2.0, "write_kib": 14645.6, "write_scale": 1.0}
-
-
-# The same counters for the 3D A* product k_astar3 at n = 32 (exact inner solve;
-# profiles/solve3d_n32_fp64.md), valid while dcg3d_kernels.hip is unchanged.
-TRAFFIC3 = {"source_digest": "261bf7a788f3d427", "n": 32,
-            "fetch_kib": 540280.0, "fetch_scale": 2.0, "write_kib": 18433.3, "write_scale": 1.0}
-
-
-def source_digest(*names):
-    import hashlib
-    h = hashlib.sha256()
-    for f in names:
-        with open(os.path.join(ROOT, "paper_2606_13429_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()[:16]
-
-
-def measured_traffic3(n):
-    """HBM bytes per k_astar3 launch from the counters, or None when they do not
-    apply (other n, or the kernel source changed since they were taken)."""
-    try:
-        if n != TRAFFIC3["n"] or source_digest("dcg3d_kernels.hip") != TRAFFIC3["source_digest"]:
-            return None
-    except OSError:
-        return None
-    return int(1024 * (TRAFFIC3["fetch_kib"] * TRAFFIC3["fetch_scale"]
-                       + TRAFFIC3["write_kib"] * TRAFFIC3["write_scale"]))
 
 
 def kernel_source_digest():
@@ -531,11 +494,10 @@ def lap3_bytes(n):
 
 
 def astar3_bytes(n):
-    """Algorithmic HBM bytes of one k_astar3 launch (the 3D A* product): the
-    24 x 24 FP64 blocks C_3 that exist, plus x read and y written once."""
-    ne = n ** 3
-    nblocks = ne + 6 * n * n * (n - 1)
-    return 8 * (576 * nblocks + 144 * ne)
+    """Algorithmic HBM bytes of one k_astar3 launch (the 3D A* product): x read
+    and y written once (72 FP64 values per cube each); the operator is a table of
+    its class blocks, read from cache."""
+    return 8 * 144 * n ** 3
 
 
 def mg3_ras_flops(n):
@@ -613,7 +575,7 @@ def three_d(args):
         nbytes = mg3_ras_bytes(n)
         tfs = flops / (k_avg * 1e-3) / 1e12
         gbs = nbytes / (k_avg * 1e-3) / 1e9
-        roof = {"bound": "alu", "kernel": "k_mg3_ras (finest-level RAS step, FP64 FMA)",
+        roof = {"bound": "mfma", "kernel": "k_mg3_ras (finest-level RAS step, FP64 MFMA)",
                 "achieved": round(tfs, 3), "peak": FP64_VECTOR_PEAK_TFS, "unit": "TFLOP/s",
                 "frac": round(tfs / FP64_VECTOR_PEAK_TFS, 4), "traffic": None,
                 "flops_per_launch": flops, "bytes_per_launch": nbytes,
@@ -627,7 +589,7 @@ def three_d(args):
         roof = {"bound": "hbm", "kernel": kname,
                 "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(gbs / HBM_PEAK_GBS, 4),
-                "traffic": measured_traffic3(n) if exact else None,
+                "traffic": None,
                 "avg_launch_us": round(k_avg * 1e3, 2), "launches": k_n,
                 "bytes_per_launch": nbytes}
     print(json.dumps({
