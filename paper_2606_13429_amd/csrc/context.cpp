@@ -18,6 +18,17 @@ void hip_check(hipError_t e, const char* what) {
   throw Error(s, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+void* try_device_alloc(size_t b) {
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, b);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();   // the next launch must not report it
+    return nullptr;
+  }
+  DCG_HIP(e);
+  return p;
+}
+
 void* MeshContext::alloc(size_t b) {
   void* p = nullptr;
   DCG_HIP(hipMalloc(&p, b));

@@ -68,7 +68,9 @@ void cycle(const OuterMg& g, int k, int mode, hipStream_t st) {
 // W = E^m (P_m + P C P^T (I - A* P_m)) + P_m, P_m = sum_{i < m} E^i S, C the map
 // of the level below (the exact solve), and two are 2 W - W A* W.  The level of
 // 16 x 16 squares is 134 MB, read in about 21 us, against 2 (4 m + 3) + 2 launches
-// of 3-4 us; the next one would be 2.1 GB, slower than its steps.
+// of 3-4 us; the next one would be 2.1 GB, slower than its steps.  The cycle runs
+// the steps of a level that has no matrix, so where the memory of the matrix or of
+// its scratch (805 MB during set-up) cannot be had there is none.
 void fold_level(OuterMg& g, int k, Workspace& ws) {
   const int i = k - 1;
   const int64_t m = level_len(g, k);
@@ -77,9 +79,10 @@ void fold_level(OuterMg& g, int k, Workspace& ws) {
     double* p = nullptr;
     ~Temp() { (void)hipFree(p); }
   } tmp;
-  DCG_HIP(hipMalloc(&tmp.p, 6 * m * m * sizeof(double)));
+  tmp.p = static_cast<double*>(try_device_alloc(6 * m * m * sizeof(double)));
+  double* C = tmp.p ? static_cast<double*>(ws.try_alloc(m * m * sizeof(double))) : nullptr;
+  if (!C) return;
   double *A = tmp.p, *S = A + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
-  double* C = static_cast<double*>(ws.alloc(m * m * sizeof(double)));
   const hipStream_t st = nullptr;
   auto mul = [&](const double* X, const double* Y, double* out, double a, const double* add) {
     DCG_HIP(launch_gemm(int(m), X, Y, out, a, add, st));
@@ -154,9 +157,9 @@ void omg_setup(dcg_ctx* h) {
     g->lev.push_back(d);
   }
   g->cinv = upload(ws, H.coarse_inv);
+  g->zp = static_cast<double*>(ws.alloc((int64_t)D * g->n[g->J - 1] * g->n[g->J - 1] * sizeof(double)));
   g->fold.assign(g->J, nullptr);
   for (int k = 2; k < g->J; ++k) fold_level(*g, k, ws);
-  g->zp = static_cast<double*>(ws.alloc((int64_t)D * g->n[g->J - 1] * g->n[g->J - 1] * sizeof(double)));
   h->omg = std::move(g);
 }
 

@@ -26,6 +26,9 @@ struct Error : std::runtime_error {
 void hip_check(hipError_t e, const char* what);
 #define DCG_HIP(expr) ::dcg::hip_check((expr), #expr)
 
+// Device memory the library can do without: NULL when there is none.
+void* try_device_alloc(size_t bytes);
+
 // One multigrid level on the device.
 struct DeviceLevel {
   int n = 0, ne = 0;
@@ -166,6 +169,7 @@ struct Workspace {
   LevelBuffers lvb_batch;                 // batched level operators (allocated on first use)
   FcgStore fcg;                           // DCG_OUTER_FCG directions
   void* alloc(size_t bytes);
+  void* try_alloc(size_t bytes);          // NULL when the memory cannot be had
   void release();
   ~Workspace();
 };

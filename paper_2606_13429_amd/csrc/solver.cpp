@@ -23,6 +23,14 @@ void* Workspace::alloc(size_t b) {
   return p;
 }
 
+void* Workspace::try_alloc(size_t b) {
+  void* p = try_device_alloc(b);
+  if (!p) return nullptr;
+  allocations.push_back(p);
+  bytes += b;
+  return p;
+}
+
 void Workspace::release() {
   for (void* p : allocations) (void)hipFree(p);
   allocations.clear();

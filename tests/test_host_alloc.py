@@ -1,0 +1,56 @@
+"""Set-up when device memory runs short, on the host: libdcg.so linked with a
+HIP runtime whose device memory is host memory under a capacity and whose
+kernels do nothing (tests/native), so that allocations can be made to fail one
+by one.
+
+The dense matrices of the coarse cycles are optional: a set-up that cannot have
+one (128 MiB, and 805 MB of scratch where it is made by products) succeeds
+without it and holds what it would hold otherwise.  A set-up that fails gives
+back all it took and leaves nothing that a later one holds twice."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+NATIVE = os.path.join(ROOT, "tests", "native")
+PKG = os.path.join(ROOT, "paper_2606_13429_amd")
+MATRIX = 4096 * 4096 * 8
+OK, ENOMEM = 0, -2
+
+
+@pytest.fixture(scope="session")
+def program(tmp_path_factory):
+    lib = os.path.join(PKG, "libdcg.so")
+    if not os.path.exists(lib):
+        pytest.skip("libdcg.so is not built")
+    exe = str(tmp_path_factory.mktemp("alloc") / "alloc_main")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(NATIVE, "fake_hip.cpp"), os.path.join(NATIVE, "alloc_main.cpp"), "-o", exe,
+                    "-rdynamic", "-Wl,--unresolved-symbols=ignore-in-shared-libs", lib, "-Wl,-rpath," + PKG,
+                    "-lpthread"], check=True)
+
+    def run(*args):
+        out = subprocess.run([exe] + [str(a) for a in args], check=True, capture_output=True, text=True,
+                             timeout=120).stdout
+        return {k: int(v) for k, v in (line.split() for line in out.splitlines())}
+    return run
+
+
+def _clean(r):
+    assert r["clean_status"] == OK and r["clean_left"] == 0
+    assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0 and r["device"] == 0
+
+
+# the set-ups that keep a matrix
+SETUPS = [("omg", 32)]
+
+
+@pytest.mark.parametrize("what,n", SETUPS)
+@pytest.mark.parametrize("short", [1, 6 * MATRIX])
+def test_setup_without_the_memory_of_the_matrix(program, what, n, short):
+    r = program("setup", what, n, "room", short)
+    assert r["clean_matrices"] == 1
+    assert r["status"] == OK and r["matrices"] == 0 and r["last_error"] == 0
+    assert r["bytes"] == r["clean_bytes"] - MATRIX
+    _clean(r)
