@@ -307,6 +307,19 @@ T* dev_alloc(size_t count) {
   return static_cast<T*>(p);
 }
 
+// NULL where the memory cannot be had.
+template <typename T>
+T* try_dev_alloc(size_t count) {
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, count * sizeof(T));
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();   // the next launch must not report it
+    return nullptr;
+  }
+  H3(e);
+  return static_cast<T*>(p);
+}
+
 }  // namespace
 
 struct dcg3d_ctx {
@@ -434,6 +447,7 @@ struct dcg3d_ctx {
     H3(hipMalloc(&sc, sizeof(dcg3::PcgScalars)));
     H3(hipHostMalloc(&sc_host, sizeof(dcg3::PcgScalars), hipHostMallocDefault));
     H3(hipHostMalloc(&dots_host, 8 * sizeof(double), hipHostMallocDefault));
+    for (int k = 2; k < mg_J; ++k) fold_level(k);   // last: the matrices are optional
   }
 
   template <typename T>
@@ -476,7 +490,6 @@ struct dcg3d_ctx {
     }
     mg_cinv = upload(H.coarse_inv);
     mg_fold.assign(mg_J, nullptr);
-    for (int k = 2; k < mg_J; ++k) fold_level(k);
     mg_part = dev_alloc<double>(dcg3::mg3_res_blocks(mg_lev[mg_J - 1]));
     H3(hipMalloc(&mg_sc, sizeof(dcg3::Mg3Scalars)));
     H3(hipHostMalloc(&mg_sc_host, sizeof(dcg3::Mg3Scalars), hipHostMallocDefault));
@@ -490,6 +503,8 @@ struct dcg3d_ctx {
   // map of the level below, and two are 2 W - W L W.  A level of 8 x 8 x 8 cubes
   // is 134 MB, read in 21 us, against 84 launches of 3.6-4.3 us and the levels below;
   // the next size (12 or 16 cubes) would be 1.5 or 8.6 GB, slower than its steps.
+  // The cycle runs the steps of a level that has no matrix, so where the memory of
+  // the matrix or of its scratch (805 MB during set-up) cannot be had there is none.
   void fold_level(int k) {
     const int i = k - 1, nk = mg_n[i];
     const int64_t m = 8 * (int64_t)nk * nk * nk;
@@ -498,10 +513,11 @@ struct dcg3d_ctx {
       double* p = nullptr;
       ~Temp() { (void)hipFree(p); }
     } tmp;
-    tmp.p = dev_alloc<double>(6 * m * m);
-    double *L = tmp.p, *S = L + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
-    double* C = dev_alloc<double>(m * m);
+    tmp.p = try_dev_alloc<double>(6 * m * m);
+    double* C = tmp.p ? try_dev_alloc<double>(m * m) : nullptr;
+    if (!C) return;
     mg_fold[i] = C;
+    double *L = tmp.p, *S = L + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
     const size_t bytes = size_t(m * m) * sizeof(double);
     auto gemm = [&](const double* A, const double* B, double* out, double a, const double* D) {
       H3(dcg::launch_gemm(int(m), A, B, out, a, D, nullptr));

@@ -43,7 +43,7 @@ def _clean(r):
 
 
 # the set-ups that keep a matrix
-SETUPS = [("omg", 32)]
+SETUPS = [("omg", 32), ("3d", 16)]
 
 
 @pytest.mark.parametrize("what,n", SETUPS)
