@@ -6,6 +6,7 @@
 #include <map>
 #include <thread>
 #include <tuple>
+#include <type_traits>
 
 #include "mg_common.hpp"
 #include "runtime.hpp"
@@ -14,6 +15,7 @@ namespace dcg {
 
 void hip_check(hipError_t e, const char* what) {
   if (e == hipSuccess) return;
+  (void)hipGetLastError();   // reported here; the next launch must not report it again
   const dcg_status s = (e == hipErrorOutOfMemory) ? DCG_ENOMEM : DCG_EDEVICE;
   throw Error(s, std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -367,44 +369,48 @@ std::shared_ptr<MeshContext> build_context(int device, int n, double penalty) {
 
 }  // namespace
 
-void MeshContext::ensure_factors(bool fp32) {
+void MeshContext::ensure_factors(bool fp32, int levels) {
   std::lock_guard<std::mutex> lk(mu);
   if (fp32 ? have_f32 : have_f64) return;
   if (!host) throw Error(DCG_EDEVICE, "mesh context lost its host data");
-  int cur = 0;
-  DCG_HIP(hipGetDevice(&cur));
+  struct Device {   // given back also where an allocation fails
+    int cur = 0;
+    ~Device() { (void)hipSetDevice(cur); }
+  } dev;
+  DCG_HIP(hipGetDevice(&dev.cur));
   DCG_HIP(hipSetDevice(device));
-  for (int k = 1; k <= J; ++k) {
+  // an array that a call before this one, cut short by a failed allocation or
+  // for fewer levels, has uploaded is not made again
+  auto array = [&](auto*& dst, size_t count, auto upload) {
+    if (dst) return;
+    auto* p = static_cast<std::remove_reference_t<decltype(dst)>>(alloc(sizeof(*dst) * count));
+    upload(p);
+    dst = p;
+  };
+  for (int k = 1; k <= (levels > 0 ? levels : J); ++k) {
     const HostLevel& hl = host->levels[k - 1];
     DeviceLevel& dl = lv[k - 1];
     if (fp32) {
-      dl.L32 = static_cast<float*>(alloc(sizeof(float) * dl.ne * kSlots * 16));
-      upload_level_L<float>(hl, dl.L32);
-      dl.Lc32 = upload_class_table<float>(this, square_class_table(hl));
+      array(dl.L32, size_t(dl.ne) * kSlots * 16, [&](float* p) { upload_level_L<float>(hl, p); });
+      if (!dl.Lc32) dl.Lc32 = upload_class_table<float>(this, square_class_table(hl));
     }
     if (k >= 2) {
       const size_t cnt = size_t(dl.classes) * 36 * 256;
       const size_t fcnt = size_t(dl.classes) * 64 * 64 * 4;
       if (fp32) {
-        dl.F32 = static_cast<float*>(alloc(sizeof(float) * cnt));
-        upload_factors<float>(hl, dl.F32);
-        dl.Fm32 = static_cast<float*>(alloc(sizeof(float) * fcnt));
-        upload_fragments<float>(hl, dl.Fm32);
-        dl.dw32 = static_cast<float*>(alloc(sizeof(float) * dl.ne));
-        upload_weights<float>(hl, dl.dw32);
+        array(dl.F32, cnt, [&](float* p) { upload_factors<float>(hl, p); });
+        array(dl.Fm32, fcnt, [&](float* p) { upload_fragments<float>(hl, p); });
+        array(dl.dw32, dl.ne, [&](float* p) { upload_weights<float>(hl, p); });
       } else {
-        dl.F64 = static_cast<double*>(alloc(sizeof(double) * cnt));
-        upload_factors<double>(hl, dl.F64);
-        dl.Fm64 = static_cast<double*>(alloc(sizeof(double) * fcnt));
-        upload_fragments<double>(hl, dl.Fm64);
-        dl.dw64 = static_cast<double*>(alloc(sizeof(double) * dl.ne));
-        upload_weights<double>(hl, dl.dw64);
+        array(dl.F64, cnt, [&](double* p) { upload_factors<double>(hl, p); });
+        array(dl.Fm64, fcnt, [&](double* p) { upload_fragments<double>(hl, p); });
+        array(dl.dw64, dl.ne, [&](double* p) { upload_weights<double>(hl, p); });
       }
     }
   }
+  if (levels > 0 && levels < J) return;
   (fp32 ? have_f32 : have_f64) = true;
   if (have_f32 && have_f64) host.reset();
-  DCG_HIP(hipSetDevice(cur));
 }
 
 std::shared_ptr<MeshContext> get_context(int n, double penalty, bool fp32) {

@@ -92,7 +92,9 @@ struct MeshContext {
   std::shared_ptr<FoldMatrix> last_fold;
 
   ~MeshContext();
-  void ensure_factors(bool fp32);   // uploads L_k and tile inverses of that precision
+  // uploads L_k and tile inverses of that precision, with levels > 0 of the
+  // coarsest ``levels`` only; what an earlier call uploaded is kept
+  void ensure_factors(bool fp32, int levels = 0);
   void* alloc(size_t bytes);
   std::vector<void*> allocations;
 };
