@@ -132,6 +132,7 @@ dcg_status dcg_setup(const dcg_mesh* mesh, double dt, double nu, const dcg_optio
     h->mesh = dcg::get_context(mesh->n, mesh->penalty, h->fp32);
     dcg::handle_init(h);
     if (o.outer_mg > 0) dcg::omg_setup(h);
+    dcg::handle_fold(h);
     h->t_setup_ms =
         std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return DCG_OK;

@@ -100,8 +100,9 @@ struct MeshContext {
 };
 
 // True when cycles with post-smoothing m2 on the full hierarchy of J levels use
-// the fold matrix; get_fold returns it (made on first use), or NULL where its
-// memory cannot be had.  The calling thread's device is the mesh's.
+// the fold matrix; get_fold returns it (made on first use), or NULL where the
+// memory of the matrix or of its construction (20 MB of level buffers, the FP64
+// inverses of level 2) cannot be had.  The calling thread's device is the mesh's.
 inline bool fold_applies(int J, int post) { return J >= 3 && post >= 1; }
 std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post);
 
@@ -250,6 +251,7 @@ struct dcg_ctx {
 
 namespace dcg {
 void handle_init(dcg_ctx* h);             // allocates the workspace
+void handle_fold(dcg_ctx* h);             // the fold matrix, after everything the handle needs
 dcg_status solve(dcg_ctx* h, const double* b, double* x, double tol, dcg_stats* st,
                  hipStream_t stream);
 void kernel_timing(dcg_ctx* h, int stride);   // 0 = off

@@ -92,24 +92,16 @@ FoldMatrix::~FoldMatrix() {
   (void)hipSetDevice(cur);
 }
 
+namespace {
+
 // The matrix is what the two cycles make of the unit vectors: 256 batches of 16
 // columns through the FP64 batched cycle, on four streams (a batch fills a
 // quarter of the compute units and is bound by its launches).
-std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
-  if (!fold_applies(m.J, post)) return nullptr;
-  m.ensure_factors(false);
-  std::lock_guard<std::mutex> lk(m.fold_mu);
-  std::weak_ptr<FoldMatrix>& slot = m.folds[{pre, post}];
-  if (auto have = slot.lock()) {
-    m.last_fold = have;
-    return have;
-  }
+std::shared_ptr<FoldMatrix> build_fold(MeshContext& m, int pre, int post) {
   auto F = std::make_shared<FoldMatrix>();
   F->device = m.device;
-  if (hipMalloc(reinterpret_cast<void**>(&F->C), kFoldBytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;   // the cycles run their steps
-  }
+  DCG_HIP(hipMalloc(reinterpret_cast<void**>(&F->C), kFoldBytes));
+  m.ensure_factors(false, 2);
   constexpr int kStreams = 4;
   struct Lane {
     Workspace ws;
@@ -135,7 +127,25 @@ std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
     DCG_HIP(launch_store_columns(ne, j0, s.has_z, c.z(2, s.zb), s.has_y ? c.Y(2, s.yb) : nullptr, F->C, l.st));
   }
   for (Lane& l : lane) DCG_HIP(hipStreamSynchronize(l.st));
-  slot = F;
+  return F;
+}
+
+}  // namespace
+
+std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
+  if (!fold_applies(m.J, post)) return nullptr;
+  std::lock_guard<std::mutex> lk(m.fold_mu);
+  std::weak_ptr<FoldMatrix>& slot = m.folds[{pre, post}];
+  std::shared_ptr<FoldMatrix> F = slot.lock();
+  if (!F) {
+    try {
+      F = build_fold(m, pre, post);
+    } catch (const Error& e) {
+      if (e.status != DCG_ENOMEM) throw;
+      return nullptr;   // the cycles run their steps
+    }
+    slot = F;
+  }
   m.last_fold = F;
   return F;
 }
@@ -412,7 +422,11 @@ void handle_init(dcg_ctx* h) {
     h->cfdm.VT = VT;
     h->cfdm.lam = lam;
   }
-  if (h->opt.inner == DCG_INNER_MG && h->lbase == 0) h->fold = get_fold(m, h->mp.pre, h->mp.post);
+}
+
+void handle_fold(dcg_ctx* h) {
+  if (h->opt.inner == DCG_INNER_MG && h->lbase == 0)
+    h->fold = get_fold(*h->mesh, h->mp.pre, h->mp.post);
 }
 
 // ------------------------------------------------------------ stored directions

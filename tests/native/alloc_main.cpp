@@ -54,40 +54,54 @@ struct Handle {
   }
 };
 
-// setup WHAT N fail CALL: that allocation fails; then again without a failure.
-// setup WHAT N room BYTES: BYTES less than the set-up's peak.
-int setup(const std::string& what, int n, const std::string& how, int64_t v) {
+// What a set-up with all the memory it wants takes.
+int64_t clean(const std::string& what, int n) {
   fake::State& s = fake::state();
-  {
-    Handle h;
-    put("clean_status", h.create(what, n));
-    put("clean_calls", s.malloc_calls);
-    put("clean_peak", s.peak);
-    put("clean_bytes", fake::live_bytes());
-    put("clean_matrices", fake::live_blocks(kMatrix));
-    h.destroy();
-    put("clean_left", fake::live_bytes());
-  }
-  const int64_t peak = s.peak, full = s.capacity;
   Handle h;
-  if (how == "fail") s.fail_call = s.malloc_calls + v;
-  if (how == "room") s.capacity = peak - v;
+  put("clean_status", h.create(what, n));
+  const int64_t bytes = fake::live_bytes();
+  put("clean_bytes", bytes);
+  put("clean_matrices", fake::live_blocks(kMatrix));
+  put("clean_calls", s.malloc_calls);
+  h.destroy();
+  put("clean_left", fake::live_bytes());
+  return bytes;
+}
+
+// room WHAT N BYTES: a device with BYTES less than the set-up's peak.
+int room(const std::string& what, int n, int64_t less) {
+  fake::State& s = fake::state();
+  clean(what, n);
+  Handle h;
+  s.capacity = s.peak - less;
   put("status", h.create(what, n));
   put("bytes", fake::live_bytes());
   put("matrices", fake::live_blocks(kMatrix));
-  if (h.h2 || h.h3) {   // a set-up that succeeded leaves no error behind
-    put("last_error", hipGetLastError());
-  }
-  s.fail_call = -1;
-  s.capacity = full;
-  if (how == "fail") {   // the next set-up, on what the failed one left in the cache
-    Handle again;
-    put("again_status", again.create(what, n));
+  put("last_error", hipGetLastError());
+  h.destroy();
+  put_left_over();
+  return 0;
+}
+
+// fail WHAT N CALL...: a set-up whose allocation CALL fails, then one without a
+// failure on what the first left in the cache.
+int fail(const std::string& what, int n, const std::vector<std::string>& calls) {
+  fake::State& s = fake::state();
+  const int64_t bytes = clean(what, n);
+  int64_t refused = 0, again_ok = 0, again_equal = 0;
+  for (const std::string& c : calls) {
+    Handle h, again;
+    s.fail_call = s.malloc_calls + std::atoll(c.c_str());
+    refused += h.create(what, n) == DCG_ENOMEM;
+    s.fail_call = -1;
+    again_ok += again.create(what, n) == DCG_OK;
+    again_equal += fake::live_bytes() == bytes;
     h.destroy();
-    put("again_bytes", fake::live_bytes());
     again.destroy();
   }
-  h.destroy();
+  put("refused", refused);
+  put("again_ok", again_ok);
+  put("again_equal", again_equal);
   put_left_over();
   return 0;
 }
@@ -96,7 +110,9 @@ int setup(const std::string& what, int n, const std::string& how, int64_t v) {
 
 int main(int argc, char** argv) {
   const std::vector<std::string> a(argv + 1, argv + argc);
-  if (a.size() == 5 && a[0] == "setup") return setup(a[1], std::atoi(a[2].c_str()), a[3], std::atoll(a[4].c_str()));
+  if (a.size() == 4 && a[0] == "room") return room(a[1], std::atoi(a[2].c_str()), std::atoll(a[3].c_str()));
+  if (a.size() > 3 && a[0] == "fail")
+    return fail(a[1], std::atoi(a[2].c_str()), std::vector<std::string>(a.begin() + 3, a.end()));
   std::fprintf(stderr, "unknown scenario\n");
   return 2;
 }
