@@ -408,9 +408,12 @@ dcg_status dcg_poll(dcg_server s, uint64_t ticket, dcg_stats* st);
 
 /* Device bytes a server group of ``mesh`` occupies in precision ``prec``:
  * its mesh context plus the workspace of 16 request slots (the quantity the
- * admission test charges against hbm_budget_bytes); -1 for a bad mesh.  A
- * server whose budget is at least 2 GiB also keeps the matrix of the coarse
- * cycles of the 32 x 32 level, 128 MiB, per group of n >= 64 and charges it. */
+ * admission test charges against hbm_budget_bytes); -1 for a bad mesh.  With a
+ * budget of at least 2 GiB a group of n >= 64 also keeps the matrix of the coarse
+ * cycles of the 32 x 32 level, 128 MiB, while the budget has room for it beside
+ * every admitted group: a group gives it back, after its step, when another needs the
+ * room (no request waits for longer or is refused because of it), and without it runs
+ * the steps of those cycles (the same map to rounding). */
 int64_t dcg_server_group_bytes(const dcg_mesh* mesh, dcg_precision prec);
 
 /* Steps run so far and the occupied request slots summed over them

@@ -105,6 +105,7 @@ struct MeshContext {
 // inverses of level 2) cannot be had.  The calling thread's device is the mesh's.
 inline bool fold_applies(int J, int post) { return J >= 3 && post >= 1; }
 std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post);
+void release_fold(MeshContext& m);   // frees the matrix kept with the context if nobody else holds it
 
 // Exact coarsest-level solve of a shortened hierarchy (coarsest level larger
 // than the stored 16 x 16 one) by fast diagonalisation: the axis factors of

@@ -122,11 +122,15 @@ struct Group {
   bool inflight = false;
   bool any_cycle = false;
   Clock::time_point last_used;
+  void discard_graph() {
+    if (graph) (void)hipGraphExecDestroy(graph);
+    graph = nullptr;
+  }
   ~Group();
 };
 
 Group::~Group() {
-  if (graph) (void)hipGraphExecDestroy(graph);
+  discard_graph();
   if (done) (void)hipEventDestroy(done);
   if (stream) (void)hipStreamDestroy(stream);
   if (capture) (void)hipStreamDestroy(capture);
@@ -165,10 +169,16 @@ size_t context_bytes(int n, bool fp32) {
   return b + size_t(kCoarseDofs) * kCoarseDofs * sizeof(double);
 }
 
-// A group takes the fold matrix when the budget holds 16 of them: a smaller
-// budget keeps the memory (and so the admissions) of the stepwise cycle.
-size_t group_fold_bytes(int n, int post, size_t budget) {
-  return fold_applies(num_levels(n), post) && kFoldBytes <= budget / 16 ? kFoldBytes : 0;
+// What the fold matrix adds to a group, 0 where none is used: the matrix and, in
+// the mixed form, the FP64 inverses of the context's level 2 that it is made with.
+// It is optional, so it counts for nothing at admission: a group takes it only where
+// the budget has room for it, and gives it back when another group needs the room
+// (make_room).  Budgets below 16 matrices do without: there the memory of one holds
+// several small groups (about 0.1 GB each at n = 64).
+size_t group_fold_bytes(int n, int post, bool fp32, size_t budget) {
+  if (!fold_applies(num_levels(n), post) || kFoldBytes > budget / 16) return 0;
+  constexpr size_t kInv = 9 * (36 + 64) * 256 + size_t(kFoldN) * kFoldN;
+  return kFoldBytes + (fp32 ? kInv * sizeof(double) : 0);
 }
 
 }  // namespace
@@ -194,6 +204,8 @@ struct Server::Impl {
   void step_all();
   void admit();
   bool make_room(size_t need);
+  void take_fold(Group& g);
+  void drop_fold(Group& g);
   size_t used_bytes() const;
   Group* create_group(const GroupKey& key);
   void assign(Group& g, int i, Request* r);
@@ -231,9 +243,22 @@ size_t Server::Impl::used_bytes() const {
   return b;
 }
 
-// Frees idle groups (oldest first) until ``need`` more bytes fit the budget.
+// Makes ``need`` more bytes fit the budget: matrices are given back where that is
+// enough (idle groups' first; a group in flight gives its own back after the step),
+// else idle groups are freed, oldest first.
 bool Server::Impl::make_room(size_t need) {
   while (used_bytes() + need > budget) {
+    size_t folds = 0;
+    for (const auto& kv : groups)
+      if (kv.second->fold) folds += kFoldBytes;
+    if (used_bytes() - folds + need <= budget) {
+      for (const bool idle : {true, false})
+        for (auto& kv : groups)
+          if (kv.second->fold && !kv.second->inflight && (kv.second->active == 0) == idle &&
+              used_bytes() + need > budget)
+            drop_fold(*kv.second);
+      return used_bytes() + need <= budget;
+    }
     auto victim = groups.end();
     for (auto it = groups.begin(); it != groups.end(); ++it)
       if (it->second->active == 0 && !it->second->inflight &&
@@ -246,6 +271,20 @@ bool Server::Impl::make_room(size_t need) {
     release_context_if_unused(n, pen);
   }
   return true;
+}
+
+// The matrix for a group that is not in flight, where the budget has room for it.
+void Server::Impl::take_fold(Group& g) {
+  const size_t add = group_fold_bytes(g.key.n, g.key.post, fp32, budget);
+  if (g.fold || !add || used_bytes() + add > budget) return;
+  g.fold = get_fold(*g.mesh, g.key.pre, g.key.post);
+  if (g.fold) g.discard_graph();   // captured for the steps
+}
+
+void Server::Impl::drop_fold(Group& g) {
+  g.discard_graph();
+  g.fold.reset();
+  release_fold(*g.mesh);
 }
 
 Group* Server::Impl::create_group(const GroupKey& key) {
@@ -279,7 +318,6 @@ Group* Server::Impl::create_group(const GroupKey& key) {
   DCG_HIP(hipHostMalloc(reinterpret_cast<void**>(&g->lists_host),
                         sizeof(int32_t) * kNumLists * kBatch, hipHostMallocDefault));
   ws.lvb.allocate(m, fp32, true, ws);
-  if (group_fold_bytes(key.n, key.post, budget)) g->fold = get_fold(*g->mesh, key.pre, key.post);
   DCG_HIP(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking));
   DCG_HIP(hipStreamCreateWithFlags(&g->capture, hipStreamNonBlocking));
   DCG_HIP(hipEventCreateWithFlags(&g->done, hipEventDisableTiming));
@@ -332,8 +370,7 @@ void Server::Impl::admit() {
       bool have_ctx = false;
       for (const auto& kv : groups)
         if (kv.first.n == key.n && kv.first.penalty == key.penalty) have_ctx = true;
-      const size_t need = workspace_bytes(key.n, fp32) + (have_ctx ? 0 : context_bytes(key.n, fp32)) +
-                          group_fold_bytes(key.n, key.post, budget);
+      const size_t need = workspace_bytes(key.n, fp32) + (have_ctx ? 0 : context_bytes(key.n, fp32));
       if (need > budget) {
         failed.emplace_back(r, Error(DCG_ENOMEM, "request needs " + std::to_string(need) +
                                                      " bytes of HBM, the budget is " +
@@ -357,6 +394,7 @@ void Server::Impl::admit() {
       }
     if (free_slot < 0) continue;
     try {
+      if (g->active == 0 && !g->inflight) take_fold(*g);
       assign(*g, free_slot, r);
       placed.push_back(r);
     } catch (const Error& e) {
@@ -788,7 +826,9 @@ void Server::prepare(const dcg_mesh& mesh) {
   DCG_HIP(hipSetDevice(impl->device));
   try {
     const auto m = get_context(mesh.n, mesh.penalty, impl->fp32);
-    if (group_fold_bytes(mesh.n, mesh.post, impl->budget)) (void)get_fold(*m, mesh.pre, mesh.post);
+    const size_t add = group_fold_bytes(mesh.n, mesh.post, impl->fp32, impl->budget);
+    if (add && size_t(group_bytes(mesh.n, impl->fp32)) + add <= impl->budget)
+      (void)get_fold(*m, mesh.pre, mesh.post);
   } catch (...) {
     (void)hipSetDevice(cur);
     throw;

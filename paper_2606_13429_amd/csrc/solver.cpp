@@ -150,6 +150,11 @@ std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
   return F;
 }
 
+void release_fold(MeshContext& m) {
+  std::lock_guard<std::mutex> lk(m.fold_mu);
+  if (m.last_fold && m.last_fold.use_count() == 1) m.last_fold.reset();
+}
+
 }  // namespace dcg
 
 dcg_ctx::~dcg_ctx() {

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/dcg.h"
+#include "../../paper_2606_13429_amd/csrc/kernels.hpp"
 #include "fake_hip.hpp"
 
 namespace {
@@ -106,6 +107,106 @@ int fail(const std::string& what, int n, const std::vector<std::string>& calls) 
   return 0;
 }
 
+// ---- the server
+struct Server {
+  dcg_server s = nullptr;
+  dcg_options opt{};
+  std::vector<std::vector<double>> b, x;
+  Server(int64_t budget, bool fp32) {
+    dcg_defaults(nullptr, &opt);
+    opt.prec = fp32 ? DCG_MIXED : DCG_FP64;
+    opt.hbm_budget_bytes = budget;
+    opt.max_inner = 1 << 30;   // a request whose residual never falls stays in its first inner solve
+    dcg_server_create(&opt, &s);
+  }
+  ~Server() {
+    dcg_server_destroy(s);
+    dcg_clear_cache();
+  }
+  uint64_t submit(int n) {
+    uint64_t t = 0;
+    const dcg_mesh m = mesh(n);
+    b.emplace_back(size_t(16) * n * n);
+    x.emplace_back(size_t(16) * n * n);
+    if (dcg_submit(s, &m, 1e-3, 1.0, b.back().data(), x.back().data(), 1e-8, &t) != DCG_OK) std::abort();
+    return t;
+  }
+  dcg_status wait(uint64_t t) {
+    for (int i = 0; i < 60000; ++i) {
+      const dcg_status st = dcg_poll(s, t, nullptr);
+      if (st != DCG_PENDING) return st;
+      std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    }
+    return DCG_PENDING;
+  }
+  static dcg_mesh mesh(int n) {
+    dcg_mesh m{};
+    dcg_defaults(&m, nullptr);
+    m.n = n;
+    return m;
+  }
+};
+
+int64_t group_bytes(int n, bool fp32) {
+  const dcg_mesh m = Server::mesh(n);
+  return dcg_server_group_bytes(&m, fp32 ? DCG_MIXED : DCG_FP64);
+}
+
+// The scalars the scheduler reads from a device that is busy: residuals that never fall.
+void keep_busy(void* dst, size_t bytes) {
+  if (bytes != sizeof(dcg::Scalars) * dcg::kBatch) return;
+  for (int i = 0; i < dcg::kBatch; ++i) {
+    dcg::Scalars& s = static_cast<dcg::Scalars*>(dst)[i];
+    s.b2 = s.rho = s.s2 = s.r2 = 1.0;
+  }
+  std::this_thread::sleep_for(std::chrono::microseconds(50));
+}
+
+bool eventually(const std::function<bool()>& f) {
+  for (int i = 0; i < 10000; ++i) {
+    if (f()) return true;
+    std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  }
+  return false;
+}
+
+// budget N FP32 BYTES: one request on a server of that budget (0: what
+// dcg_server_group_bytes says).
+int budget(int n, bool fp32, int64_t bytes) {
+  const int64_t group = group_bytes(n, fp32);
+  put("group", group);
+  {
+    Server s(bytes ? bytes : group, fp32);
+    put("status", s.wait(s.submit(n)));
+    put("matrices", fake::live_blocks(kMatrix));
+    put("products", fake::launched("k_fold_b"));
+  }
+  put_left_over();
+  return 0;
+}
+
+// shared BYTES: two long requests whose groups take the matrix, and a third whose
+// group has room beside theirs only without.
+int shared(int64_t bytes) {
+  {
+    Server s(bytes, false);
+    fake::state().on_read = keep_busy;
+    const uint64_t a = s.submit(64), c = s.submit(128);
+    put("taken", eventually([] { return fake::live_blocks(kMatrix) == 2; }));
+    const uint64_t d = s.submit(256);
+    const int64_t groups = group_bytes(64, false) + group_bytes(128, false) + group_bytes(256, false);
+    put("admitted", eventually([&] { return fake::live_bytes() >= groups; }));
+    put("running", (dcg_poll(s.s, a, nullptr) == DCG_PENDING) + (dcg_poll(s.s, c, nullptr) == DCG_PENDING));
+    put("over_budget", fake::live_bytes() - bytes);
+    fake::state().on_read = nullptr;
+    put("status_64", s.wait(a));
+    put("status_128", s.wait(c));
+    put("status_256", s.wait(d));
+  }
+  put_left_over();
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -113,6 +214,9 @@ int main(int argc, char** argv) {
   if (a.size() == 4 && a[0] == "room") return room(a[1], std::atoi(a[2].c_str()), std::atoll(a[3].c_str()));
   if (a.size() > 3 && a[0] == "fail")
     return fail(a[1], std::atoi(a[2].c_str()), std::vector<std::string>(a.begin() + 3, a.end()));
+  if (a.size() == 4 && a[0] == "budget")
+    return budget(std::atoi(a[1].c_str()), a[2] == "1", std::atoll(a[3].c_str()));
+  if (a.size() == 2 && a[0] == "shared") return shared(std::atoll(a[1].c_str()));
   std::fprintf(stderr, "unknown scenario\n");
   return 2;
 }

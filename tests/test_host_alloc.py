@@ -65,3 +65,35 @@ def test_a_failed_setup_gives_everything_back(program, what, n, calls):
     r = program("fail", what, n, *calls)
     assert r["refused"] == r["again_ok"] == r["again_equal"] == len(calls)
     _clean(r)
+
+
+GIB = 1 << 30
+
+
+@pytest.mark.parametrize("n,fp32,budget,products", [
+    (64, 0, 0, 0),               # what dcg_server_group_bytes says
+    (64, 1, 0, 0),
+    (64, 1, 2 * GIB - 1, 0),     # below 16 matrices
+    (64, 0, 2 * GIB, 1),
+    (64, 1, 2 * GIB, 1),
+    (32, 0, 2 * GIB, 0),         # two levels
+    (512, 1, 0, 0),              # a group above 2 GiB that fits without the matrix only
+])
+def test_server_admits_what_group_bytes_says(program, n, fp32, budget, products):
+    """The matrix is no part of what a group needs: a budget of dcg_server_group_bytes
+    holds the group at every size, and with room for it the cycles use it."""
+    r = program("budget", n, fp32, budget)
+    assert r["status"] == OK
+    assert r["products"] == products
+    assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
+
+
+def test_matrices_make_room_for_a_group(program):
+    """A third group that fits beside two running ones without their matrices is
+    admitted while they run."""
+    r = program("shared", 2 * GIB)
+    assert r["taken"] == 1
+    assert r["admitted"] == 1 and r["running"] == 2
+    assert r["over_budget"] <= 0
+    assert r["status_64"] == r["status_128"] == r["status_256"] == OK
+    assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
