@@ -267,6 +267,7 @@ bool Server::Impl::make_room(size_t need) {
     if (victim == groups.end()) return false;
     const int n = victim->first.n;
     const double pen = victim->first.penalty;
+    drop_fold(*victim->second);   // the context may have other holders
     groups.erase(victim);
     release_context_if_unused(n, pen);
   }
@@ -276,9 +277,12 @@ bool Server::Impl::make_room(size_t need) {
 // The matrix for a group that is not in flight, where the budget has room for it.
 void Server::Impl::take_fold(Group& g) {
   const size_t add = group_fold_bytes(g.key.n, g.key.post, fp32, budget);
-  if (g.fold || !add || used_bytes() + add > budget) return;
-  g.fold = get_fold(*g.mesh, g.key.pre, g.key.post);
-  if (g.fold) g.discard_graph();   // captured for the steps
+  if (g.fold) return;
+  if (add && used_bytes() + add <= budget) g.fold = get_fold(*g.mesh, g.key.pre, g.key.post);
+  if (g.fold)
+    g.discard_graph();        // captured for the steps
+  else
+    release_fold(*g.mesh);    // one that prepare() or an earlier group left would not be charged
 }
 
 void Server::Impl::drop_fold(Group& g) {

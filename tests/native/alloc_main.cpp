@@ -123,9 +123,10 @@ struct Server {
     dcg_server_destroy(s);
     dcg_clear_cache();
   }
-  uint64_t submit(int n) {
+  uint64_t submit(int n, int pre = 2) {
     uint64_t t = 0;
-    const dcg_mesh m = mesh(n);
+    dcg_mesh m = mesh(n);
+    m.pre = pre;
     b.emplace_back(size_t(16) * n * n);
     x.emplace_back(size_t(16) * n * n);
     if (dcg_submit(s, &m, 1e-3, 1.0, b.back().data(), x.back().data(), 1e-8, &t) != DCG_OK) std::abort();
@@ -207,6 +208,49 @@ int shared(int64_t bytes) {
   return 0;
 }
 
+// evicted BYTES: the group of a mesh that a handle holds too is freed for another.
+// The seven vectors of a group of n = 256 are as large as a matrix.
+int evicted(int64_t bytes) {
+  {
+    Server s(bytes, false);
+    dcg_options o{};
+    const dcg_mesh m = Server::mesh(64);
+    dcg_defaults(nullptr, &o);
+    o.prec = DCG_FP64;
+    o.levels = 1;
+    dcg_handle h = nullptr;
+    put("handle", dcg_setup(&m, 1e-3, 1.0, &o, &h));
+    put("status", s.wait(s.submit(64)));
+    put("with_64", fake::live_blocks(kMatrix));
+    put("status_256", s.wait(s.submit(256)));
+    put("with_256", fake::live_blocks(kMatrix));
+    put("status_again", s.wait(s.submit(256, 3)));
+    put("after", fake::live_blocks(kMatrix));
+    dcg_destroy(h);
+  }
+  put_left_over();
+  return 0;
+}
+
+// prepared BYTES: a mesh prepared on a server that has no room for its matrix any
+// more when the group comes.
+int prepared(int64_t bytes) {
+  {
+    Server s(bytes, false);
+    const dcg_mesh m = Server::mesh(64);
+    put("status_256", s.wait(s.submit(256)));
+    put("status_128", s.wait(s.submit(128)));
+    put("before", fake::live_blocks(kMatrix));
+    put("prepare", dcg_server_prepare(s.s, &m));
+    put("prepared", fake::live_blocks(kMatrix));
+    put("status", s.wait(s.submit(64)));
+    put("after", fake::live_blocks(kMatrix));
+    put("over_budget", fake::live_bytes() - bytes);
+  }
+  put_left_over();
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -217,6 +261,8 @@ int main(int argc, char** argv) {
   if (a.size() == 4 && a[0] == "budget")
     return budget(std::atoi(a[1].c_str()), a[2] == "1", std::atoll(a[3].c_str()));
   if (a.size() == 2 && a[0] == "shared") return shared(std::atoll(a[1].c_str()));
+  if (a.size() == 2 && a[0] == "evicted") return evicted(std::atoll(a[1].c_str()));
+  if (a.size() == 2 && a[0] == "prepared") return prepared(std::atoll(a[1].c_str()));
   std::fprintf(stderr, "unknown scenario\n");
   return 2;
 }

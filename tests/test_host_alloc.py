@@ -97,3 +97,25 @@ def test_matrices_make_room_for_a_group(program):
     assert r["over_budget"] <= 0
     assert r["status_64"] == r["status_128"] == r["status_256"] == OK
     assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
+
+
+GROUP_256_VECTORS = 7            # as large as a matrix each
+
+
+def test_matrix_goes_with_the_group_that_was_charged_for_it(program):
+    """Freed with its group, also where a handle without a matrix holds the mesh."""
+    r = program("evicted", 2 * GIB)
+    assert r["handle"] == r["status"] == r["status_256"] == r["status_again"] == OK
+    assert r["with_64"] == 1 and r["with_256"] == 2 + GROUP_256_VECTORS
+    assert r["after"] == 1 + GROUP_256_VECTORS
+    assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
+
+
+def test_prepared_matrix_stays_within_the_budget(program):
+    """What prepare() made is freed when the group that comes has no room for it."""
+    r = program("prepared", 2 * GIB)
+    assert r["status_256"] == r["status_128"] == r["prepare"] == r["status"] == OK
+    assert r["before"] == 1 + GROUP_256_VECTORS and r["prepared"] == r["before"] + 1
+    assert r["after"] == GROUP_256_VECTORS
+    assert r["over_budget"] <= 0
+    assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
