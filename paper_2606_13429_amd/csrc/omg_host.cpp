@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <stdexcept>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -212,20 +213,26 @@ std::vector<double> coarsest_inverse(const std::vector<double>& op, int n) {
       }
     }
   cholesky(A, m);
-  // the columns are independent: one strided share per thread
-  std::vector<double> inv((size_t)m * m);
+  // the columns are independent: one strided share per thread; this one takes the
+  // shares that no thread could be started for
   const int nt = int(std::max(1u, std::min(8u, std::thread::hardware_concurrency())));
+  std::vector<double> inv((size_t)m * m), cols((size_t)nt * m);
+  auto share = [&](int t) {
+    double* col = &cols[(size_t)t * m];
+    for (int j = t; j < m; j += nt) {
+      std::fill(col, col + m, 0.0);
+      col[j] = 1.0;
+      cho_solve(A, m, col);
+      for (int i = 0; i < m; ++i) inv[(size_t)i * m + j] = col[i];
+    }
+  };
   std::vector<std::thread> th;
-  for (int t = 0; t < nt; ++t)
-    th.emplace_back([&, t] {
-      std::vector<double> col(m);
-      for (int j = t; j < m; j += nt) {
-        std::fill(col.begin(), col.end(), 0.0);
-        col[j] = 1.0;
-        cho_solve(A, m, col.data());
-        for (int i = 0; i < m; ++i) inv[(size_t)i * m + j] = col[i];
-      }
-    });
+  th.reserve(nt);
+  try {
+    while (int(th.size()) < nt) th.emplace_back(share, int(th.size()));
+  } catch (const std::system_error&) {
+  }
+  for (int t = int(th.size()); t < nt; ++t) share(t);
   for (auto& x : th) x.join();
   return inv;
 }

@@ -1,5 +1,9 @@
 // Set-ups and server admissions on the host HIP runtime (fake_hip.cpp): one
 // scenario per run, results as "key value" lines.
+#include <dlfcn.h>
+#include <pthread.h>
+
+#include <cerrno>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -11,6 +15,16 @@
 #include "../../include/dcg.h"
 #include "../../paper_2606_13429_amd/csrc/kernels.hpp"
 #include "fake_hip.hpp"
+
+namespace {
+std::atomic<int> g_threads{1 << 30};   // threads that can still be started
+}
+
+// in the place of the C library's, for the whole process
+extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*f)(void*), void* arg) {
+  static auto real = reinterpret_cast<decltype(&pthread_create)>(dlsym(RTLD_NEXT, "pthread_create"));
+  return g_threads-- > 0 ? real(t, a, f, arg) : EAGAIN;
+}
 
 namespace {
 
@@ -251,6 +265,17 @@ int prepared(int64_t bytes) {
   return 0;
 }
 
+// threads STARTED: the outer multigrid's tables where only that many threads can be
+// started.
+int threads(int started) {
+  std::vector<double> want(1024 * 1024), got(want.size());
+  put("clean_status", dcg_host_outer_mg(16, 10.0, 1e-3, 1.0, 1, 2, want.data(), int64_t(want.size())));
+  g_threads = started;
+  put("status", dcg_host_outer_mg(16, 10.0, 1e-3, 1.0, 1, 2, got.data(), int64_t(got.size())));
+  put("equal", std::memcmp(want.data(), got.data(), got.size() * sizeof(double)) == 0);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -263,6 +288,7 @@ int main(int argc, char** argv) {
   if (a.size() == 2 && a[0] == "shared") return shared(std::atoll(a[1].c_str()));
   if (a.size() == 2 && a[0] == "evicted") return evicted(std::atoll(a[1].c_str()));
   if (a.size() == 2 && a[0] == "prepared") return prepared(std::atoll(a[1].c_str()));
+  if (a.size() == 2 && a[0] == "threads") return threads(std::atoi(a[1].c_str()));
   std::fprintf(stderr, "unknown scenario\n");
   return 2;
 }

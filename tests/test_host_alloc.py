@@ -28,7 +28,7 @@ def program(tmp_path_factory):
     subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     os.path.join(NATIVE, "fake_hip.cpp"), os.path.join(NATIVE, "alloc_main.cpp"), "-o", exe,
                     "-rdynamic", "-Wl,--unresolved-symbols=ignore-in-shared-libs", lib, "-Wl,-rpath," + PKG,
-                    "-lpthread"], check=True)
+                    "-lpthread", "-ldl"], check=True)
 
     def run(*args):
         out = subprocess.run([exe] + [str(a) for a in args], check=True, capture_output=True, text=True,
@@ -119,3 +119,9 @@ def test_prepared_matrix_stays_within_the_budget(program):
     assert r["after"] == GROUP_256_VECTORS
     assert r["over_budget"] <= 0
     assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
+
+
+@pytest.mark.parametrize("started", [0, 3])
+def test_set_up_where_threads_cannot_be_started(program, started):
+    r = program("threads", started)
+    assert r["clean_status"] == r["status"] == OK and r["equal"] == 1
