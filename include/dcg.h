@@ -26,7 +26,8 @@
  * Scalar (Laplace / multigrid) vectors: length 4 n_k^2, idx = 4 e + j.
  *
  * Pointers: every vector argument is a DEVICE pointer on the current HIP
- * device unless stated otherwise; host buffers are marked "host".  The caller
+ * device unless stated otherwise, aligned to its element type (4 or 8 bytes);
+ * host buffers are marked "host".  The caller
  * owns all vectors; the library owns every matrix, hierarchy, workspace and
  * scratch buffer and frees them in dcg_destroy / dcg_server_destroy.  The
  * library never frees caller memory.  A stream argument is a hipStream_t

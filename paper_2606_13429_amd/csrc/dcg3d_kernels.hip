@@ -11,9 +11,12 @@
 #include <cmath>
 
 #include "dcg3d.hpp"
+#include "mg_common.hpp"
 
 namespace dcg3 {
 namespace {
+
+using dcg::mg::double2_any;   // in the caller's vectors
 
 constexpr int kThreads = 256;
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
     const int nb = live ? nbr3(n, e, sl) : -1;
-    const double2* p = reinterpret_cast<const double2*>(x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q);
+    const double2_any* p = reinterpret_cast<const double2_any*>(x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q);
 #pragma unroll
     for (int t = 0; t < 3; ++t) {   // unconditional loads (of element 0 outside the domain)
       v[sl][t] = p[4 * t];
@@ -116,8 +119,8 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
   // sigma_{k1 k1} + sigma_{k2 k2} of the other two rows, for the mass term
   const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
   const double* xe = x + (int64_t)(live ? e : 0) * kDof + 2 * q;
-  const double2 o1 = *reinterpret_cast<const double2*>(xe + 32 * k1);
-  const double2 o2 = *reinterpret_cast<const double2*>(xe + 32 * k2);
+  const double2 o1 = *reinterpret_cast<const double2_any*>(xe + 32 * k1);
+  const double2 o2 = *reinterpret_cast<const double2_any*>(xe + 32 * k2);
   constexpr int TT = G * 192, NS = (kFixedTiles * 32 + TT - 1) / TT;
   double2 tv[NS];
 #pragma unroll
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
 #pragma unroll
   for (int i = 0; i < 2; ++i) r1[i] = inv_nu * m1[i] + dt * a1[i];
   if (live) {   // rows 4 q .. 4 q + 3 and 16 + 2 q, 16 + 2 q + 1
-    double2* yp = reinterpret_cast<double2*>(y + (int64_t)e * kDof + 24 * k);
+    double2_any* yp = reinterpret_cast<double2_any*>(y + (int64_t)e * kDof + 24 * k);
     yp[2 * q] = make_double2(r0[0], r0[1]);
     yp[2 * q + 1] = make_double2(r0[2], r0[3]);
     yp[8 + q] = make_double2(r1[0], r1[1]);
@@ -224,12 +227,12 @@ __global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict_
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
     const int nb = live ? nbr3(n, e, sl) : -1;
-    const double2 yv = *reinterpret_cast<const double2*>(yh + (int64_t)(nb >= 0 ? nb : 0) * kNb + 2 * q);
+    const double2 yv = *reinterpret_cast<const double2_any*>(yh + (int64_t)(nb >= 0 ? nb : 0) * kNb + 2 * q);
     v[sl].x = nb >= 0 ? yv.x * inv_sqrt3 : 0.0;
     v[sl].y = nb >= 0 ? yv.y * inv_sqrt3 : 0.0;
   }
   double2 wv[3];
-  const double2* wp = reinterpret_cast<const double2*>(w + (int64_t)(live ? e : 0) * kDof + 24 * k);
+  const double2_any* wp = reinterpret_cast<const double2_any*>(w + (int64_t)(live ? e : 0) * kDof + 24 * k);
   wv[0] = wp[2 * q];
   wv[1] = wp[2 * q + 1];
   wv[2] = wp[8 + q];
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict_
     pending &= ~__ballot(mine);
   }
   if (!live) return;
-  double2* op = reinterpret_cast<double2*>(qv + (int64_t)e * kDof + 24 * k);
+  double2_any* op = reinterpret_cast<double2_any*>(qv + (int64_t)e * kDof + 24 * k);
   op[2 * q] = make_double2(wv[0].x - dt * a0[0], wv[0].y - dt * a0[1]);
   op[2 * q + 1] = make_double2(wv[1].x - dt * a0[2], wv[1].y - dt * a0[3]);
   op[8 + q] = make_double2(wv[2].x - dt * a1[0], wv[2].y - dt * a1[1]);
@@ -565,7 +568,7 @@ __global__ __launch_bounds__(kFdmThreads) void k_fdm_plane(int n, const double* 
         b0[u] = b1[u] = 0.0;
         if (kk < N) {
           if (row < N)
-            a[u] = *reinterpret_cast<const double2*>(
+            a[u] = *reinterpret_cast<const double2_any*>(
                 in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
           if (c < N) {
             b0[u] = Bx[(int64_t)kk * N + c];

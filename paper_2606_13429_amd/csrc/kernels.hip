@@ -35,8 +35,8 @@ __device__ inline double block_sum(double v, double* lds) {
   return s;
 }
 
-using mg::ld4;   // 4-vector loads and stores shared with the multigrid kernels
-using mg::st4;
+using mg::ld4_any;   // 4-vector loads and stores: most vectors here can be a caller's
+using mg::st4_any;
 
 inline int grid_for(int64_t items, int per_block, int cap) {
   int64_t g = (items + per_block - 1) / per_block;
@@ -106,12 +106,12 @@ __global__ __launch_bounds__(kThreads) void k_astar(
   const int ex = e & (n - 1), ey = e / n;
   auto load = [&](int64_t i, bool ok, double (&u)[8]) {   // u of stress row i = 2 e + k
     if (ok) {
-      ld4(x + 8 * i, u);
-      ld4(x + 8 * i + 4, u + 4);
+      ld4_any(x + 8 * i, u);
+      ld4_any(x + 8 * i + 4, u + 4);
       if (MODE == kAstarDir) {
         double p[8];
-        ld4(p_old + 8 * i, p);
-        ld4(p_old + 8 * i + 4, p + 4);
+        ld4_any(p_old + 8 * i, p);
+        ld4_any(p_old + 8 * i + 4, p + 4);
 #pragma unroll
         for (int m = 0; m < 8; ++m) u[m] += beta * p[m];
       }
@@ -174,8 +174,8 @@ __global__ __launch_bounds__(kThreads) void k_astar(
   double dot = 0.0;
   if (MODE == kAstarResidual && valid) {
     double bv[8];
-    ld4(b + 8 * (int64_t)id, bv);
-    ld4(b + 8 * (int64_t)id + 4, bv + 4);
+    ld4_any(b + 8 * (int64_t)id, bv);
+    ld4_any(b + 8 * (int64_t)id + 4, bv + 4);
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       wv[r] = bv[r] - wv[r];
@@ -184,19 +184,19 @@ __global__ __launch_bounds__(kThreads) void k_astar(
   }
   if (valid) {
     if (w) {
-      st4(w + 8 * (int64_t)id, wv);
-      st4(w + 8 * (int64_t)id + 4, wv + 4);
+      st4_any(w + 8 * (int64_t)id, wv);
+      st4_any(w + 8 * (int64_t)id + 4, wv + 4);
     }
     if (MODE == kAstarDir || MODE == kAstarFirst) {
-      st4(p_new + 8 * (int64_t)id, u0);
-      st4(p_new + 8 * (int64_t)id + 4, u0 + 4);
+      st4_any(p_new + 8 * (int64_t)id, u0);
+      st4_any(p_new + 8 * (int64_t)id + 4, u0 + 4);
     }
   }
   if (s) {   // s = Z^T w: w11 of the even lane, w22 of the odd one
     double sv[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) sv[j] = (wv[j] + pair_swap(wv[4 + j])) * kInvSqrt2;
-    if (valid && !k) st4(s + 4 * (int64_t)e, sv);
+    if (valid && !k) st4_any(s + 4 * (int64_t)e, sv);
   }
   if (MODE == kAstarResidual) {
     const double t = block_sum(dot, lds);
@@ -216,7 +216,7 @@ __device__ __forceinline__ double az_row(const double* az, int r, int e, int n,
     const bool in = sn == 0 || (sn == 1 ? ex > 0 : (sn == 2 ? ex < n - 1 : (sn == 3 ? ey > 0 : ey < n - 1)));
 #pragma unroll
     for (int m = 0; m < 4; ++m) zc[sn][m] = 0.0;
-    if (in) ld4(z + 4 * ((int64_t)e + off), zc[sn]);
+    if (in) ld4_any(z + 4 * ((int64_t)e + off), zc[sn]);
   }
   double acc = 0.0;
 #pragma unroll
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(kThreads) void k_bdf2_rhs(int ne, const double* __r
   for (int k = 0; k < 16; ++k)
     u[k] = 4.0 / 3.0 * s1[16 * e + k] - 1.0 / 3.0 * s2[16 * e + k];
   double m[4];
-  ld4(Ct + kCtMass + 4 * j, m);
+  ld4_any(Ct + kCtMass + 4 * j, m);
   double mu;
   if (cc == 0 || cc == 3) {
     mu = 0.5 * (m[0] * (u[0] - u[12]) + m[1] * (u[1] - u[13]) + m[2] * (u[2] - u[14]) +
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(64) void k_refine_residual(
     const int e = (g << 6) + threadIdx.x;
     if (e >= ne) continue;
     double r[4];
-    ld4(s + 4 * (int64_t)e, r);
+    ld4_any(s + 4 * (int64_t)e, r);
     if (!FIRST) {                // blocks of the square's class, neighbours from (ex, ey)
       const int ex = e % n, ey = e / n;
       double zq[5][4], acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -600,14 +600,14 @@ __global__ __launch_bounds__(64) void k_refine_residual(
         const int dx = sn == 1 ? -1 : (sn == 2 ? 1 : 0), dy = sn == 3 ? -1 : (sn == 4 ? 1 : 0);
         zq[sn][0] = zq[sn][1] = zq[sn][2] = zq[sn][3] = 0.0;
         if (ex + dx >= 0 && ex + dx < n && ey + dy >= 0 && ey + dy < n)
-          ld4(z + 4 * ((int64_t)e + dx + (int64_t)dy * n), zq[sn]);
+          ld4_any(z + 4 * ((int64_t)e + dx + (int64_t)dy * n), zq[sn]);
       }
       mg::class_rows(Lc, square_class(ex, ey, n), zq, acc);
 #pragma unroll
       for (int a = 0; a < 4; ++a) r[a] -= acc[a];
     }
     const T o[4] = {static_cast<T>(r[0]), static_cast<T>(r[1]), static_cast<T>(r[2]), static_cast<T>(r[3])};
-    st4(fJ + e * sl.lsq, o);
+    st4_any(fJ + e * sl.lsq, o);
     nrm += (r[0] * r[0] + r[1] * r[1]) + (r[2] * r[2] + r[3] * r[3]);
   }
   for (int o = 32; o > 0; o >>= 1) nrm += __shfl_xor(nrm, o);
@@ -630,8 +630,8 @@ __global__ __launch_bounds__(kThreads) void k_lap(const T* __restrict__ L,
     const int col = cols[slot * ne + e];
     if (col < 0) continue;
     T l[4], zc[4];
-    ld4(L + (((int64_t)slot * ne + e) * 4 + a) * 4, l);
-    ld4(z + 4 * (int64_t)col, zc);
+    ld4_any(L + (((int64_t)slot * ne + e) * 4 + a) * 4, l);
+    ld4_any(z + 4 * (int64_t)col, zc);
     acc += l[0] * zc[0] + l[1] * zc[1] + l[2] * zc[2] + l[3] * zc[3];
   }
   const int64_t i = 4 * (int64_t)e + a;
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kThreads) void k_restrict(int nc, const T* __restri
   for (int ch = 0; ch < 4; ++ch) {
     const int64_t e = (int64_t)(2 * EY + (ch >> 1)) * nf + 2 * EX + (ch & 1);
     T v[4];
-    ld4(r + 4 * e, v);
+    ld4_any(r + 4 * e, v);
 #pragma unroll
     for (int a = 0; a < 4; ++a) acc += pcoef<T>(ch, a, A) * v[a];
   }
@@ -684,7 +684,7 @@ __global__ __launch_bounds__(kThreads) void k_prolong(int nc, const T* __restric
   const int ch = (ex & 1) + 2 * (ey & 1);
   const int64_t E = (int64_t)(ey >> 1) * nc + (ex >> 1);
   T v[4];
-  ld4(ec + 4 * E, v);
+  ld4_any(ec + 4 * E, v);
   T acc = T(0);
 #pragma unroll
   for (int A = 0; A < 4; ++A) acc += pcoef<T>(ch, a, A) * v[A];

@@ -11,11 +11,14 @@
 #include <hip/hip_runtime.h>
 
 #include "host_setup.hpp"
+#include "mg_common.hpp"
 #include "omg.hpp"
 
 namespace dcg {
 
 namespace {
+
+using mg::double2_any;   // in the caller's vectors
 
 constexpr int D = kOmgDofs;
 constexpr int kThreads = 256;
@@ -485,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void k_omg_dense(int m, const double* __r
   const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (i >= m) return;   // whole wavefronts
   const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
-  const double2* f2 = reinterpret_cast<const double2*>(f);
+  const double2_any* f2 = reinterpret_cast<const double2_any*>(f);
   double acc = 0.0;
 #pragma unroll 8
   for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
