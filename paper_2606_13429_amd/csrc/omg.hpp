@@ -116,12 +116,12 @@ hipError_t launch_omg_prolong(int nf, const double* zc, double* z, bool assign, 
 // z = A f (dense m x m, row-major, m even).
 hipError_t launch_omg_dense(int m, const double* A, const double* f, double* z, hipStream_t st);
 
-// ---- dense forms of a small level (set-up; nk <= kOmgSplitMaxN)
-// L = the level operator, S = the RAS update, m x m row-major, m = 16 nk^2.
-hipError_t launch_omg_dense_tables(const OmgLevelDev& L, double* A, double* S, hipStream_t st);
+// ---- the matrix of a small level (set-up; nk <= kOmgSplitMaxN, m = 16 nk^2 a multiple
+// of 256, matrices m x m row-major)
+// R = I - A* Z (Z = NULL: R = I); Z = (zero ? 0 : Z) + S R.
+hipError_t launch_omg_res_cols(const OmgLevelDev& L, const double* Z, double* R, hipStream_t st);
+hipError_t launch_omg_ras_cols(const OmgLevelDev& L, const double* R, double* Z, bool zero, hipStream_t st);
 // K = P C P^T of level nk, C dense on the next coarser one.
 hipError_t launch_omg_dense_coarse(int nk, const double* C, double* K, hipStream_t st);
-// A += c B (m x m; B = NULL: c times the identity).
-hipError_t launch_omg_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st);
 
 }  // namespace dcg

@@ -4,7 +4,10 @@
 // operators for dcg_apply.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstring>
+#include <random>
 #include <vector>
 
 #include "kernels.hpp"
@@ -62,15 +65,63 @@ void cycle(const OuterMg& g, int k, int mode, hipStream_t st) {
   }
 }
 
+// True when the matrix C of level k does to the vectors it will meet -- restricted
+// residuals of the parent's pre-smoothed random vectors -- what the two cycles step
+// by step do, within twice the rounding of the steps themselves (their change when
+// the input is scaled by 3).  The steps damp their rounding through the residual, the
+// product cannot: where A* is ill-conditioned and its entries cancel it is the less
+// accurate one.  At n = 32 the ratio is 0.5 to 1.3 for dt <= 1e-2, 2 to 50 at dt = 1
+// (m = 6 .. 1) and some thousands at dt = 100.
+bool matrix_holds(const OuterMg& g, int k, const double* C) {
+  const int i = k - 1, m = int(level_len(g, k)), mp = int(level_len(g, k + 1));
+  const hipStream_t st = nullptr;
+  std::mt19937_64 rng(1);
+  std::uniform_real_distribution<double> uniform(-1.0, 1.0);
+  std::vector<double> f(mp), a(m), b(m), c(m);
+  auto steps = [&](std::vector<double>& out) {
+    cycle(g, k, kZero, st);
+    cycle(g, k, kWarm, st);
+    DCG_HIP(hipMemcpy(out.data(), g.z[i], m * sizeof(double), hipMemcpyDeviceToHost));
+  };
+  double dist2 = 0.0, round2 = 0.0;
+  for (int probe = 0; probe < 8; ++probe) {
+    for (double& x : f) x = uniform(rng);
+    DCG_HIP(hipMemcpy(g.f[i + 1], f.data(), mp * sizeof(double), hipMemcpyHostToDevice));
+    for (int s = 0; s < g.m; ++s) {
+      if (s > 0) DCG_HIP(launch_omg_res(g.lev[i + 1], g.f[i + 1], g.z[i + 1], g.r[i + 1], st));
+      DCG_HIP(launch_omg_ras(g.lev[i + 1], s > 0 ? g.r[i + 1] : g.f[i + 1], g.z[i + 1], s == 0, st));
+    }
+    DCG_HIP(launch_omg_res(g.lev[i + 1], g.f[i + 1], g.z[i + 1], g.r[i + 1], st));
+    DCG_HIP(launch_omg_restrict(g.n[i + 1], g.r[i + 1], g.f[i], st));
+    DCG_HIP(launch_omg_dense(m, C, g.f[i], g.r[i], st));
+    DCG_HIP(hipMemcpy(c.data(), g.r[i], m * sizeof(double), hipMemcpyDeviceToHost));
+    steps(a);
+    DCG_HIP(launch_scale(m, 3.0, g.f[i], g.r[i], st));
+    copy(g.r[i], g.f[i], m, st);
+    steps(b);
+    double top = 0.0, dist = 0.0, round = 0.0;
+    for (int j = 0; j < m; ++j) {
+      if (!std::isfinite(a[j] + b[j] + c[j])) return false;
+      top = std::max(top, std::fabs(a[j]));
+      dist = std::max(dist, std::fabs(c[j] - a[j]));
+      round = std::max(round, std::fabs(b[j] / 3.0 - a[j]));
+    }
+    if (dist == 0.0) continue;
+    dist2 += (dist / top) * (dist / top);
+    round2 += (round / top) * (round / top);
+  }
+  return dist2 <= 4.0 * round2;
+}
+
 // The two coarse cycles that level k gives its parent (Algorithm 4: from zero,
 // then from the first's result) as one matrix, on levels of at most
-// kOmgFoldMaxDofs unknowns.  With E = I - S A* one cycle from zero is
-// W = E^m (P_m + P C P^T (I - A* P_m)) + P_m, P_m = sum_{i < m} E^i S, C the map
-// of the level below (the exact solve), and two are 2 W - W A* W.  The level of
-// 16 x 16 squares is 134 MB, read in about 21 us, against 2 (4 m + 3) + 2 launches
-// of 3-4 us; the next one would be 2.1 GB, slower than its steps.  The cycle runs
-// the steps of a level that has no matrix, so where the memory of the matrix or of
-// its scratch (805 MB during set-up) cannot be had there is none.
+// kOmgFoldMaxDofs unknowns: the cycles of the columns of the identity, step by step
+// (2 W - W A* W with one cycle W in powers of I - S A* was up to 10 times further
+// from the exact map at dt = 1).  The level of 16 x 16 squares is 134 MB, read in
+// about 21 us, against 2 (4 m + 3) + 2 launches of 3-4 us; the next one would be
+// 2.1 GB, slower than its steps.  The cycle runs the steps of a level that has no
+// matrix: where the memory of the matrix or of its scratch (403 MB during set-up)
+// cannot be had, or where the matrix is less accurate than they are (matrix_holds).
 void fold_level(OuterMg& g, int k, Workspace& ws) {
   const int i = k - 1;
   const int64_t m = level_len(g, k);
@@ -79,43 +130,31 @@ void fold_level(OuterMg& g, int k, Workspace& ws) {
     double* p = nullptr;
     ~Temp() { (void)hipFree(p); }
   } tmp;
-  tmp.p = static_cast<double*>(try_device_alloc(6 * m * m * sizeof(double)));
-  double* C = tmp.p ? static_cast<double*>(ws.try_alloc(m * m * sizeof(double))) : nullptr;
-  if (!C) return;
-  double *A = tmp.p, *S = A + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
+  tmp.p = static_cast<double*>(try_device_alloc(3 * m * m * sizeof(double)));
+  double* Z = tmp.p ? static_cast<double*>(ws.try_alloc(m * m * sizeof(double))) : nullptr;
+  if (!Z) return;
+  double *R = tmp.p, *K = R + m * m, *T = K + m * m;
   const hipStream_t st = nullptr;
-  auto mul = [&](const double* X, const double* Y, double* out, double a, const double* add) {
-    DCG_HIP(launch_gemm(int(m), X, Y, out, a, add, st));
-  };
-  DCG_HIP(launch_omg_dense_tables(g.lev[i], A, S, st));
-  mul(S, A, E, -1.0, nullptr);
-  DCG_HIP(launch_omg_dense_add(m, 1.0, nullptr, E, st));
-  DCG_HIP(hipMemcpyAsync(Ei, E, m * m * sizeof(double), hipMemcpyDeviceToDevice, st));
-  DCG_HIP(hipMemcpyAsync(P, S, m * m * sizeof(double), hipMemcpyDeviceToDevice, st));
-  int top = 0;
-  while ((g.m >> (top + 1)) > 0) ++top;
-  for (int b = top - 1; b >= 0; --b) {   // (E^s, P_s) for the leading bits s of m
-    mul(Ei, P, T, 1.0, P);
-    std::swap(P, T);
-    mul(Ei, Ei, T, 1.0, nullptr);
-    std::swap(Ei, T);
-    if ((g.m >> b) & 1) {
-      mul(E, P, T, 1.0, S);
-      std::swap(P, T);
-      mul(E, Ei, T, 1.0, nullptr);
-      std::swap(Ei, T);
+  DCG_HIP(launch_omg_dense_coarse(g.n[i], k == 2 ? g.cinv : g.fold[i - 1], K, st));
+  bool zero = true;
+  auto smooth = [&]() {
+    for (int s = 0; s < g.m; ++s, zero = false) {
+      DCG_HIP(launch_omg_res_cols(g.lev[i], zero ? nullptr : Z, R, st));
+      DCG_HIP(launch_omg_ras_cols(g.lev[i], R, Z, zero, st));
     }
+  };
+  for (int c = 0; c < 2; ++c) {        // two swaps: Z ends where it began
+    smooth();
+    DCG_HIP(launch_omg_res_cols(g.lev[i], Z, R, st));
+    DCG_HIP(launch_gemm(int(m), K, R, T, 1.0, Z, st));   // Z + P C P^T R
+    std::swap(Z, T);
+    smooth();
   }
-  mul(A, P, T, -1.0, nullptr);           // I - A* P_m
-  DCG_HIP(launch_omg_dense_add(m, 1.0, nullptr, T, st));
-  DCG_HIP(launch_omg_dense_coarse(g.n[i], k == 2 ? g.cinv : g.fold[i - 1], S, st));
-  mul(S, T, E, 1.0, P);
-  mul(Ei, E, T, 1.0, P);                 // W
-  mul(A, T, E, 1.0, nullptr);
-  mul(T, E, C, -1.0, nullptr);
-  DCG_HIP(launch_omg_dense_add(m, 2.0, T, C, st));
   DCG_HIP(hipStreamSynchronize(st));
-  g.fold[i] = C;
+  if (matrix_holds(g, k, Z))
+    g.fold[i] = Z;
+  else
+    ws.free_last(Z, m * m * sizeof(double));
 }
 
 }  // namespace

@@ -500,35 +500,61 @@ __global__ __launch_bounds__(kThreads) void k_omg_dense(int m, const double* __r
   if ((threadIdx.x & 63) == 0) z[i] = acc;
 }
 
-// Dense operator and RAS update of a small level from its row-major tables (both
-// cleared before): thread (square, row, diamond square).
-__global__ __launch_bounds__(kThreads) void k_omg_dense_tables(int n, const double* __restrict__ op,
-                                                               const double* __restrict__ ras,
-                                                               double* __restrict__ A,
-                                                               double* __restrict__ S) {
-  constexpr Diamond2 DM;
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+// The residual and the RAS step of a small level on the m columns of a matrix Z at
+// once (set-up): thread (square, column), the table rows through scalar loads, the
+// columns of a wavefront contiguous.  R = I - A* Z (Z = NULL: R = I).
+__global__ __launch_bounds__(kThreads) void k_omg_res_cols(int n, const double* __restrict__ op,
+                                                           const double* __restrict__ Z,
+                                                           double* __restrict__ R) {
   const int64_t m = D * (int64_t)n * n;
-  if (i >= m * 16) return;
-  const int d = int(i & 15), row = int((i >> 4) % D);
-  const int64_t e = i / (16 * D);
-  if (d >= kOmgDiamond) return;
-  int dx = 0, dy = 0;
-  for (int k = 0; k < kOmgDiamond; ++k)
-    if (k == d) {
-      dx = DM.d[k][0];
-      dy = DM.d[k][1];
+  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int e = blockIdx.y, x = e % n, y = e / n;
+  const int cls = op_axis(x, n) + 3 * op_axis(y, n);
+  double acc[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) acc[i] = D * (int64_t)e + i == j ? 1.0 : 0.0;
+  for (int s = 0; Z && s < kSlots; ++s) {
+    const int qx = x + kSlotOff[s][0], qy = y + kSlotOff[s][1];
+    if (qx < 0 || qy < 0 || qx >= n || qy >= n) continue;
+    const double* B = op + (cls * kSlots + s) * D * D;
+#pragma unroll 4
+    for (int b = 0; b < D; ++b) {
+      const double v = Z[(D * ((int64_t)qy * n + qx) + b) * m + j];
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] -= B[D * i + b] * v;
     }
-  const int x = int(e % n), y = int(e / n), qx = x + dx, qy = y + dy;
-  if (qx < 0 || qy < 0 || qx >= n || qy >= n) return;
-  const int64_t at = (D * e + row) * m + D * ((int64_t)qy * n + qx);
-  const double* K = ras + ((int64_t)ras_class(x, y, n) * D + row) * kOmgRasCols + D * d;
-  for (int b = 0; b < D; ++b) S[at + b] = K[b];
-  for (int s = 0; s < kSlots; ++s)
-    if (kSlotOff[s][0] == dx && kSlotOff[s][1] == dy) {
-      const double* B = op + (((op_axis(x, n) + 3 * op_axis(y, n)) * kSlots + s) * D + row) * D;
-      for (int b = 0; b < D; ++b) A[at + b] = B[b];
+  }
+#pragma unroll
+  for (int i = 0; i < D; ++i) R[(D * (int64_t)e + i) * m + j] = acc[i];
+}
+
+// Z = (zero ? 0 : Z) + S R.
+__global__ __launch_bounds__(kThreads) void k_omg_ras_cols(int n, const double* __restrict__ ras,
+                                                           const double* __restrict__ R,
+                                                           double* __restrict__ Z, int zero) {
+  constexpr Diamond2 DM;
+  const int64_t m = D * (int64_t)n * n;
+  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int e = blockIdx.y, x = e % n, y = e / n;
+  const double* K = ras + (int64_t)ras_class(x, y, n) * D * kOmgRasCols;
+  double acc[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) acc[i] = 0.0;
+  for (int d = 0; d < kOmgDiamond; ++d) {
+    const int qx = x + DM.d[d][0], qy = y + DM.d[d][1];
+    if (qx < 0 || qy < 0 || qx >= n || qy >= n) continue;
+#pragma unroll 4
+    for (int b = 0; b < D; ++b) {
+      const double v = R[(D * ((int64_t)qy * n + qx) + b) * m + j];
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] += K[kOmgRasCols * i + D * d + b] * v;
     }
+  }
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    double* z = Z + (D * (int64_t)e + i) * m + j;
+    *z = (zero ? 0.0 : *z) + acc[i];
+  }
 }
 
 // K = P C P^T: entry (16 e + 4 c + i, 16 e' + 4 c' + i') sums the injection
@@ -555,14 +581,6 @@ __global__ __launch_bounds__(kThreads) void k_omg_dense_coarse(int n, const doub
     acc += inject(q, i, I) * a;
   }
   K[t] = acc;
-}
-
-__global__ __launch_bounds__(kThreads) void k_omg_dense_add(int64_t m, double c, const double* B,
-                                                            double* A) {
-  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (t >= m * m) return;
-  if (B) A[t] += c * B[t];
-  else if (t / m == t % m) A[t] += c;
 }
 
 unsigned bricks(int nk) { return unsigned((nk / kBrick) * (nk / kBrick)); }
@@ -603,26 +621,25 @@ hipError_t launch_omg_ras(const OmgLevelDev& L, const double* r, double* z, bool
   return hipGetLastError();
 }
 
-hipError_t launch_omg_dense_tables(const OmgLevelDev& L, double* A, double* S, hipStream_t st) {
-  if (L.n > kOmgSplitMaxN) return hipErrorInvalidValue;
+hipError_t launch_omg_res_cols(const OmgLevelDev& L, const double* Z, double* R, hipStream_t st) {
   const int64_t m = D * (int64_t)L.n * L.n;
-  for (double* M : {A, S}) {
-    const hipError_t e = hipMemsetAsync(M, 0, m * m * sizeof(double), st);   // set-up, never captured
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_omg_dense_tables, dim3(blocks_for(m * 16)), dim3(kThreads), 0, st, L.n, L.op, L.ras,
-                     A, S);
+  if (L.n > kOmgSplitMaxN || m % kThreads) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_omg_res_cols, dim3(unsigned(m / kThreads), L.n * L.n), dim3(kThreads), 0, st, L.n,
+                     L.op, Z, R);
+  return hipGetLastError();
+}
+
+hipError_t launch_omg_ras_cols(const OmgLevelDev& L, const double* R, double* Z, bool zero, hipStream_t st) {
+  const int64_t m = D * (int64_t)L.n * L.n;
+  if (L.n > kOmgSplitMaxN || m % kThreads || !L.ras) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_omg_ras_cols, dim3(unsigned(m / kThreads), L.n * L.n), dim3(kThreads), 0, st, L.n,
+                     L.ras, R, Z, int(zero));
   return hipGetLastError();
 }
 
 hipError_t launch_omg_dense_coarse(int nk, const double* C, double* K, hipStream_t st) {
   const int64_t m = D * (int64_t)nk * nk;
   hipLaunchKernelGGL(k_omg_dense_coarse, dim3(blocks_for(m * m)), dim3(kThreads), 0, st, nk, C, K);
-  return hipGetLastError();
-}
-
-hipError_t launch_omg_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st) {
-  hipLaunchKernelGGL(k_omg_dense_add, dim3(blocks_for(m * m)), dim3(kThreads), 0, st, m, c, B, A);
   return hipGetLastError();
 }
 

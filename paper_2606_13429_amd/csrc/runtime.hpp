@@ -174,6 +174,7 @@ struct Workspace {
   FcgStore fcg;                           // DCG_OUTER_FCG directions
   void* alloc(size_t bytes);
   void* try_alloc(size_t bytes);          // NULL when the memory cannot be had
+  void free_last(void* p, size_t bytes);  // gives back the latest allocation
   void release();
   ~Workspace();
 };

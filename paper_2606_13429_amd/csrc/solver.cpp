@@ -31,6 +31,13 @@ void* Workspace::try_alloc(size_t b) {
   return p;
 }
 
+void Workspace::free_last(void* p, size_t b) {
+  if (allocations.empty() || allocations.back() != p) return;
+  allocations.pop_back();
+  bytes -= b;
+  (void)hipFree(p);
+}
+
 void Workspace::release() {
   for (void* p : allocations) (void)hipFree(p);
   allocations.clear();
