@@ -16,7 +16,8 @@
 namespace dcg3 {
 namespace {
 
-using dcg::mg::double2_any;   // in the caller's vectors
+using dcg::mg::ld2_any;   // the caller's vectors
+using dcg::mg::st2_any;
 
 constexpr int kThreads = 256;
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -108,19 +109,18 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
     const int nb = live ? nbr3(n, e, sl) : -1;
-    const double2_any* p = reinterpret_cast<const double2_any*>(x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q);
+    const double* p = x + (int64_t)(nb < 0 ? 0 : nb) * kDof + 24 * k + 2 * q;
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {   // unconditional loads (of element 0 outside the domain)
-      v[sl][t] = p[4 * t];
-      v[sl][t].x = nb >= 0 ? v[sl][t].x : 0.0;
-      v[sl][t].y = nb >= 0 ? v[sl][t].y : 0.0;
+    for (int t = 0; t < 3; ++t) {
+      v[sl][t] = make_double2(0.0, 0.0);
+      if (nb >= 0) v[sl][t] = ld2_any(p + 8 * t);
     }
   }
   // sigma_{k1 k1} + sigma_{k2 k2} of the other two rows, for the mass term
   const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
   const double* xe = x + (int64_t)(live ? e : 0) * kDof + 2 * q;
-  const double2 o1 = *reinterpret_cast<const double2_any*>(xe + 32 * k1);
-  const double2 o2 = *reinterpret_cast<const double2_any*>(xe + 32 * k2);
+  const double2 o1 = ld2_any(xe + 32 * k1);
+  const double2 o2 = ld2_any(xe + 32 * k2);
   constexpr int TT = G * 192, NS = (kFixedTiles * 32 + TT - 1) / TT;
   double2 tv[NS];
 #pragma unroll
@@ -187,10 +187,10 @@ __global__ __launch_bounds__(G * 192) void k_astar3(int n, const double* __restr
 #pragma unroll
   for (int i = 0; i < 2; ++i) r1[i] = inv_nu * m1[i] + dt * a1[i];
   if (live) {   // rows 4 q .. 4 q + 3 and 16 + 2 q, 16 + 2 q + 1
-    double2_any* yp = reinterpret_cast<double2_any*>(y + (int64_t)e * kDof + 24 * k);
-    yp[2 * q] = make_double2(r0[0], r0[1]);
-    yp[2 * q + 1] = make_double2(r0[2], r0[3]);
-    yp[8 + q] = make_double2(r1[0], r1[1]);
+    double* yp = y + (int64_t)e * kDof + 24 * k;
+    st2_any(yp + 4 * q, r0[0], r0[1]);
+    st2_any(yp + 4 * q + 2, r0[2], r0[3]);
+    st2_any(yp + 16 + 2 * q, r1[0], r1[1]);
   }
   if (!s) return;
   // s = Z^T y: rows 8 k .. 8 k + 7 of the three tensor rows
@@ -227,15 +227,15 @@ __global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict_
 #pragma unroll
   for (int sl = 0; sl < kSlots; ++sl) {
     const int nb = live ? nbr3(n, e, sl) : -1;
-    const double2 yv = *reinterpret_cast<const double2_any*>(yh + (int64_t)(nb >= 0 ? nb : 0) * kNb + 2 * q);
+    const double2 yv = ld2_any(yh + (int64_t)(nb >= 0 ? nb : 0) * kNb + 2 * q);
     v[sl].x = nb >= 0 ? yv.x * inv_sqrt3 : 0.0;
     v[sl].y = nb >= 0 ? yv.y * inv_sqrt3 : 0.0;
   }
   double2 wv[3];
-  const double2_any* wp = reinterpret_cast<const double2_any*>(w + (int64_t)(live ? e : 0) * kDof + 24 * k);
-  wv[0] = wp[2 * q];
-  wv[1] = wp[2 * q + 1];
-  wv[2] = wp[8 + q];
+  const double* wp = w + (int64_t)(live ? e : 0) * kDof + 24 * k;
+  wv[0] = ld2_any(wp + 4 * q);
+  wv[1] = ld2_any(wp + 4 * q + 2);
+  wv[2] = ld2_any(wp + 16 + 2 * q);
   v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
 #pragma unroll
   for (int sl = 1; sl < kSlots; ++sl) {
@@ -269,10 +269,10 @@ __global__ __launch_bounds__(192) void k_adivz3(int n, const double* __restrict_
     pending &= ~__ballot(mine);
   }
   if (!live) return;
-  double2_any* op = reinterpret_cast<double2_any*>(qv + (int64_t)e * kDof + 24 * k);
-  op[2 * q] = make_double2(wv[0].x - dt * a0[0], wv[0].y - dt * a0[1]);
-  op[2 * q + 1] = make_double2(wv[1].x - dt * a0[2], wv[1].y - dt * a0[3]);
-  op[8 + q] = make_double2(wv[2].x - dt * a1[0], wv[2].y - dt * a1[1]);
+  double* op = qv + (int64_t)e * kDof + 24 * k;
+  st2_any(op + 4 * q, wv[0].x - dt * a0[0], wv[0].y - dt * a0[1]);
+  st2_any(op + 4 * q + 2, wv[1].x - dt * a0[2], wv[1].y - dt * a0[3]);
+  st2_any(op + 16 + 2 * q, wv[2].x - dt * a1[0], wv[2].y - dt * a1[1]);
 }
 
 __global__ __launch_bounds__(kThreads) void k_zt3(int64_t ne, double inv_sqrt3,
@@ -568,8 +568,7 @@ __global__ __launch_bounds__(kFdmThreads) void k_fdm_plane(int n, const double* 
         b0[u] = b1[u] = 0.0;
         if (kk < N) {
           if (row < N)
-            a[u] = *reinterpret_cast<const double2_any*>(
-                in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
+            a[u] = ld2_any(in + (IN_ELEM ? elem(kk, row) : ((int64_t)Iz * N + row) * N + kk));
           if (c < N) {
             b0[u] = Bx[(int64_t)kk * N + c];
             b1[u] = Bx[(int64_t)(kk + 1) * N + c];

@@ -16,7 +16,8 @@ namespace dcg3 {
 
 namespace {
 
-using dcg::mg::double2_any;   // in the caller's vectors
+using dcg::mg::ld2_any;   // the caller's vectors
+using dcg::mg::st2_any;
 
 constexpr int kThreads = 256;
 constexpr int kCubesPerBlock = kThreads / 8;
@@ -118,11 +119,11 @@ __device__ __forceinline__ double2 task_input(const Task& t, int n, int dx, int 
                                               const double* __restrict__ v) {
   const double* own = v + 8 * (int64_t)t.e + 2 * t.q;
   const int64_t o = 8 * ((dz * n + dy) * n + dx);
-  if (IN) return *reinterpret_cast<const double2_any*>(own + o);
+  if (IN) return ld2_any(own + o);
   // the load is unconditional (from the cube itself outside the domain)
   const int x = t.x + dx, y = t.y + dy, z = t.z + dz;
   const bool in = x >= 0 && y >= 0 && z >= 0 && x < n && y < n && z < n;
-  double2 r = *reinterpret_cast<const double2_any*>(own + (in ? o : 0));
+  double2 r = ld2_any(own + (in ? o : 0));
   r.x = in ? r.x : 0.0;
   r.y = in ? r.y : 0.0;
   return r;
@@ -185,10 +186,10 @@ __global__ __launch_bounds__(64) void k_mg3_res(int n, int tasks, const int32_t*
   }
   double2 rv = make_double2(0.0, 0.0);
   if (t.valid) {
-    if (f) rv = *reinterpret_cast<const double2_any*>(f + 8 * (int64_t)t.e + 2 * t.q);
+    if (f) rv = ld2_any(f + 8 * (int64_t)t.e + 2 * t.q);
     rv.x -= a0[0] + a1[0];
     rv.y -= a0[1] + a1[1];
-    *reinterpret_cast<double2_any*>(r + 8 * (int64_t)t.e + 2 * t.q) = rv;
+    st2_any(r + 8 * (int64_t)t.e + 2 * t.q, rv.x, rv.y);
   }
   if (part) {   // the task's sum of r^2, fixed order
     double v = rv.x * rv.x + rv.y * rv.y;
@@ -209,14 +210,14 @@ __global__ __launch_bounds__(64) void k_mg3_ras(int n, int tasks, const int32_t*
   // rasT[cls][column 200][row]
   const double* A = rasT + (int64_t)t.cls * 8 * kRasCols + 16 * t.q + t.row;
   double2 zv = make_double2(0.0, 0.0);
-  if (t.valid && !zero) zv = *reinterpret_cast<const double2_any*>(z + 8 * (int64_t)t.e + 2 * t.q);
+  if (t.valid && !zero) zv = ld2_any(z + 8 * (int64_t)t.e + 2 * t.q);
   v4d a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
   if (t.cls == kInterior) ras_products<true>(t, n, A, r, a0, a1);
   else ras_products<false>(t, n, A, r, a0, a1);
   if (t.valid) {
     zv.x += a0[0] + a1[0];
     zv.y += a0[1] + a1[1];
-    *reinterpret_cast<double2_any*>(z + 8 * (int64_t)t.e + 2 * t.q) = zv;
+    st2_any(z + 8 * (int64_t)t.e + 2 * t.q, zv.x, zv.y);
   }
 }
 
@@ -365,11 +366,10 @@ __global__ __launch_bounds__(kThreads) void k_mg3_dense(int m, const double* __r
   const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (i >= m) return;   // whole wavefronts
   const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
-  const double2_any* f2 = reinterpret_cast<const double2_any*>(f);
   double acc = 0.0;
 #pragma unroll 8
   for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
-    const double2 a = row[j], b = f2[j];
+    const double2 a = row[j], b = ld2_any(f + 2 * j);
     acc += a.x * b.x + a.y * b.y;
   }
 #pragma unroll

@@ -36,24 +36,30 @@ __device__ __forceinline__ void st4(double* p, const double v[4]) {
 // The same for the vectors of a caller, which are aligned to their elements only (a
 // slice may start anywhere): gfx950 makes a 16-byte global access at any 4-byte
 // address, and the compiler emits the same instructions as for aligned vectors.
-typedef float4 float4_any __attribute__((aligned(4)));
-typedef double2 double2_any __attribute__((aligned(8)));
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2_any __attribute__((ext_vector_type(2), aligned(8)));
 
+__device__ __forceinline__ double2 ld2_any(const double* p) {
+  const double2_any t = *reinterpret_cast<const double2_any*>(p);
+  return make_double2(t.x, t.y);
+}
+__device__ __forceinline__ void st2_any(double* p, double x, double y) {
+  *reinterpret_cast<double2_any*>(p) = double2_any{x, y};
+}
 __device__ __forceinline__ void ld4_any(const float* p, float v[4]) {
-  const float4 t = *reinterpret_cast<const float4_any*>(p);
+  const float4_any t = *reinterpret_cast<const float4_any*>(p);
   v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
 }
 __device__ __forceinline__ void ld4_any(const double* p, double v[4]) {
-  const double2 a = reinterpret_cast<const double2_any*>(p)[0];
-  const double2 b = reinterpret_cast<const double2_any*>(p)[1];
+  const double2 a = ld2_any(p), b = ld2_any(p + 2);
   v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
 }
 __device__ __forceinline__ void st4_any(float* p, const float v[4]) {
-  *reinterpret_cast<float4_any*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  *reinterpret_cast<float4_any*>(p) = float4_any{v[0], v[1], v[2], v[3]};
 }
 __device__ __forceinline__ void st4_any(double* p, const double v[4]) {
-  reinterpret_cast<double2_any*>(p)[0] = make_double2(v[0], v[1]);
-  reinterpret_cast<double2_any*>(p)[1] = make_double2(v[2], v[3]);
+  st2_any(p, v[0], v[1]);
+  st2_any(p + 2, v[2], v[3]);
 }
 
 // 16 x 16 x 4 MFMA of the level type.  Operand lanes: A holds (row l % 16,

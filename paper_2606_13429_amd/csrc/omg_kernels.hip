@@ -18,7 +18,7 @@ namespace dcg {
 
 namespace {
 
-using mg::double2_any;   // in the caller's vectors
+using mg::ld2_any;   // the caller's vectors
 
 constexpr int D = kOmgDofs;
 constexpr int kThreads = 256;
@@ -488,11 +488,10 @@ __global__ __launch_bounds__(kThreads) void k_omg_dense(int m, const double* __r
   const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
   if (i >= m) return;   // whole wavefronts
   const double2* row = reinterpret_cast<const double2*>(A + (int64_t)i * m);
-  const double2_any* f2 = reinterpret_cast<const double2_any*>(f);
   double acc = 0.0;
 #pragma unroll 8
   for (int j = threadIdx.x & 63; j < m / 2; j += 64) {
-    const double2 a = row[j], b = f2[j];
+    const double2 a = row[j], b = ld2_any(f + 2 * j);
     acc += a.x * b.x + a.y * b.y;
   }
 #pragma unroll
