@@ -498,13 +498,15 @@ struct dcg3d_ctx {
 
   // The two coarse cycles that level k gives its parent (Algorithm 4: from zero,
   // then from the first's result) are one linear map of f_k, kept as a matrix on
-  // levels of at most kFoldMaxDofs unknowns.  With E = I - S L one cycle from zero
-  // is W = E^m (P_m + P C P^T (I - L P_m)) + P_m, P_m = sum_{i < m} E^i S, C the
-  // map of the level below, and two are 2 W - W L W.  A level of 8 x 8 x 8 cubes
-  // is 134 MB, read in 21 us, against 84 launches of 3.6-4.3 us and the levels below;
-  // the next size (12 or 16 cubes) would be 1.5 or 8.6 GB, slower than its steps.
-  // The cycle runs the steps of a level that has no matrix, so where the memory of
-  // the matrix or of its scratch (805 MB during set-up) cannot be had there is none.
+  // levels of at most kFoldMaxDofs unknowns: the cycles of the columns of the
+  // identity, step by step, so that the matrix carries the rounding of the steps.
+  // (Products of matrices, 2 W - W L W, carried a quarter more at n = 8 and the 3D
+  // workload's penalty; unlike A*, L keeps the error of the product with the matrix
+  // at that of the steps: 0.6 to 2.1 times for penalties from 40 to 1e6.)  A level of
+  // 8 x 8 x 8 cubes is 134 MB, read in 21 us, against 84 launches of 3.6-4.3 us and the
+  // levels below; the next size (12 or 16 cubes) would be 1.5 or 8.6 GB, slower than its
+  // steps.  The cycle runs the steps of a level that has no matrix, so where the memory
+  // of the matrix or of its scratch (403 MB during set-up) cannot be had there is none.
   void fold_level(int k) {
     const int i = k - 1, nk = mg_n[i];
     const int64_t m = 8 * (int64_t)nk * nk * nk;
@@ -513,42 +515,26 @@ struct dcg3d_ctx {
       double* p = nullptr;
       ~Temp() { (void)hipFree(p); }
     } tmp;
-    tmp.p = try_dev_alloc<double>(6 * m * m);
-    double* C = tmp.p ? try_dev_alloc<double>(m * m) : nullptr;
-    if (!C) return;
-    mg_fold[i] = C;
-    double *L = tmp.p, *S = L + m * m, *E = S + m * m, *Ei = E + m * m, *P = Ei + m * m, *T = P + m * m;
-    const size_t bytes = size_t(m * m) * sizeof(double);
-    auto gemm = [&](const double* A, const double* B, double* out, double a, const double* D) {
-      H3(dcg::launch_gemm(int(m), A, B, out, a, D, nullptr));
-    };
-    H3(dcg3::launch_mg3_dense_tables(nk, mg_op[i], mg_ras[i], L, S, nullptr));
-    gemm(S, L, E, -1.0, nullptr);
-    H3(dcg3::launch_mg3_dense_add(m, 1.0, nullptr, E, nullptr));
-    H3(hipMemcpyAsync(Ei, E, bytes, hipMemcpyDeviceToDevice, nullptr));
-    H3(hipMemcpyAsync(P, S, bytes, hipMemcpyDeviceToDevice, nullptr));
-    int top = 0;
-    while ((mg_m >> (top + 1)) > 0) ++top;
-    for (int b = top - 1; b >= 0; --b) {   // (E^s, P_s) for the leading bits s of m
-      gemm(Ei, P, T, 1.0, P);
-      std::swap(P, T);
-      gemm(Ei, Ei, T, 1.0, nullptr);
-      std::swap(Ei, T);
-      if ((mg_m >> b) & 1) {
-        gemm(E, P, T, 1.0, S);
-        std::swap(P, T);
-        gemm(E, Ei, T, 1.0, nullptr);
-        std::swap(Ei, T);
+    tmp.p = try_dev_alloc<double>(3 * m * m);
+    double* Z = tmp.p ? try_dev_alloc<double>(m * m) : nullptr;
+    if (!Z) return;
+    mg_fold[i] = Z;
+    double *R = tmp.p, *K = R + m * m, *T = K + m * m;
+    H3(dcg3::launch_mg3_dense_coarse(nk, k == 2 ? mg_cinv : mg_fold[i - 1], K, nullptr));
+    bool zero = true;
+    auto smooth = [&]() {
+      for (int s = 0; s < mg_m; ++s, zero = false) {
+        H3(dcg3::launch_mg3_res_cols(mg_lev[i], zero ? nullptr : Z, R, nullptr));
+        H3(dcg3::launch_mg3_ras_cols(mg_lev[i], R, Z, zero, nullptr));
       }
+    };
+    for (int c = 0; c < 2; ++c) {          // two swaps: Z ends where it began
+      smooth();
+      H3(dcg3::launch_mg3_res_cols(mg_lev[i], Z, R, nullptr));
+      H3(dcg::launch_gemm(int(m), K, R, T, Z, nullptr));   // Z + P C P^T R
+      std::swap(Z, T);
+      smooth();
     }
-    gemm(L, P, T, -1.0, nullptr);           // I - L P_m
-    H3(dcg3::launch_mg3_dense_add(m, 1.0, nullptr, T, nullptr));
-    H3(dcg3::launch_mg3_dense_coarse(nk, k == 2 ? mg_cinv : mg_fold[i - 1], S, nullptr));
-    gemm(S, T, E, 1.0, P);
-    gemm(Ei, E, T, 1.0, P);                 // W
-    gemm(L, T, E, 1.0, nullptr);
-    gemm(T, E, C, -1.0, nullptr);
-    H3(dcg3::launch_mg3_dense_add(m, 2.0, T, C, nullptr));
     H3(hipStreamSynchronize(nullptr));
   }
 

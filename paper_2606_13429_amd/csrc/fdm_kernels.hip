@@ -22,8 +22,8 @@ __device__ __forceinline__ int64_t tensor_to_elem(int n, int a, int c) {
   return 4 * ((int64_t)(a >> 1) * n + (c >> 1)) + (c & 1) + 2 * (a & 1);
 }
 
-// C = alpha A B (+ D), N x N row-major FP64; with la: (A B)[i][k] is multiplied
-// by 1 / (la[i] + lb[k]).  D may be C.
+// C = A B (+ D), N x N row-major FP64; with la: (A B)[i][k] is multiplied
+// by 1 / (la[i] + lb[k]).
 // AELEM: A is an element-major vector (of type TIN);
 // CELEM: C is written element-major (as TOUT), so the layout changes need no
 // launches of their own.  One TILE x TILE block of C per workgroup; two groups
@@ -39,7 +39,7 @@ template <int TILE, int KK, bool AELEM, bool CELEM, typename TIN, typename TOUT>
 __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm(int N, const TIN* __restrict__ A,
                                                     const double* __restrict__ B, TOUT* __restrict__ C,
                                                     const double* __restrict__ la,
-                                                    const double* __restrict__ lb, double alpha,
+                                                    const double* __restrict__ lb,
                                                     const double* D) {
   using V = mg::Mfma<double>::v4;
   constexpr int SA = KK + 2, SB = TILE + 16, R = TILE / 32, NL = TILE * KK / (2 * kGThreads);
@@ -128,22 +128,21 @@ __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2, 2)
         const int gr = row0 + wr + 16 * i + 4 * v + (lane >> 4), gc = col0 + wc + 16 * j + (lane & 15);
         double x = acc[i][j][v] + red[(((i * R + j) * 4 + v) * 4 + w) * 64 + lane];
         if (la) x *= 1.0 / (la[gr] + lb[gc]);
-        if (D) x = alpha * x + D[(int64_t)gr * N + gc];
-        else x *= alpha;
+        if (D) x += D[(int64_t)gr * N + gc];
         C[CELEM ? tensor_to_elem(n, gr, gc) : (int64_t)gr * N + gc] = TOUT(x);
       }
 }
 
 template <bool AELEM, bool CELEM, typename TIN, typename TOUT>
 hipError_t gemm(int N, const TIN* A, const double* B, TOUT* C, const double* la, const double* lb,
-                hipStream_t st, double alpha = 1.0, const double* D = nullptr) {
+                hipStream_t st, const double* D = nullptr) {
   // 64 x 64 tiles fill the compute units from N = 1024 on (256 workgroups);
   // below, 32 x 32 tiles do
   if (N % 64) return hipErrorInvalidValue;
   if (N >= 1024)
-    k_gemm<64, 32, AELEM, CELEM><<<dim3(N / 64, N / 64), kGThreads, 0, st>>>(N, A, B, C, la, lb, alpha, D);
+    k_gemm<64, 32, AELEM, CELEM><<<dim3(N / 64, N / 64), kGThreads, 0, st>>>(N, A, B, C, la, lb, D);
   else
-    k_gemm<32, 64, AELEM, CELEM><<<dim3(N / 32, N / 32), kGThreads, 0, st>>>(N, A, B, C, la, lb, alpha, D);
+    k_gemm<32, 64, AELEM, CELEM><<<dim3(N / 32, N / 32), kGThreads, 0, st>>>(N, A, B, C, la, lb, D);
   return hipGetLastError();
 }
 
@@ -240,9 +239,8 @@ hipError_t fdm_solve(int n, const double* V, const double* VT, const double* lam
 
 }  // namespace
 
-hipError_t launch_gemm(int N, const double* A, const double* B, double* C, double alpha,
-                       const double* D, hipStream_t st) {
-  return gemm<false, false>(N, A, B, C, nullptr, nullptr, st, alpha, D);
+hipError_t launch_gemm(int N, const double* A, const double* B, double* C, const double* D, hipStream_t st) {
+  return gemm<false, false>(N, A, B, C, nullptr, nullptr, st, D);
 }
 
 hipError_t launch_fdm_solve2d(int n, const double* V, const double* VT, const double* lam,

@@ -279,10 +279,8 @@ hipError_t launch_store_columns(int ne, int j0, bool has_z, const double* z, con
 template <typename T>
 hipError_t launch_resolve_b(int ne, bool has_z, const T* z, const T* Ye, T* out, hipStream_t st);
 
-// C = alpha A B (+ D), dense N x N row-major FP64, N a multiple of 64; C is
-// neither A nor B, D may be C.
-hipError_t launch_gemm(int N, const double* A, const double* B, double* C, double alpha,
-                       const double* D, hipStream_t st);
+// C = A B + D, dense N x N row-major FP64, N a multiple of 64; C is none of the others.
+hipError_t launch_gemm(int N, const double* A, const double* B, double* C, const double* D, hipStream_t st);
 // Exact inner solve on the uniform grid: z = L^{-1} s by fast
 // diagonalisation, L = M (x) K + K (x) M on the tensor index (Iy, Ix) of the
 // 2n x 2n grid of dofs, with K V = M V diag(lam), V^T M V = I (V, its

@@ -125,15 +125,13 @@ hipError_t launch_mg3_prolong(int nf, const double* zc, double* z, bool assign,
 hipError_t launch_mg3_dense(int m, const double* inv, const double* f, double* z,
                             const int32_t* guard, hipStream_t st);
 
-// ---- dense forms of a small level (set-up)
-// L = the level operator, S = the RAS update, dense m x m row-major, m = 8 nk^3
-// (nk <= kSplitMaxN: row-major tables).
-hipError_t launch_mg3_dense_tables(int nk, const double* op, const double* ras, double* L, double* S,
-                                   hipStream_t st);
+// ---- the matrix of a small level (set-up; nk <= kSplitMaxN: row-major tables,
+// m = 8 nk^3 a multiple of 64, matrices m x m row-major)
+// R = I - L Z (Z = NULL: R = I); Z = (zero ? 0 : Z) + S R.
+hipError_t launch_mg3_res_cols(const Mg3LevelDev& L, const double* Z, double* R, hipStream_t st);
+hipError_t launch_mg3_ras_cols(const Mg3LevelDev& L, const double* R, double* Z, bool zero, hipStream_t st);
 // K = P C P^T of the level nk, C dense on the next coarser one.
 hipError_t launch_mg3_dense_coarse(int nk, const double* C, double* K, hipStream_t st);
-// A += c B (len elements; B = NULL: c times the identity, len = m^2).
-hipError_t launch_mg3_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st);
 
 // Device state of one Multigrid iteration (Algorithm 3).
 struct Mg3Scalars {

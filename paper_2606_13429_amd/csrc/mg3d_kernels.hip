@@ -377,42 +377,64 @@ __global__ __launch_bounds__(kThreads) void k_mg3_dense(int m, const double* __r
   if ((threadIdx.x & 63) == 0) z[i] = acc;
 }
 
-// Dense L and S of a small level from its row-major tables (both cleared
-// before): thread (cube, row, diamond cube).
-__global__ __launch_bounds__(kThreads) void k_mg3_dense_tables(int n, const double* __restrict__ op,
-                                                               const double* __restrict__ ras,
-                                                               double* __restrict__ L,
-                                                               double* __restrict__ S) {
-  constexpr DiamondOff D;
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int64_t ne = (int64_t)n * n * n, m = 8 * ne;
-  if (i >= m * 32) return;
-  const int d = int(i & 31), row = int((i >> 5) & 7);
-  const int64_t e = i >> 8;
-  if (d >= kDiamond) return;
-  const int x = int(e % n), y = int((e / n) % n), zz = int(e / ((int64_t)n * n));
-  int off[3] = {0, 0, 0};
-  for (int k = 0; k < kDiamond; ++k)
-    if (k == d) {
-      off[0] = D.d[k][0];
-      off[1] = D.d[k][1];
-      off[2] = D.d[k][2];
+// The residual and the RAS step of a small level on the m columns of a matrix Z at
+// once (set-up; row-major tables): thread (cube, column), the table rows through
+// scalar loads, the columns of a wavefront contiguous.  R = I - L Z (Z = NULL: R = I).
+__global__ __launch_bounds__(64) void k_mg3_res_cols(int n, const double* __restrict__ op,
+                                                     const double* __restrict__ Z,
+                                                     double* __restrict__ R) {
+  const int64_t m = 8 * (int64_t)n * n * n;
+  const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int e = blockIdx.y, c[3] = {e % n, (e / n) % n, e / (n * n)};
+  const int cls = op_axis(c[0], n) + 3 * op_axis(c[1], n) + 9 * op_axis(c[2], n);
+  double acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 8 * (int64_t)e + i == j ? 1.0 : 0.0;
+  for (int s = 0; Z && s < kSlots; ++s) {
+    const int ax = s == 0 ? 0 : (s - 1) >> 1, dir = s == 0 ? 0 : ((s & 1) ? -1 : 1);
+    const int q = (ax == 0 ? c[0] : (ax == 1 ? c[1] : c[2])) + dir;
+    if (q < 0 || q >= n) continue;
+    const int nb = e + dir * (ax == 0 ? 1 : (ax == 1 ? n : n * n));
+    const double* B = op + (cls * kSlots + s) * 64;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const double v = Z[(8 * (int64_t)nb + b) * m + j];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] -= B[8 * i + b] * v;
     }
-  const int qx = x + off[0], qy = y + off[1], qz = zz + off[2];
-  if (qx < 0 || qy < 0 || qz < 0 || qx >= n || qy >= n || qz >= n) return;
-  const int64_t at = (8 * e + row) * m + 8 * (((int64_t)qz * n + qy) * n + qx);
-  const int rc = n < kRasClassMinN ? int(e) : ras_axis(x, n) + 7 * ras_axis(y, n) + 49 * ras_axis(zz, n);
-  const double* K = ras + ((int64_t)rc * 8 + row) * kRasCols + 8 * d;
-  for (int b = 0; b < 8; ++b) S[at + b] = K[b];
-  int slot = -1;
-  if (!off[0] && !off[1] && !off[2]) slot = 0;
-  for (int a = 0; a < 3; ++a)
-    if (!off[(a + 1) % 3] && !off[(a + 2) % 3] && (off[a] == 1 || off[a] == -1))
-      slot = 1 + 2 * a + (off[a] > 0);
-  if (slot < 0) return;
-  const int oc = op_axis(x, n) + 3 * op_axis(y, n) + 9 * op_axis(zz, n);
-  const double* B = op + ((oc * kSlots + slot) * 8 + row) * 8;
-  for (int b = 0; b < 8; ++b) L[at + b] = B[b];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) R[(8 * (int64_t)e + i) * m + j] = acc[i];
+}
+
+// Z = (zero ? 0 : Z) + S R.
+__global__ __launch_bounds__(64) void k_mg3_ras_cols(int n, const double* __restrict__ ras,
+                                                     const double* __restrict__ R,
+                                                     double* __restrict__ Z, int zero) {
+  constexpr DiamondOff D;
+  const int64_t m = 8 * (int64_t)n * n * n;
+  const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int e = blockIdx.y, x = e % n, y = (e / n) % n, z = e / (n * n);
+  const int cls = n < kRasClassMinN ? e : ras_axis(x, n) + 7 * ras_axis(y, n) + 49 * ras_axis(z, n);
+  const double* K = ras + (int64_t)cls * 8 * kRasCols;
+  double acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+  for (int d = 0; d < kDiamond; ++d) {
+    const int qx = x + D.d[d][0], qy = y + D.d[d][1], qz = z + D.d[d][2];
+    if (qx < 0 || qy < 0 || qz < 0 || qx >= n || qy >= n || qz >= n) continue;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const double v = R[(8 * (((int64_t)qz * n + qy) * n + qx) + b) * m + j];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] += K[kRasCols * i + 8 * d + b] * v;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    double* p = Z + (8 * (int64_t)e + i) * m + j;
+    *p = (zero ? 0.0 : *p) + acc[i];
+  }
 }
 
 // K = P C P^T: entry (8 c + i, 8 c' + i') sums the injection coefficients of the
@@ -442,14 +464,6 @@ __global__ __launch_bounds__(kThreads) void k_mg3_dense_coarse(int n, const doub
     acc += pi * a;
   }
   K[t] = acc;
-}
-
-__global__ __launch_bounds__(kThreads) void k_mg3_dense_add(int64_t m, double c, const double* B,
-                                                            double* A) {
-  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (t >= m * m) return;
-  if (B) A[t] += c * B[t];
-  else if (t / m == t % m) A[t] += c;
 }
 
 __global__ __launch_bounds__(kThreads) void k_mg3_start(int64_t len, double* __restrict__ z,
@@ -559,16 +573,18 @@ hipError_t launch_mg3_dense(int m, const double* inv, const double* f, double* z
   return hipGetLastError();
 }
 
-hipError_t launch_mg3_dense_tables(int nk, const double* op, const double* ras, double* L, double* S,
-                                   hipStream_t st) {
-  if (!mg3_split(nk)) return hipErrorInvalidValue;
-  const int64_t m = 8 * (int64_t)nk * nk * nk;
-  for (double* A : {L, S}) {
-    const hipError_t e = hipMemsetAsync(A, 0, m * m * sizeof(double), st);   // set-up, never captured
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_mg3_dense_tables, dim3(unsigned((m * 32 + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, st, nk, op, ras, L, S);
+hipError_t launch_mg3_res_cols(const Mg3LevelDev& L, const double* Z, double* R, hipStream_t st) {
+  const int64_t m = 8 * (int64_t)L.n * L.n * L.n;
+  if (!mg3_split(L.n) || m % 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_mg3_res_cols, dim3(unsigned(m / 64), L.n * L.n * L.n), dim3(64), 0, st, L.n, L.op, Z, R);
+  return hipGetLastError();
+}
+
+hipError_t launch_mg3_ras_cols(const Mg3LevelDev& L, const double* R, double* Z, bool zero, hipStream_t st) {
+  const int64_t m = 8 * (int64_t)L.n * L.n * L.n;
+  if (!mg3_split(L.n) || m % 64 || !L.ras) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_mg3_ras_cols, dim3(unsigned(m / 64), L.n * L.n * L.n), dim3(64), 0, st, L.n, L.ras, R, Z,
+                     int(zero));
   return hipGetLastError();
 }
 
@@ -576,12 +592,6 @@ hipError_t launch_mg3_dense_coarse(int nk, const double* C, double* K, hipStream
   const int64_t m = 8 * (int64_t)nk * nk * nk;
   hipLaunchKernelGGL(k_mg3_dense_coarse, dim3(unsigned((m * m + kThreads - 1) / kThreads)), dim3(kThreads),
                      0, st, nk, C, K);
-  return hipGetLastError();
-}
-
-hipError_t launch_mg3_dense_add(int64_t m, double c, const double* B, double* A, hipStream_t st) {
-  hipLaunchKernelGGL(k_mg3_dense_add, dim3(unsigned((m * m + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                     st, m, c, B, A);
   return hipGetLastError();
 }
 

@@ -146,7 +146,7 @@ void fold_level(OuterMg& g, int k, Workspace& ws) {
   for (int c = 0; c < 2; ++c) {        // two swaps: Z ends where it began
     smooth();
     DCG_HIP(launch_omg_res_cols(g.lev[i], Z, R, st));
-    DCG_HIP(launch_gemm(int(m), K, R, T, 1.0, Z, st));   // Z + P C P^T R
+    DCG_HIP(launch_gemm(int(m), K, R, T, Z, st));   // Z + P C P^T R
     std::swap(Z, T);
     smooth();
   }

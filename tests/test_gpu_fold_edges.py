@@ -60,8 +60,9 @@ def test_two_handles_of_one_mesh_take_turns():
 
 
 class _Exact:
-    """The W-cycle on A* in extended precision: level operators by exact Galerkin
-    products, local inverses by Newton steps, the coarsest solve by refinement."""
+    """The W-cycle on an oracle hierarchy in extended precision: level operators by
+    exact Galerkin products, local inverses by Newton steps, the coarsest solve by
+    refinement."""
     L = np.longdouble
 
     def __init__(self, H):
@@ -101,22 +102,30 @@ class _Exact:
         return self.smooth(k, f, z + self.P[k] @ c, m)
 
 
-def _steps(s, f, J, m):
-    """The cycle at level J = 3 with the two cycles of level 2 (which run their steps)."""
+_OMG = (lib.DCG_OP_OMG_RAS, lib.DCG_OP_OMG_LEVEL, lib.DCG_OP_OMG_RESTRICT, lib.DCG_OP_OMG_PROLONG,
+        lib.DCG_OP_OMG_WCYCLE)
+_MG3 = (lib.DCG3D_MG_RAS, lib.DCG3D_MG_LAPLACE, lib.DCG3D_MG_RESTRICT, lib.DCG3D_MG_PROLONG,
+        lib.DCG3D_MG_WCYCLE)
+
+
+def _steps(apply, ops, f, J, m):
+    """The cycle at level J = 3 with the two cycles of level 2 (which run their steps);
+    apply(op, level, in, out, in2)."""
     def op(o, k, x, size, x2=None):
         out = torch.full((size,), float("nan"), dtype=torch.float64, device="cuda")
-        s.apply(o, x, out, level=k, in2=x2)
+        apply(o, k, x, out, x2)
         return out
-    N = f.numel()
+    ras, level, restrict, prolong, wcycle = ops
+    N, M = f.numel(), f.numel() // (4 if ops is _OMG else 8)
     z = None
     for _ in range(m):
-        z = op(lib.DCG_OP_OMG_RAS, J, f, N, z)
-    r = op(lib.DCG_OP_OMG_RESTRICT, J, f - op(lib.DCG_OP_OMG_LEVEL, J, z, N), N // 4)
-    c = op(lib.DCG_OP_OMG_WCYCLE, J - 1, r, N // 4)
-    c = op(lib.DCG_OP_OMG_WCYCLE, J - 1, r, N // 4, c)
-    z = z + op(lib.DCG_OP_OMG_PROLONG, J, c, N)
+        z = op(ras, J, f, N, z)
+    r = op(restrict, J, f - op(level, J, z, N), M)
+    c = op(wcycle, J - 1, r, M)
+    c = op(wcycle, J - 1, r, M, c)
+    z = z + op(prolong, J, c, N)
     for _ in range(m):
-        z = op(lib.DCG_OP_OMG_RAS, J, f, N, z)
+        z = op(ras, J, f, N, z)
     return z
 
 
@@ -137,7 +146,8 @@ def test_outer_multigrid_matrix_is_as_accurate_as_the_steps(dt, m):
         fd = torch.from_numpy(f).cuda()
         out = torch.full_like(fd, float("nan"))
         s.apply(lib.DCG_OP_OMG_APPLY, fd, out, level=H.J)
-        for i, y in enumerate((out, _steps(s, fd, H.J, m))):
+        y = _steps(lambda o, k, x, t, w: s.apply(o, x, t, level=k, in2=w), _OMG, fd, H.J, m)
+        for i, y in enumerate((out, y)):
             err[i, seed] = np.abs(y.cpu().numpy() - x).max() / np.abs(x).max()
     s.close()
     matrix, steps = np.sqrt((err ** 2).mean(axis=1))
@@ -157,3 +167,26 @@ def test_3d_many_smoothing_steps():
     s.mg_apply(lib.DCG3D_MG_WCYCLE, J, fd, out)
     _close(out, mg.wcycle(H, f, np.zeros_like(f), J, m, m), m)
     s.close()
+
+
+@pytest.mark.parametrize("penalty,m", [(40.0, 1), (40.0, 3), (1e5, 3)])
+def test_3d_matrix_is_as_accurate_as_the_steps(penalty, m):
+    """The same for the 3D inner multigrid (levels of 16, 8 and 4 cubes)."""
+    n = 16
+    H = mg3.Hierarchy(d3.sipg_laplacian(n, penalty), n, coarsest=4)
+    X = _Exact(H)
+    s = dcg.Solver3D(n, 1e-3, penalty=penalty, inner="mg", levels=3, smooth=m)
+    err = np.zeros((2, 4))
+    for seed in range(4):
+        f = np.random.default_rng(seed).standard_normal(8 * n ** 3)
+        x = X.cycle(3, f.astype(X.L), np.zeros(f.size, dtype=X.L), m)
+        fd = torch.from_numpy(f).cuda()
+        out = torch.full_like(fd, float("nan"))
+        s.mg_apply(lib.DCG3D_MG_WCYCLE, 3, fd, out)
+        y = _steps(lambda o, k, x, t, w: s.mg_apply(o, k, x, t, w), _MG3, fd, 3, m)
+        for i, y in enumerate((out, y)):
+            err[i, seed] = np.abs(y.cpu().numpy() - x).max() / np.abs(x).max()
+    s.close()
+    matrix, steps = np.sqrt((err ** 2).mean(axis=1))
+    print("3d n=%d penalty=%g m=%d: matrix %.1e steps %.1e" % (n, penalty, m, matrix, steps), flush=True)
+    assert matrix <= 2 * steps
