@@ -4,10 +4,7 @@
 // operators for dcg_apply.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <cmath>
 #include <cstring>
-#include <random>
 #include <vector>
 
 #include "kernels.hpp"
@@ -65,27 +62,21 @@ void cycle(const OuterMg& g, int k, int mode, hipStream_t st) {
   }
 }
 
-// True when the matrix C of level k does to the vectors it will meet -- restricted
-// residuals of the parent's pre-smoothed random vectors -- what the two cycles step
-// by step do, within twice the rounding of the steps themselves (their change when
-// the input is scaled by 3).  The steps damp their rounding through the residual, the
-// product cannot: where A* is ill-conditioned and its entries cancel it is the less
-// accurate one.  At n = 32 the ratio is 0.5 to 1.3 for dt <= 1e-2, 2 to 50 at dt = 1
-// (m = 6 .. 1) and some thousands at dt = 100.
+// FoldCheck of the matrix C of level k.  At n = 32 the distance is 0.5 to 1.3 times the
+// steps' rounding for dt <= 1e-2, 2 to 50 times at dt = 1 (m = 6 .. 1) and some
+// thousand times at dt = 100.
 bool matrix_holds(const OuterMg& g, int k, const double* C) {
   const int i = k - 1, m = int(level_len(g, k)), mp = int(level_len(g, k + 1));
   const hipStream_t st = nullptr;
-  std::mt19937_64 rng(1);
-  std::uniform_real_distribution<double> uniform(-1.0, 1.0);
-  std::vector<double> f(mp), a(m), b(m), c(m);
+  std::vector<double> a(m), a3(m), c(m);
   auto steps = [&](std::vector<double>& out) {
     cycle(g, k, kZero, st);
     cycle(g, k, kWarm, st);
     DCG_HIP(hipMemcpy(out.data(), g.z[i], m * sizeof(double), hipMemcpyDeviceToHost));
   };
-  double dist2 = 0.0, round2 = 0.0;
-  for (int probe = 0; probe < 8; ++probe) {
-    for (double& x : f) x = uniform(rng);
+  FoldCheck check;
+  for (unsigned probe = 0; probe < 8; ++probe) {
+    const std::vector<double> f = fold_probe(mp, probe);
     DCG_HIP(hipMemcpy(g.f[i + 1], f.data(), mp * sizeof(double), hipMemcpyHostToDevice));
     for (int s = 0; s < g.m; ++s) {
       if (s > 0) DCG_HIP(launch_omg_res(g.lev[i + 1], g.f[i + 1], g.z[i + 1], g.r[i + 1], st));
@@ -98,19 +89,10 @@ bool matrix_holds(const OuterMg& g, int k, const double* C) {
     steps(a);
     DCG_HIP(launch_scale(m, 3.0, g.f[i], g.r[i], st));
     copy(g.r[i], g.f[i], m, st);
-    steps(b);
-    double top = 0.0, dist = 0.0, round = 0.0;
-    for (int j = 0; j < m; ++j) {
-      if (!std::isfinite(a[j] + b[j] + c[j])) return false;
-      top = std::max(top, std::fabs(a[j]));
-      dist = std::max(dist, std::fabs(c[j] - a[j]));
-      round = std::max(round, std::fabs(b[j] / 3.0 - a[j]));
-    }
-    if (dist == 0.0) continue;
-    dist2 += (dist / top) * (dist / top);
-    round2 += (round / top) * (round / top);
+    steps(a3);
+    check.add(m, [](int j) { return j; }, a, a3, c);
   }
-  return dist2 <= 4.0 * round2;
+  return check.holds();
 }
 
 // The two coarse cycles that level k gives its parent (Algorithm 4: from zero,

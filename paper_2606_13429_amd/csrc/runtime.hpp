@@ -2,9 +2,12 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <map>
 #include <memory>
 #include <mutex>
+#include <set>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -90,6 +93,7 @@ struct MeshContext {
   std::mutex fold_mu;
   std::map<std::pair<int, int>, std::weak_ptr<FoldMatrix>> folds;
   std::shared_ptr<FoldMatrix> last_fold;
+  std::set<std::pair<int, int>> no_fold;   // (m1, m2) whose matrix is less accurate than the steps
 
   ~MeshContext();
   // uploads L_k and tile inverses of that precision, with levels > 0 of the
@@ -99,10 +103,40 @@ struct MeshContext {
   std::vector<void*> allocations;
 };
 
+// Whether the matrix of a level's two coarse cycles does to the vectors it will meet
+// (restricted residuals of the parent's pre-smoothed random vectors) what the steps
+// do, within twice the rounding of the steps themselves.  The steps damp their
+// rounding through the residual, the product cannot: where the operator is
+// ill-conditioned and the matrix's entries cancel it is the less accurate one.
+struct FoldCheck {
+  double dist2 = 0.0, round2 = 0.0;
+  bool finite = true;
+  // one vector of m entries: the steps, the steps on 3 times the input, the matrix
+  template <typename At>
+  void add(int m, At at, const std::vector<double>& a, const std::vector<double>& a3,
+           const std::vector<double>& c) {
+    double top = 0.0, dist = 0.0, round = 0.0;
+    for (int i = 0; i < m; ++i) {
+      const auto j = at(i);
+      if (!std::isfinite(a[j] + a3[j] + c[j])) finite = false;
+      top = std::max(top, std::fabs(a[j]));
+      dist = std::max(dist, std::fabs(c[j] - a[j]));
+      round = std::max(round, std::fabs(a3[j] / 3.0 - a[j]));
+    }
+    if (dist == 0.0) return;
+    dist2 += (dist / top) * (dist / top);
+    round2 += (round / top) * (round / top);
+  }
+  bool holds() const { return finite && dist2 <= 4.0 * round2; }
+};
+// Uniform random entries in (-1, 1) for it, the same on every call.
+std::vector<double> fold_probe(size_t n, unsigned seed);
+
 // True when cycles with post-smoothing m2 on the full hierarchy of J levels use
 // the fold matrix; get_fold returns it (made on first use), or NULL where the
-// memory of the matrix or of its construction (20 MB of level buffers, the FP64
-// inverses of level 2) cannot be had.  The calling thread's device is the mesh's.
+// memory of the matrix or of its construction (45 MB of level buffers, the FP64
+// inverses of levels 2 and 3) cannot be had or the matrix is less accurate than the
+// steps.  The calling thread's device is the mesh's.
 inline bool fold_applies(int J, int post) { return J >= 3 && post >= 1; }
 std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post);
 void release_fold(MeshContext& m);   // frees the matrix kept with the context if nobody else holds it

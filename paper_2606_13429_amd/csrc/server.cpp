@@ -170,14 +170,14 @@ size_t context_bytes(int n, bool fp32) {
 }
 
 // What the fold matrix adds to a group, 0 where none is used: the matrix and, in
-// the mixed form, the FP64 inverses of the context's level 2 that it is made with.
+// the mixed form, the FP64 inverses of the context's levels 2 and 3 that it is made with.
 // It is optional, so it counts for nothing at admission: a group takes it only where
 // the budget has room for it, and gives it back when another group needs the room
 // (make_room).  Budgets below 16 matrices do without: there the memory of one holds
 // several small groups (about 0.1 GB each at n = 64).
 size_t group_fold_bytes(int n, int post, bool fp32, size_t budget) {
   if (!fold_applies(num_levels(n), post) || kFoldBytes > budget / 16) return 0;
-  constexpr size_t kInv = 9 * (36 + 64) * 256 + size_t(kFoldN) * kFoldN;
+  constexpr size_t kInv = 2 * 9 * (36 + 64) * 256 + 5 * size_t(kFoldN) * kFoldN;
   return kFoldBytes + (fp32 ? kInv * sizeof(double) : 0);
 }
 

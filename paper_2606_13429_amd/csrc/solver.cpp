@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <random>
 
 #include "fdm_host.hpp"
 #include "wcycle.hpp"
@@ -99,7 +100,54 @@ FoldMatrix::~FoldMatrix() {
   (void)hipSetDevice(cur);
 }
 
+std::vector<double> fold_probe(size_t n, unsigned seed) {
+  std::mt19937_64 rng(seed);
+  std::uniform_real_distribution<double> uniform(-1.0, 1.0);
+  std::vector<double> f(n);
+  for (double& x : f) x = uniform(rng);
+  return f;
+}
+
 namespace {
+
+// FoldCheck of the matrix C on one batch of columns of level 3.  With the paper's
+// penalty the distance is 0.5 to 1.0 times the steps' rounding, from a penalty of
+// 3000 on (which makes L ill-conditioned) up to thousands of times.
+bool matrix_holds(MeshContext& m, int pre, int post, const double* C) {
+  Workspace ws;
+  LevelBuffers lb;
+  lb.allocate(m, false, true, ws, 3);
+  const int ne = kFoldN * kFoldN, len = int(kFoldDofs) * kBatch;
+  double* out = static_cast<double*>(ws.alloc(sizeof(double) * len));
+  const hipStream_t st = nullptr;
+  const Cycle<double> cyc(m, lb, pre, post);
+  std::vector<double> a(len), a3(len), c(len);
+  auto fetch = [&](std::vector<double>& v) {
+    DCG_HIP(hipMemcpy(v.data(), out, sizeof(double) * len, hipMemcpyDeviceToHost));
+  };
+  auto steps = [&](std::vector<double>& v) {
+    LvState s;
+    cyc.wcycle(2, s, st);
+    cyc.wcycle(2, s, st);
+    DCG_HIP(launch_resolve_b<double>(ne, s.has_z, cyc.z(2, s.zb), cyc.Y(2, s.yb), out, st));
+    fetch(v);
+  };
+  const std::vector<double> f = fold_probe(size_t(4) * len, 0);
+  DCG_HIP(hipMemcpy(cyc.f(3), f.data(), sizeof(double) * f.size(), hipMemcpyHostToDevice));
+  LvState s;
+  for (int i = 0; i < pre; ++i) cyc.sweep_step(3, s, nullptr, st);
+  cyc.restrict_step(3, s, st);
+  DCG_HIP(launch_fold_b<double>(int(kFoldDofs), C, cyc.f(2), out, st));
+  fetch(c);
+  steps(a);
+  DCG_HIP(launch_scale(len, 3.0, cyc.f(2), out, st));
+  DCG_HIP(launch_copy<double>(len, out, cyc.f(2), st));
+  steps(a3);
+  FoldCheck check;
+  for (int col = 0; col < kBatch; ++col)
+    check.add(int(kFoldDofs), [col](int i) { return (i / 4 * kBatch + col) * 4 + i % 4; }, a, a3, c);
+  return check.holds();
+}
 
 // The matrix is what the two cycles make of the unit vectors: 256 batches of 16
 // columns through the FP64 batched cycle, on four streams (a batch fills a
@@ -108,7 +156,7 @@ std::shared_ptr<FoldMatrix> build_fold(MeshContext& m, int pre, int post) {
   auto F = std::make_shared<FoldMatrix>();
   F->device = m.device;
   DCG_HIP(hipMalloc(reinterpret_cast<void**>(&F->C), kFoldBytes));
-  m.ensure_factors(false, 2);
+  m.ensure_factors(false, 3);
   constexpr int kStreams = 4;
   struct Lane {
     Workspace ws;
@@ -134,7 +182,7 @@ std::shared_ptr<FoldMatrix> build_fold(MeshContext& m, int pre, int post) {
     DCG_HIP(launch_store_columns(ne, j0, s.has_z, c.z(2, s.zb), s.has_y ? c.Y(2, s.yb) : nullptr, F->C, l.st));
   }
   for (Lane& l : lane) DCG_HIP(hipStreamSynchronize(l.st));
-  return F;
+  return matrix_holds(m, pre, post, F->C) ? F : nullptr;
 }
 
 }  // namespace
@@ -142,6 +190,7 @@ std::shared_ptr<FoldMatrix> build_fold(MeshContext& m, int pre, int post) {
 std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
   if (!fold_applies(m.J, post)) return nullptr;
   std::lock_guard<std::mutex> lk(m.fold_mu);
+  if (m.no_fold.count({pre, post})) return nullptr;
   std::weak_ptr<FoldMatrix>& slot = m.folds[{pre, post}];
   std::shared_ptr<FoldMatrix> F = slot.lock();
   if (!F) {
@@ -150,6 +199,10 @@ std::shared_ptr<FoldMatrix> get_fold(MeshContext& m, int pre, int post) {
     } catch (const Error& e) {
       if (e.status != DCG_ENOMEM) throw;
       return nullptr;   // the cycles run their steps
+    }
+    if (!F) {
+      m.no_fold.insert({pre, post});
+      return nullptr;
     }
     slot = F;
   }

@@ -104,6 +104,7 @@ class _Exact:
 
 _OMG = (lib.DCG_OP_OMG_RAS, lib.DCG_OP_OMG_LEVEL, lib.DCG_OP_OMG_RESTRICT, lib.DCG_OP_OMG_PROLONG,
         lib.DCG_OP_OMG_WCYCLE)
+_MG2 = (lib.DCG_OP_RAS, lib.DCG_OP_LAPLACE, lib.DCG_OP_RESTRICT, lib.DCG_OP_PROLONG, lib.DCG_OP_WCYCLE)
 _MG3 = (lib.DCG3D_MG_RAS, lib.DCG3D_MG_LAPLACE, lib.DCG3D_MG_RESTRICT, lib.DCG3D_MG_PROLONG,
         lib.DCG3D_MG_WCYCLE)
 
@@ -116,7 +117,7 @@ def _steps(apply, ops, f, J, m):
         apply(o, k, x, out, x2)
         return out
     ras, level, restrict, prolong, wcycle = ops
-    N, M = f.numel(), f.numel() // (4 if ops is _OMG else 8)
+    N, M = f.numel(), f.numel() // (8 if ops is _MG3 else 4)
     z = None
     for _ in range(m):
         z = op(ras, J, f, N, z)
@@ -167,6 +168,39 @@ def test_3d_many_smoothing_steps():
     s.mg_apply(lib.DCG3D_MG_WCYCLE, J, fd, out)
     _close(out, mg.wcycle(H, f, np.zeros_like(f), J, m, m), m)
     s.close()
+
+
+@pytest.mark.parametrize("penalty,m", [(10.0, 1), (10.0, 2), (1e4, 2), (1e6, 2)])
+def test_2d_matrix_is_as_accurate_as_the_steps(penalty, m):
+    """The same for the inner multigrid (levels of 64, 32 and 16 squares), single and
+    batched; a penalty of 1e4 and more makes the Laplacian ill-conditioned."""
+    n, M = 64, 4 * 64 * 64
+    H = mg.Hierarchy(d.sipg_laplacian(n, penalty), n)
+    X = _Exact(H)
+    s = dcg.Solver(n, 1e-3, prec="fp64", penalty=penalty, pre=m, post=m)
+    zero = torch.zeros(M, dtype=torch.float64, device="cuda")
+
+    def apply(o, k, x, t, w):
+        s.apply(o, x, t, level=k, in2=zero if o == lib.DCG_OP_RAS and w is None else w)
+    err = np.zeros((3, 4))
+    f = np.random.default_rng(3).standard_normal((16, M))
+    fb = torch.from_numpy(np.ascontiguousarray(f.reshape(16, n * n, 4).transpose(1, 0, 2)).reshape(-1)).cuda()
+    zb = torch.full_like(fb, float("nan"))
+    s.apply(lib.DCG_OP_WCYCLE_BATCH, fb, zb, level=3)
+    zb = zb.cpu().numpy().reshape(n * n, 16, 4)
+    for c in range(4):
+        x = X.cycle(3, f[c].astype(X.L), np.zeros(M, dtype=X.L), m)
+        fd = torch.from_numpy(f[c].copy()).cuda()
+        out = torch.full_like(fd, float("nan"))
+        s.apply(lib.DCG_OP_WCYCLE, fd, out, level=3)
+        y = _steps(apply, _MG2, fd, 3, m)
+        for i, v in enumerate((out.cpu().numpy(), zb[:, c].reshape(-1), y.cpu().numpy())):
+            err[i, c] = np.abs(v - x).max() / np.abs(x).max()
+    s.close()
+    matrix, batch, steps = np.sqrt((err ** 2).mean(axis=1))
+    print("2d n=%d penalty=%g m=%d: matrix %.1e batch %.1e steps %.1e" % (n, penalty, m, matrix, batch, steps),
+          flush=True)
+    assert max(matrix, batch) <= 2 * steps
 
 
 @pytest.mark.parametrize("penalty,m", [(40.0, 1), (40.0, 3), (1e5, 3)])

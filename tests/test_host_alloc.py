@@ -70,7 +70,7 @@ def test_a_failed_setup_gives_everything_back(program, what, n, calls):
 GIB = 1 << 30
 
 
-@pytest.mark.parametrize("n,fp32,budget,products", [
+@pytest.mark.parametrize("n,fp32,budget,matrix", [
     (64, 0, 0, 0),               # what dcg_server_group_bytes says
     (64, 1, 0, 0),
     (64, 1, 2 * GIB - 1, 0),     # below 16 matrices
@@ -79,12 +79,12 @@ GIB = 1 << 30
     (32, 0, 2 * GIB, 0),         # two levels
     (512, 1, 0, 0),              # a group above 2 GiB that fits without the matrix only
 ])
-def test_server_admits_what_group_bytes_says(program, n, fp32, budget, products):
+def test_server_admits_what_group_bytes_says(program, n, fp32, budget, matrix):
     """The matrix is no part of what a group needs: a budget of dcg_server_group_bytes
     holds the group at every size, and with room for it the cycles use it."""
     r = program("budget", n, fp32, budget)
     assert r["status"] == OK
-    assert r["products"] == products
+    assert (r["products"] > 0) == bool(matrix)
     assert r["left_bytes"] == 0 and r["left_objects"] == 0 and r["bad_frees"] == 0
 
 
