@@ -224,3 +224,31 @@ def test_3d_matrix_is_as_accurate_as_the_steps(penalty, m):
     matrix, steps = np.sqrt((err ** 2).mean(axis=1))
     print("3d n=%d penalty=%g m=%d: matrix %.1e steps %.1e" % (n, penalty, m, matrix, steps), flush=True)
     assert matrix <= 2 * steps
+
+
+def test_server_groups_give_the_matrix_back_and_go_on():
+    """Two running groups of a 2 GiB server give their matrices back when a third needs
+    the room (FP64, n = 64, 128 and 256 hold 0.12 + 0.38 + 1.43 GiB), go on with the steps
+    and serve further requests: every solution within 1e-8 of the single solver's."""
+    budget, dt = 2 << 30, 1e-4
+    need = [lib.dcg_server_group_bytes(dcg.Server.mesh(n), lib.DCG_FP64) for n in (64, 128, 256)]
+    assert sum(need) <= budget < sum(need) + (1 << 27)
+    ref, bs = {}, {}
+    for n in (64, 128, 256):
+        bs[n] = torch.from_numpy(np.random.default_rng(n).standard_normal(16 * n * n)).cuda()
+        ref[n] = torch.empty_like(bs[n])
+        s = dcg.Solver(n, dt, prec="fp64")
+        status, _ = s.solve(bs[n], ref[n], tol=1e-8)
+        s.close()
+        assert status == lib.DCG_OK
+    srv = dcg.Server(prec="fp64", hbm_budget_bytes=budget)
+    for mix in ((64, 128, 256), (64, 64, 128), (256, 64)):
+        print("server mix", mix, flush=True)
+        xs = [torch.full_like(bs[n], float("nan")) for n in mix]
+        torch.cuda.synchronize()
+        tickets = [srv.submit(n, dt, bs[n], x, tol=1e-8) for n, x in zip(mix, xs)]
+        for n, x, t in zip(mix, xs, tickets):
+            status, _ = srv.wait(t, timeout=100)
+            assert status == lib.DCG_OK
+            assert float((x - ref[n]).norm()) <= 1e-8 * float(ref[n].norm()), n
+    srv.close()
